@@ -311,14 +311,16 @@ int sbn_conv3x3_sparse(const sbn_packed_t* p, const float* x, float* y,
  * a time, input channels split over waves).  This call forces one form for all
  * later launches of that kind in the process (0 = back to automatic), so that
  * every form can be checked on every shape; results never depend on the form
- * beyond summation order.  kind: SBN_CONV1X1 (forms 11, 12, 14, 21, 22: pixels
+ * beyond rounding.  kind: SBN_CONV1X1 (forms 11, 12, 14, 21, 22: pixels
  * per lane and accumulator sets; 504, 508, 516: 4, 8, 16 waves splitting the
  * input channels; 112, 121: forms 12 / 21 with the last pixel tiles run as
  * four-wave channel-splitting workgroups inside the same launch; 1012, 1021,
  * 1112, 1121: forms 12, 21, 112, 121 on the every-piece tables of layers that
  * have them (sbn_packed_layout), the plain form otherwise -- forms below 1000
  * never use those tables, the automatic choice always does; 1: the automatic
- * choice without those tables) or SBN_CONV3X3 (1, 2, 3: one pixel per lane, two pixels per
+ * choice without those tables; 2064, 2256: 64 x 128 and 128 x 256 tiles on
+ * pairs of 16-bit floats, for layers of at least 128 kept weights per filter,
+ * the automatic choice otherwise) or SBN_CONV3X3 (1, 2, 3: one pixel per lane, two pixels per
  * lane, entry-ahead fetch; 32: entry-ahead with the input channels split over
  * two halves of an eight-wave workgroup).  Layers whose shape leaves no choice (c_in <= 64,
  * c_in not a multiple of 4, stride 2) ignore it.  Unknown values: SBN_EINVAL.

@@ -377,7 +377,7 @@ const char* sbn_last_error(void) { return sbn::g_err.c_str(); }
 int sbn_force_kernel_form(int kind, int form)
 {
     clear_error();
-    static const int forms1x1[] = {0, 1, 11, 12, 14, 21, 22, 112, 121, 504, 508, 516, 1012, 1021, 1112, 1121}, forms3x3[] = {0, 1, 2, 3, 32};
+    static const int forms1x1[] = {0, 1, 11, 12, 14, 21, 22, 112, 121, 504, 508, 516, 1012, 1021, 1112, 1121, 2064, 2256}, forms3x3[] = {0, 1, 2, 3, 32};
     bool ok = false;
     if (kind == SBN_CONV1X1)
         for (int f : forms1x1) ok |= f == form;
@@ -1051,7 +1051,8 @@ int sbn_packed_layout(const sbn_packed_t* p, size_t* entries, size_t* table_byte
     if (entries) *entries = L.n_entries;
     if (table_bytes)
         *table_bytes = (L.records.size() + L.woff.size() + L.records32.size() + L.woff32.size() + L.desc_s.size()) * sizeof(uint32_t) +
-                       (L.wts.size() + L.wts_s.size() + L.bias_padded.size()) * sizeof(float);
+                       (L.wts.size() + L.wts_s.size() + L.bias_padded.size()) * sizeof(float) + L.wh.size() * sizeof(uint16_t) +
+                       L.wh_exp.size() * sizeof(int32_t);
     if (every_piece) *every_piece = L.desc_s.empty() ? 0 : 1;
     return SBN_OK;
 }

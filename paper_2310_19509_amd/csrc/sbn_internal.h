@@ -56,6 +56,7 @@ constexpr int kBundleGroups = 4;                       // groups of 4 filters pe
 constexpr int kBundleChannels = 4 * kBundleGroups;     // 16 output channels per bundle
 constexpr int kChunk = 64;                             // input channels per record
 constexpr int kSlots = kChunk / 4;                     // descriptors per record
+constexpr int kHalfMinKept = 128;                      // mean products per output from which the 16-bit pairs are built (sbn_layout.cpp)
 constexpr double kStaticWalkMinFill = 0.60;            // share of (bundle, piece) pairs kept, from which the every-piece tables are built
 
 struct DeviceLayout {
@@ -78,6 +79,17 @@ struct DeviceLayout {
     // for absent pieces.  Empty when the layer does not qualify.
     std::vector<uint32_t> desc_s;
     std::vector<float> wts_s;
+    // Layers whose outputs sum at least kHalfMinKept products also get their weights as pairs of
+    // 16-bit floats for the wide matrix instructions (see sbn_conv1x1_half.hip): filter f's weights
+    // times 2^-wh_exp[f] are hi + lo / 2048, hi the nearest 16-bit float, lo the nearest 16-bit
+    // float to 2048 times what hi leaves.  Zeros stand for removed weights.  One FRAGMENT = the
+    // A operand of a 16 x 16 x 32 multiply, [lane 64][8]: lane l holds filter l % 16 of the bundle,
+    // channels 8 * (l / 16) .. + 7 of the 32.  wh[bundle][step][hi, lo][64][8], a step = 32 input
+    // channels (1x1: an even number of steps, the last may be all zeros).  Empty when the layer
+    // does not qualify.
+    int n_steps = 0;                      // fragments pairs per bundle
+    std::vector<uint16_t> wh;
+    std::vector<int32_t> wh_exp;          // [n_bundles * 16]
     // device copies (one allocation)
     void* d_blob = nullptr;
     uint32_t* d_records = nullptr;
@@ -88,6 +100,8 @@ struct DeviceLayout {
     float* d_bias = nullptr;
     uint32_t* d_desc_s = nullptr;         // NULL when the layer has no every-piece tables
     float* d_wts_s = nullptr;
+    uint16_t* d_wh = nullptr;             // NULL when the layer has no 16-bit pairs
+    int32_t* d_wh_exp = nullptr;
 };
 
 }  // namespace sbn
@@ -119,6 +133,7 @@ void release_device_layout(sbn_packed* p);
 
 // Kernel launchers (defined in the .hip files).
 int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long m, void* stream);
+int launch_conv1x1_half(const sbn_packed* p, const float* x, float* y, long long m, int form, void* stream);
 int launch_conv3x3(const sbn_packed* p, const float* x, float* y, int n, int h, int w, void* stream);
 int launch_dw3x3(const float* x, float* y, const float* w_dev, const float* b_dev, int n, int h, int w,
                  int c, int stride, int act, void* stream);

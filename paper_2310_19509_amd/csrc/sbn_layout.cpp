@@ -12,6 +12,97 @@
 
 namespace sbn {
 
+// Nearest 16-bit float (ties to even) of a finite v, |v| < 65520, returned as bits; *back is its value.
+static uint16_t to_half(float v, float* back)
+{
+    uint32_t u;
+    std::memcpy(&u, &v, 4);
+    const uint32_t sign = u >> 16 & 0x8000u;
+    u &= 0x7FFFFFFFu;
+    float a;
+    std::memcpy(&a, &u, 4);
+    if (u < 0x38800000u) {                       // below 2^-14: a multiple of 2^-24; 0.5 has that spacing
+        const float r = (a + 0.5f) - 0.5f;
+        *back = sign ? -r : r;
+        return (uint16_t)(sign | (uint32_t)(r * 16777216.0f));
+    }
+    u += 0xFFFu + (u >> 13 & 1u);
+    u &= ~0x1FFFu;
+    std::memcpy(&a, &u, 4);
+    *back = sign ? -a : a;
+    return (uint16_t)(sign | ((u - 0x38000000u) >> 13));
+}
+
+// The weights as pairs of 16-bit floats (DeviceLayout::wh).  Only layers whose outputs sum enough
+// products: a pair carries 22 to 23 bits of a 24-bit weight and the product of the two low halves is
+// left out, about 9e-8 of the result in all, whatever the length of the sum, while a sum of n
+// products in 32-bit floats loses about 1e-8 * sqrt(n) (simulated and measured: 8.2e-8 against 9.2e-8
+// with 64 products, 1.09e-7 against 9.8e-8 with 128, 2.0e-7 against 1.1e-7 with 512).
+static void build_half_pairs(sbn_packed* p)
+{
+    DeviceLayout& L = p->dev;
+    L.wh.clear();
+    L.wh_exp.clear();
+    L.n_steps = 0;
+    const int taps = p->kh * p->kw;
+    const size_t kept = p->kidx.size() * (size_t)p->go * p->gi * taps;
+    if (taps != 1 || p->c_in % 4 || kept < (size_t)kHalfMinKept * p->c_out) return;
+    const int n_steps = L.n_chunks * 2;
+    const size_t n_filters = (size_t)L.n_bundles * kBundleChannels;
+    if (n_filters * (size_t)n_steps * 128 >= 0xFFFFFFFFull) return;      // 32-bit byte offsets on the device
+
+    // per filter: the power of two that takes its largest weight to [2^14, 2^15)
+    std::vector<uint32_t> top(n_filters, 0u);
+    for (int b = 0; b < L.n_bundles; ++b)
+        for (size_t e = L.woff[(size_t)b * (L.n_chunks + 1)]; e < L.woff[(size_t)b * (L.n_chunks + 1) + L.n_chunks]; ++e)
+            for (int i = 0; i < 64; ++i) {
+                uint32_t u;
+                std::memcpy(&u, &L.wts[e * 64 + i], 4);
+                uint32_t& t = top[(size_t)b * kBundleChannels + i / 4];   // [g][co][ci]
+                t = std::max(t, u & 0x7FFFFFFFu);
+            }
+    // (a filter whose weights span so much that a whole kept piece would lose bits: 32-bit kernels)
+    for (int b = 0; b < L.n_bundles; ++b)
+        for (size_t e = L.woff[(size_t)b * (L.n_chunks + 1)]; e < L.woff[(size_t)b * (L.n_chunks + 1) + L.n_chunks]; ++e)
+            for (int i = 0; i < 64; i += 4) {
+                uint32_t u[4];
+                std::memcpy(u, &L.wts[e * 64 + i], 16);
+                const uint32_t m = std::max(std::max(u[0] & 0x7FFFFFFFu, u[1] & 0x7FFFFFFFu), std::max(u[2] & 0x7FFFFFFFu, u[3] & 0x7FFFFFFFu));
+                if (m != 0 && (m >> 23) + 26 < (top[(size_t)b * kBundleChannels + i / 4] >> 23)) return;
+            }
+    L.wh_exp.assign(n_filters, 0);
+    std::vector<float> scale(n_filters, 1.0f);
+    for (size_t f = 0; f < n_filters; ++f) {
+        const int e = std::max((int)(top[f] >> 23), 27);
+        if (e == 255) {                                                  // infinite or NaN weights stay with the 32-bit kernels
+            L.wh_exp.clear();
+            return;
+        }
+        L.wh_exp[f] = e - 141;
+        const uint32_t s = (uint32_t)(268 - e) << 23;
+        std::memcpy(&scale[f], &s, 4);
+    }
+    L.n_steps = n_steps;
+    L.wh.assign(n_filters * (size_t)n_steps * 64, 0);
+    for (int b = 0; b < L.n_bundles; ++b)
+        for (int c = 0; c < L.n_chunks; ++c) {
+            const uint32_t* r = &L.records[((size_t)b * L.n_chunks + c) * kSlots];
+            const float* w = &L.wts[(size_t)L.woff[(size_t)b * (L.n_chunks + 1) + c] * 64];
+            for (int q = 0; q < kSlots && r[q] != 0; ++q, w += 64) {
+                const int kb4 = (int)(r[q] >> 12);                       // channels 4 * kb4 .. + 3 of the chunk
+                uint16_t* frag = &L.wh[(((size_t)b * n_steps + c * 2 + kb4 / 8) * 2) * 512];
+                for (int f = 0; f < kBundleChannels; ++f)
+                    for (int ci = 0; ci < 4; ++ci) {
+                        const size_t at = (size_t)((kb4 % 8) / 2 * 16 + f) * 8 + (kb4 % 2) * 4 + ci;
+                        const float v = w[f * 4 + ci] * scale[(size_t)b * kBundleChannels + f];
+                        float hi, lo;
+                        frag[at] = to_half(v, &hi);
+                        frag[at + 512] = to_half((v - hi) * 2048.0f, &lo);
+                    }
+            }
+        }
+}
+
 void build_device_layout(sbn_packed* p)
 {
     DeviceLayout& L = p->dev;
@@ -103,6 +194,7 @@ void build_device_layout(sbn_packed* p)
                 }
             }
     }
+    build_half_pairs(p);
     L.bias_padded.assign((size_t)L.n_bundles * kBundleChannels, 0.0f);
     std::copy(p->bias.begin(), p->bias.end(), L.bias_padded.begin());
 }
@@ -158,6 +250,10 @@ const char* check_device_layout(const sbn_packed* p)
     } else if (!L.wts_s.empty()) {
         return "every-piece weights without masks";
     }
+    if (L.wh.empty() ? !L.wh_exp.empty() || L.n_steps != 0
+                     : L.n_steps != 2 * L.n_chunks || L.wh.size() != (size_t)L.n_bundles * L.n_steps * 1024 ||
+                           L.wh_exp.size() != (size_t)L.n_bundles * kBundleChannels)
+        return "16-bit pair table sizes";
     return nullptr;
 }
 
@@ -187,7 +283,9 @@ int upload_device_layout(sbn_packed* p)
     const size_t b_bias = align256(L.bias_padded.size() * sizeof(float));
     const size_t b_desc_s = align256(L.desc_s.size() * sizeof(uint32_t));
     const size_t b_wts_s = align256(L.wts_s.size() * sizeof(float));
-    const size_t total = b_rec + b_woff + b_rec32 + b_woff32 + b_wts + b_bias + b_desc_s + b_wts_s;
+    const size_t b_wh = align256(L.wh.size() * sizeof(uint16_t));
+    const size_t b_wh_exp = align256(L.wh_exp.size() * sizeof(int32_t));
+    const size_t total = b_rec + b_woff + b_rec32 + b_woff32 + b_wts + b_bias + b_desc_s + b_wts_s + b_wh + b_wh_exp;
     char* blob = nullptr;
     if ((e = hipMalloc((void**)&blob, total)) != hipSuccess) {
         (void)hipSetDevice(prev);
@@ -221,6 +319,16 @@ int upload_device_layout(sbn_packed* p)
         off += b_desc_s;
         std::memcpy(host.data() + off, L.wts_s.data(), L.wts_s.size() * sizeof(float));
         L.d_wts_s = (float*)(blob + off);
+        off += b_wts_s;
+    }
+    L.d_wh = nullptr;
+    L.d_wh_exp = nullptr;
+    if (!L.wh.empty()) {
+        std::memcpy(host.data() + off, L.wh.data(), L.wh.size() * sizeof(uint16_t));
+        L.d_wh = (uint16_t*)(blob + off);
+        off += b_wh;
+        std::memcpy(host.data() + off, L.wh_exp.data(), L.wh_exp.size() * sizeof(int32_t));
+        L.d_wh_exp = (int32_t*)(blob + off);
     }
     e = hipMemcpy(blob, host.data(), total, hipMemcpyHostToDevice);
     (void)hipSetDevice(prev);
