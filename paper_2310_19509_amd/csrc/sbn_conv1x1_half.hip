@@ -46,66 +46,14 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "sbn_half.h"
 #include "sbn_internal.h"
 
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-typedef unsigned int v2u __attribute__((ext_vector_type(2)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+using namespace sbn_half;
 
 constexpr int KC = 64;                    // channels staged at a time
-constexpr int kSpoilt = 255;              // exponent that marks a group of rows with an infinite activation
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ v4u buf_load(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t scalar_off)
-{
-    return __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)scalar_off, 0));
-}
-__device__ __forceinline__ float as_float(uint32_t u) { return __builtin_bit_cast(float, u); }
-__device__ __forceinline__ uint32_t as_uint(float f) { return __builtin_bit_cast(uint32_t, f); }
-
-// max(|a|, |b|, c), one instruction; a NaN among them is passed over
-__device__ __forceinline__ float max3_abs(float a, float b, float c)
-{
-    float d;
-    asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-    return d;
-}
-
-// Largest of 64 lanes' non-negative values, as bits (which order like the values), in a scalar register.
-__device__ __forceinline__ uint32_t wave_max(float v)
-{
-    int m = (int)as_uint(v);
-#define SBN_STEP(CTRL) m = max(m, __builtin_amdgcn_update_dpp(0, m, CTRL, 0xF, 0xF, true));
-    SBN_STEP(0x111) SBN_STEP(0x112) SBN_STEP(0x114) SBN_STEP(0x118)      // row_shr 1, 2, 4, 8: lane 15 of every row
-    SBN_STEP(0x142) SBN_STEP(0x143)                                      // row_bcast 15, 31: lane 63
-#undef SBN_STEP
-    return (uint32_t)__builtin_amdgcn_readlane(m, 63);
-}
-
-// Two values as pairs: hi of both, lo of both.  sc: the scale, sc11: 2048 times the scale.
-__device__ __forceinline__ void split2(float a, float b, float sc, float sc11, uint32_t& hi, uint32_t& lo)
-{
-    const v2h h = __builtin_convertvector((v2f){a * sc, b * sc}, v2h);
-    const v2f r = {__builtin_fmaf((float)h.x, -2048.0f, a * sc11), __builtin_fmaf((float)h.y, -2048.0f, b * sc11)};   // exact
-    const v2h l = __builtin_convertvector(r, v2h);
-    hi = __builtin_bit_cast(uint32_t, h);
-    lo = __builtin_bit_cast(uint32_t, l);
-}
-
-__device__ __forceinline__ v4f relu4(v4f v)                              // as in the 32-bit form
-{
-    typedef int v4i __attribute__((ext_vector_type(4)));
-    const v4i b = __builtin_bit_cast(v4i, v);
-    return __builtin_bit_cast(v4f, (v4i){b.x > 0 ? b.x : 0, b.y > 0 ? b.y : 0, b.z > 0 ? b.z : 0, b.w > 0 ? b.w : 0});
-}
 
 // The outputs [pix0, pix0 + npix) x [ch0, ch0 + nch) by 32-bit multiply-adds over the kept blocks.
 // One wave; reached only for data outside the pairs' range.
@@ -188,7 +136,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv1x1_half_kernel(
             stage[i] = __builtin_bit_cast(v4f, buf_load(xres, xoff[i / 4] | outside, (uint32_t)c * (KC * 4) + (i & 3) * 64));
         }
     };
-    int run = 27;                                  // running exponent of the rows this wave stages (a scale stays below 2^127)
+    int run = kFirstExp;                           // running exponent of the rows this wave stages
     uint32_t least = 0xFFFFFFFFu;                  // smallest non-zero piece of four channels (its largest), as bits - 1
     float top = 0.f;
     auto measure_slot = [&](const v4f& v) {
@@ -200,21 +148,16 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv1x1_half_kernel(
         const int e = (int)(wave_max(top) >> 23);
         run = e > run ? e : run;
     };
-    auto start_measuring = [&]() { run = 27, least = 0xFFFFFFFFu, top = 0.f; };
+    auto start_measuring = [&]() { run = kFirstExp, least = 0xFFFFFFFFu, top = 0.f; };
     char* const wr = lds[0] + ((lane >> 1) & 1) * PLANE + (wave * ROWS + (lane >> 2)) * 16 + (lane & 1) * 8;
     auto publish_slot = [&](const v4f& v, int i, int buf, float sc, float sc11) {
-        uint32_t h0, h1, l0, l1;
-        split2(v.x, v.y, sc, sc11, h0, l0);
-        split2(v.z, v.w, sc, sc11, h1, l1);
-        *(v2u*)(wr + buf * (2 * HALF) + (i & 3) * (2 * PLANE) + (i / 4) * 256) = (v2u){h0, h1};
-        *(v2u*)(wr + buf * (2 * HALF) + (i & 3) * (2 * PLANE) + (i / 4) * 256 + HALF) = (v2u){l0, l1};
+        split4_to(wr + buf * (2 * HALF) + (i & 3) * (2 * PLANE) + (i / 4) * 256, HALF, v, sc, sc11);
     };
     auto publish_scale = [&](int buf) {
         // a piece below 2^-27 of the largest activation (zeros apart)
-        const int tiny = __builtin_amdgcn_ballot_w64(least < ((uint32_t)(run - 26) << 23) - 1u) != 0;
+        const int tiny = __builtin_amdgcn_ballot_w64(least < tiny_limit(run)) != 0;
         group[buf][wave] = run + tiny * 256;                             // (all lanes write the same)
     };
-    auto scale = [&](int more) { return as_float((uint32_t)(268 + more - run) << 23); };
 
     // ---- weights: four fragments (two bundles, hi and lo) per step
     const __amdgpu_buffer_rsrc_t wres = make_rsrc(wh, 0xFFFFFFFFu);      // (the packer keeps the table below 4 GiB)
@@ -228,7 +171,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv1x1_half_kernel(
     };
 
     v4f main[PT][2], cross[PT][2];
-    int cur = 27;                                  // lane g % NG: group's word of group g, whose exponent the sums are in
+    int cur = kFirstExp;                                  // lane g % NG: group's word of group g, whose exponent the sums are in
     auto exponent = [&](int v, int g) { return __builtin_amdgcn_readlane(v, g) & 255; };
     auto rescale = [&](int buf) {
         const int now = group[buf][lane % NG];
@@ -358,7 +301,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv1x1_half_kernel(
     for (int i = 0; i < NL; ++i) measure_slot(x_far[i]);
     measured();
 #pragma unroll
-    for (int i = 0; i < NL; ++i) publish_slot(x_far[i], i, 0, scale(0), scale(11));
+    for (int i = 0; i < NL; ++i) publish_slot(x_far[i], i, 0, scale_of(run, 0), scale_of(run, 11));
     publish_scale(0);
     __syncthreads();
     int buf = 0;
@@ -367,7 +310,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv1x1_half_kernel(
         for (int t = 0; t < PT; ++t)
 #pragma unroll
             for (int j = 0; j < 2; ++j) main[t][j] = cross[t][j] = (v4f){0.f, 0.f, 0.f, 0.f};
-        cur = 27;
+        cur = kFirstExp;
         for (int c = 0; c < n_chunks; ++c) {
             if constexpr (PIPE) {
                 load_w(2 * c + 1, wb);
@@ -384,7 +327,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv1x1_half_kernel(
                     if (t == NL) measured();
                 }, std::integral_constant<int, 2>());
                 load_w(c + 1 < n_chunks ? 2 * c + 2 : 0, wa);
-                const float sc = scale(0), sc11 = scale(11);
+                const float sc = scale_of(run, 0), sc11 = scale_of(run, 11);
                 step(buf, 1, wb, [&](int t) {
 #pragma unroll
                     for (int i = t * NL / PT; i < (t + 1) * NL / PT; ++i) publish_slot(x_next[i], i, buf ^ 1, sc, sc11);
@@ -408,7 +351,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv1x1_half_kernel(
 #pragma unroll
                 for (int i = 0; i < NL; ++i) measure_slot(x_far[i]);
                 measured();
-                const float sc = scale(0), sc11 = scale(11);
+                const float sc = scale_of(run, 0), sc11 = scale_of(run, 11);
 #pragma unroll
                 for (int i = 0; i < NL; ++i) publish_slot(x_far[i], i, buf ^ 1, sc, sc11);
                 publish_scale(buf ^ 1);

@@ -85,7 +85,7 @@ struct DeviceLayout {
     // float to 2048 times what hi leaves.  Zeros stand for removed weights.  One FRAGMENT = the
     // A operand of a 16 x 16 x 32 multiply, [lane 64][8]: lane l holds filter l % 16 of the bundle,
     // channels 8 * (l / 16) .. + 7 of the 32.  wh[bundle][step][hi, lo][64][8], a step = 32 input
-    // channels (1x1: an even number of steps, the last may be all zeros).  Empty when the layer
+    // channels (1x1: an even number of steps, the last may be all zeros) or one tap of 32 input channels (3x3).  Empty when the layer
     // does not qualify.
     int n_steps = 0;                      // fragments pairs per bundle
     std::vector<uint16_t> wh;
@@ -134,6 +134,8 @@ void release_device_layout(sbn_packed* p);
 // Kernel launchers (defined in the .hip files).
 int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long m, void* stream);
 int launch_conv1x1_half(const sbn_packed* p, const float* x, float* y, long long m, int form, void* stream);
+bool conv3x3_half_takes(const sbn_packed* p, int n, int h, int w);
+int launch_conv3x3_half(const sbn_packed* p, const float* x, float* y, int n, int h, int w, int form, void* stream);
 int launch_conv3x3(const sbn_packed* p, const float* x, float* y, int n, int h, int w, void* stream);
 int launch_dw3x3(const float* x, float* y, const float* w_dev, const float* b_dev, int n, int h, int w,
                  int c, int stride, int act, void* stream);

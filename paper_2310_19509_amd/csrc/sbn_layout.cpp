@@ -46,32 +46,45 @@ static void build_half_pairs(sbn_packed* p)
     L.n_steps = 0;
     const int taps = p->kh * p->kw;
     const size_t kept = p->kidx.size() * (size_t)p->go * p->gi * taps;
-    if (taps != 1 || p->c_in % 4 || kept < (size_t)kHalfMinKept * p->c_out) return;
-    const int n_steps = L.n_chunks * 2;
-    const size_t n_filters = (size_t)L.n_bundles * kBundleChannels;
+    if (p->c_in % 4 || kept < (size_t)kHalfMinKept * p->c_out) return;
+    const int n_steps = taps == 1 ? L.n_chunks * 2 : L.n_chunks32 * taps;
+    const size_t n_filters = (size_t)L.n_bundles * kBundleChannels, wstride = (size_t)taps * 64;
     if (n_filters * (size_t)n_steps * 128 >= 0xFFFFFFFFull) return;      // 32-bit byte offsets on the device
 
-    // per filter: the power of two that takes its largest weight to [2^14, 2^15)
+    // Per filter: the power of two that takes its largest weight to [2^14, 2^15).  An entry holds its
+    // weights as [g][co][ci] (1x1) or [tap][g][ci][co] (3x3).
     std::vector<uint32_t> top(n_filters, 0u);
-    for (int b = 0; b < L.n_bundles; ++b)
-        for (size_t e = L.woff[(size_t)b * (L.n_chunks + 1)]; e < L.woff[(size_t)b * (L.n_chunks + 1) + L.n_chunks]; ++e)
-            for (int i = 0; i < 64; ++i) {
-                uint32_t u;
-                std::memcpy(&u, &L.wts[e * 64 + i], 4);
-                uint32_t& t = top[(size_t)b * kBundleChannels + i / 4];   // [g][co][ci]
-                t = std::max(t, u & 0x7FFFFFFFu);
+    auto filter_of = [&](int b, size_t i) {
+        return (size_t)b * kBundleChannels + (taps == 1 ? i / 4 : i % 64 / 16 * 4 + i % 4);
+    };
+    auto bits_of = [](float v) {
+        uint32_t u;
+        std::memcpy(&u, &v, 4);
+        return u & 0x7FFFFFFFu;
+    };
+    for (int b = 0; b < L.n_bundles; ++b) {
+        const uint32_t* wo = &L.woff[(size_t)b * (L.n_chunks + 1)];
+        for (size_t e = wo[0]; e < wo[L.n_chunks]; ++e)
+            for (size_t i = 0; i < wstride; ++i) {
+                uint32_t& t = top[filter_of(b, i)];
+                t = std::max(t, bits_of(L.wts[e * wstride + i]));
             }
+    }
     // (a filter whose weights span so much that a whole kept piece would lose bits: 32-bit kernels)
-    for (int b = 0; b < L.n_bundles; ++b)
-        for (size_t e = L.woff[(size_t)b * (L.n_chunks + 1)]; e < L.woff[(size_t)b * (L.n_chunks + 1) + L.n_chunks]; ++e)
-            for (int i = 0; i < 64; i += 4) {
-                uint32_t u[4];
-                std::memcpy(u, &L.wts[e * 64 + i], 16);
-                const uint32_t m = std::max(std::max(u[0] & 0x7FFFFFFFu, u[1] & 0x7FFFFFFFu), std::max(u[2] & 0x7FFFFFFFu, u[3] & 0x7FFFFFFFu));
-                if (m != 0 && (m >> 23) + 26 < (top[(size_t)b * kBundleChannels + i / 4] >> 23)) return;
+    for (int b = 0; b < L.n_bundles; ++b) {
+        const uint32_t* wo = &L.woff[(size_t)b * (L.n_chunks + 1)];
+        for (size_t e = wo[0]; e < wo[L.n_chunks]; ++e) {
+            uint32_t piece[kBundleChannels] = {};                        // largest weight of the entry per filter
+            for (size_t i = 0; i < wstride; ++i) {
+                uint32_t& m = piece[filter_of(0, i)];
+                m = std::max(m, bits_of(L.wts[e * wstride + i]));
             }
-    L.wh_exp.assign(n_filters, 0);
+            for (int f = 0; f < kBundleChannels; ++f)
+                if (piece[f] != 0 && (piece[f] >> 23) + 26 < (top[(size_t)b * kBundleChannels + f] >> 23)) return;
+        }
+    }
     std::vector<float> scale(n_filters, 1.0f);
+    L.wh_exp.assign(n_filters, 0);
     for (size_t f = 0; f < n_filters; ++f) {
         const int e = std::max((int)(top[f] >> 23), 27);
         if (e == 255) {                                                  // infinite or NaN weights stay with the 32-bit kernels
@@ -85,20 +98,22 @@ static void build_half_pairs(sbn_packed* p)
     L.n_steps = n_steps;
     L.wh.assign(n_filters * (size_t)n_steps * 64, 0);
     for (int b = 0; b < L.n_bundles; ++b)
-        for (int c = 0; c < L.n_chunks; ++c) {
-            const uint32_t* r = &L.records[((size_t)b * L.n_chunks + c) * kSlots];
-            const float* w = &L.wts[(size_t)L.woff[(size_t)b * (L.n_chunks + 1) + c] * 64];
-            for (int q = 0; q < kSlots && r[q] != 0; ++q, w += 64) {
-                const int kb4 = (int)(r[q] >> 12);                       // channels 4 * kb4 .. + 3 of the chunk
-                uint16_t* frag = &L.wh[(((size_t)b * n_steps + c * 2 + kb4 / 8) * 2) * 512];
-                for (int f = 0; f < kBundleChannels; ++f)
-                    for (int ci = 0; ci < 4; ++ci) {
-                        const size_t at = (size_t)((kb4 % 8) / 2 * 16 + f) * 8 + (kb4 % 2) * 4 + ci;
-                        const float v = w[f * 4 + ci] * scale[(size_t)b * kBundleChannels + f];
-                        float hi, lo;
-                        frag[at] = to_half(v, &hi);
-                        frag[at + 512] = to_half((v - hi) * 2048.0f, &lo);
-                    }
+        for (int c = 0; c < L.n_chunks32; ++c) {
+            const uint32_t* r = &L.records32[((size_t)b * L.n_chunks32 + c) * 8];
+            const float* w = &L.wts[(size_t)L.woff32[(size_t)b * (L.n_chunks32 + 1) + c] * wstride];
+            for (int q = 0; q < 8 && r[q] != 0; ++q, w += wstride) {
+                const int kb4 = (int)(r[q] >> 12);                       // channels 4 * kb4 .. + 3 of the 32
+                uint16_t* frag = &L.wh[(((size_t)b * n_steps + (size_t)c * taps) * 2) * 512];
+                for (int t = 0; t < taps; ++t, frag += 1024)
+                    for (int f = 0; f < kBundleChannels; ++f)
+                        for (int ci = 0; ci < 4; ++ci) {
+                            const size_t at = (size_t)(kb4 / 2 * 16 + f) * 8 + (kb4 % 2) * 4 + ci;
+                            const float v = w[taps == 1 ? f * 4 + ci : t * 64 + f / 4 * 16 + ci * 4 + f % 4] *
+                                            scale[(size_t)b * kBundleChannels + f];
+                            float hi, lo;
+                            frag[at] = to_half(v, &hi);
+                            frag[at + 512] = to_half((v - hi) * 2048.0f, &lo);
+                        }
             }
         }
 }
@@ -251,7 +266,7 @@ const char* check_device_layout(const sbn_packed* p)
         return "every-piece weights without masks";
     }
     if (L.wh.empty() ? !L.wh_exp.empty() || L.n_steps != 0
-                     : L.n_steps != 2 * L.n_chunks || L.wh.size() != (size_t)L.n_bundles * L.n_steps * 1024 ||
+                     : L.n_steps != (p->kh == 1 ? 2 * L.n_chunks : 9 * L.n_chunks32) || L.wh.size() != (size_t)L.n_bundles * L.n_steps * 1024 ||
                            L.wh_exp.size() != (size_t)L.n_bundles * kBundleChannels)
         return "16-bit pair table sizes";
     return nullptr;
