@@ -6,7 +6,7 @@
 
 #include <algorithm>
 #include <cstring>
-#include <map>
+#include <memory>
 
 #include "sbn_internal.h"
 
@@ -52,36 +52,35 @@ static void build_half_pairs(sbn_packed* p)
     if (n_filters * (size_t)n_steps * 128 >= 0xFFFFFFFFull) return;      // 32-bit byte offsets on the device
 
     // Per filter: the power of two that takes its largest weight to [2^14, 2^15).  An entry holds its
-    // weights as [g][co][ci] (1x1) or [tap][g][ci][co] (3x3).
-    std::vector<uint32_t> top(n_filters, 0u);
-    auto filter_of = [&](int b, size_t i) {
-        return (size_t)b * kBundleChannels + (taps == 1 ? i / 4 : i % 64 / 16 * 4 + i % 4);
-    };
+    // weights as [g][co][ci] (1x1) or [tap][g][ci][co] (3x3); per entry, the largest of every filter first.
     auto bits_of = [](float v) {
         uint32_t u;
         std::memcpy(&u, &v, 4);
         return u & 0x7FFFFFFFu;
     };
+    std::vector<uint32_t> top(n_filters, 0u), piece(L.n_entries * kBundleChannels, 0u);
     for (int b = 0; b < L.n_bundles; ++b) {
         const uint32_t* wo = &L.woff[(size_t)b * (L.n_chunks + 1)];
-        for (size_t e = wo[0]; e < wo[L.n_chunks]; ++e)
-            for (size_t i = 0; i < wstride; ++i) {
-                uint32_t& t = top[filter_of(b, i)];
-                t = std::max(t, bits_of(L.wts[e * wstride + i]));
-            }
+        for (size_t e = wo[0]; e < wo[L.n_chunks]; ++e) {
+            const float* w = &L.wts[e * wstride];
+            uint32_t* m = &piece[e * kBundleChannels];
+            if (taps == 1)
+                for (int f = 0; f < kBundleChannels; ++f)
+                    m[f] = std::max(std::max(bits_of(w[f * 4]), bits_of(w[f * 4 + 1])), std::max(bits_of(w[f * 4 + 2]), bits_of(w[f * 4 + 3])));
+            else
+                for (int i = 0; i < taps * kBundleGroups; ++i, w += 16)
+                    for (int j = 0; j < 16; ++j) m[i % kBundleGroups * 4 + j % 4] = std::max(m[i % kBundleGroups * 4 + j % 4], bits_of(w[j]));
+            for (int f = 0; f < kBundleChannels; ++f) top[(size_t)b * kBundleChannels + f] = std::max(top[(size_t)b * kBundleChannels + f], m[f]);
+        }
     }
     // (a filter whose weights span so much that a whole kept piece would lose bits: 32-bit kernels)
     for (int b = 0; b < L.n_bundles; ++b) {
         const uint32_t* wo = &L.woff[(size_t)b * (L.n_chunks + 1)];
-        for (size_t e = wo[0]; e < wo[L.n_chunks]; ++e) {
-            uint32_t piece[kBundleChannels] = {};                        // largest weight of the entry per filter
-            for (size_t i = 0; i < wstride; ++i) {
-                uint32_t& m = piece[filter_of(0, i)];
-                m = std::max(m, bits_of(L.wts[e * wstride + i]));
+        for (size_t e = wo[0]; e < wo[L.n_chunks]; ++e)
+            for (int f = 0; f < kBundleChannels; ++f) {
+                const uint32_t m = piece[e * kBundleChannels + f];
+                if (m != 0 && (m >> 23) + 26 < (top[(size_t)b * kBundleChannels + f] >> 23)) return;
             }
-            for (int f = 0; f < kBundleChannels; ++f)
-                if (piece[f] != 0 && (piece[f] >> 23) + 26 < (top[(size_t)b * kBundleChannels + f] >> 23)) return;
-        }
     }
     std::vector<float> scale(n_filters, 1.0f);
     L.wh_exp.assign(n_filters, 0);
@@ -105,15 +104,20 @@ static void build_half_pairs(sbn_packed* p)
                 const int kb4 = (int)(r[q] >> 12);                       // channels 4 * kb4 .. + 3 of the 32
                 uint16_t* frag = &L.wh[(((size_t)b * n_steps + (size_t)c * taps) * 2) * 512];
                 for (int t = 0; t < taps; ++t, frag += 1024)
-                    for (int f = 0; f < kBundleChannels; ++f)
-                        for (int ci = 0; ci < 4; ++ci) {
-                            const size_t at = (size_t)(kb4 / 2 * 16 + f) * 8 + (kb4 % 2) * 4 + ci;
-                            const float v = w[taps == 1 ? f * 4 + ci : t * 64 + f / 4 * 16 + ci * 4 + f % 4] *
-                                            scale[(size_t)b * kBundleChannels + f];
-                            float hi, lo;
-                            frag[at] = to_half(v, &hi);
-                            frag[at + 512] = to_half((v - hi) * 2048.0f, &lo);
+                    for (int g = 0; g < kBundleGroups; ++g) {
+                        if (!(r[q] >> g & 1u)) continue;                 // removed: stays zero
+                        for (int co = 0; co < 4; ++co) {
+                            const int f = g * 4 + co;
+                            const float sc = scale[(size_t)b * kBundleChannels + f];
+                            uint16_t* const to = frag + (size_t)(kb4 / 2 * 16 + f) * 8 + (kb4 % 2) * 4;
+                            for (int ci = 0; ci < 4; ++ci) {
+                                const float v = w[taps == 1 ? f * 4 + ci : t * 64 + g * 16 + ci * 4 + co] * sc;
+                                float hi, lo;
+                                to[ci] = to_half(v, &hi);
+                                to[512 + ci] = to_half((v - hi) * 2048.0f, &lo);
+                            }
                         }
+                    }
             }
         }
 }
@@ -137,41 +141,60 @@ void build_device_layout(sbn_packed* p)
     size_t n_entries = 0;
 
     const int sub = go / 4;                                          // 4-filter groups per canonical row
+    const size_t n_pos = (size_t)(p->c_in + 3) / 4;
+    std::vector<uint32_t> present(n_pos);                            // per piece: which groups keep it
+    std::vector<size_t> entry(n_pos);                                // and its entry
+    std::vector<int> kept;                                           // the bundle's pieces, ascending
+    kept.reserve(n_pos);
+    {
+        size_t most = 0;                                             // room for all entries at once
+        for (int b = 0; b < L.n_bundles; ++b) {
+            size_t blocks = 0;
+            for (int row = b * kBundleGroups / sub; row < std::min(p->c_out / go, (b + 1) * kBundleGroups / sub); ++row)
+                blocks += p->row_ptr[(size_t)row + 1] - p->row_ptr[(size_t)row];
+            most += std::min(n_pos, blocks * std::max<size_t>(1, (size_t)gi / 4));
+        }
+        L.wts.reserve(most * wstride);
+    }
     for (int b = 0; b < L.n_bundles; ++b) {
-        // kb4 -> (entry index, present mask); std::map keeps channels ascending
-        std::map<int, std::pair<size_t, uint32_t>> pos;
         const int g_lo = b * kBundleGroups, g_hi = std::min(n_groups4, g_lo + kBundleGroups);
+        std::fill(present.begin(), present.end(), 0u);
         for (int g4 = g_lo; g4 < g_hi; ++g4) {
             const int row = g4 / sub;
             for (uint32_t e = p->row_ptr[(size_t)row]; e < p->row_ptr[(size_t)row + 1]; ++e)
-                for (int c = 0; c < gi; ++c) pos[(p->kidx[e] + c) / 4].second |= 1u << (g4 - g_lo);
+                for (int c = 0; c < gi; ++c) present[(size_t)(p->kidx[e] + c) / 4] |= 1u << (g4 - g_lo);
         }
-        const size_t first = n_entries;
-        for (auto& kv : pos) kv.second.first = n_entries++;
+        kept.clear();
+        for (size_t kb4 = 0; kb4 < n_pos; ++kb4)
+            if (present[kb4] != 0) {
+                entry[kb4] = n_entries++;
+                kept.push_back((int)kb4);
+            }
         L.wts.resize(n_entries * wstride, 0.0f);
         for (int g4 = g_lo; g4 < g_hi; ++g4) {
             const int row = g4 / sub, s = g4 % sub, g = g4 - g_lo;
             for (uint32_t e = p->row_ptr[(size_t)row]; e < p->row_ptr[(size_t)row + 1]; ++e)
                 for (int c = 0; c < gi; ++c) {
                     const int ch = p->kidx[e] + c;
-                    const size_t en = pos[ch / 4].first;
-                    for (int t = 0; t < taps; ++t)
-                        for (int co = 0; co < 4; ++co) {
-                            // 1x1: [g][co][ci] (16-byte loads per lane); 3x3: [tap][g][ci][co] (4-byte loads)
-                            const size_t inner = taps == 1 ? (size_t)co * 4 + (ch % 4) : (size_t)(ch % 4) * 4 + co;
-                            L.wts[en * wstride + ((size_t)t * kBundleGroups + g) * 16 + inner] =
-                                p->vals[e * blk + ((size_t)t * gi + c) * go + (size_t)s * 4 + co];
-                        }
+                    float* const to = &L.wts[entry[(size_t)ch / 4] * wstride + (size_t)g * 16];
+                    const float* const from = &p->vals[e * blk + (size_t)c * go + (size_t)s * 4];
+                    // 1x1: [g][co][ci] (16-byte loads per lane); 3x3: [tap][g][ci][co] (4-byte loads)
+                    if (taps == 1)
+                        for (int co = 0; co < 4; ++co) to[co * 4 + ch % 4] = from[co];
+                    else
+                        for (int t = 0; t < taps; ++t)
+                            for (int co = 0; co < 4; ++co)
+                                to[(size_t)t * kBundleGroups * 16 + (size_t)(ch % 4) * 4 + co] = from[(size_t)t * gi * go + co];
                 }
         }
         // records and chunk offsets
         uint32_t* wo = &L.woff[(size_t)b * (L.n_chunks + 1)];
         std::vector<int> fill((size_t)L.n_chunks, 0);
         for (int c = 0; c <= L.n_chunks; ++c) wo[c] = (uint32_t)n_entries;
-        for (const auto& kv : pos) {
-            const int c = kv.first / kSlots, q = fill[(size_t)c]++;
-            L.records[((size_t)b * L.n_chunks + c) * kSlots + q] = ((uint32_t)(kv.first % kSlots) << 12) | kv.second.second;
-            wo[c] = std::min(wo[c], (uint32_t)kv.second.first);
+        for (const int kb4 : kept) {
+            const int c = kb4 / kSlots, q = fill[(size_t)c]++;
+            L.records[((size_t)b * L.n_chunks + c) * kSlots + q] = ((uint32_t)(kb4 % kSlots) << 12) | present[(size_t)kb4];
+            wo[c] = std::min(wo[c], (uint32_t)entry[(size_t)kb4]);
         }
         // empty chunks start where the next non-empty one does
         for (int c = L.n_chunks - 1; c >= 0; --c) wo[c] = std::min(wo[c], wo[c + 1]);
@@ -179,13 +202,12 @@ void build_device_layout(sbn_packed* p)
         uint32_t* wo32 = &L.woff32[(size_t)b * (L.n_chunks32 + 1)];
         std::vector<int> fill32((size_t)L.n_chunks32, 0);
         for (int c = 0; c <= L.n_chunks32; ++c) wo32[c] = (uint32_t)n_entries;
-        for (const auto& kv : pos) {
-            const int c = kv.first / 8, q = fill32[(size_t)c]++;
-            L.records32[((size_t)b * L.n_chunks32 + c) * 8 + q] = ((uint32_t)(kv.first % 8) << 12) | kv.second.second;
-            wo32[c] = std::min(wo32[c], (uint32_t)kv.second.first);
+        for (const int kb4 : kept) {
+            const int c = kb4 / 8, q = fill32[(size_t)c]++;
+            L.records32[((size_t)b * L.n_chunks32 + c) * 8 + q] = ((uint32_t)(kb4 % 8) << 12) | present[(size_t)kb4];
+            wo32[c] = std::min(wo32[c], (uint32_t)entry[(size_t)kb4]);
         }
         for (int c = L.n_chunks32 - 1; c >= 0; --c) wo32[c] = std::min(wo32[c], wo32[c + 1]);
-        (void)first;
     }
     L.n_entries = n_entries;
     // every-piece tables for 1x1 layers of more than one chunk that keep most of their pieces
@@ -301,51 +323,32 @@ int upload_device_layout(sbn_packed* p)
     const size_t b_wh = align256(L.wh.size() * sizeof(uint16_t));
     const size_t b_wh_exp = align256(L.wh_exp.size() * sizeof(int32_t));
     const size_t total = b_rec + b_woff + b_rec32 + b_woff32 + b_wts + b_bias + b_desc_s + b_wts_s + b_wh + b_wh_exp;
+    // (written once: not zeroed first, the gaps behind the arrays are; before the device memory, as it may throw)
+    std::unique_ptr<char[]> host(new char[total]);
     char* blob = nullptr;
     if ((e = hipMalloc((void**)&blob, total)) != hipSuccess) {
         (void)hipSetDevice(prev);
         return fail(e == hipErrorOutOfMemory ? SBN_ENOMEM : SBN_EHIP, "hipMalloc(%zu): %s", total, hipGetErrorString(e));
     }
-    std::vector<char> host(total, 0);
     size_t off = 0;
-    std::memcpy(host.data() + off, L.records.data(), L.records.size() * sizeof(uint32_t));
-    L.d_records = (uint32_t*)(blob + off);
-    off += b_rec;
-    std::memcpy(host.data() + off, L.woff.data(), L.woff.size() * sizeof(uint32_t));
-    L.d_woff = (uint32_t*)(blob + off);
-    off += b_woff;
-    std::memcpy(host.data() + off, L.records32.data(), L.records32.size() * sizeof(uint32_t));
-    L.d_records32 = (uint32_t*)(blob + off);
-    off += b_rec32;
-    std::memcpy(host.data() + off, L.woff32.data(), L.woff32.size() * sizeof(uint32_t));
-    L.d_woff32 = (uint32_t*)(blob + off);
-    off += b_woff32;
-    std::memcpy(host.data() + off, L.wts.data(), L.wts.size() * sizeof(float));
-    L.d_wts = (float*)(blob + off);
-    off += b_wts;
-    std::memcpy(host.data() + off, L.bias_padded.data(), L.bias_padded.size() * sizeof(float));
-    L.d_bias = (float*)(blob + off);
-    off += b_bias;
-    L.d_desc_s = nullptr;
-    L.d_wts_s = nullptr;
-    if (!L.desc_s.empty()) {
-        std::memcpy(host.data() + off, L.desc_s.data(), L.desc_s.size() * sizeof(uint32_t));
-        L.d_desc_s = (uint32_t*)(blob + off);
-        off += b_desc_s;
-        std::memcpy(host.data() + off, L.wts_s.data(), L.wts_s.size() * sizeof(float));
-        L.d_wts_s = (float*)(blob + off);
-        off += b_wts_s;
-    }
-    L.d_wh = nullptr;
-    L.d_wh_exp = nullptr;
-    if (!L.wh.empty()) {
-        std::memcpy(host.data() + off, L.wh.data(), L.wh.size() * sizeof(uint16_t));
-        L.d_wh = (uint16_t*)(blob + off);
-        off += b_wh;
-        std::memcpy(host.data() + off, L.wh_exp.data(), L.wh_exp.size() * sizeof(int32_t));
-        L.d_wh_exp = (int32_t*)(blob + off);
-    }
-    e = hipMemcpy(blob, host.data(), total, hipMemcpyHostToDevice);
+    auto put = [&](const void* data, size_t used, size_t reserved) {
+        if (used) std::memcpy(host.get() + off, data, used);
+        std::memset(host.get() + off + used, 0, reserved - used);
+        char* const at = blob + off;
+        off += reserved;
+        return reserved ? at : nullptr;
+    };
+    L.d_records = (uint32_t*)put(L.records.data(), L.records.size() * sizeof(uint32_t), b_rec);
+    L.d_woff = (uint32_t*)put(L.woff.data(), L.woff.size() * sizeof(uint32_t), b_woff);
+    L.d_records32 = (uint32_t*)put(L.records32.data(), L.records32.size() * sizeof(uint32_t), b_rec32);
+    L.d_woff32 = (uint32_t*)put(L.woff32.data(), L.woff32.size() * sizeof(uint32_t), b_woff32);
+    L.d_wts = (float*)put(L.wts.data(), L.wts.size() * sizeof(float), b_wts);
+    L.d_bias = (float*)put(L.bias_padded.data(), L.bias_padded.size() * sizeof(float), b_bias);
+    L.d_desc_s = (uint32_t*)put(L.desc_s.data(), L.desc_s.size() * sizeof(uint32_t), b_desc_s);       // NULL when there are none
+    L.d_wts_s = (float*)put(L.wts_s.data(), L.wts_s.size() * sizeof(float), b_wts_s);
+    L.d_wh = (uint16_t*)put(L.wh.data(), L.wh.size() * sizeof(uint16_t), b_wh);
+    L.d_wh_exp = (int32_t*)put(L.wh_exp.data(), L.wh_exp.size() * sizeof(int32_t), b_wh_exp);
+    e = hipMemcpy(blob, host.get(), total, hipMemcpyHostToDevice);
     (void)hipSetDevice(prev);
     if (e != hipSuccess) {
         (void)hipFree(blob);
