@@ -279,9 +279,9 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv1x1_half_kernel(
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int ch = (bundle + j) * 16 + ch_lane;
-                // (Streaming stores only in the small form: the halves of a 128-byte line leave in two instructions here, and in
-            // the streaming form, 512 channels at 100352 pixels, letting L2 put them together is 4 % faster.)
-            const uint32_t off = ch < N ? ((uint32_t)(row_lane + t * 16) * (uint32_t)N + (uint32_t)ch) * 4u : 0xFFFFFFF0u;
+                // (A pixel's 128 bytes leave in two instructions.  As streaming stores the halves go to memory one by one,
+                // which costs the form that walks many tiles 4 % at 512 channels and 100352 pixels.)
+                const uint32_t off = ch < N ? ((uint32_t)(row_lane + t * 16) * (uint32_t)N + (uint32_t)ch) * 4u : 0xFFFFFFF0u;
                 v4f o = main[t][j];
                 if (act == SBN_ACT_RELU) o = relu4(o);
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o), yres, (int)off, 0,
