@@ -318,9 +318,10 @@ int sbn_conv3x3_sparse(const sbn_packed_t* p, const float* x, float* y,
  * 1112, 1121: forms 12, 21, 112, 121 on the every-piece tables of layers that
  * have them (sbn_packed_layout), the plain form otherwise -- forms below 1000
  * never use those tables, the automatic choice always does; 1: the automatic
- * choice without those tables; 2064, 2256: 64 x 128 and 128 x 256 tiles on
- * pairs of 16-bit floats, for layers of at least 128 kept weights per filter,
- * the automatic choice otherwise) or SBN_CONV3X3 (1, 2, 3: one pixel per lane, two pixels per
+ * choice among the forms so far, without those tables; 2064, 2256: 64 x 128 and 128 x 256 tiles on
+ * triples of bfloat16, for layers of c_in > 64 and a multiple of 4 that keep enough for the automatic choice to
+ * come to use them or that were packed while one of the two was forced, the automatic
+ * choice otherwise) or SBN_CONV3X3 (1, 2, 3: one pixel per lane, two pixels per
  * lane, entry-ahead fetch; 32: entry-ahead with the input channels split over
  * two halves of an eight-wave workgroup; 2128, 2064, 2065: 128 x 64 tiles, 64 x 64
  * tiles and 64 x 64 tiles with two halves on pairs of 16-bit floats, for layers of

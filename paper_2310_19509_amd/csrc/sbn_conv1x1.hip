@@ -806,8 +806,8 @@ int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long M, v
         p->dev.wts_s.size() * sizeof(float) >= 0xFFFFFFFFull)
         return fail(SBN_EINVAL, "the layer's device weights exceed 4 GiB");
     int force = forced_kernel_form(SBN_CONV1X1);  // testing / benchmarking override
-    if (force >= 2000 && p->dev.d_wh) return launch_conv1x1_half(p, x, y, M, force, stream);
-    if (force >= 2000) force = 0;                       // (a layer without 16-bit pairs)
+    if (force >= 2000 && p->dev.d_wt) return launch_conv1x1_wide(p, x, y, M, force, stream);
+    if (force >= 2000) force = 0;                       // (a layer without triples)
     if (K % 4) {
         if (K <= 32) return launch<1, 2, 32, false, false>(p, x, y, M, st);
         if (K <= 64) return launch<1, 2, 64, false, false>(p, x, y, M, st);
@@ -838,20 +838,9 @@ int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long M, v
         // MobileNet stack at batch 64: 5-9 % over 64-pixel tiles at 3.06 tiles per CU, 15-20 %
         // behind them at 1.6)
         variant = ((M + 127) / 128) * n_col_tiles >= 3ll * cus ? 21 : 12;
-        // Layers with 16-bit pairs (sbn_conv1x1_half.hip): their sums are at least as close to the exact
-        // result as this form's, which keeps one partial sum with 128-pixel tiles and two with 64-pixel
-        // ones (relative error in units of 1e-8, c_in = 256 / 512 / 1024: pairs 12.1 / 15.0 / 19.3 at 50 %
-        // sparsity, one sum 14.6 / 20.5 / 28.8, two sums 10.8 / 14.9 / 20.6; 30 %: 12.9 / 16.0 / 21.0
-        // against 17.2 / 24.0 / 33.8 and 12.6 / 17.4 / 24.3), and the zeros that they multiply cost
-        // less than the wide instructions save down to 30 % of the weights (512 x 512, 12544 pixels, 70 %
-        // sparsity: 32 us either way).
-        const long long kept = (long long)(p->kidx.size() * (size_t)p->go * p->gi / (size_t)p->c_out);
-        if (!force && p->dev.d_wh && p->dev.n_bundles >= 6 && wg_split > 4ll * cus && kept * 10 >= 3ll * K &&
-            (variant == 21 || 4 * kept >= K + 512)) {
-            const long long tiles = (M + 127) / 128 * ((p->c_out + 255) / 256);
-            const bool fits = (p->c_out + 255) / 256 * 256 * 7 <= p->c_out * 8;      // at most an eighth of the channels past c_out
-            return launch_conv1x1_half(p, x, y, M, fits && (tiles >= 4ll * cus || (K >= 384 && 10 * tiles >= 7ll * cus)) ? 2256 : 2064, stream);
-        }
+        // Layers that keep much run on triples of bfloat16 (sbn_conv1x1_wide.hip), from more pixels on than the
+        // few-pixel form takes.  Their results are closer to the exact ones than any 32-bit form's (figures there).
+        if (!force && p->dev.d_wt && wg_split > 4ll * cus && conv1x1_wide_pays(p)) return launch_conv1x1_wide(p, x, y, M, 0, stream);
         // Whole rounds of workgroups only: when the last round would occupy at most half of
         // the compute units, the pixels of that round go to few-pixel workgroups instead.
         const int px = variant == 21 ? 128 : 64;

@@ -1,0 +1,375 @@
+// Group-sparse 1x1 convolution on the wide 16-bit matrix instructions, with every bit of the 32-bit operands,
+// for gfx950.
+//
+// v_mfma_f32_32x32x16_bf16 multiplies 16 times as many pairs per cycle as the 32-bit instructions, so even
+// six of them per product, over blocks filled up with the removed weights' zeros, take less time than 4x4x1
+// multiplies over the kept blocks where a layer keeps enough of them (launch_conv1x1 has the rule).  Every
+// operand is the exact sum of three bfloat16, v = a + b + c (8 + 8 + 8 bits; the exponent range is that of
+// 32-bit floats, so there is nothing to scale and no value depends on its neighbours).  Of the nine products
+// six are formed,
+//     main += w_a * x_a,    cross += w_a * x_c + w_c * x_a + w_b * x_b + w_a * x_b + w_b * x_a,
+// both sums in 32-bit floats; the other three are below 2^-26 of the product, a quarter of what one rounding of
+// a 32-bit sum costs.  `main`, the only long sum of full-sized terms, is rounded c_in / 16 times instead of
+// once per kept weight.  Relative error (2-norm, units of 1e-8, half-zero activations, c_in = 128 / 256 / 512 / 1024,
+// 50 % kept): 4.2 / 5.5 / 7.1 / 10.1 with 16x16x32 multiplies; one 32-bit sum 11.1 / 14.8 / 19.9 / 28.3, two sums
+// 8.2 / 10.6 / 14.0 / 20.8; one active channel per pixel 2.6 and 2.5.  (The splitting is that of the known emulations of
+// single precision on bfloat16 units: Henry, Tang, Heinecke, "Leveraging the bfloat16 artificial intelligence
+// datatype for higher-precision computations", 2019.)
+//
+// What bfloat16 cannot hold is done again with 32-bit multiply-adds over the kept blocks, output by output, by the
+// lane that owns the output: results that are not finite (an infinite or NaN activation, times the stored
+// zeros, reaches every output of its pixel), sums below 2^-100, and, in pixels that hold a non-zero
+// activation below 2^-100 (whose last bits can lie below the smallest bfloat16), sums so small that those bits could matter.
+//
+// Mapping.  A workgroup owns T = 32 * PX pixels x 32 * NWV output channels; a wave T pixels x 32 channels
+// (two bundles).  Weights are operand A, activations operand B, so a lane ends with four times four consecutive
+// output channels (filter groups) of one pixel: 16-byte stores, no transpose.  Per chunk of 64 input
+// channels the activations go global -> registers -> triples -> LDS (two buffers, one barrier per
+// chunk), the weights' fragments go straight to registers, one step of 16 channels ahead.
+//
+// Two forms (launch_conv1x1_wide has the rule):
+//   PX = 2, NWV = 4: 64 x 128 tiles, a workgroup per tile, three to a compute unit, which cover each
+//     other's waits.
+//   PX = 4, NWV = 8, PIPE: 128 x 256 tiles halve the weights' and the conversions' share of the work; one
+//     workgroup per compute unit walks its tiles as one stream of chunks.
+// In both the next chunk's conversion goes between the multiplies of this one.  The matrix unit is busy 65 % of the
+// time in the second form (512 x 512, 100352 pixels, 260 us: 1.2 PFLOP/s; a loop of these multiplies alone on random
+// data reaches 1.85): activations, weights and LDS reads that arrive late cost 22 %, uneven rounds 13 %.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "sbn_internal.h"
+#include "sbn_wide.h"
+
+namespace {
+
+using namespace sbn_wide;
+
+constexpr int KC = 64;                    // channels staged at a time
+constexpr int STEPS = KC / 16;            // multiplies per chunk, tile and product
+
+// Four output channels ch .. ch + 3 (one filter group) of pixel pix by 32-bit multiply-adds over the kept blocks.
+__device__ __forceinline__ void exact_group(const float* __restrict__ x, float* __restrict__ y,
+                                            const uint32_t* __restrict__ records, const uint32_t* __restrict__ woff,
+                                            const float* __restrict__ wts, const float* __restrict__ bias, int K, int N,
+                                            int n_chunks, long long pix, int ch, int act)
+{
+    const int b = ch >> 4, g = (ch >> 2) & 3;
+    v4f acc = *(const v4f*)(bias + ch);
+    for (int c = 0; c < n_chunks; ++c) {
+        const uint32_t* r = records + ((size_t)b * n_chunks + c) * 16;
+        const v4f* w = (const v4f*)(wts + (size_t)woff[(size_t)b * (n_chunks + 1) + c] * 64 + g * 16);
+        const float* xc = x + pix * K + c * 64;
+        for (int q = 0; q < 16 && r[q] != 0; ++q, w += 16) {
+            if (!(r[q] >> g & 1u)) continue;
+            const v4f xv = *(const v4f*)(xc + (int)(r[q] >> 12) * 4);
+#pragma unroll
+            for (int co = 0; co < 4; ++co)
+#pragma unroll
+                for (int ci = 0; ci < 4; ++ci) acc[co] = __builtin_fmaf(w[co][ci], xv[ci], acc[co]);
+        }
+    }
+    if (act == SBN_ACT_RELU) acc = relu4(acc);
+    *(v4f*)(y + pix * N + ch) = acc;
+}
+
+template <int PX, int NWV, bool PIPE>
+__global__ __launch_bounds__(64 * NWV, PIPE ? 2 : 3) void conv1x1_wide_kernel(
+    const float* __restrict__ x, float* __restrict__ y, const uint16_t* __restrict__ wt, uint32_t wt_bytes,
+    const float* __restrict__ bias, const uint32_t* __restrict__ records, const uint32_t* __restrict__ woff,
+    const float* __restrict__ wts, long long M, int K, int N, int n_bundles, int n_chunks, int n_col_tiles, int n_pix_tiles,
+    int pix_stride, float tiny_sum, int act)
+{
+    constexpr int T = 32 * PX;                     // pixels of the workgroup
+    constexpr int NL = T * 16 / (64 * NWV);        // 16-byte slots per lane and chunk
+    constexpr int ROWS = 16;                       // rows that a wave stages, four lanes to a row
+    // LDS image, a, b and c alike: per 8 channels a plane of T rows of 16 bytes.  The 32 rows that a read
+    // takes from each of two planes and the 16 that a write stores then cover all banks evenly.
+    constexpr int PLANE = T * 16, PART = 8 * PLANE, IMAGE = 3 * PART;
+    static_assert(ROWS * NWV == T && NL == 4, "tile shape");
+    __shared__ __attribute__((aligned(16))) char lds[2][IMAGE];
+    __shared__ unsigned long long mark[2][NWV];    // per staging wave: four bits per row, set by lanes that met tiny values in it
+
+    // A workgroup keeps its column tile and walks every pix_stride-th pixel tile.  Column tiles of one
+    // pixel tile run on one XCD (workgroup ids go round the eight XCDs).
+    const int xcd = blockIdx.x & 7, jj = blockIdx.x >> 3;
+    int pix_tile = (jj / n_col_tiles) * 8 + xcd;
+    const int col_tile = jj % n_col_tiles;
+    if (pix_tile >= n_pix_tiles) return;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int pair = col_tile * NWV + wave;                              // 32 channels, two bundles
+    const bool active = pair * 2 < n_bundles;
+    const int n_steps = STEPS * n_chunks;
+    auto rows_of = [&](int tile) -> int {                                // pixels of the tile that exist
+        const long long left = M - (long long)tile * T;
+        return (int)(left < 0 ? 0 : left < T ? left : T);
+    };
+
+    // ---- activations: slot i of a lane = row wave * 16 + lane / 4, channels 16 * i + 4 * (lane % 4) of the
+    // chunk.  Rows past the last pixel lie outside the buffer and read as zero; channels past c_in are sent there.
+    const uint32_t xoff = ((uint32_t)(wave * ROWS + (lane >> 2)) * (uint32_t)K + (uint32_t)(lane & 3) * 4u) * 4u;
+    auto issue_x = [&](int tile, int c, int i, v4f& to) {
+        const int rows = rows_of(tile);
+        const __amdgpu_buffer_rsrc_t xres = make_rsrc(rows ? x + (long long)tile * T * K : x, (uint32_t)rows * (uint32_t)K * 4u);
+        const uint32_t outside = c * KC + i * 16 + (lane & 3) * 4 < K ? 0u : 0x80000000u;
+        to = __builtin_bit_cast(v4f, buf_load(xres, xoff | outside, (uint32_t)c * (KC * 4) + i * 64));
+    };
+    uint32_t least = 0xFFFFFFFFu;                  // smallest non-zero magnitude of this lane's row so far
+    char* const wr = lds[0] + ((lane >> 1) & 1) * PLANE + (wave * ROWS + (lane >> 2)) * 16 + (lane & 1) * 8;
+    auto publish_slot = [&](const v4f& v, int i, int buf) {
+        least = least_magnitude(v, least);
+        split4_to(wr + buf * IMAGE + i * (2 * PLANE), PART, v);
+    };
+    auto publish_mark = [&](int buf) { mark[buf][wave] = __builtin_amdgcn_ballot_w64(least < kTiny); };  // (all lanes write the same)
+
+    // ---- weights: three fragments (a, b, c) per step of 16 channels
+    const __amdgpu_buffer_rsrc_t wres = make_rsrc(wt, wt_bytes);
+    const uint32_t w0 = (uint32_t)(active ? pair : 0) * (uint32_t)n_steps * 3072u;
+    auto load_w = [&](int step, v8b (&w)[3]) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) w[s] = __builtin_bit_cast(v8b, buf_load(wres, (uint32_t)lane * 16u + s * 1024u, w0 + (uint32_t)step * 3072u));
+    };
+
+    v16f main[PX], cross[PX];
+    const char* const rd = lds[0] + (lane >> 5) * PLANE + (lane & 31) * 16;
+    auto read_x = [&](int buf, int s, int t, int part) {
+        return *(const v8b*)(rd + buf * IMAGE + s * (2 * PLANE) + t * 512 + part * PART);
+    };
+    // A step: two 32-pixel tiles at a time, their multiplies in turn (a multiply takes 32 cycles, one that adds to the same
+    // sum can follow after 56).  The activations' parts c, a, b are read a phase before they are used, into the
+    // registers that the phase before has finished with; a share of the staging of the next chunk goes between the multiplies.
+    v8b fa[2], fb[2], fc[2];
+    auto step = [&](int buf, int s, const v8b (&w)[3], auto&& share) {
+#pragma unroll
+        for (int t = 0; t < PX; t += 2) {
+            const int tn = t + 2 < PX ? t + 2 : 0, sn = t + 2 < PX ? s : s + 1;
+            auto mul = [&](const v8b& wp, const v8b (&xp)[2], v16f* sum) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) sum[t + u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wp, xp[u], sum[t + u], 0, 0, 0);
+            };
+            auto read = [&](int at_s, int at_t, int part, v8b (&to)[2]) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) to[u] = read_x(buf, at_s, at_t + u, part);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto spread = [&](auto n_c) {          // vector instructions go between the multiplies
+#pragma unroll
+                for (int i = 0; i < decltype(n_c)::value; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            read(s, t, 1, fb);
+            mul(w[0], fc, cross);
+            spread(std::integral_constant<int, 2>());
+            if (sn < STEPS) read(sn, tn, 2, fc);
+            mul(w[2], fa, cross);
+            mul(w[0], fa, main);
+            mul(w[1], fa, cross);
+            share(t);
+            spread(std::integral_constant<int, 6>());
+            if (sn < STEPS) read(sn, tn, 0, fa);
+            mul(w[1], fb, cross);
+            mul(w[0], fb, cross);
+            spread(std::integral_constant<int, 4>());
+        }
+    };
+
+    // ---- main + (cross + bias), activation, store
+    auto finish = [&](int tile, uint32_t marked) {
+        int l = lane;
+        asm volatile("" : "+v"(l));               // (offsets are worked out here: kept across the tiles they cost the loop its registers)
+        const long long pix0 = (long long)tile * T;
+        const int rows_valid = rows_of(tile);
+        const __amdgpu_buffer_rsrc_t yres = make_rsrc(y + pix0 * N, (uint32_t)rows_valid * (uint32_t)N * 4u);
+        const __amdgpu_buffer_rsrc_t bres = make_rsrc(bias, (uint32_t)n_bundles * 64u);
+        const int ch_lane = pair * 32 + (l >> 5) * 4, row_lane = l & 31;                  // + 8 * g, + 32 * t
+        float odd = 0.f;                           // NaN once a result is not finite
+        uint32_t low = 0xFFFFFFFFu;                // smallest non-zero sum
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const v4f bg = __builtin_bit_cast(v4f, buf_load(bres, (uint32_t)(ch_lane + 8 * g) * 4u, 0));
+#pragma unroll
+            for (int t = 0; t < PX; ++t) {
+                v4f o;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    o[i] = main[t][4 * g + i] + (cross[t][4 * g + i] + bg[i]);
+                    low = min(low, magnitude(main[t][4 * g + i]));
+                    cross[t][4 * g + i] = o[i];
+                }
+                odd = __builtin_fmaf((o.x + o.y) + (o.z + o.w), 0.f, odd);
+            }
+        }
+        uint32_t redo = 0;                         // bit 4 * t + g: to be done again
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd != odd || low < kTiny || marked != 0) != 0, 0)) {
+#pragma unroll
+            for (int t = 0; t < PX; ++t)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    bool bad = false;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float o = cross[t][4 * g + i], m = main[t][4 * g + i];
+                        bad |= o - o != 0.f || magnitude(m) < kTiny || ((marked >> t & 1u) && __builtin_fabsf(m) < tiny_sum);
+                    }
+                    if (bad && t * 32 + row_lane < rows_valid && ch_lane + 8 * g < N) redo |= 1u << (4 * t + g);
+                }
+        }
+        // Two groups of 32 pixels (lanes 0-31 and 32-63 hold different channels of a pixel) become twice all four groups
+        // of 16 pixels: 64 bytes of a pixel leave in one instruction.
+        const int ch_row = pair * 32 + ((l >> 4) & 1) * 8 + (l >> 5) * 4;                // + 16 * k
+#pragma unroll
+        for (int t = 0; t < PX; ++t)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                v4u o[2];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const auto r = __builtin_amdgcn_permlane16_swap(as_uint(cross[t][8 * k + i]), as_uint(cross[t][8 * k + 4 + i]), false, false);
+                    o[0][i] = r[0];
+                    o[1][i] = r[1];
+                }
+                const int ch = ch_row + 16 * k;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const uint32_t off = ch < N ? ((uint32_t)((l & 15) + 16 * u + t * 32) * (uint32_t)N + (uint32_t)ch) * 4u : 0xFFFFFFF0u;
+                    if (act == SBN_ACT_RELU) o[u] = __builtin_bit_cast(v4u, relu4(__builtin_bit_cast(v4f, o[u])));
+                    __builtin_amdgcn_raw_buffer_store_b128(o[u], yres, (int)off, 0, PIPE ? 0 : 2 /* slc: streaming */);
+                }
+            }
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(redo != 0) != 0, 0)) {
+            __builtin_amdgcn_s_waitcnt(0);         // the wave's stores above are done: these replace some of them
+#pragma unroll 1
+            for (int k = 0; k < 4 * PX; ++k)
+                if (redo >> k & 1u)
+                    exact_group(x, y, records, woff, wts, bias, K, N, n_chunks, pix0 + (k >> 2) * 32 + row_lane, ch_lane + 8 * (k & 3), act);
+        }
+    };
+
+    // The chunks of all the workgroup's tiles in one stream.  In step s of a chunk its weights of step s + 2 are asked
+    // for, slot s of the next chunk's activations, asked for a chunk ago, is published and, into the same
+    // registers, that of the chunk after it asked for.  (Loads return in order: weights two steps ahead leave the
+    // activations, which come from further away, three steps.)  Past the last tile the loads lie outside the buffer and
+    // bring zeros, which are published and never read.
+    v8b w[4][3];
+    v4f xs[NL];
+    {
+        v4f first[NL];
+#pragma unroll
+        for (int i = 0; i < NL; ++i) issue_x(pix_tile, 0, i, first[i]);
+        load_w(0, w[0]);
+        load_w(1, w[1]);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) issue_x(pix_tile, 1, i, xs[i]);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) publish_slot(first[i], i, 0);
+    }
+    publish_mark(0);
+    __syncthreads();
+    int buf = 0;
+    for (; pix_tile < n_pix_tiles; pix_tile += pix_stride) {
+#pragma unroll
+        for (int t = 0; t < PX; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) main[t][i] = cross[t][i] = 0.f;
+        uint32_t marked = 0;
+        for (int c = 0; c < n_chunks; ++c) {
+            const bool last = c + 1 == n_chunks;
+            if (last) {                            // bit t: the pixel of tile t holds tiny values
+                least = 0xFFFFFFFFu;               // (what is published from here on is the next tile's)
+#pragma unroll
+                for (int t = 0; t < PX; ++t)
+                    marked |= ((mark[buf][2 * t + ((lane >> 4) & 1)] >> (4 * (lane & 15))) & 15u) != 0 ? 1u << t : 0u;
+            }
+            const bool wrap = c + 2 >= n_chunks;   // the chunk after the next is the next tile's
+            const int far_tile = wrap ? pix_tile + pix_stride : pix_tile, far = wrap ? c + 2 - n_chunks : c + 2;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) fc[u] = read_x(buf, 0, u, 2);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) fa[u] = read_x(buf, 0, u, 0);
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+                load_w(s + 2 < STEPS ? STEPS * c + s + 2 : (last ? 0 : STEPS * (c + 1)) + s + 2 - STEPS, w[(s + 2) & 3]);
+                step(buf, s, w[s], [&](int t) {
+                    if (t) return;
+                    publish_slot(xs[s], s, buf ^ 1);
+                    issue_x(far_tile, far, s, xs[s]);
+                });
+            }
+            publish_mark(buf ^ 1);
+            buf ^= 1;
+            __syncthreads();
+        }
+        if (active) finish(pix_tile, marked);
+    }
+}
+
+template <int PX, int NWV, bool PIPE>
+int launch(const sbn_packed* p, const float* x, float* y, long long M, hipStream_t st)
+{
+    const sbn::DeviceLayout& L = p->dev;
+    constexpr int T = 32 * PX;
+    const long long n_pix_tiles = (M + T - 1) / T;
+    const int per_tile = 2 * NWV, n_col_tiles = (L.n_bundles + per_tile - 1) / per_tile;
+    // PIPE: one workgroup per compute unit, which walks its pixel tiles as one stream of chunks; otherwise a
+    // workgroup per tile.  The column tiles of a pixel tile go to one of the eight XCDs.
+    const long long room = PIPE ? std::max(1, L.cus / 8 / n_col_tiles) : (n_pix_tiles + 7) / 8;
+    const long long pix_slots = 8 * std::min(room, (n_pix_tiles + 7) / 8);
+    const long long grid = pix_slots * n_col_tiles;
+    if (grid > 0x7FFFFFFFll || n_pix_tiles + pix_slots > 0x7FFFFFFFll)
+        return sbn::fail(SBN_EINVAL, "too many pixels for one launch (%lld)", M);
+    // sums below this may have lost more than 2^-24 of themselves to activations below 2^-100 (c_in terms, each off by 2^-125 of a weight)
+    const float tiny_sum = std::max((float)p->c_in * L.w_top * 0x1p-101f, 0x1p-100f);
+    hipLaunchKernelGGL((conv1x1_wide_kernel<PX, NWV, PIPE>), dim3((unsigned)grid), dim3(64 * NWV), 0, st, x, y, L.d_wt,
+                       (uint32_t)(L.wt.size() * sizeof(uint16_t)), L.d_bias, L.d_records, L.d_woff, L.d_wts, M, p->c_in, p->c_out,
+                       L.n_bundles, L.n_chunks, n_col_tiles, (int)n_pix_tiles, (int)pix_slots, tiny_sum, p->act);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return sbn::fail(SBN_EHIP, "conv1x1 launch: %s", hipGetErrorString(e));
+    return SBN_OK;
+}
+
+}  // namespace
+
+namespace sbn {
+
+// The wide multiplies take the time of all c_in x c_out weights, channels past c_out in a 128-channel tile included;
+// the 32-bit forms that of the kept ones plus a share that does not shrink with them.  Gain over the 32-bit
+// form that the rule replaces, at a share kept of 1 / 0.7 / 0.6 / 0.5 / 0.4 (the line lies in the gap marked |):
+//   c_in  128, 25088 pixels x 128     1.16 | 1.03 0.96 0.91
+//         256, 50176 x 256            1.52 1.10 | 1.01 0.91 0.79
+//         512, 50176 x 512            1.66 1.32 1.19 1.08 | 0.97
+//         768, 10000 x 384            1.94 1.55 1.43 1.30 1.15 |
+//        1024, 12544 x 1024           1.62 1.31 1.22 1.13 1.00 |
+// (Fewer than 96 output channels leave a quarter of a tile or more idle.)
+bool conv1x1_wide_pays(const sbn_packed* p)
+{
+    const long long kept = (long long)p->kidx.size() * p->go * p->gi;                 // of all filters
+    const long long padded = (p->c_out + 127) / 128 * 128;
+    return p->c_out > 80 && 4 * kept >= (p->c_in + 384) * padded;
+}
+
+// form 0: 128 x 256 tiles where they fill the rounds that one tile per compute unit makes, else 64 x 128 tiles (512 x 512:
+// 100352 pixels, 6.1 rounds of tiles, 260 us against 298; 50176 pixels, 3.06 rounds, 149 against 135; 1024 x 1024:
+// 6272 pixels, 0.77 of a round, 69 us against 79).  Layers of few chunks spend too much of a tile on its ends
+// (128 x 128, 200704 pixels: 84 against 55).
+int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long M, int form, void* stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    if (!p->dev.d_wt) return fail(SBN_EINVAL, "internal error: the layer has no bfloat16 triples");
+    if (!form) {
+        const long long col_tiles = (p->c_out + 255) / 256, tiles = (M + 127) / 128 * col_tiles, cus = p->dev.cus;
+        const long long rounds = (tiles + cus - 1) / cus;
+        const bool fits = col_tiles * 256 * 7 <= p->c_out * 8;                        // at most an eighth of the channels past c_out
+        const bool filled = 100 * tiles >= (rounds == 1 ? 75 : 85) * rounds * cus;
+        form = fits && filled && p->c_in >= 384 ? 2256 : 2064;
+    }
+    return form == 2256 ? launch<4, 8, true>(p, x, y, M, st) : launch<2, 4, false>(p, x, y, M, st);
+}
+
+}  // namespace sbn

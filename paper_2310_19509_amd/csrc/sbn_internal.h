@@ -79,17 +79,23 @@ struct DeviceLayout {
     // for absent pieces.  Empty when the layer does not qualify.
     std::vector<uint32_t> desc_s;
     std::vector<float> wts_s;
-    // Layers whose outputs sum at least kHalfMinKept products also get their weights as pairs of
-    // 16-bit floats for the wide matrix instructions (see sbn_conv1x1_half.hip): filter f's weights
+    // 3x3 layers whose outputs sum at least kHalfMinKept products also get their weights as pairs of
+    // 16-bit floats for the wide matrix instructions (see sbn_conv3x3_half.hip): filter f's weights
     // times 2^-wh_exp[f] are hi + lo / 2048, hi the nearest 16-bit float, lo the nearest 16-bit
     // float to 2048 times what hi leaves.  Zeros stand for removed weights.  One FRAGMENT = the
     // A operand of a 16 x 16 x 32 multiply, [lane 64][8]: lane l holds filter l % 16 of the bundle,
-    // channels 8 * (l / 16) .. + 7 of the 32.  wh[bundle][step][hi, lo][64][8], a step = 32 input
-    // channels (1x1: an even number of steps, the last may be all zeros) or one tap of 32 input channels (3x3).  Empty when the layer
-    // does not qualify.
+    // channels 8 * (l / 16) .. + 7 of the 32.  wh[bundle][step][hi, lo][64][8], a step = one tap of 32 input
+    // channels.  Empty when the layer does not qualify.
     int n_steps = 0;                      // fragments pairs per bundle
     std::vector<uint16_t> wh;
     std::vector<int32_t> wh_exp;          // [n_bundles * 16]
+    // 1x1 layers: the weights as triples of bfloat16 for the wide matrix instructions (see sbn_conv1x1_wide.hip),
+    // w = a + b + c exactly, zeros for removed weights.  One FRAGMENT = the A operand of a 32 x 32 x 16
+    // multiply, [lane 64][8]: lane l holds filter l % 32 of the 32 (two bundles), channels 8 * (l / 32) .. + 7 of the 16.
+    // wt[pair of bundles][step][a, b, c][64][8], a step = 16 input channels, four per chunk (past c_in and c_out:
+    // zeros).  Empty unless conv1x1_wide_pays (or a wide form was forced while the layer was packed).
+    std::vector<uint16_t> wt;
+    float w_top = 0.0f;                   // largest magnitude of a weight
     // device copies (one allocation)
     void* d_blob = nullptr;
     uint32_t* d_records = nullptr;
@@ -102,6 +108,7 @@ struct DeviceLayout {
     float* d_wts_s = nullptr;
     uint16_t* d_wh = nullptr;             // NULL when the layer has no 16-bit pairs
     int32_t* d_wh_exp = nullptr;
+    uint16_t* d_wt = nullptr;             // NULL when the layer has no triples
 };
 
 }  // namespace sbn
@@ -133,7 +140,10 @@ void release_device_layout(sbn_packed* p);
 
 // Kernel launchers (defined in the .hip files).
 int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long m, void* stream);
-int launch_conv1x1_half(const sbn_packed* p, const float* x, float* y, long long m, int form, void* stream);
+// Whether a layer keeps enough for the wide multiplies, whatever the pixels: the launch rule and the packer, which
+// builds the triples only where a launch can come to use them.
+bool conv1x1_wide_pays(const sbn_packed* p);
+int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long m, int form, void* stream);
 bool conv3x3_half_takes(const sbn_packed* p, int n, int h, int w);
 int launch_conv3x3_half(const sbn_packed* p, const float* x, float* y, int n, int h, int w, int form, void* stream);
 int launch_conv3x3(const sbn_packed* p, const float* x, float* y, int n, int h, int w, void* stream);

@@ -46,13 +46,13 @@ static void build_half_pairs(sbn_packed* p)
     L.n_steps = 0;
     const int taps = p->kh * p->kw;
     const size_t kept = p->kidx.size() * (size_t)p->go * p->gi * taps;
-    if (p->c_in % 4 || kept < (size_t)kHalfMinKept * p->c_out) return;
-    const int n_steps = taps == 1 ? L.n_chunks * 2 : L.n_chunks32 * taps;
+    if (taps == 1 || p->c_in % 4 || kept < (size_t)kHalfMinKept * p->c_out) return;
+    const int n_steps = L.n_chunks32 * taps;
     const size_t n_filters = (size_t)L.n_bundles * kBundleChannels, wstride = (size_t)taps * 64;
     if (n_filters * (size_t)n_steps * 128 >= 0xFFFFFFFFull) return;      // 32-bit byte offsets on the device
 
     // Per filter: the power of two that takes its largest weight to [2^14, 2^15).  An entry holds its
-    // weights as [g][co][ci] (1x1) or [tap][g][ci][co] (3x3); per entry, the largest of every filter first.
+    // weights as [tap][g][ci][co]; per entry, the largest of every filter first.
     auto bits_of = [](float v) {
         uint32_t u;
         std::memcpy(&u, &v, 4);
@@ -64,12 +64,8 @@ static void build_half_pairs(sbn_packed* p)
         for (size_t e = wo[0]; e < wo[L.n_chunks]; ++e) {
             const float* w = &L.wts[e * wstride];
             uint32_t* m = &piece[e * kBundleChannels];
-            if (taps == 1)
-                for (int f = 0; f < kBundleChannels; ++f)
-                    m[f] = std::max(std::max(bits_of(w[f * 4]), bits_of(w[f * 4 + 1])), std::max(bits_of(w[f * 4 + 2]), bits_of(w[f * 4 + 3])));
-            else
-                for (int i = 0; i < taps * kBundleGroups; ++i, w += 16)
-                    for (int j = 0; j < 16; ++j) m[i % kBundleGroups * 4 + j % 4] = std::max(m[i % kBundleGroups * 4 + j % 4], bits_of(w[j]));
+            for (int i = 0; i < taps * kBundleGroups; ++i, w += 16)
+                for (int j = 0; j < 16; ++j) m[i % kBundleGroups * 4 + j % 4] = std::max(m[i % kBundleGroups * 4 + j % 4], bits_of(w[j]));
             for (int f = 0; f < kBundleChannels; ++f) top[(size_t)b * kBundleChannels + f] = std::max(top[(size_t)b * kBundleChannels + f], m[f]);
         }
     }
@@ -111,13 +107,66 @@ static void build_half_pairs(sbn_packed* p)
                             const float sc = scale[(size_t)b * kBundleChannels + f];
                             uint16_t* const to = frag + (size_t)(kb4 / 2 * 16 + f) * 8 + (kb4 % 2) * 4;
                             for (int ci = 0; ci < 4; ++ci) {
-                                const float v = w[taps == 1 ? f * 4 + ci : t * 64 + g * 16 + ci * 4 + co] * sc;
+                                const float v = w[t * 64 + g * 16 + ci * 4 + co] * sc;
                                 float hi, lo;
                                 to[ci] = to_half(v, &hi);
                                 to[512 + ci] = to_half((v - hi) * 2048.0f, &lo);
                             }
                         }
                     }
+            }
+        }
+}
+
+// Nearest bfloat16 (ties to even) of a finite v that does not overflow, returned as bits; *back is its value.
+static inline uint16_t to_bf16(float v, float* back)
+{
+    uint32_t u;
+    std::memcpy(&u, &v, 4);
+    u = (u + 0x7FFFu + (u >> 16 & 1u)) & 0xFFFF0000u;
+    std::memcpy(back, &u, 4);
+    return (uint16_t)(u >> 16);
+}
+
+// The weights as exact triples of bfloat16 (DeviceLayout::wt).
+static void build_triples(sbn_packed* p)
+{
+    DeviceLayout& L = p->dev;
+    L.wt.clear();
+    L.w_top = 0.0f;
+    if (p->kh * p->kw != 1 || p->c_in % 4 || p->c_in <= kChunk) return;
+    if (!conv1x1_wide_pays(p) && forced_kernel_form(SBN_CONV1X1) < 2000) return;
+    const size_t n_pairs = ((size_t)L.n_bundles + 1) / 2, n_steps = (size_t)L.n_chunks * 4;
+    if (n_pairs * n_steps * 3072 >= 0xFFFFFFFFull) return;               // 32-bit byte offsets on the device
+    // Infinite, NaN and nearly infinite weights (the first bfloat16 would overflow), and weights whose last bits
+    // lie below the smallest normal bfloat16, stay with the 32-bit kernels.
+    uint32_t top = 0;
+    for (const float v : L.wts) {
+        uint32_t u;
+        std::memcpy(&u, &v, 4);
+        u &= 0x7FFFFFFFu;
+        if (u >= 0x7F7F8000u || (u != 0 && u < 0x0D800000u)) return;     // (2^-100)
+        top = std::max(top, u);
+    }
+    std::memcpy(&L.w_top, &top, 4);
+    L.wt.assign(n_pairs * n_steps * 1536, 0);
+    for (int b = 0; b < L.n_bundles; ++b)
+        for (int c = 0; c < L.n_chunks; ++c) {
+            const uint32_t* r = &L.records[((size_t)b * L.n_chunks + c) * kSlots];
+            const float* w = &L.wts[(size_t)L.woff[(size_t)b * (L.n_chunks + 1) + c] * 64];
+            for (int q = 0; q < kSlots && r[q] != 0; ++q, w += 64) {
+                const int piece = (int)(r[q] >> 12);                     // channels 4 * piece .. + 3 of the 64
+                uint16_t* const frag = &L.wt[((size_t)(b / 2) * n_steps + (size_t)c * 4 + piece / 4) * 1536];
+                for (int f = 0; f < kBundleChannels; ++f) {              // (removed groups' weights are zeros)
+                    uint16_t* const to = frag + (size_t)(piece % 4 / 2 * 32 + b % 2 * kBundleChannels + f) * 8 + piece % 2 * 4;
+                    for (int ci = 0; ci < 4; ++ci) {
+                        const float v = w[f * 4 + ci];
+                        float hi, mid, lo;
+                        to[ci] = to_bf16(v, &hi);
+                        to[512 + ci] = to_bf16(v - hi, &mid);
+                        to[1024 + ci] = to_bf16(v - hi - mid, &lo);
+                    }
+                }
             }
         }
 }
@@ -232,6 +281,7 @@ void build_device_layout(sbn_packed* p)
             }
     }
     build_half_pairs(p);
+    build_triples(p);
     L.bias_padded.assign((size_t)L.n_bundles * kBundleChannels, 0.0f);
     std::copy(p->bias.begin(), p->bias.end(), L.bias_padded.begin());
 }
@@ -288,9 +338,11 @@ const char* check_device_layout(const sbn_packed* p)
         return "every-piece weights without masks";
     }
     if (L.wh.empty() ? !L.wh_exp.empty() || L.n_steps != 0
-                     : L.n_steps != (p->kh == 1 ? 2 * L.n_chunks : 9 * L.n_chunks32) || L.wh.size() != (size_t)L.n_bundles * L.n_steps * 1024 ||
+                     : p->kh != 3 || L.n_steps != 9 * L.n_chunks32 || L.wh.size() != (size_t)L.n_bundles * L.n_steps * 1024 ||
                            L.wh_exp.size() != (size_t)L.n_bundles * kBundleChannels)
         return "16-bit pair table sizes";
+    if (!L.wt.empty() && (p->kh != 1 || p->c_in <= kChunk || L.wt.size() != (size_t)((L.n_bundles + 1) / 2) * L.n_chunks * 4 * 1536))
+        return "bfloat16 triple table size";
     return nullptr;
 }
 
@@ -322,7 +374,8 @@ int upload_device_layout(sbn_packed* p)
     const size_t b_wts_s = align256(L.wts_s.size() * sizeof(float));
     const size_t b_wh = align256(L.wh.size() * sizeof(uint16_t));
     const size_t b_wh_exp = align256(L.wh_exp.size() * sizeof(int32_t));
-    const size_t total = b_rec + b_woff + b_rec32 + b_woff32 + b_wts + b_bias + b_desc_s + b_wts_s + b_wh + b_wh_exp;
+    const size_t b_wt = align256(L.wt.size() * sizeof(uint16_t));
+    const size_t total = b_rec + b_woff + b_rec32 + b_woff32 + b_wts + b_bias + b_desc_s + b_wts_s + b_wh + b_wh_exp + b_wt;
     // (written once: not zeroed first, the gaps behind the arrays are; before the device memory, as it may throw)
     std::unique_ptr<char[]> host(new char[total]);
     char* blob = nullptr;
@@ -348,6 +401,7 @@ int upload_device_layout(sbn_packed* p)
     L.d_wts_s = (float*)put(L.wts_s.data(), L.wts_s.size() * sizeof(float), b_wts_s);
     L.d_wh = (uint16_t*)put(L.wh.data(), L.wh.size() * sizeof(uint16_t), b_wh);
     L.d_wh_exp = (int32_t*)put(L.wh_exp.data(), L.wh_exp.size() * sizeof(int32_t), b_wh_exp);
+    L.d_wt = (uint16_t*)put(L.wt.data(), L.wt.size() * sizeof(uint16_t), b_wt);
     e = hipMemcpy(blob, host.get(), total, hipMemcpyHostToDevice);
     (void)hipSetDevice(prev);
     if (e != hipSuccess) {

@@ -1,0 +1,67 @@
+// Device helpers of the kernels on triples of bfloat16 (sbn_conv1x1_wide.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace sbn_wide {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+
+// Magnitudes are compared as twice their bits (the sign drops out) less one (zero comes out largest).
+constexpr uint32_t kTiny = 2u * 0x0D800000u - 1u;                      // 2^-100
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ v4u buf_load(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t scalar_off)
+{
+    return __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)scalar_off, 0));
+}
+__device__ __forceinline__ uint32_t as_uint(float f) { return __builtin_bit_cast(uint32_t, f); }
+__device__ __forceinline__ uint32_t magnitude(float f) { return (as_uint(f) << 1) - 1u; }
+__device__ __forceinline__ uint32_t least_magnitude(const v4f& v, uint32_t least)
+{
+    return min(min(min(magnitude(v.x), magnitude(v.y)), least), min(magnitude(v.z), magnitude(v.w)));
+}
+
+// Two values as triples a + b + c, exact: a the nearest bfloat16, b the nearest one to the rest (16 bits and a
+// sign, so that at most 8 bits are left for c).
+__device__ __forceinline__ void split2(float v0, float v1, uint32_t& a, uint32_t& b, uint32_t& c)
+{
+    const v2b h = __builtin_convertvector((v2f){v0, v1}, v2b);
+    const float r0 = v0 - (float)h.x, r1 = v1 - (float)h.y;
+    const v2b m = __builtin_convertvector((v2f){r0, r1}, v2b);
+    const v2b l = __builtin_convertvector((v2f){r0 - (float)m.x, r1 - (float)m.y}, v2b);
+    a = __builtin_bit_cast(uint32_t, h);
+    b = __builtin_bit_cast(uint32_t, m);
+    c = __builtin_bit_cast(uint32_t, l);
+}
+
+// Four values as triples, written to LDS: a at p, b at p + part, c at p + 2 * part.
+__device__ __forceinline__ void split4_to(char* p, int part, const v4f& v)
+{
+    uint32_t a0, a1, b0, b1, c0, c1;
+    split2(v.x, v.y, a0, b0, c0);
+    split2(v.z, v.w, a1, b1, c1);
+    *(v2u*)p = (v2u){a0, a1};
+    *(v2u*)(p + part) = (v2u){b0, b1};
+    *(v2u*)(p + 2 * part) = (v2u){c0, c1};
+}
+
+__device__ __forceinline__ v4f relu4(v4f v)                              // as in the 32-bit form
+{
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    const v4i b = __builtin_bit_cast(v4i, v);
+    return __builtin_bit_cast(v4f, (v4i){b.x > 0 ? b.x : 0, b.y > 0 ? b.y : 0, b.z > 0 ? b.z : 0, b.w > 0 ? b.w : 0});
+}
+
+}  // namespace sbn_wide
