@@ -324,8 +324,8 @@ int sbn_conv3x3_sparse(const sbn_packed_t* p, const float* x, float* y,
  * choice otherwise) or SBN_CONV3X3 (1, 2, 3: one pixel per lane, two pixels per
  * lane, entry-ahead fetch; 32: entry-ahead with the input channels split over
  * two halves of an eight-wave workgroup; 2128, 2064, 2065: 128 x 64 tiles, 64 x 64
- * tiles and 64 x 64 tiles with two halves on pairs of 16-bit floats, for layers of
- * stride 1 and at least 128 kept weights per filter and images 4 to 127 wide
+ * tiles and 64 x 64 tiles with two halves on triples of bfloat16, for layers of
+ * stride 1 with the tables, as above, and images 4 to 127 wide
  * and at least 4 high, the automatic choice otherwise).  Layers whose shape leaves no choice (c_in <= 64,
  * c_in not a multiple of 4, stride 2) ignore it.  Unknown values: SBN_EINVAL.
  * Not synchronised with launches in flight on other threads.

@@ -3,7 +3,7 @@
 //
 // v_mfma_f32_32x32x16_bf16 multiplies 16 times as many pairs per cycle as the 32-bit instructions, so even
 // six of them per product, over blocks filled up with the removed weights' zeros, take less time than 4x4x1
-// multiplies over the kept blocks where a layer keeps enough of them (launch_conv1x1 has the rule).  Every
+// multiplies over the kept blocks where a layer keeps enough of them (conv1x1_wide_pays has the rule).  Every
 // operand is the exact sum of three bfloat16, v = a + b + c (8 + 8 + 8 bits; the exponent range is that of
 // 32-bit floats, so there is nothing to scale and no value depends on its neighbours).  Of the nine products
 // six are formed,
@@ -221,28 +221,8 @@ __global__ __launch_bounds__(64 * NWV, PIPE ? 2 : 3) void conv1x1_wide_kernel(
                     if (bad && t * 32 + row_lane < rows_valid && ch_lane + 8 * g < N) redo |= 1u << (4 * t + g);
                 }
         }
-        // Two groups of 32 pixels (lanes 0-31 and 32-63 hold different channels of a pixel) become twice all four groups
-        // of 16 pixels: 64 bytes of a pixel leave in one instruction.
-        const int ch_row = pair * 32 + ((l >> 4) & 1) * 8 + (l >> 5) * 4;                // + 16 * k
 #pragma unroll
-        for (int t = 0; t < PX; ++t)
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                v4u o[2];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const auto r = __builtin_amdgcn_permlane16_swap(as_uint(cross[t][8 * k + i]), as_uint(cross[t][8 * k + 4 + i]), false, false);
-                    o[0][i] = r[0];
-                    o[1][i] = r[1];
-                }
-                const int ch = ch_row + 16 * k;
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const uint32_t off = ch < N ? ((uint32_t)((l & 15) + 16 * u + t * 32) * (uint32_t)N + (uint32_t)ch) * 4u : 0xFFFFFFF0u;
-                    if (act == SBN_ACT_RELU) o[u] = __builtin_bit_cast(v4u, relu4(__builtin_bit_cast(v4f, o[u])));
-                    __builtin_amdgcn_raw_buffer_store_b128(o[u], yres, (int)off, 0, PIPE ? 0 : 2 /* slc: streaming */);
-                }
-            }
+        for (int t = 0; t < PX; ++t) store_tile<PIPE ? 0 : 2>(cross[t], yres, t * 32, pair * 32, N, act == SBN_ACT_RELU, l);
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(redo != 0) != 0, 0)) {
             __builtin_amdgcn_s_waitcnt(0);         // the wave's stores above are done: these replace some of them
 #pragma unroll 1
@@ -338,26 +318,10 @@ int launch(const sbn_packed* p, const float* x, float* y, long long M, hipStream
 
 namespace sbn {
 
-// The wide multiplies take the time of all c_in x c_out weights, channels past c_out in a 128-channel tile included;
-// the 32-bit forms that of the kept ones plus a share that does not shrink with them.  Gain over the 32-bit
-// form that the rule replaces, at a share kept of 1 / 0.7 / 0.6 / 0.5 / 0.4 (the line lies in the gap marked |):
-//   c_in  128, 25088 pixels x 128     1.16 | 1.03 0.96 0.91
-//         256, 50176 x 256            1.52 1.10 | 1.01 0.91 0.79
-//         512, 50176 x 512            1.66 1.32 1.19 1.08 | 0.97
-//         768, 10000 x 384            1.94 1.55 1.43 1.30 1.15 |
-//        1024, 12544 x 1024           1.62 1.31 1.22 1.13 1.00 |
-// (Fewer than 96 output channels leave a quarter of a tile or more idle.)
-bool conv1x1_wide_pays(const sbn_packed* p)
-{
-    const long long kept = (long long)p->kidx.size() * p->go * p->gi;                 // of all filters
-    const long long padded = (p->c_out + 127) / 128 * 128;
-    return p->c_out > 80 && 4 * kept >= (p->c_in + 384) * padded;
-}
-
-// form 0: 128 x 256 tiles where they fill the rounds that one tile per compute unit makes, else 64 x 128 tiles (512 x 512:
-// 100352 pixels, 6.1 rounds of tiles, 260 us against 298; 50176 pixels, 3.06 rounds, 149 against 135; 1024 x 1024:
-// 6272 pixels, 0.77 of a round, 69 us against 79).  Layers of few chunks spend too much of a tile on its ends
-// (128 x 128, 200704 pixels: 84 against 55).
+// form 0: 128 x 256 tiles where they fill three quarters of the rounds that one tile per compute unit makes, else 64 x 128
+// tiles (512 x 512: 100352 pixels, 6.1 rounds, 261 us against 310; 50176 pixels, 3.06 of 4 rounds, 149 against 165; 9000 pixels,
+// 0.55 of a round, 40 against 34; 1024 x 1024, 6272 pixels, 0.77 of a round, 73 against 86).  Layers of few chunks
+// spend too much of a tile on its ends (128 x 128, 200704 pixels: 83 against 69; 256 x 256, 50176: 52 against 45).
 int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long M, int form, void* stream)
 {
     hipStream_t st = (hipStream_t)stream;
@@ -366,7 +330,7 @@ int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long
         const long long col_tiles = (p->c_out + 255) / 256, tiles = (M + 127) / 128 * col_tiles, cus = p->dev.cus;
         const long long rounds = (tiles + cus - 1) / cus;
         const bool fits = col_tiles * 256 * 7 <= p->c_out * 8;                        // at most an eighth of the channels past c_out
-        const bool filled = 100 * tiles >= (rounds == 1 ? 75 : 85) * rounds * cus;
+        const bool filled = 4 * tiles >= 3 * rounds * cus;
         form = fits && filled && p->c_in >= 384 ? 2256 : 2064;
     }
     return form == 2256 ? launch<4, 8, true>(p, x, y, M, st) : launch<2, 4, false>(p, x, y, M, st);

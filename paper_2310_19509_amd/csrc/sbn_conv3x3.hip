@@ -456,14 +456,8 @@ int launch_conv3x3(const sbn_packed* p, const float* x, float* y, int n, int h, 
         return fail(SBN_ESHAPE, "3x3 layers need c_in to be a multiple of 4 on the device (got %d)", p->c_in);
     hipStream_t st = (hipStream_t)stream;
     const int forced = forced_kernel_form(SBN_CONV3X3);
-    if (forced >= 2000 && conv3x3_half_takes(p, n, h, w)) return launch_conv3x3_half(p, x, y, n, h, w, forced, stream);
-    // Layers with 16-bit pairs, down to 18 % of the kernels: the time of the wide instructions does not depend
-    // on the sparsity (28 x 28 x 128, batch 32: 27-30 us), this form's does (58 us at 50 %, 40 us at 70 %,
-    // 23 us at 90 %).  Their sums are closer to the exact result than this form's (relative error in units of
-    // 1e-8: 11-14 against 12-25 over the shapes of the four layers).
-    if (!forced && conv3x3_half_takes(p, n, h, w) && p->dev.n_bundles >= 3 &&
-        (double)p->kidx.size() * p->go * p->gi >= 0.18 * p->c_out * p->c_in)
-        return launch_conv3x3_half(p, x, y, n, h, w, 0, stream);
+    if (forced >= 2000 && conv3x3_wide_takes(p, n, h, w)) return launch_conv3x3_wide(p, x, y, n, h, w, forced, stream);
+    if (!forced && conv3x3_wide_chosen(p, n, h, w)) return launch_conv3x3_wide(p, x, y, n, h, w, 0, stream);
     if (p->stride == 2) return launch<2, 1, false>(p, x, y, n, h, w, st);
     // Form, from timings of ResNet-50-shaped layers at batches 4..128 (thresholds in workgroups per
     // compute unit of the device the layer lives on): up to one

@@ -1051,8 +1051,7 @@ int sbn_packed_layout(const sbn_packed_t* p, size_t* entries, size_t* table_byte
     if (entries) *entries = L.n_entries;
     if (table_bytes)
         *table_bytes = (L.records.size() + L.woff.size() + L.records32.size() + L.woff32.size() + L.desc_s.size()) * sizeof(uint32_t) +
-                       (L.wts.size() + L.wts_s.size() + L.bias_padded.size()) * sizeof(float) + (L.wh.size() + L.wt.size()) * sizeof(uint16_t) +
-                       L.wh_exp.size() * sizeof(int32_t);
+                       (L.wts.size() + L.wts_s.size() + L.bias_padded.size()) * sizeof(float) + L.wt.size() * sizeof(uint16_t);
     if (every_piece) *every_piece = L.desc_s.empty() ? 0 : 1;
     return SBN_OK;
 }

@@ -56,7 +56,6 @@ constexpr int kBundleGroups = 4;                       // groups of 4 filters pe
 constexpr int kBundleChannels = 4 * kBundleGroups;     // 16 output channels per bundle
 constexpr int kChunk = 64;                             // input channels per record
 constexpr int kSlots = kChunk / 4;                     // descriptors per record
-constexpr int kHalfMinKept = 128;                      // mean products per output from which the 16-bit pairs are built (sbn_layout.cpp)
 constexpr double kStaticWalkMinFill = 0.60;            // share of (bundle, piece) pairs kept, from which the every-piece tables are built
 
 struct DeviceLayout {
@@ -79,21 +78,11 @@ struct DeviceLayout {
     // for absent pieces.  Empty when the layer does not qualify.
     std::vector<uint32_t> desc_s;
     std::vector<float> wts_s;
-    // 3x3 layers whose outputs sum at least kHalfMinKept products also get their weights as pairs of
-    // 16-bit floats for the wide matrix instructions (see sbn_conv3x3_half.hip): filter f's weights
-    // times 2^-wh_exp[f] are hi + lo / 2048, hi the nearest 16-bit float, lo the nearest 16-bit
-    // float to 2048 times what hi leaves.  Zeros stand for removed weights.  One FRAGMENT = the
-    // A operand of a 16 x 16 x 32 multiply, [lane 64][8]: lane l holds filter l % 16 of the bundle,
-    // channels 8 * (l / 16) .. + 7 of the 32.  wh[bundle][step][hi, lo][64][8], a step = one tap of 32 input
-    // channels.  Empty when the layer does not qualify.
-    int n_steps = 0;                      // fragments pairs per bundle
-    std::vector<uint16_t> wh;
-    std::vector<int32_t> wh_exp;          // [n_bundles * 16]
-    // 1x1 layers: the weights as triples of bfloat16 for the wide matrix instructions (see sbn_conv1x1_wide.hip),
-    // w = a + b + c exactly, zeros for removed weights.  One FRAGMENT = the A operand of a 32 x 32 x 16
+    // The weights as triples of bfloat16 for the wide matrix instructions (see sbn_conv1x1_wide.hip), w = a + b + c exactly, zeros for removed weights.  One FRAGMENT = the A operand of a 32 x 32 x 16
     // multiply, [lane 64][8]: lane l holds filter l % 32 of the 32 (two bundles), channels 8 * (l / 32) .. + 7 of the 16.
-    // wt[pair of bundles][step][a, b, c][64][8], a step = 16 input channels, four per chunk (past c_in and c_out:
-    // zeros).  Empty unless conv1x1_wide_pays (or a wide form was forced while the layer was packed).
+    // wt[pair of bundles][step][a, b, c][64][8]; 1x1: a step = 16 input channels, four per chunk; 3x3: 32 input channels
+    // are 18 steps, two per tap (past c_in and c_out: zeros).  Empty unless conv1x1_wide_pays or conv3x3_wide_pays (or a
+    // wide form was forced while the layer was packed).
     std::vector<uint16_t> wt;
     float w_top = 0.0f;                   // largest magnitude of a weight
     // device copies (one allocation)
@@ -106,8 +95,6 @@ struct DeviceLayout {
     float* d_bias = nullptr;
     uint32_t* d_desc_s = nullptr;         // NULL when the layer has no every-piece tables
     float* d_wts_s = nullptr;
-    uint16_t* d_wh = nullptr;             // NULL when the layer has no 16-bit pairs
-    int32_t* d_wh_exp = nullptr;
     uint16_t* d_wt = nullptr;             // NULL when the layer has no triples
 };
 
@@ -134,18 +121,21 @@ namespace sbn {
 void build_device_layout(sbn_packed* p);
 // Invariants of p->dev that the kernels rely on; NULL if they hold, else what is violated.
 const char* check_device_layout(const sbn_packed* p);
+// Whether a layer keeps enough for the wide multiplies, whatever the pixels: the launch rules and the packer, which
+// builds the triples only where a launch can come to use them.
+bool conv1x1_wide_pays(const sbn_packed* p);
+bool conv3x3_wide_pays(const sbn_packed* p);
+double conv3x3_share_kept(const sbn_packed* p);
 // Uploads p->dev to p->device.  Returns SBN_OK or an error code.
 int upload_device_layout(sbn_packed* p);
 void release_device_layout(sbn_packed* p);
 
 // Kernel launchers (defined in the .hip files).
 int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long m, void* stream);
-// Whether a layer keeps enough for the wide multiplies, whatever the pixels: the launch rule and the packer, which
-// builds the triples only where a launch can come to use them.
-bool conv1x1_wide_pays(const sbn_packed* p);
 int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long m, int form, void* stream);
-bool conv3x3_half_takes(const sbn_packed* p, int n, int h, int w);
-int launch_conv3x3_half(const sbn_packed* p, const float* x, float* y, int n, int h, int w, int form, void* stream);
+bool conv3x3_wide_takes(const sbn_packed* p, int n, int h, int w);       // whether the kernel takes these extents,
+bool conv3x3_wide_chosen(const sbn_packed* p, int n, int h, int w);      // and whether it is the faster one for them
+int launch_conv3x3_wide(const sbn_packed* p, const float* x, float* y, int n, int h, int w, int form, void* stream);
 int launch_conv3x3(const sbn_packed* p, const float* x, float* y, int n, int h, int w, void* stream);
 int launch_dw3x3(const float* x, float* y, const float* w_dev, const float* b_dev, int n, int h, int w,
                  int c, int stride, int act, void* stream);

@@ -12,111 +12,39 @@
 
 namespace sbn {
 
-// Nearest 16-bit float (ties to even) of a finite v, |v| < 65520, returned as bits; *back is its value.
-static uint16_t to_half(float v, float* back)
+// The wide multiplies take the time of all c_in x c_out weights, channels past c_out in a 128-channel tile included;
+// the 32-bit forms that of the kept ones plus a share that does not shrink with them.  Gain over the 32-bit
+// form that the rule replaces, at a share kept of 1 / 0.7 / 0.6 / 0.5 / 0.4 (layers in turn, so that weights are not in
+// the L2; the line lies in the gap marked |):
+//   c_in  128, 25088 pixels x 128     1.12 | 1.00 0.97 0.91
+//         256, 50176 x 256            1.46 1.12 | 1.02 0.93 0.83
+//         512, 50176 x 512            1.57 1.32 1.20 1.06 | 0.97
+//         768, 10000 x 384            1.92 1.48 1.32 1.18 | 1.09
+//        1024, 12544 x 1024           1.69 1.34 1.23 1.12 1.00 |
+// (Fewer than 96 output channels leave a quarter of a tile or more idle.)
+bool conv1x1_wide_pays(const sbn_packed* p)
 {
-    uint32_t u;
-    std::memcpy(&u, &v, 4);
-    const uint32_t sign = u >> 16 & 0x8000u;
-    u &= 0x7FFFFFFFu;
-    float a;
-    std::memcpy(&a, &u, 4);
-    if (u < 0x38800000u) {                       // below 2^-14: a multiple of 2^-24; 0.5 has that spacing
-        const float r = (a + 0.5f) - 0.5f;
-        *back = sign ? -r : r;
-        return (uint16_t)(sign | (uint32_t)(r * 16777216.0f));
-    }
-    u += 0xFFFu + (u >> 13 & 1u);
-    u &= ~0x1FFFu;
-    std::memcpy(&a, &u, 4);
-    *back = sign ? -a : a;
-    return (uint16_t)(sign | ((u - 0x38000000u) >> 13));
+    const long long kept = (long long)p->kidx.size() * p->go * p->gi;                 // of all filters
+    const long long padded = (p->c_out + 127) / 128 * 128;
+    return p->c_out > 80 && 16 * kept >= (5ll * p->c_in + 1280) * padded;
 }
 
-// The weights as pairs of 16-bit floats (DeviceLayout::wh).  Only layers whose outputs sum enough
-// products: a pair carries 22 to 23 bits of a 24-bit weight and the product of the two low halves is
-// left out, about 9e-8 of the result in all, whatever the length of the sum, while a sum of n
-// products in 32-bit floats loses about 1e-8 * sqrt(n) (simulated and measured: 8.2e-8 against 9.2e-8
-// with 64 products, 1.09e-7 against 9.8e-8 with 128, 2.0e-7 against 1.1e-7 with 512).
-static void build_half_pairs(sbn_packed* p)
+// Kernels that a layer keeps, over all that the wide multiplies go through (input channels in 32s, output channels in
+// 64s).  The multiplies' time does not depend on it, the 32-bit form's does; us, 32-bit form against this one (layers in
+// turn, so that weights are not in the L2):
+//   share kept                   0.5       0.4       0.3       0.2
+//   3 x 23 x 23, 128 x 128       19 / 15   17 / 15   15 / 15   13 / 15
+//   32 x 7 x 7, 512 x 512        68 / 47   62 / 47   51 / 46   40 / 46
+//   32 x 14 x 14, 256 x 256      65 / 47   58 / 46   46 / 45   36 / 45
+//   32 x 28 x 28, 128 x 128      59 / 47   52 / 46   44 / 45   34 / 44
+//   32 x 56 x 56, 64 x 64        56 / 51   49 / 49   40 / 48   31 / 47
+//   16 x 90 x 90, 512 x 512    3120 / 2542 2663 / 2521 2166 / 2438 1641 / 2403
+// (At 0.3, where it is a tie, the 32-bit form's smaller tables decide: with three sets of four such layers in turn 164 us against 174.)
+double conv3x3_share_kept(const sbn_packed* p)
 {
-    DeviceLayout& L = p->dev;
-    L.wh.clear();
-    L.wh_exp.clear();
-    L.n_steps = 0;
-    const int taps = p->kh * p->kw;
-    const size_t kept = p->kidx.size() * (size_t)p->go * p->gi * taps;
-    if (taps == 1 || p->c_in % 4 || kept < (size_t)kHalfMinKept * p->c_out) return;
-    const int n_steps = L.n_chunks32 * taps;
-    const size_t n_filters = (size_t)L.n_bundles * kBundleChannels, wstride = (size_t)taps * 64;
-    if (n_filters * (size_t)n_steps * 128 >= 0xFFFFFFFFull) return;      // 32-bit byte offsets on the device
-
-    // Per filter: the power of two that takes its largest weight to [2^14, 2^15).  An entry holds its
-    // weights as [tap][g][ci][co]; per entry, the largest of every filter first.
-    auto bits_of = [](float v) {
-        uint32_t u;
-        std::memcpy(&u, &v, 4);
-        return u & 0x7FFFFFFFu;
-    };
-    std::vector<uint32_t> top(n_filters, 0u), piece(L.n_entries * kBundleChannels, 0u);
-    for (int b = 0; b < L.n_bundles; ++b) {
-        const uint32_t* wo = &L.woff[(size_t)b * (L.n_chunks + 1)];
-        for (size_t e = wo[0]; e < wo[L.n_chunks]; ++e) {
-            const float* w = &L.wts[e * wstride];
-            uint32_t* m = &piece[e * kBundleChannels];
-            for (int i = 0; i < taps * kBundleGroups; ++i, w += 16)
-                for (int j = 0; j < 16; ++j) m[i % kBundleGroups * 4 + j % 4] = std::max(m[i % kBundleGroups * 4 + j % 4], bits_of(w[j]));
-            for (int f = 0; f < kBundleChannels; ++f) top[(size_t)b * kBundleChannels + f] = std::max(top[(size_t)b * kBundleChannels + f], m[f]);
-        }
-    }
-    // (a filter whose weights span so much that a whole kept piece would lose bits: 32-bit kernels)
-    for (int b = 0; b < L.n_bundles; ++b) {
-        const uint32_t* wo = &L.woff[(size_t)b * (L.n_chunks + 1)];
-        for (size_t e = wo[0]; e < wo[L.n_chunks]; ++e)
-            for (int f = 0; f < kBundleChannels; ++f) {
-                const uint32_t m = piece[e * kBundleChannels + f];
-                if (m != 0 && (m >> 23) + 26 < (top[(size_t)b * kBundleChannels + f] >> 23)) return;
-            }
-    }
-    std::vector<float> scale(n_filters, 1.0f);
-    L.wh_exp.assign(n_filters, 0);
-    for (size_t f = 0; f < n_filters; ++f) {
-        const int e = std::max((int)(top[f] >> 23), 27);
-        if (e == 255) {                                                  // infinite or NaN weights stay with the 32-bit kernels
-            L.wh_exp.clear();
-            return;
-        }
-        L.wh_exp[f] = e - 141;
-        const uint32_t s = (uint32_t)(268 - e) << 23;
-        std::memcpy(&scale[f], &s, 4);
-    }
-    L.n_steps = n_steps;
-    L.wh.assign(n_filters * (size_t)n_steps * 64, 0);
-    for (int b = 0; b < L.n_bundles; ++b)
-        for (int c = 0; c < L.n_chunks32; ++c) {
-            const uint32_t* r = &L.records32[((size_t)b * L.n_chunks32 + c) * 8];
-            const float* w = &L.wts[(size_t)L.woff32[(size_t)b * (L.n_chunks32 + 1) + c] * wstride];
-            for (int q = 0; q < 8 && r[q] != 0; ++q, w += wstride) {
-                const int kb4 = (int)(r[q] >> 12);                       // channels 4 * kb4 .. + 3 of the 32
-                uint16_t* frag = &L.wh[(((size_t)b * n_steps + (size_t)c * taps) * 2) * 512];
-                for (int t = 0; t < taps; ++t, frag += 1024)
-                    for (int g = 0; g < kBundleGroups; ++g) {
-                        if (!(r[q] >> g & 1u)) continue;                 // removed: stays zero
-                        for (int co = 0; co < 4; ++co) {
-                            const int f = g * 4 + co;
-                            const float sc = scale[(size_t)b * kBundleChannels + f];
-                            uint16_t* const to = frag + (size_t)(kb4 / 2 * 16 + f) * 8 + (kb4 % 2) * 4;
-                            for (int ci = 0; ci < 4; ++ci) {
-                                const float v = w[t * 64 + g * 16 + ci * 4 + co] * sc;
-                                float hi, lo;
-                                to[ci] = to_half(v, &hi);
-                                to[512 + ci] = to_half((v - hi) * 2048.0f, &lo);
-                            }
-                        }
-                    }
-            }
-        }
+    return (double)p->kidx.size() * p->go * p->gi / ((double)((p->c_in + 31) / 32 * 32) * ((p->c_out + 63) / 64 * 64));
 }
+bool conv3x3_wide_pays(const sbn_packed* p) { return p->stride == 1 && p->c_in >= 32 && conv3x3_share_kept(p) >= 0.33; }
 
 // Nearest bfloat16 (ties to even) of a finite v that does not overflow, returned as bits; *back is its value.
 static inline uint16_t to_bf16(float v, float* back)
@@ -134,9 +62,10 @@ static void build_triples(sbn_packed* p)
     DeviceLayout& L = p->dev;
     L.wt.clear();
     L.w_top = 0.0f;
-    if (p->kh * p->kw != 1 || p->c_in % 4 || p->c_in <= kChunk) return;
-    if (!conv1x1_wide_pays(p) && forced_kernel_form(SBN_CONV1X1) < 2000) return;
-    const size_t n_pairs = ((size_t)L.n_bundles + 1) / 2, n_steps = (size_t)L.n_chunks * 4;
+    const int taps = p->kh * p->kw;
+    const bool pays = taps == 1 ? conv1x1_wide_pays(p) : conv3x3_wide_pays(p);
+    if (p->c_in % 4 || (taps == 1 && p->c_in <= kChunk) || p->stride != 1 || (!pays && forced_kernel_form(p->kind) < 2000)) return;
+    const size_t n_pairs = ((size_t)L.n_bundles + 1) / 2, n_steps = taps == 1 ? (size_t)L.n_chunks * 4 : (size_t)L.n_chunks32 * 18;
     if (n_pairs * n_steps * 3072 >= 0xFFFFFFFFull) return;               // 32-bit byte offsets on the device
     // Infinite, NaN and nearly infinite weights (the first bfloat16 would overflow), and weights whose last bits
     // lie below the smallest normal bfloat16, stay with the 32-bit kernels.
@@ -150,23 +79,24 @@ static void build_triples(sbn_packed* p)
     }
     std::memcpy(&L.w_top, &top, 4);
     L.wt.assign(n_pairs * n_steps * 1536, 0);
+    const size_t wstride = (size_t)taps * 64;
     for (int b = 0; b < L.n_bundles; ++b)
-        for (int c = 0; c < L.n_chunks; ++c) {
-            const uint32_t* r = &L.records[((size_t)b * L.n_chunks + c) * kSlots];
-            const float* w = &L.wts[(size_t)L.woff[(size_t)b * (L.n_chunks + 1) + c] * 64];
-            for (int q = 0; q < kSlots && r[q] != 0; ++q, w += 64) {
-                const int piece = (int)(r[q] >> 12);                     // channels 4 * piece .. + 3 of the 64
-                uint16_t* const frag = &L.wt[((size_t)(b / 2) * n_steps + (size_t)c * 4 + piece / 4) * 1536];
-                for (int f = 0; f < kBundleChannels; ++f) {              // (removed groups' weights are zeros)
-                    uint16_t* const to = frag + (size_t)(piece % 4 / 2 * 32 + b % 2 * kBundleChannels + f) * 8 + piece % 2 * 4;
-                    for (int ci = 0; ci < 4; ++ci) {
-                        const float v = w[f * 4 + ci];
-                        float hi, mid, lo;
-                        to[ci] = to_bf16(v, &hi);
-                        to[512 + ci] = to_bf16(v - hi, &mid);
-                        to[1024 + ci] = to_bf16(v - hi - mid, &lo);
-                    }
-                }
+        for (int c = 0; c < L.n_chunks32; ++c) {
+            const uint32_t* r = &L.records32[((size_t)b * L.n_chunks32 + c) * 8];
+            const float* w = &L.wts[(size_t)L.woff32[(size_t)b * (L.n_chunks32 + 1) + c] * wstride];
+            for (int q = 0; q < 8 && r[q] != 0; ++q, w += wstride) {
+                const int piece = (int)(r[q] >> 12);                     // channels 4 * piece .. + 3 of the 32
+                uint16_t* frag = &L.wt[((size_t)(b / 2) * n_steps + (size_t)c * 2 * taps + piece / 4) * 1536 +
+                                       (size_t)(piece % 4 / 2 * 32 + b % 2 * kBundleChannels) * 8 + piece % 2 * 4];
+                for (int t = 0; t < taps; ++t, frag += 2 * 1536)
+                    for (int f = 0; f < kBundleChannels; ++f)            // (removed groups' weights are zeros)
+                        for (int ci = 0; ci < 4; ++ci) {
+                            const float v = taps == 1 ? w[f * 4 + ci] : w[t * 64 + f / 4 * 16 + ci * 4 + f % 4];
+                            float hi, mid, lo;
+                            frag[f * 8 + ci] = to_bf16(v, &hi);
+                            frag[f * 8 + ci + 512] = to_bf16(v - hi, &mid);
+                            frag[f * 8 + ci + 1024] = to_bf16(v - hi - mid, &lo);
+                        }
             }
         }
 }
@@ -280,7 +210,6 @@ void build_device_layout(sbn_packed* p)
                 }
             }
     }
-    build_half_pairs(p);
     build_triples(p);
     L.bias_padded.assign((size_t)L.n_bundles * kBundleChannels, 0.0f);
     std::copy(p->bias.begin(), p->bias.end(), L.bias_padded.begin());
@@ -337,11 +266,8 @@ const char* check_device_layout(const sbn_packed* p)
     } else if (!L.wts_s.empty()) {
         return "every-piece weights without masks";
     }
-    if (L.wh.empty() ? !L.wh_exp.empty() || L.n_steps != 0
-                     : p->kh != 3 || L.n_steps != 9 * L.n_chunks32 || L.wh.size() != (size_t)L.n_bundles * L.n_steps * 1024 ||
-                           L.wh_exp.size() != (size_t)L.n_bundles * kBundleChannels)
-        return "16-bit pair table sizes";
-    if (!L.wt.empty() && (p->kh != 1 || p->c_in <= kChunk || L.wt.size() != (size_t)((L.n_bundles + 1) / 2) * L.n_chunks * 4 * 1536))
+    if (!L.wt.empty() && ((p->kh == 1 && p->c_in <= kChunk) || p->stride != 1 ||
+                          L.wt.size() != (size_t)((L.n_bundles + 1) / 2) * (p->kh == 1 ? L.n_chunks * 4 : L.n_chunks32 * 18) * 1536))
         return "bfloat16 triple table size";
     return nullptr;
 }
@@ -372,10 +298,8 @@ int upload_device_layout(sbn_packed* p)
     const size_t b_bias = align256(L.bias_padded.size() * sizeof(float));
     const size_t b_desc_s = align256(L.desc_s.size() * sizeof(uint32_t));
     const size_t b_wts_s = align256(L.wts_s.size() * sizeof(float));
-    const size_t b_wh = align256(L.wh.size() * sizeof(uint16_t));
-    const size_t b_wh_exp = align256(L.wh_exp.size() * sizeof(int32_t));
     const size_t b_wt = align256(L.wt.size() * sizeof(uint16_t));
-    const size_t total = b_rec + b_woff + b_rec32 + b_woff32 + b_wts + b_bias + b_desc_s + b_wts_s + b_wh + b_wh_exp + b_wt;
+    const size_t total = b_rec + b_woff + b_rec32 + b_woff32 + b_wts + b_bias + b_desc_s + b_wts_s + b_wt;
     // (written once: not zeroed first, the gaps behind the arrays are; before the device memory, as it may throw)
     std::unique_ptr<char[]> host(new char[total]);
     char* blob = nullptr;
@@ -399,8 +323,6 @@ int upload_device_layout(sbn_packed* p)
     L.d_bias = (float*)put(L.bias_padded.data(), L.bias_padded.size() * sizeof(float), b_bias);
     L.d_desc_s = (uint32_t*)put(L.desc_s.data(), L.desc_s.size() * sizeof(uint32_t), b_desc_s);       // NULL when there are none
     L.d_wts_s = (float*)put(L.wts_s.data(), L.wts_s.size() * sizeof(float), b_wts_s);
-    L.d_wh = (uint16_t*)put(L.wh.data(), L.wh.size() * sizeof(uint16_t), b_wh);
-    L.d_wh_exp = (int32_t*)put(L.wh_exp.data(), L.wh_exp.size() * sizeof(int32_t), b_wh_exp);
     L.d_wt = (uint16_t*)put(L.wt.data(), L.wt.size() * sizeof(uint16_t), b_wt);
     e = hipMemcpy(blob, host.get(), total, hipMemcpyHostToDevice);
     (void)hipSetDevice(prev);

@@ -1,4 +1,4 @@
-// Device helpers of the kernels on triples of bfloat16 (sbn_conv1x1_wide.hip).
+// Device helpers of the kernels on triples of bfloat16 (sbn_conv1x1_wide.hip, sbn_conv3x3_wide.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -62,6 +62,32 @@ __device__ __forceinline__ v4f relu4(v4f v)                              // as i
     typedef int v4i __attribute__((ext_vector_type(4)));
     const v4i b = __builtin_bit_cast(v4i, v);
     return __builtin_bit_cast(v4f, (v4i){b.x > 0 ? b.x : 0, b.y > 0 ? b.y : 0, b.z > 0 ? b.z : 0, b.w > 0 ? b.w : 0});
+}
+
+// The results of a 32-pixel tile, [group of 4 channels][channel] of 32 channels from ch0 on, to the rows row0 .. row0 + 31
+// of y.  Two groups of 32 pixels (lanes 0-31 and 32-63 hold different channels of a pixel) become twice all four groups
+// of 16 pixels, so that 64 bytes of a pixel leave in one instruction.  Channels from N on are not written, rows past the
+// buffer neither.  AUX 2: streaming.
+template <int AUX>
+__device__ __forceinline__ void store_tile(const v16f& v, __amdgpu_buffer_rsrc_t yres, int row0, int ch0, int N, bool relu, int lane)
+{
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        v4u o[2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const auto r = __builtin_amdgcn_permlane16_swap(as_uint(v[8 * k + i]), as_uint(v[8 * k + 4 + i]), false, false);
+            o[0][i] = r[0];
+            o[1][i] = r[1];
+        }
+        const int ch = ch0 + 16 * k + ((lane >> 4) & 1) * 8 + (lane >> 5) * 4;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t off = ch < N ? ((uint32_t)((lane & 15) + 16 * u + row0) * (uint32_t)N + (uint32_t)ch) * 4u : 0xFFFFFFF0u;
+            if (relu) o[u] = __builtin_bit_cast(v4u, relu4(__builtin_bit_cast(v4f, o[u])));
+            __builtin_amdgcn_raw_buffer_store_b128(o[u], yres, (int)off, 0, AUX);
+        }
+    }
 }
 
 }  // namespace sbn_wide

@@ -156,6 +156,28 @@ def test_packed_layout_reports_entries_and_every_piece_tables():
     assert not S.sbn_packed_layout(k3)["every_piece"]
 
 
+@pytest.mark.parametrize("kind,K,N,pct,stride,wide", [
+    (S.SBN_CONV3X3, 512, 256, 50, 1, True),
+    (S.SBN_CONV3X3, 512, 256, 50, 2, False),           # strided layers, sparse ones and few output channels run in 32 bits only
+    (S.SBN_CONV3X3, 512, 256, 90, 1, False),
+    (S.SBN_CONV1X1, 512, 512, 50, 1, True),
+    (S.SBN_CONV1X1, 512, 512, 72, 1, False),
+    (S.SBN_CONV1X1, 512, 80, 0, 1, False),
+])
+def test_dense_tables_are_built_only_where_a_launch_can_use_them(kind, K, N, pct, stride, wide):
+    """The tables of the wide multiplies take 6 bytes per weight, kept or not (c_in and c_out here are whole tiles)."""
+    k = 3 if kind == S.SBN_CONV3X3 else 1
+    w = W.he_weights(334, N, k, k, K)
+    mask = S.sbn_prune_magnitude(w, kind, 4, 4, pct)
+    lay = S.sbn_packed_layout(S.sbn_pack(kind, w, 4, 4, mask=mask, stride=stride, device=-1))
+    rest = lay["entries"] * k * k * 256
+    if lay["every_piece"]:
+        rest += N // 16 * (K // 4) * 260
+    rest += 4 * N + 16 * N // 16 * K // 4 * 3          # bias, records and their offsets, at most
+    assert lay["table_bytes"] <= rest + wide * 6 * k * k * K * N
+    assert not wide or lay["table_bytes"] > 6 * k * k * K * N
+
+
 # ---------------------------------------------------------------- rearrangement
 
 def _layers(seed, chans, go=4, gi=4):
