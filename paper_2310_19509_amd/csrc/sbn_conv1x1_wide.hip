@@ -50,30 +50,60 @@ using namespace sbn_wide;
 constexpr int KC = 64;                    // channels staged at a time
 constexpr int STEPS = KC / 16;            // multiplies per chunk, tile and product
 
-// Four output channels ch .. ch + 3 (one filter group) of pixel pix by 32-bit multiply-adds over the kept blocks.
-__device__ __forceinline__ void exact_group(const float* __restrict__ x, float* __restrict__ y,
-                                            const uint32_t* __restrict__ records, const uint32_t* __restrict__ woff,
-                                            const float* __restrict__ wts, const float* __restrict__ bias, int K, int N,
-                                            int n_chunks, long long pix, int ch, int act)
-{
-    const int b = ch >> 4, g = (ch >> 2) & 3;
-    v4f acc = *(const v4f*)(bias + ch);
-    for (int c = 0; c < n_chunks; ++c) {
-        const uint32_t* r = records + ((size_t)b * n_chunks + c) * 16;
-        const v4f* w = (const v4f*)(wts + (size_t)woff[(size_t)b * (n_chunks + 1) + c] * 64 + g * 16);
-        const float* xc = x + pix * K + c * 64;
-        for (int q = 0; q < 16 && r[q] != 0; ++q, w += 16) {
-            if (!(r[q] >> g & 1u)) continue;
-            const v4f xv = *(const v4f*)(xc + (int)(r[q] >> 12) * 4);
-#pragma unroll
-            for (int co = 0; co < 4; ++co)
-#pragma unroll
-                for (int ci = 0; ci < 4; ++ci) acc[co] = __builtin_fmaf(w[co][ci], xv[ci], acc[co]);
-        }
+// Four output channels ch .. ch + 3 (one filter group) of pixel pix by 32-bit multiply-adds over the kept blocks: by one
+// lane, four pieces' loads at a time, or by a wave, a lane per piece of four chunks.
+struct Exact {
+    const float* __restrict__ x;
+    float* __restrict__ y;
+    const uint32_t* __restrict__ records;
+    const uint32_t* __restrict__ woff;
+    const float* __restrict__ wts;
+    const float* __restrict__ bias;
+    int K, N, n_chunks, act;
+
+    __device__ __forceinline__ void store(v4f acc, long long pix, int ch) const
+    {
+        acc += *(const v4f*)(bias + ch);
+        if (act == SBN_ACT_RELU) acc = relu4(acc);
+        *(v4f*)(y + pix * N + ch) = acc;
     }
-    if (act == SBN_ACT_RELU) acc = relu4(acc);
-    *(v4f*)(y + pix * N + ch) = acc;
-}
+    __device__ __forceinline__ void by_lane(long long pix, int ch) const
+    {
+        const int b = ch >> 4, g = (ch >> 2) & 3;
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < n_chunks; ++c) {
+            const uint32_t* r = records + ((size_t)b * n_chunks + c) * 16;
+            const v4f* w = (const v4f*)(wts + (size_t)woff[(size_t)b * (n_chunks + 1) + c] * 64 + g * 16);
+            const float* xc = x + pix * K + c * 64;
+            for (int q = 0; q < 16 && r[q] != 0; q += 4, w += 64) {      // (past the record's end: other entries, or the slack behind the table)
+                v4f xv[4], wv[4][4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    xv[u] = *(const v4f*)(xc + (int)(r[q + u] >> 12) * 4);
+#pragma unroll
+                    for (int co = 0; co < 4; ++co) wv[u][co] = w[u * 16 + co];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) add_piece(acc, wv[u], xv[u], r[q + u] >> g & 1u);
+            }
+        }
+        store(acc, pix, ch);
+    }
+    __device__ __forceinline__ void by_wave(long long pix, int ch, int lane) const
+    {
+        const int b = ch >> 4, g = (ch >> 2) & 3;
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        for (int c = lane >> 4; c < n_chunks; c += 4) {
+            const uint32_t r = records[((size_t)b * n_chunks + c) * 16 + (lane & 15)];
+            if (!(r >> g & 1u)) continue;
+            const v4f* w = (const v4f*)(wts + ((size_t)woff[(size_t)b * (n_chunks + 1) + c] + (lane & 15)) * 64 + g * 16);
+            const v4f xv = *(const v4f*)(x + pix * K + c * 64 + (int)(r >> 12) * 4), wv[4] = {w[0], w[1], w[2], w[3]};
+            add_piece(acc, wv, xv, true);
+        }
+        acc = sum_over_wave(acc);
+        if (lane == 0) store(acc, pix, ch);
+    }
+};
 
 template <int PX, int NWV, bool PIPE>
 __global__ __launch_bounds__(64 * NWV, PIPE ? 2 : 3) void conv1x1_wide_kernel(
@@ -224,11 +254,11 @@ __global__ __launch_bounds__(64 * NWV, PIPE ? 2 : 3) void conv1x1_wide_kernel(
 #pragma unroll
         for (int t = 0; t < PX; ++t) store_tile<PIPE ? 0 : 2>(cross[t], yres, t * 32, pair * 32, N, act == SBN_ACT_RELU, l);
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(redo != 0) != 0, 0)) {
-            __builtin_amdgcn_s_waitcnt(0);         // the wave's stores above are done: these replace some of them
-#pragma unroll 1
-            for (int k = 0; k < 4 * PX; ++k)
-                if (redo >> k & 1u)
-                    exact_group(x, y, records, woff, wts, bias, K, N, n_chunks, pix0 + (k >> 2) * 32 + row_lane, ch_lane + 8 * (k & 3), act);
+            const Exact exact = {x, y, records, woff, wts, bias, K, N, n_chunks, act};
+            auto pixel = [&](int k, int ln) { return pix0 + (k >> 2) * 32 + (ln & 31); };
+            auto channel = [&](int k, int ln) { return pair * 32 + (ln >> 5) * 4 + 8 * (k & 3); };
+            do_again(redo, 4 * PX, [&](int k, int ln) { exact.by_wave(pixel(k, ln), channel(k, ln), l); },
+                     [&](int k) { exact.by_lane(pixel(k, l), channel(k, l)); });
         }
     };
 

@@ -30,35 +30,73 @@ using namespace sbn_wide;
 constexpr int KC = 32;                    // channels staged at a time
 constexpr int STEPS = 18;                 // nine taps of two halves of 16 channels
 
-// Four output channels ch .. ch + 3 (one filter group) of pixel pix by 32-bit multiply-adds over the kept kernels.
-__device__ __forceinline__ void exact_group(const float* __restrict__ x, float* __restrict__ y,
-                                            const uint32_t* __restrict__ records, const uint32_t* __restrict__ woff,
-                                            const float* __restrict__ wts, const float* __restrict__ bias, int H, int W, int K,
-                                            int N, int n_sub, long long pix, int ch, int act)
-{
-    const int b = ch >> 4, g = (ch >> 2) & 3;
-    const int ox = (int)(pix % W), oy = (int)(pix / W % H);
-    v4f acc = *(const v4f*)(bias + ch);
-    for (int c = 0; c < n_sub; ++c) {
-        const uint32_t* r = records + ((size_t)b * n_sub + c) * 8;
-        const v4f* w = (const v4f*)(wts + (size_t)woff[(size_t)b * (n_sub + 1) + c] * 576 + g * 16);
-        for (int q = 0; q < 8 && r[q] != 0; ++q, w += 144) {
-            if (!(r[q] >> g & 1u)) continue;
-#pragma unroll 3
-            for (int t = 0; t < 9; ++t) {
-                const int dy = t / 3 - 1, dx = t % 3 - 1;
-                if (oy + dy < 0 || oy + dy >= H || ox + dx < 0 || ox + dx >= W) continue;
-                const v4f xv = *(const v4f*)(x + (pix + (long long)dy * W + dx) * K + c * KC + (int)(r[q] >> 12) * 4);
+// Four output channels ch .. ch + 3 (one filter group) of pixel pix by 32-bit multiply-adds over the kept kernels: by one
+// lane, a row of taps' loads at a time, or by a wave, a lane per piece of eight sub-chunks.
+struct Exact {
+    const float* __restrict__ x;
+    float* __restrict__ y;
+    const uint32_t* __restrict__ records;
+    const uint32_t* __restrict__ woff;
+    const float* __restrict__ wts;
+    const float* __restrict__ bias;
+    int H, W, K, N, n_sub, act;
+
+    __device__ __forceinline__ void store(v4f acc, long long pix, int ch) const
+    {
+        acc += *(const v4f*)(bias + ch);
+        if (act == SBN_ACT_RELU) acc = relu4(acc);
+        *(v4f*)(y + pix * N + ch) = acc;
+    }
+    // one entry: w = its group's [tap][ci][co], xp = its piece of the centre pixel
+    __device__ __forceinline__ void entry(v4f& acc, const v4f* w, const float* xp, int ox, int oy) const
+    {
+#pragma unroll 1
+        for (int dy = -1; dy <= 1; ++dy, w += 48) {
+            if (oy + dy < 0 || oy + dy >= H) continue;
+            v4f xv[3], wv[3][4];
+            bool in[3];
 #pragma unroll
-                for (int ci = 0; ci < 4; ++ci)
+            for (int u = 0; u < 3; ++u) {
+                in[u] = ox + u - 1 >= 0 && ox + u - 1 < W;
+                xv[u] = *(const v4f*)(xp + ((long long)dy * W + (in[u] ? u - 1 : 0)) * K);
 #pragma unroll
-                    for (int co = 0; co < 4; ++co) acc[co] = __builtin_fmaf(w[t * 16 + ci][co], xv[ci], acc[co]);
+                for (int ci = 0; ci < 4; ++ci) wv[u][ci] = w[u * 16 + ci];
             }
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
+                if (in[u])
+#pragma unroll
+                    for (int ci = 0; ci < 4; ++ci)
+#pragma unroll
+                        for (int co = 0; co < 4; ++co) acc[co] = __builtin_fmaf(wv[u][ci][co], xv[u][ci], acc[co]);
         }
     }
-    if (act == SBN_ACT_RELU) acc = relu4(acc);
-    *(v4f*)(y + pix * N + ch) = acc;
-}
+    __device__ __forceinline__ void by_lane(int pix, int ch) const
+    {
+        const int b = ch >> 4, g = (ch >> 2) & 3, ox = pix % W, oy = pix / W % H;
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < n_sub; ++c) {
+            const uint32_t* r = records + ((size_t)b * n_sub + c) * 8;
+            const v4f* w = (const v4f*)(wts + (size_t)woff[(size_t)b * (n_sub + 1) + c] * 576 + g * 16);
+            for (int q = 0; q < 8 && r[q] != 0; ++q, w += 144)
+                if (r[q] >> g & 1u) entry(acc, w, x + (long long)pix * K + c * KC + (int)(r[q] >> 12) * 4, ox, oy);
+        }
+        store(acc, pix, ch);
+    }
+    __device__ __forceinline__ void by_wave(int pix, int ch, int lane) const
+    {
+        const int b = ch >> 4, g = (ch >> 2) & 3, ox = pix % W, oy = pix / W % H;
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        for (int c = lane >> 3; c < n_sub; c += 8) {
+            const uint32_t r = records[((size_t)b * n_sub + c) * 8 + (lane & 7)];
+            if (r >> g & 1u)
+                entry(acc, (const v4f*)(wts + ((size_t)woff[(size_t)b * (n_sub + 1) + c] + (lane & 7)) * 576 + g * 16),
+                      x + (long long)pix * K + c * KC + (int)(r >> 12) * 4, ox, oy);
+        }
+        acc = sum_over_wave(acc);
+        if (lane == 0) store(acc, pix, ch);
+    }
+};
 
 // U: 32-pixel tiles of a wave.  NL: staged 16-byte slots per lane; NL * 32 >= T + 2 * W + 2 pixels.
 // S: slices of four waves; slice s multiplies the sub-chunks s, s + S, ... out of its own image, and the sums meet at the end.
@@ -277,11 +315,11 @@ __global__ __launch_bounds__(256 * S, 2) void conv3x3_wide_kernel(
 #pragma unroll
     for (int t = 0; t < U; ++t) store_tile<0>(total[t], yres, first + t * 32, pair * 32, N, act == SBN_ACT_RELU, lane);
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(redo != 0) != 0, 0)) {
-        __builtin_amdgcn_s_waitcnt(0);             // the wave's stores above are done: these replace some of them
-#pragma unroll 1
-        for (int k = 0; k < 4 * U; ++k)
-            if (redo >> k & 1u)
-                exact_group(x, y, records, woff, wts, bias, H, W, K, N, n_sub, (long long)p0 + first + (k >> 2) * 32 + (lane & 31), ch_lane + 8 * (k & 3), act);
+        const Exact exact = {x, y, records, woff, wts, bias, H, W, K, N, n_sub, act};
+        auto pixel = [&](int k, int ln) { return p0 + first + (k >> 2) * 32 + (ln & 31); };
+        auto channel = [&](int k, int ln) { return pair * 32 + (ln >> 5) * 4 + 8 * (k & 3); };
+        do_again(redo, 4 * U, [&](int k, int ln) { exact.by_wave(pixel(k, ln), channel(k, ln), lane); },
+                 [&](int k) { exact.by_lane(pixel(k, lane), channel(k, lane)); });
     }
 }
 

@@ -214,3 +214,21 @@ def test_long_sums_are_no_further_off_than_32_bit_ones(K, N, pct):
     limit = np.linalg.norm(chain - ref)
     for form in FORMS:
         assert np.linalg.norm(run(p, x, N, form)[0, 0] - ref) <= limit
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("spoilt", [1, 12, 13, 200])
+def test_outputs_done_again_one_by_one_and_side_by_side(form, spoilt):
+    """Up to 12 of a wave's outputs are done again by the wave together, more by their lanes; an overflowing activation
+    that only a part of the filters keeps."""
+    p, w, mask, b = pack(324, 96, 30, relu=False)
+    x = W.uniform_activation(9012, (1, 1, 200, 324))
+    x[0, 0, :spoilt, 131] = np.inf
+    y = run(p, x, 96, form)
+    keeps = np.repeat(mask.reshape(24, 81)[:, 131 // 4] != 0, 4)
+    assert not np.isfinite(y[0, 0, :spoilt, keeps]).any()
+    x[0, 0, :spoilt, 131] = 0
+    ref, bound = R.sparse_conv_reference(x, w, mask, 4, 4, bias=b)
+    ok = np.isfinite(y)
+    assert ok[0, 0, spoilt:].all() and ok[0, 0, :, ~keeps].all()
+    assert np.all(np.abs(y - ref)[ok] <= 324 * 2.0 ** -24 * bound[ok] + 2.0 ** -23 * np.abs(ref[ok]))

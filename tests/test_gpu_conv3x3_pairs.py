@@ -176,3 +176,23 @@ def test_long_sums_are_no_further_off_than_32_bit_ones(K, N, pct):
     limit = np.linalg.norm(run(p, x, N, 1) - ref)
     for form in FORMS:
         assert np.linalg.norm(run(p, x, N, form) - ref) <= limit
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("spoilt", [1, 3, 40])
+def test_outputs_done_again_one_by_one_and_side_by_side(form, spoilt):
+    """Up to 12 of a wave's outputs are done again by the wave together, more by their lanes."""
+    p, wt, mask, b = pack(68, 96, 50, relu=False)
+    x = W.uniform_activation(9111, (3, 7, 9, 68))
+    at = np.zeros((3, 7, 9), bool)
+    at.reshape(-1)[60:60 + spoilt] = True
+    x[at, 33] = np.inf
+    y = run(p, x, 96, form)
+    x[at, 33] = 0
+    wm = kept_weights(wt, mask, 4, 4)
+    ref, bound = convolve64(x, wm) + b, convolve64(np.abs(x), np.abs(wm)) + np.abs(b)
+    hot = np.zeros_like(x)
+    hot[at, 33] = 1
+    ok = convolve64(hot, np.abs(wm)) == 0
+    assert np.array_equal(np.isfinite(y), ok)
+    assert np.all(np.abs(y - ref)[ok] <= 9 * 68 * 2.0 ** -24 * bound[ok] + 2.0 ** -24 * np.abs(ref[ok]))
