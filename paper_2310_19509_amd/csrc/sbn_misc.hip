@@ -103,6 +103,71 @@ __global__ __launch_bounds__(256) void dw3x3_kernel(const float* __restrict__ x,
     }
 }
 
+// The same for rows of few channel quads, of which half a wave or less would find work in one strip: threads take quads,
+// columns, strips and images in one row of numbers.
+template <int STRIDE, int R>
+__global__ __launch_bounds__(256) void dw3x3_narrow_kernel(const float* __restrict__ x, float* __restrict__ y,
+                                                          const float* __restrict__ wt, const float* __restrict__ bias,
+                                                          int h, int w, int c, int oh, int ow, int act, long long total)
+{
+    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (t >= total) return;
+    const int c4n = c >> 2;
+    const int c4 = (int)(t % c4n) * 4;
+    long long r = t / c4n;
+    const int ox = (int)(r % ow);
+    r /= ow;
+    const int strips = (oh + R - 1) / R;
+    const int oy0 = (int)(r % strips) * R;
+    const long long b = r / strips;
+
+    v4f wv[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) wv[k] = *(const v4f*)(wt + k * c + c4);
+    const v4f bv = *(const v4f*)(bias + c4);
+    v4f acc[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) acc[i] = bv;
+
+    constexpr int ROWS = (R - 1) * STRIDE + 3;              // input rows touched by the strip
+    const int iy0 = oy0 * STRIDE - 1, ix0 = ox * STRIDE - 1;
+    const float* xb = x + b * h * w * c + c4;
+#pragma unroll
+    for (int ir = 0; ir < ROWS; ++ir) {
+        const int iy = iy0 + ir;
+        v4f row[3];
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+            const int ix = ix0 + kx;
+            const bool ok = iy >= 0 && iy < h && ix >= 0 && ix < w;
+            const v4f v = *(const v4f*)(xb + ((long long)(ok ? iy : 0) * w + (ok ? ix : 0)) * c);
+            row[kx] = ok ? v : (v4f){0.f, 0.f, 0.f, 0.f};
+        }
+        // input row ir is tap row ky of output i when ir == i*STRIDE + ky
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int ky = ir - i * STRIDE;
+            if (ky >= 0 && ky < 3) {
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx) acc[i] += row[kx] * wv[ky * 3 + kx];
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int oy = oy0 + i;
+        if (oy >= oh) break;
+        v4f o = acc[i];
+        if (act == SBN_ACT_RELU) {
+            o.x = fmaxf(o.x, 0.f);
+            o.y = fmaxf(o.y, 0.f);
+            o.z = fmaxf(o.z, 0.f);
+            o.w = fmaxf(o.w, 0.f);
+        }
+        *(v4f*)(y + ((b * oh + oy) * (long long)ow + ox) * c + c4) = o;
+    }
+}
+
 // Dense 3x3 convolution of a few input channels (network stem), pad 1.  One thread: 4 output
 // channels of one output pixel; the (c_out x 9 x c_in) weights sit in LDS as [tap][ci][c_out].
 // x [n][h][w][c_in], y [n][oh][ow][c_out].
@@ -278,9 +343,22 @@ int launch_dw3x3(const float* x, float* y, const float* w_dev, const float* b_de
     const int oh = (h - 1) / stride + 1, ow = (w - 1) / stride + 1;
     const long long quads = (long long)ow * (c / 4);
     if ((long long)n * oh * quads == 0) return SBN_OK;
+    // Rows of at most half a wave (4096 x 7 x 7 x 4: 9.5 us, 18.2 with a block per strip; x 16: 9.4 and 11.2; rows of 56
+    // quads, x 32: 13.2 and 12.1)
+    if (quads <= 32) {
+        const long long total = (long long)n * ((oh + 3) / 4) * quads, blocks = (total + 255) / 256;
+        if (blocks > 0x7FFFFFFFll) return fail(SBN_EINVAL, "depthwise layer too large for one launch");
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, x, y, w_dev, b_dev, h, w, c, oh, ow, act, total);
+        };
+        stride == 1 ? go(dw3x3_narrow_kernel<1, 4>) : go(dw3x3_narrow_kernel<2, 4>);
+        return check_launch("dw3x3");
+    }
     // Strips of four rows load 4.5 (stride 2: 6.75) values per output instead of 9; where they leave fewer than four
-    // waves per compute unit (of 256, the device these figures are from), one row each: the chain of loads is shorter.
-    const bool small = (long long)n * ((oh + 3) / 4) * quads < 64ll * 4 * 256;
+    // waves per compute unit, one row each: the chain of loads is shorter.
+    int device = 0, cus = 0;
+    if (hipGetDevice(&device) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) cus = 256;
+    const bool small = (long long)n * ((oh + 3) / 4) * quads < 64ll * 4 * cus;
     const int R = small ? 1 : 4;
     // (blocks of 64 threads where a row is short: at most 63 idle lanes per strip)
     const unsigned threads = quads % 256 == 0 || quads >= 2048 ? 256 : 64;

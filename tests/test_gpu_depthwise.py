@@ -14,6 +14,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("stride", [1, 2])
 @pytest.mark.parametrize("n,h,w,c", [
+    (70, 9, 1, 4),           # rows of one quad, a block across many images
+    (3, 13, 4, 20),          # a block ends within a row
+    (2, 34, 8, 16),          # rows of 32 quads (stride 1), the longest of the narrow kernel; half of that (stride 2)
+    (2, 34, 11, 12),         # and one more
     (1, 1, 1, 4),            # one pixel, one lane
     (2, 3, 1, 20),           # one column
     (1, 1, 40, 12),          # one row; rows of 120 quads (stride 1), 60 (stride 2)
