@@ -281,12 +281,6 @@ int upload_device_layout(sbn_packed* p)
     hipError_t e = hipGetDeviceCount(&ndev);
     if (e != hipSuccess) return fail(SBN_EHIP, "hipGetDeviceCount: %s", hipGetErrorString(e));
     if (p->device >= ndev) return fail(SBN_EINVAL, "device %d does not exist (%d visible)", p->device, ndev);
-    int prev = 0;
-    (void)hipGetDevice(&prev);
-    if ((e = hipSetDevice(p->device)) != hipSuccess) return fail(SBN_EHIP, "hipSetDevice: %s", hipGetErrorString(e));
-    int cus = 0;                           // the launchers size their grids by it
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess && cus > 0) L.cus = cus;
-
     // One allocation.  The kernels fetch the weights of a whole record (up to
     // 16 entries) at once, so the weight array carries 16 entries of slack.
     const size_t wstride = (size_t)p->kh * p->kw * kBundleGroups * 16;
@@ -300,8 +294,13 @@ int upload_device_layout(sbn_packed* p)
     const size_t b_wts_s = align256(L.wts_s.size() * sizeof(float));
     const size_t b_wt = align256(L.wt.size() * sizeof(uint16_t));
     const size_t total = b_rec + b_woff + b_rec32 + b_woff32 + b_wts + b_bias + b_desc_s + b_wts_s + b_wt;
-    // (written once: not zeroed first, the gaps behind the arrays are; before the device memory, as it may throw)
+    // (written once: not zeroed first, the gaps behind the arrays are; before the device is changed, as it may throw)
     std::unique_ptr<char[]> host(new char[total]);
+    int prev = 0;
+    (void)hipGetDevice(&prev);
+    if ((e = hipSetDevice(p->device)) != hipSuccess) return fail(SBN_EHIP, "hipSetDevice: %s", hipGetErrorString(e));
+    int cus = 0;                           // the launchers size their grids by it
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess && cus > 0) L.cus = cus;
     char* blob = nullptr;
     if ((e = hipMalloc((void**)&blob, total)) != hipSuccess) {
         (void)hipSetDevice(prev);
