@@ -19,7 +19,15 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_MFMA_F32_TFLOPS = 157.3      # MI355X published dense fp32 matrix peak
+PEAK_MFMA_BF16_TFLOPS = 2516.6    # MI355X published dense bf16 matrix peak
+LOOP_MFMA_BF16_TFLOPS = 1850.0    # what a v_mfma_f32_32x32x16_bf16 loop on random data reached on an MI355X (clock 1.8 GHz)
 PEAK_HBM_GBS = 8000.0             # MI355X published HBM3E bandwidth
+
+
+def matrix_floor_s(nonzero, whole, f32=PEAK_MFMA_F32_TFLOPS, bf16=PEAK_MFMA_BF16_TFLOPS):
+    """Shortest time of the matrix units for a layer at 32-bit precision: its nonzero FLOPs on the fp32 pipe, or
+    six bf16 products for each of its FLOPs, removed blocks included (the library's two kinds of kernels)."""
+    return min(nonzero / (f32 * 1e12), 6.0 * whole / (bf16 * 1e12))
 
 
 def parse():
@@ -169,15 +177,21 @@ def run_forms(a, torch, S, W):
                 fn()
             torch.cuda.synchronize()
 
+    def pack_wide(kind, *args, **kw):                    # with the wide forms' tables, whatever the rule would use
+        S.sbn_force_kernel_form(kind, 2064)
+        p = S.sbn_pack(kind, *args, **kw)
+        S.sbn_force_kernel_form(kind, 0)
+        return p
+
     out = {"conv1x1": [], "conv3x3": []}
-    forms1 = [0, 1, 12, 21, 112, 121, 1012, 1021, 1112, 1121, 504, 508]
+    forms1 = [0, 1, 12, 21, 112, 121, 1012, 1021, 1112, 1121, 504, 508, 2064, 2256]
     B, pct = a.batch, a.sparsity
     for L in W.MOBILENET_V1_PW:
         if L.c_in <= 64:
             continue                                   # one chunk: the shape leaves no choice
         t = W.pw_layer_tensors(3000, L, B, with_x=False)
         mask = S.sbn_prune_magnitude(t["w"], S.SBN_CONV1X1, a.go, 4, pct)
-        p = S.sbn_pack(S.SBN_CONV1X1, t["w"], a.go, 4, mask=mask, bias=t["bias"], act=S.SBN_ACT_RELU, device=0)
+        p = pack_wide(S.SBN_CONV1X1, t["w"], a.go, 4, mask=mask, bias=t["bias"], act=S.SBN_ACT_RELU, device=0)
         m = B * L.hw * L.hw
         x, y = torch.rand((m, L.c_in), device="cuda"), torch.empty((m, L.c_out), device="cuda")
         us = {f: [] for f in forms1}
@@ -192,11 +206,11 @@ def run_forms(a, torch, S, W):
         out["conv1x1"].append(dict(layer=L.index, pixels=m, c_in=L.c_in, c_out=L.c_out, us=row, best=best,
                                    rule_within_percent_of_best=round(100 * (row["0"] / row[best] - 1), 1)))
         S.sbn_free(p)
-    forms3 = [0, 1, 2, 3, 32]
+    forms3 = [0, 1, 2, 3, 32, 2064, 2065, 2128]
     for idx in range(len(W.RESNET50_3X3)):
         t = W.conv3x3_layer_tensors(5000, idx, 32, with_x=False)
         mask = S.sbn_prune_magnitude(t["w"], S.SBN_CONV3X3, 4, 4, 70)
-        p = S.sbn_pack(S.SBN_CONV3X3, t["w"], 4, 4, mask=mask, bias=t["bias"], act=S.SBN_ACT_RELU, device=0)
+        p = pack_wide(S.SBN_CONV3X3, t["w"], 4, 4, mask=mask, bias=t["bias"], act=S.SBN_ACT_RELU, device=0)
         x = torch.rand((32, t["hw"], t["hw"], t["c"]), device="cuda")
         y = torch.empty((32, t["hw"], t["hw"], t["c"]), device="cuda")
         us = {f: [] for f in forms3}
@@ -216,8 +230,10 @@ def run_forms(a, torch, S, W):
                       "n_gpus": 1, "steps": 100, "warmup": 10, "higher_is_better": False, "dtype": "f32", "data": "synthetic",
                       "config": {"workload": f"every kernel form on the 1x1 layers (batch {B}, {pct} %) and the 3x3 layers (batch 32, 70 %)"},
                       "forms": {"conv1x1": "0 rule, 1 rule without every-piece tables, 12/21 64-/128-pixel tiles, 112/121 the same with the "
-                                           "last round as few-pixel workgroups, 10xx/11xx on every-piece tables, 504/508 input channels split over 4/8 waves",
-                                "conv3x3": "0 rule, 1 one pixel per lane, 2 two pixels, 3 entry-ahead, 32 channel split"},
+                                           "last round as few-pixel workgroups, 10xx/11xx on every-piece tables, 504/508 input channels split over 4/8 waves, "
+                                           "2064/2256 bfloat16 triples, 64 x 128 / 128 x 256 tiles",
+                                "conv3x3": "0 rule, 1 one pixel per lane, 2 two pixels, 3 entry-ahead, 32 channel split, "
+                                           "2128/2064/2065 bfloat16 triples, 128 x 64 / 64 x 64 tiles / two slices"},
                       "extra": out}))
 
 
@@ -444,7 +460,8 @@ def run_mobilenet(a, torch, S, W):
     fused = [] if a.no_fuse else [i for i, (d, p) in enumerate(zip(W.MOBILENET_V1_DW, W.MOBILENET_V1_PW))
                                   if p.c_in % 32 == 0 and p.c_in <= 128 and p.c_out <= 128]
     act_bytes -= 4.0 * B * 2 * sum(W.MOBILENET_V1_DW[i].hw_out ** 2 * W.MOBILENET_V1_DW[i].c for i in fused)
-    t_roof = nz / (PEAK_MFMA_F32_TFLOPS * 1e12)
+    t_roof = sum(matrix_floor_s(2.0 * int(m["mask"].sum()) * a.go * 4 * B * L.hw * L.hw, 2.0 * B * L.hw * L.hw * L.c_in * L.c_out)
+                 for m, L in zip([m for m in meta if m["kind"] == "pw"][:13], W.MOBILENET_V1_PW))
     out = {
         "metric": "effective GFLOP/s (nonzero FLOPs), whole MobileNet-v1 forward", "value": round((nz + dense_rest) / (ms * 1e-3) / 1e9, 1),
         "unit": "GFLOP/s", "n_gpus": 1, "steps": a.steps, "warmup": a.warmup, "ms_per_step": round(ms, 4),
@@ -473,7 +490,7 @@ def run_conv3x3(a, torch, S, W):
     """Config 5: ResNet-50-shaped 3x3 layers, batch 32, kernel-level group sparsity 70 %."""
     import numpy as np
     B, pct = 32 if a.batch == 64 else a.batch, 70 if a.sparsity == 30 else a.sparsity
-    layers, dense, flops, bytes_alg, xs, ys, hws = [], [], [], [], [], [], []
+    layers, dense, flops, whole, bytes_alg, xs, ys, hws = [], [], [], [], [], [], [], []
     for idx in range(len(W.RESNET50_3X3)):
         t = W.conv3x3_layer_tensors(5000, idx, B, with_x=False)
         if a.k3_pattern_share:
@@ -498,6 +515,7 @@ def run_conv3x3(a, torch, S, W):
         xs.append(torch.rand((B, t["hw"], t["hw"], t["c"]), device="cuda") * 2 - 1)
         ys.append(torch.empty((B, t["hw"], t["hw"], t["c"]), device="cuda"))
         flops.append(2.0 * S.sbn_packed_work(p)["macs_per_pixel"] * B * t["hw"] ** 2)
+        whole.append(2.0 * 9 * t["c"] ** 2 * B * t["hw"] ** 2)
     side = [torch.cuda.Stream() for _ in range(max(1, a.streams))]
 
     def step():
@@ -541,6 +559,8 @@ def run_conv3x3(a, torch, S, W):
     avg_launch_s = sum(r["us"] for r in per) * 1e-6 / len(per)
     ach = sum(flops) / len(layers) / avg_launch_s / 1e12
     measured = measure_roofs(torch, S)
+    peak = sum(flops) / sum(matrix_floor_s(f, d) for f, d in zip(flops, whole)) / 1e12
+    reach = sum(flops) / sum(matrix_floor_s(f, d, measured["mfma_f32_4x4x1_tflops"], LOOP_MFMA_BF16_TFLOPS) for f, d in zip(flops, whole)) / 1e12
     out = {
         "metric": "effective GFLOP/s (nonzero FLOPs), ResNet-50-shaped 3x3 layers", "value": round(sum(flops) / (ms * 1e-3) / 1e9, 1),
         "unit": "GFLOP/s", "n_gpus": 1, "steps": a.steps, "warmup": a.warmup, "ms_per_step": round(ms, 4),
@@ -551,12 +571,13 @@ def run_conv3x3(a, torch, S, W):
                                + (f", 4-of-9 patterns inside kept kernels shared by {a.k3_pattern_share} filters "
                                   "(stored zeros are multiplied and counted)" if a.k3_pattern_share else ""), "batch": B,
                    "sparsity_percent": pct},
-        "roofline": {"bound": "mfma", "achieved": round(ach, 3), "peak": PEAK_MFMA_F32_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(ach / PEAK_MFMA_F32_TFLOPS, 4),
-                     "measured_roofs": measured,
-                     "frac_of_measured": round(ach / measured["mfma_f32_4x4x1_tflops"], 4),
+        "roofline": {"bound": "mfma", "achieved": round(ach, 3), "peak": round(peak, 1), "unit": "TFLOP/s",
+                     "peak_is": "nonzero FLOPs over the matrix units' shortest time: fp32 pipe, or six bf16 products for every FLOP, removed ones included",
+                     "frac": round(ach / peak, 4),
+                     "measured_roofs": dict(measured, mfma_bf16_32x32x16_tflops=LOOP_MFMA_BF16_TFLOPS),
+                     "frac_of_measured": round(ach / reach, 4),
                      "traffic": profiled_traffic("conv3x3_r50_b32_rho70_traffic.txt", SOURCES_3X3) if (B, pct, a.go) == (32, 70, 4) else None,
-                     "kernel": "conv3x3_kernel (4 launches per step, one per layer; durations from serial single-stream passes)",
+                     "kernel": "conv3x3_kernel, conv3x3_wide_kernel (4 launches per step, one per layer; durations from serial single-stream passes)",
                      "avg_launch_us": round(avg_launch_s * 1e6, 2)},
         "extra": {"streams": len(side), "serial_ms_per_step": round(avg_launch_s * len(per) * 1e3, 4),
                   "nonzero_gflop_per_step": round(sum(flops) / 1e9, 3),
@@ -653,13 +674,14 @@ def main():
                                               device=0) for t in tens]
 
     g = torch.Generator(device="cuda").manual_seed(3000)
-    xs, ys, flops, bytes_alg = [], [], [], []
+    xs, ys, flops, whole, bytes_alg = [], [], [], [], []
     for L, p in zip(W.MOBILENET_V1_PW, packed):
         m = B * L.hw * L.hw
         xs.append(torch.rand((m, L.c_in), device="cuda", generator=g) * 2 - 1)
         ys.append(torch.empty((m, L.c_out), device="cuda"))
         work = S.sbn_packed_work(p)
         flops.append(2.0 * work["macs_per_pixel"] * m)
+        whole.append(2.0 * m * L.c_in * L.c_out)
         # algorithmic bytes: activations in and out once, kept weights + indices + bias once
         bytes_alg.append(4.0 * m * (L.c_in + L.c_out) + work["nnz_blocks"] * (4 * a.go * 4 + 2)
                          + 4 * (L.c_out // a.go + 1) + 4 * L.c_out)
@@ -755,7 +777,7 @@ def main():
         e1.record()
         torch.cuda.synchronize()
         t = e0.elapsed_time(e1) / reps * 1e-3
-        t_c, t_m = flops[i] / (PEAK_MFMA_F32_TFLOPS * 1e12), bytes_alg[i] / (PEAK_HBM_GBS * 1e9)
+        t_c, t_m = matrix_floor_s(flops[i], whole[i]), bytes_alg[i] / (PEAK_HBM_GBS * 1e9)
         per_layer.append(dict(layer=L.index, us=round(t * 1e6, 1), tflops=round(flops[i] / t / 1e12, 2),
                               gbs=round(bytes_alg[i] / t / 1e9, 1), bound="mfma" if t_c >= t_m else "hbm",
                               frac=round(max(t_c, t_m) / t, 3)))
@@ -767,29 +789,33 @@ def main():
     value = total_flops / (ms * 1e-3) / 1e9
     n_launch = len(packed)
     avg_launch_s = ms_serial * 1e-3 / n_launch
-    t_cmp = total_flops / (PEAK_MFMA_F32_TFLOPS * 1e12)
+    t_cmp = sum(matrix_floor_s(f, d) for f, d in zip(flops, whole))
     t_mem = sum(bytes_alg) / (PEAK_HBM_GBS * 1e9)
     traffic = None
     if a.sparsity == 30 and a.go == 4 and B == 64:
         traffic = profiled_traffic("conv1x1_pw13_b64_rho30_traffic.txt", SOURCES_1X1)
+    measured = measure_roofs(torch, S)          # what this machine's units deliver (stand-alone loops)
     if t_cmp >= t_mem:
+        # the peak in the same unit, nonzero FLOPs: over the matrix units' shortest time for these layers
+        reach = sum(matrix_floor_s(f, d, measured["mfma_f32_4x4x1_tflops"], LOOP_MFMA_BF16_TFLOPS) for f, d in zip(flops, whole))
         roof = dict(bound="mfma", achieved=round(total_flops / n_launch / avg_launch_s / 1e12, 3),
-                    peak=PEAK_MFMA_F32_TFLOPS, unit="TFLOP/s")
+                    peak=round(total_flops / t_cmp / 1e12, 1), unit="TFLOP/s",
+                    peak_is="nonzero FLOPs over the matrix units' shortest time: fp32 pipe, or six bf16 products for every "
+                            "FLOP, removed ones included")
+        frac_of_measured = reach / (ms_serial * 1e-3)
     else:
         roof = dict(bound="hbm", achieved=round(sum(bytes_alg) / n_launch / avg_launch_s / 1e9, 1),
                     peak=PEAK_HBM_GBS, unit="GB/s")
+        frac_of_measured = roof["achieved"] / measured["hbm_read_gbs"]
     roof["frac"] = round(roof["achieved"] / roof["peak"], 4)
-    measured = measure_roofs(torch, S)          # what this machine's units deliver (stand-alone loops)
-    roof["measured_roofs"] = measured
-    roof["frac_of_measured"] = round(roof["achieved"] / (measured["mfma_f32_4x4x1_tflops"] if roof["bound"] == "mfma"
-                                                          else measured["hbm_read_gbs"]), 4)
+    roof["measured_roofs"] = dict(measured, mfma_bf16_32x32x16_tflops=LOOP_MFMA_BF16_TFLOPS)
+    roof["frac_of_measured"] = round(frac_of_measured, 4)
     roof["traffic"] = traffic
-    roof["kernel"] = "conv1x1_kernel (13 launches per step, one per layer; durations from a serial single-stream pass)"
+    roof["kernel"] = "conv1x1_kernel, conv1x1_mixed_kernel, conv1x1_wide_kernel (13 launches per step, one per layer; durations from a serial single-stream pass)"
     roof["avg_launch_us"] = round(avg_launch_s * 1e6, 2)
-    t_roof_layers = sum(max(f / (PEAK_MFMA_F32_TFLOPS * 1e12), b / (PEAK_HBM_GBS * 1e9))
-                        for f, b in zip(flops, bytes_alg))
+    t_roof_layers = sum(max(matrix_floor_s(f, d), b / (PEAK_HBM_GBS * 1e9)) for f, d, b in zip(flops, whole, bytes_alg))
     roof["per_layer_roofline_frac"] = round(t_roof_layers / (ms_serial * 1e-3), 4)
-    roof["frac_whole_step_overlapped"] = round(total_flops / (ms * 1e-3) / 1e12 / PEAK_MFMA_F32_TFLOPS, 4)
+    roof["frac_whole_step_overlapped"] = round(max(t_cmp, t_mem) / (ms * 1e-3), 4)
 
     out = {
         "metric": "effective GFLOP/s (nonzero FLOPs), MobileNet-v1 1x1 layers",
