@@ -27,9 +27,10 @@
  *   - sbn_packed_t / sbn_chain_t are opaque, created by the library and
  *     released by sbn_free / sbn_chain_free.  A chain borrows its packed
  *     layers: free the chain first.
- *   - Removed blocks are skipped, not multiplied by zero: with finite activations the result is
- *     that of the dense convolution with W~ (up to fp32 summation order); a NaN or infinity in a
- *     channel that only removed blocks read may or may not reach the output.
+ *   - Removed blocks contribute nothing: they are skipped or, in layers that keep so much that wide
+ *     matrix instructions over stored zeros are faster, multiplied by zero.  With finite activations
+ *     the result is that of the dense convolution with W~ (up to fp32 summation order); a NaN or
+ *     infinity in a channel that only removed blocks read may or may not reach the output.
  *   - Single-layer run calls work in PERMUTED channel space: x carries its
  *     channels in perm_in order and y comes out in perm_out order.  That is
  *     what makes the rearrangement free at run time (Section 3.4).
@@ -291,7 +292,10 @@ void sbn_free(sbn_packed_t* p);
  * group j,  y[p, j*go:(j+1)*go] = act(bias + sum over kept blocks kb of row j
  * of x[p, kb:kb+gi] . Wblk[j, kb]).  x: device [n][h][w][c_in], y: device
  * [n][h][w][c_out], both in packed channel order; x and y must not overlap.
- * n*h*w may be 0 (nothing is launched).  fp32 multiply-add, fp32 accumulate.
+ * n*h*w may be 0 (nothing is launched).  Products and sums are those of fp32: multiply-adds, or
+ * six partial products of operands split without loss into three bfloat16 each, summed in fp32 (a
+ * product is then off by at most 2^-24 of itself before it is added).  Which of the two, and the order
+ * of the sums, depends on the layer and on n*h*w.
  */
 int sbn_conv1x1_sparse(const sbn_packed_t* p, const float* x, float* y,
                        int n, int h, int w, void* stream);
@@ -301,6 +305,7 @@ int sbn_conv1x1_sparse(const sbn_packed_t* p, const float* x, float* y,
  * connectivity pruning with gi x go kernels per group): as above with every
  * kept block carrying its 9 taps; zero padding 1, stride from the descriptor.
  * x: device [n][h][w][c_in]; y: device [n][oh][ow][c_out], oh = (h-1)/stride+1.
+ * Arithmetic as for 1x1 layers.
  */
 int sbn_conv3x3_sparse(const sbn_packed_t* p, const float* x, float* y,
                        int n, int h, int w, void* stream);

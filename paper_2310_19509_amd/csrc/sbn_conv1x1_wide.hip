@@ -8,24 +8,23 @@
 // 32-bit floats, so there is nothing to scale and no value depends on its neighbours).  Of the nine products
 // six are formed,
 //     main += w_a * x_a,    cross += w_a * x_c + w_c * x_a + w_b * x_b + w_a * x_b + w_b * x_a,
-// both sums in 32-bit floats; the other three are below 2^-26 of the product, a quarter of what one rounding of
-// a 32-bit sum costs.  `main`, the only long sum of full-sized terms, is rounded c_in / 16 times instead of
-// once per kept weight.  Relative error (2-norm, units of 1e-8, half-zero activations, c_in = 128 / 256 / 512 / 1024,
-// 50 % kept): 4.2 / 5.5 / 7.1 / 10.1 with 16x16x32 multiplies; one 32-bit sum 11.1 / 14.8 / 19.9 / 28.3, two sums
-// 8.2 / 10.6 / 14.0 / 20.8; one active channel per pixel 2.6 and 2.5.  (The splitting is that of the known emulations of
-// single precision on bfloat16 units: Henry, Tang, Heinecke, "Leveraging the bfloat16 artificial intelligence
-// datatype for higher-precision computations", 2019.)
+// both sums in 32-bit floats; the other three are at most 2^-24 of the product, 2e-9 of it on average, where one
+// rounding of a 32-bit sum is at most 2^-24 and 2.5e-8 on average.  `main`, the only long sum of full-sized terms, is
+// rounded c_in / 16 times instead of once per kept weight.  Relative error (2-norm, units of 1e-8, half-zero
+// activations, c_in = 128 / 256 / 512 / 1024, 50 % kept): 4.1 / 5.3 / 7.1 / 9.9; one 32-bit sum 10.6 / 14.6 / 20.5 / 28.8,
+// two sums 8.2 / 10.8 / 14.9 / 20.6; one active channel per pixel 2.6 against 2.5.  (The splitting is that of the known
+// emulations of single precision on bfloat16 units: Henry, Tang, Heinecke, "Leveraging the bfloat16 artificial
+// intelligence datatype for higher-precision computations", 2019.)
 //
-// What bfloat16 cannot hold is done again with 32-bit multiply-adds over the kept blocks, output by output, by the
-// lane that owns the output: results that are not finite (an infinite or NaN activation, times the stored
+// What bfloat16 cannot hold is done again with 32-bit multiply-adds over the kept blocks, output by output: results that are not finite (an infinite or NaN activation, times the stored
 // zeros, reaches every output of its pixel), sums below 2^-100, and, in pixels that hold a non-zero
 // activation below 2^-100 (whose last bits can lie below the smallest bfloat16), sums so small that those bits could matter.
 //
 // Mapping.  A workgroup owns T = 32 * PX pixels x 32 * NWV output channels; a wave T pixels x 32 channels
 // (two bundles).  Weights are operand A, activations operand B, so a lane ends with four times four consecutive
-// output channels (filter groups) of one pixel: 16-byte stores, no transpose.  Per chunk of 64 input
+// output channels (filter groups) of one pixel: 16-byte stores.  Per chunk of 64 input
 // channels the activations go global -> registers -> triples -> LDS (two buffers, one barrier per
-// chunk), the weights' fragments go straight to registers, one step of 16 channels ahead.
+// chunk), the weights' fragments go straight to registers, two steps of 16 channels ahead.
 //
 // Two forms (launch_conv1x1_wide has the rule):
 //   PX = 2, NWV = 4: 64 x 128 tiles, a workgroup per tile, three to a compute unit, which cover each

@@ -59,7 +59,10 @@ def test_edges(form, n, h, w, K, N, pct, go, gi):
     p, wt, mask, b = pack(K, N, pct, go, gi)
     x = W.uniform_activation(9102 + h + w, (n, h, w, K))
     ref, bound = R.sparse_conv_reference(x, wt, mask, go, gi, bias=b, stride=1, pad=1, act=R.ACT_RELU)
-    assert_within_bound(run(p, x, N, form), ref, bound, f"form {form}")
+    y = run(p, x, N, form)
+    assert_within_bound(y, ref, bound, f"form {form}")
+    # a rounding of 2^-23 of what has been summed per row of taps of 32 channels and six within it, 8 for the rest
+    assert np.all(np.abs(y - ref) <= (3 * ((K + 31) // 32) + 14) * 2.0 ** -23 * (bound + np.abs(b)))
 
 
 @pytest.mark.parametrize("form", FORMS)
@@ -119,7 +122,7 @@ def test_single_products_keep_every_bit(form, n, h, w, K, N, pct, go, gi):
     at = np.stack(np.meshgrid(np.arange(n), np.arange(0, h, 3), np.arange(0, w, 3), indexing="ij"), -1).reshape(-1, 3)
     x[at[:, 0], at[:, 1], at[:, 2], np.arange(len(at)) % K] = W.uniform_activation(9105, (len(at),)) + np.float32(1.5)
     ref = convolve64(x, kept_weights(wt, mask, go, gi))
-    assert np.all(np.abs(run(p, x, N, form) - ref) <= 2.0 ** -23 * np.abs(ref))
+    assert np.all(np.abs(run(p, x, N, form) - ref) <= 2.25 * 2.0 ** -24 * np.abs(ref))
 
 
 @pytest.mark.parametrize("form", FORMS + (0,))

@@ -11,7 +11,8 @@ from helpers import assert_within_bound
 
 pytestmark = pytest.mark.gpu
 
-FORMS = {S.SBN_CONV1X1: [0, 11, 12, 14, 21, 22, 112, 121, 504, 508, 516, 1012, 1021, 1112, 1121], S.SBN_CONV3X3: [0, 1, 2, 3, 32]}
+FORMS = {S.SBN_CONV1X1: [0, 11, 12, 14, 21, 22, 112, 121, 504, 508, 516, 1012, 1021, 1112, 1121, 2064, 2256],
+         S.SBN_CONV3X3: [0, 1, 2, 3, 32, 2064, 2065, 2128]}
 
 
 def random_case(rng):
@@ -44,6 +45,7 @@ def test_random_layers_every_form(seed):
             mask = S.sbn_prune_magnitude(wp, kind, c["go"], c["gi"], c["pct"])
             assert np.array_equal(mask, R.prune_mask(wp, c["go"], c["gi"], c["pct"])), c
             act = S.SBN_ACT_RELU if c["relu"] else S.SBN_ACT_NONE
+            S.sbn_force_kernel_form(kind, 2064)        # (so that the layer gets the wide forms' tables)
             p = S.sbn_pack(kind, wt, c["go"], c["gi"], mask=mask, bias=b, perm_out=po, perm_in=pi,
                            stride=c["stride"], act=act)
             ref, bound = R.sparse_conv_reference(x, wt, mask, c["go"], c["gi"], bias=b, perm_out=po, perm_in=pi,
