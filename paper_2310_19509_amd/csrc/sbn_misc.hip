@@ -26,18 +26,19 @@ __global__ __launch_bounds__(256) void copy_kernel(const v4f* __restrict__ src, 
 // scalar and which is empty when the row lies outside the image, a lane's three column offsets are worked out once
 // and lead outside the buffer where the column does.  (With a pixel per thread decoded by three 64-bit
 // divisions and a select per load, the 14 x 14 x 512 layer at batch 64 took 17.2 us, 3.0 TB/s;
-// so 15.6, and 15.0 with the blocks in XCD order.  28 x 28 x 256, stride 1 and from 56 x 56 by stride 2: 27.0 -> 23.5,
-// 23.0 -> 19.9 us.)
+// so 15.6.)
 template <int STRIDE, int R>
 __global__ __launch_bounds__(256) void dw3x3_kernel(const float* __restrict__ x, float* __restrict__ y,
                                                    const float* __restrict__ wt, const float* __restrict__ bias,
                                                    int h, int w, int c, int oh, int ow, int act, unsigned strips,
-                                                   unsigned blocks_per_strip, unsigned blocks)
+                                                   unsigned blocks_per_strip, unsigned blocks_per_image, unsigned eights)
 {
-    // Workgroup ids go round the eight XCDs; every XCD gets a run of neighbouring blocks, whose columns and rows
-    // overlap, so that the overlap is read from its L2.
-    const unsigned id = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    if (id >= blocks) return;
+    // Workgroup ids go round the eight XCDs.  Of every eight images each XCD gets one whole, so that the rows and columns
+    // that its blocks share are read from its L2; images past the last eight (block `eights` on) are spread block by
+    // block.  (MobileNet-v1, 70 %, us, in plain order, with one run of images per XCD, and so: 64 images of 224 x 224 721, 708, 703;
+    // 32 of 224 x 224 453, 457, 446; 64 of 128 x 128 349, 373, 332 -- the runs then begin at a power of two from each other.)
+    unsigned id = blockIdx.x;
+    if (id < eights) id = ((id >> 3) / blocks_per_image * 8u + (id & 7u)) * blocks_per_image + (id >> 3) % blocks_per_image;
     const unsigned row_block = id / blocks_per_strip, ib = id % blocks_per_strip;
     const unsigned c4n = (unsigned)c >> 2;
     const unsigned i0 = ib * blockDim.x, i = i0 + threadIdx.x;            // position in the row of ow * c / 4 quads
@@ -354,19 +355,20 @@ int launch_dw3x3(const float* x, float* y, const float* w_dev, const float* b_de
         stride == 1 ? go(dw3x3_narrow_kernel<1, 4>) : go(dw3x3_narrow_kernel<2, 4>);
         return check_launch("dw3x3");
     }
-    // Strips of four rows load 4.5 (stride 2: 6.75) values per output instead of 9; where they leave fewer than four
-    // waves per compute unit, one row each: the chain of loads is shorter.
+    // Strips of four rows load 4.5 (stride 2: 6.75) values per output instead of 9; where they leave fewer than two
+    // waves per compute unit, one row each: the chain of loads is shorter.  (49 images, 1.5 waves, 8 x 8 x 512 by stride 2: 5.4 and 5.1 us; 3
+    // waves, 16 x 16 x 256 by stride 2: 5.7 and 6.8, 4 x 4 x 1024: 6.1 and 7.2.)
     int device = 0, cus = 0;
     if (hipGetDevice(&device) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) cus = 256;
-    const bool small = (long long)n * ((oh + 3) / 4) * quads < 64ll * 4 * cus;
+    const bool small = (long long)n * ((oh + 3) / 4) * quads < 64ll * 2 * cus;
     const int R = small ? 1 : 4;
     // (blocks of 64 threads where a row is short: at most 63 idle lanes per strip)
     const unsigned threads = quads % 256 == 0 || quads >= 2048 ? 256 : 64;
     const long long strips = (oh + R - 1) / R, per_strip = (quads + threads - 1) / threads, blocks = n * strips * per_strip;
-    if (blocks > 0x7FFFFFF0ll) return fail(SBN_EINVAL, "depthwise layer too large for one launch");
+    if (blocks > 0x7FFFFFFFll) return fail(SBN_EINVAL, "depthwise layer too large for one launch");
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(threads), 0, (hipStream_t)stream, x, y, w_dev, b_dev, h, w, c,
-                           oh, ow, act, (unsigned)strips, (unsigned)per_strip, (unsigned)blocks);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, (hipStream_t)stream, x, y, w_dev, b_dev, h, w, c,
+                           oh, ow, act, (unsigned)strips, (unsigned)per_strip, (unsigned)(strips * per_strip), (unsigned)(n / 8 * 8 * strips * per_strip));
     };
     if (stride == 1)
         small ? go(dw3x3_kernel<1, 1>) : go(dw3x3_kernel<1, 4>);
