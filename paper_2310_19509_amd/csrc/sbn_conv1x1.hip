@@ -840,7 +840,7 @@ int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long M, v
         variant = ((M + 127) / 128) * n_col_tiles >= 3ll * cus ? 21 : 12;
         // Layers that keep much run on triples of bfloat16 (sbn_conv1x1_wide.hip), from more pixels on than the
         // few-pixel form takes.  Their results are closer to the exact ones than any 32-bit form's (figures there).
-        if (!force && p->dev.d_wt && wg_split > 4ll * cus && conv1x1_wide_pays(p)) return launch_conv1x1_wide(p, x, y, M, 0, stream);
+        if (!force && wg_split > 4ll * cus && conv1x1_wide_chosen(p, M)) return launch_conv1x1_wide(p, x, y, M, 0, stream);
         // Whole rounds of workgroups only: when the last round would occupy at most half of
         // the compute units, the pixels of that round go to few-pixel workgroups instead.
         const int px = variant == 21 ? 128 : 64;

@@ -347,6 +347,14 @@ int launch(const sbn_packed* p, const float* x, float* y, long long M, hipStream
 
 namespace sbn {
 
+// Launches of a few more 64 x 128 tiles than compute units, where some units have two and most one, need more of a margin
+// (2254 pixels, 55 % kept: 512 x 1024 21.1 us against 19.5 of the 32-bit form, 1024 x 1024 35.5 against 34.3; 1 568 pixels 14 against 18).
+bool conv1x1_wide_chosen(const sbn_packed* p, long long M)
+{
+    const long long tiles = (M + 63) / 64 * ((p->c_out + 127) / 128), cus = p->dev.cus;
+    return p->dev.d_wt && conv1x1_wide_margin(p) >= (tiles > cus && 3 * tiles < 4 * cus ? 1.45 : 1.0);
+}
+
 // form 0: 128 x 256 tiles where they fill three quarters of the rounds that one tile per compute unit makes, else 64 x 128
 // tiles (512 x 512: 100352 pixels, 6.1 rounds, 261 us against 310; 50176 pixels, 3.06 of 4 rounds, 149 against 165; 9000 pixels,
 // 0.55 of a round, 40 against 34; 1024 x 1024, 6272 pixels, 0.77 of a round, 73 against 86).  Layers of few chunks

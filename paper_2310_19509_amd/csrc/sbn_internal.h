@@ -62,6 +62,7 @@ struct DeviceLayout {
     int n_bundles = 0;
     int n_chunks = 0;                     // ceil(c_in / 64)
     size_t n_entries = 0;
+    size_t n_present = 0;                 // (entry, group) pairs kept: 4 x 4 blocks (times taps) that the 32-bit forms multiply
     int n_chunks32 = 0;                   // ceil(c_in / 32)
     int cus = 256;                        // compute units of the device the layer lives on (set at upload)
     // host staging
@@ -123,6 +124,7 @@ void build_device_layout(sbn_packed* p);
 const char* check_device_layout(const sbn_packed* p);
 // Whether a layer keeps enough for the wide multiplies, whatever the pixels: the launch rules and the packer, which
 // builds the triples only where a launch can come to use them.
+double conv1x1_wide_margin(const sbn_packed* p);
 bool conv1x1_wide_pays(const sbn_packed* p);
 bool conv3x3_wide_pays(const sbn_packed* p);
 double conv3x3_share_kept(const sbn_packed* p);
@@ -132,6 +134,7 @@ void release_device_layout(sbn_packed* p);
 
 // Kernel launchers (defined in the .hip files).
 int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long m, void* stream);
+bool conv1x1_wide_chosen(const sbn_packed* p, long long m);
 int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long m, int form, void* stream);
 bool conv3x3_wide_takes(const sbn_packed* p, int n, int h, int w);       // whether the kernel takes these extents,
 bool conv3x3_wide_chosen(const sbn_packed* p, int n, int h, int w);      // and whether it is the faster one for them

@@ -13,24 +13,24 @@
 namespace sbn {
 
 // The wide multiplies take the time of all c_in x c_out weights, channels past c_out in a 128-channel tile included;
-// the 32-bit forms that of the kept ones plus a share that does not shrink with them.  Gain over the 32-bit
-// form that the rule replaces, at a share kept of 1 / 0.7 / 0.6 / 0.5 / 0.4 (layers in turn, so that weights are not in
-// the L2; the line lies in the gap marked |):
+// the 32-bit forms that of the 4 x 4 blocks that hold a kept weight plus a share that does not shrink with them.  The
+// margin is the share of such blocks over the least that pays.  Gain over the 32-bit form that the rule replaces, at a
+// share of 1 / 0.7 / 0.6 / 0.5 / 0.4 (layers in turn, so that weights are not in the L2; margin 1 lies in the gap marked |):
 //   c_in  128, 25088 pixels x 128     1.12 | 1.00 0.97 0.91
 //         256, 50176 x 256            1.46 1.12 | 1.02 0.93 0.83
 //         512, 50176 x 512            1.57 1.32 1.20 1.06 | 0.97
 //         768, 10000 x 384            1.92 1.48 1.32 1.18 | 1.09
 //        1024, 12544 x 1024           1.69 1.34 1.23 1.12 1.00 |
 // (Fewer than 96 output channels leave a quarter of a tile or more idle.)
-bool conv1x1_wide_pays(const sbn_packed* p)
+double conv1x1_wide_margin(const sbn_packed* p)
 {
-    const long long kept = (long long)p->kidx.size() * p->go * p->gi;                 // of all filters
-    const long long padded = (p->c_out + 127) / 128 * 128;
-    return p->c_out > 80 && 16 * kept >= (5ll * p->c_in + 1280) * padded;
+    const double padded = (double)((p->c_out + 127) / 128 * 128);
+    return p->c_out > 80 ? 256.0 * (double)p->dev.n_present / ((5.0 * p->c_in + 1280.0) * padded) : 0.0;
 }
+bool conv1x1_wide_pays(const sbn_packed* p) { return conv1x1_wide_margin(p) >= 1.0; }
 
-// Kernels that a layer keeps, over all that the wide multiplies go through (input channels in 32s, output channels in
-// 64s).  The multiplies' time does not depend on it, the 32-bit form's does; us, 32-bit form against this one (layers in
+// Kernels in 4 x 4 blocks that a layer keeps, over all that the wide multiplies go through (input channels in 32s,
+// output channels in 64s).  The multiplies' time does not depend on it, the 32-bit form's does; us, 32-bit form against this one (layers in
 // turn, so that weights are not in the L2):
 //   share kept                   0.5       0.4       0.3       0.2
 //   3 x 23 x 23, 128 x 128       19 / 15   17 / 15   15 / 15   13 / 15
@@ -42,7 +42,7 @@ bool conv1x1_wide_pays(const sbn_packed* p)
 // (At 0.3, where it is a tie, the 32-bit form's smaller tables decide: with three sets of four such layers in turn 164 us against 174.)
 double conv3x3_share_kept(const sbn_packed* p)
 {
-    return (double)p->kidx.size() * p->go * p->gi / ((double)((p->c_in + 31) / 32 * 32) * ((p->c_out + 63) / 64 * 64));
+    return 16.0 * (double)p->dev.n_present / ((double)((p->c_in + 31) / 32 * 32) * ((p->c_out + 63) / 64 * 64));
 }
 bool conv3x3_wide_pays(const sbn_packed* p) { return p->stride == 1 && p->c_in >= 32 && conv3x3_share_kept(p) >= 0.33; }
 
@@ -118,6 +118,7 @@ void build_device_layout(sbn_packed* p)
     L.woff32.assign((size_t)L.n_bundles * (L.n_chunks32 + 1), 0u);
     L.wts.clear();
     size_t n_entries = 0;
+    L.n_present = 0;
 
     const int sub = go / 4;                                          // 4-filter groups per canonical row
     const size_t n_pos = (size_t)(p->c_in + 3) / 4;
@@ -147,6 +148,7 @@ void build_device_layout(sbn_packed* p)
         for (size_t kb4 = 0; kb4 < n_pos; ++kb4)
             if (present[kb4] != 0) {
                 entry[kb4] = n_entries++;
+                L.n_present += (size_t)__builtin_popcount(present[kb4]);
                 kept.push_back((int)kb4);
             }
         L.wts.resize(n_entries * wstride, 0.0f);
