@@ -235,3 +235,31 @@ def test_outputs_done_again_one_by_one_and_side_by_side(form, spoilt):
     ok = np.isfinite(y)
     assert ok[0, 0, spoilt:].all() and ok[0, 0, :, ~keeps].all()
     assert np.all(np.abs(y - ref)[ok] <= 324 * 2.0 ** -24 * bound[ok] + 2.0 ** -23 * np.abs(ref[ok]))
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_marks_stay_with_their_tile(form):
+    """Pixels below the range here and there in many tiles, which the streaming form walks one after the other."""
+    K, N, m = 128, 256, 128 * 128 * 2 + 77
+    w = W.he_weights(9013, N, 1, 1, K) * np.float32(1e30)
+    mask = np.ones((N // 4, K // 4), np.uint8)
+    x = np.abs(W.uniform_activation(9014, (1, 1, m, K)))
+    x[0, 0, 5::97] *= np.float32(1e-36)
+    p = pack_wide(w, 4, 4, mask=mask)
+    wm = kept_weights(w, mask, 4, 4)
+    ref, bound = x[0, 0].astype(np.float64) @ wm.T, x[0, 0].astype(np.float64) @ np.abs(wm).T
+    assert np.all(np.abs(run(p, x, N, form)[0, 0] - ref) <= K * 2.0 ** -24 * bound)
+
+
+@pytest.mark.parametrize("form", FORMS + (0,))
+@pytest.mark.parametrize("value", [1e-38, 1e-44, 3.4e38])
+def test_weights_outside_the_range_stay_with_the_32_bit_kernels(form, value):
+    K, N, m = 128, 128, 300
+    w = W.he_weights(9015, N, 1, 1, K)
+    w[7, 0, 0, 60:64] = np.float32(value)
+    mask = np.ones((N // 4, K // 4), np.uint8)
+    x = np.zeros((1, 1, m, K), np.float32)
+    x[0, 0, :, 60] = 0.25
+    p = pack_wide(w, 4, 4, mask=mask)
+    ref = 0.25 * w[:, 0, 0, 60].astype(np.float64)
+    assert np.all(np.abs(run(p, x, N, form)[0, 0] - ref) <= 2.0 ** -23 * np.abs(ref) + 2.0 ** -149)
