@@ -83,7 +83,7 @@ static void build_triples(sbn_packed* p)
     for (int b = 0; b < L.n_bundles; ++b)
         for (int c = 0; c < L.n_chunks32; ++c) {
             const uint32_t* r = &L.records32[((size_t)b * L.n_chunks32 + c) * 8];
-            const float* w = &L.wts[(size_t)L.woff32[(size_t)b * (L.n_chunks32 + 1) + c] * wstride];
+            const float* w = L.wts.data() + (size_t)L.woff32[(size_t)b * (L.n_chunks32 + 1) + c] * wstride;
             for (int q = 0; q < 8 && r[q] != 0; ++q, w += wstride) {
                 const int piece = (int)(r[q] >> 12);                     // channels 4 * piece .. + 3 of the 32
                 uint16_t* frag = &L.wt[((size_t)(b / 2) * n_steps + (size_t)c * 2 * taps + piece / 4) * 1536 +

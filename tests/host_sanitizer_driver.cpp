@@ -125,6 +125,10 @@ static int one_layer(int kind, int c_in, int c_out, int go, int gi, int pct, boo
     sbn_packed_t* q = nullptr;
     CHECK(sbn_pack(&d, -1, &q) == SBN_OK && q);
     sbn_free(q);
+    // with the tables of the wide kernels, whatever the layer keeps
+    d.mask = mask.data();
+    CHECK(sbn_force_kernel_form(kind, 2064) == SBN_OK && sbn_pack(&d, -1, &q) == SBN_OK && q && sbn_force_kernel_form(kind, 0) == SBN_OK);
+    sbn_free(q);
     sbn_free(p);
     return 0;
 }
@@ -244,7 +248,7 @@ int main()
     const int cases[][7] = {
         // kind, c_in, c_out, go, gi, pct, perms
         {SBN_CONV1X1, 64, 32, 4, 4, 50, 1}, {SBN_CONV1X1, 72, 40, 8, 4, 30, 1}, {SBN_CONV1X1, 9, 8, 4, 1, 70, 0},
-        {SBN_CONV1X1, 96, 16, 4, 8, 90, 1}, {SBN_CONV1X1, 16, 16, 4, 2, 100, 0}, {SBN_CONV1X1, 200, 24, 4, 4, 0, 1},
+        {SBN_CONV1X1, 96, 16, 4, 8, 90, 1}, {SBN_CONV1X1, 16, 16, 4, 2, 100, 0}, {SBN_CONV1X1, 128, 16, 4, 4, 100, 0}, {SBN_CONV1X1, 200, 24, 4, 4, 0, 1},
         {SBN_CONV3X3, 32, 16, 4, 4, 70, 1}, {SBN_CONV3X3, 24, 8, 8, 4, 50, 0}, {SBN_CONV3X3, 40, 24, 4, 1, 60, 1},
     };
     for (const auto& c : cases)
