@@ -17,9 +17,8 @@
 // conflicts (see the kernel).
 //
 // Per entry (a 4-channel piece kept by at least one group of the bundle) the
-// wave holds the entry's 9 x 64 weights ([tap][group][ci][co], one register
-// per tap, fetched one entry ahead; with PX = 2 one row of taps at a time,
-// fetched a row ahead) and walks the three rows of taps: the
+// wave holds the entry's 9 x 64 weights ([tap][group][co][ci], fetched one
+// entry ahead; with PX = 2 one row of taps at a time, fetched a row ahead) and walks the three rows of taps: the
 // lane reads the row's shifted 16-byte activation vectors (one row ahead of
 // the arithmetic) and, for every present group, issues 12 v_mfma_f32_4x4x1
 // per pixel: the weight column [co 0..3] of (group, ci) is broadcast from
@@ -52,35 +51,57 @@ __device__ __forceinline__ v4f mfma_bcast(float w, float x, v4f c)
     return __builtin_amdgcn_mfma_f32_4x4x1f32(w, x, c, 4, ABID, 0);
 }
 
-// One row of taps (ky = KY, kx = 0..2) of group G over the lane's PX pixels.  w holds the entry's
-// nine taps (WT = 9) or just this row's three (WT = 3), lane l = [g][ci][co]; x holds the
+// Weights of an entry in registers, in the table [tap][g][co][ci].  A 16-byte load per lane brings four taps at a time: lane
+// 16 * (tap % 4) + 4 * g + co holds the four input channels.  All nine taps (WT = 9): two such loads and one of four bytes, lane
+// [g][ci][co], for the last tap; a row of three (WT = 3): one.  (A load per tap, nine of four bytes, takes
+// the four 3x3 layers of a ResNet-50 at batch 32 and 70 % from 160 to 165 us.)
+template <int WT>
+struct Weights {
+    v4f four[WT == 9 ? 2 : 1];
+    float last;
+};
+// tap T of those held, group G, input channel CI over activation x
+template <int T, int G, int CI, int WT>
+__device__ __forceinline__ v4f tap_fma(const Weights<WT>& w, float x, v4f c)
+{
+    if constexpr (T < 8)
+        return mfma_bcast<T % 4 * 4 + G>(w.four[T / 4][CI], x, c);
+    else
+        return mfma_bcast<G * 4 + CI>(w.last, x, c);
+}
+
+// One row of taps (ky = KY, kx = 0..2) of group G over the lane's PX pixels.  x holds the
 // (PX-1)*STRIDE+3 input columns under the pixels.
 // PX = 1: acc[G][0/1] are two partial sums of the one pixel (a dependent MFMA issues later than an
 // independent one, which shows when a SIMD holds one or two waves: a single sum was measured 8-20 %
 // slower there); PX = 2: acc[G][p] is pixel p.
-template <int G, int KY, int PX, int STRIDE, int NX, int WT>
-__device__ __forceinline__ void row_fma(const float (&w)[WT], const v4f (&x)[NX], v4f (&acc)[4][2])
+template <int G, int KY, int KX, int PX, int STRIDE, int NX, int WT>
+__device__ __forceinline__ void column_fma(const Weights<WT>& w, const v4f (&x)[NX], v4f (&acc)[4][2])
 {
-#pragma unroll
-    for (int kx = 0; kx < 3; ++kx) {
-        const float wt = w[WT == 9 ? KY * 3 + kx : kx];
-        if constexpr (PX == 1) {
-            acc[G][0] = mfma_bcast<G * 4 + 0>(wt, x[kx].x, acc[G][0]);
-            acc[G][1] = mfma_bcast<G * 4 + 1>(wt, x[kx].y, acc[G][1]);
-            acc[G][0] = mfma_bcast<G * 4 + 2>(wt, x[kx].z, acc[G][0]);
-            acc[G][1] = mfma_bcast<G * 4 + 3>(wt, x[kx].w, acc[G][1]);
-        } else {
-            const v4f x0 = x[kx], x1 = x[STRIDE + kx];
-            acc[G][0] = mfma_bcast<G * 4 + 0>(wt, x0.x, acc[G][0]);
-            acc[G][1] = mfma_bcast<G * 4 + 0>(wt, x1.x, acc[G][1]);
-            acc[G][0] = mfma_bcast<G * 4 + 1>(wt, x0.y, acc[G][0]);
-            acc[G][1] = mfma_bcast<G * 4 + 1>(wt, x1.y, acc[G][1]);
-            acc[G][0] = mfma_bcast<G * 4 + 2>(wt, x0.z, acc[G][0]);
-            acc[G][1] = mfma_bcast<G * 4 + 2>(wt, x1.z, acc[G][1]);
-            acc[G][0] = mfma_bcast<G * 4 + 3>(wt, x0.w, acc[G][0]);
-            acc[G][1] = mfma_bcast<G * 4 + 3>(wt, x1.w, acc[G][1]);
-        }
+    constexpr int T = WT == 9 ? KY * 3 + KX : KX;
+    if constexpr (PX == 1) {
+        acc[G][0] = tap_fma<T, G, 0>(w, x[KX].x, acc[G][0]);
+        acc[G][1] = tap_fma<T, G, 1>(w, x[KX].y, acc[G][1]);
+        acc[G][0] = tap_fma<T, G, 2>(w, x[KX].z, acc[G][0]);
+        acc[G][1] = tap_fma<T, G, 3>(w, x[KX].w, acc[G][1]);
+    } else {
+        const v4f x0 = x[KX], x1 = x[STRIDE + KX];
+        acc[G][0] = tap_fma<T, G, 0>(w, x0.x, acc[G][0]);
+        acc[G][1] = tap_fma<T, G, 0>(w, x1.x, acc[G][1]);
+        acc[G][0] = tap_fma<T, G, 1>(w, x0.y, acc[G][0]);
+        acc[G][1] = tap_fma<T, G, 1>(w, x1.y, acc[G][1]);
+        acc[G][0] = tap_fma<T, G, 2>(w, x0.z, acc[G][0]);
+        acc[G][1] = tap_fma<T, G, 2>(w, x1.z, acc[G][1]);
+        acc[G][0] = tap_fma<T, G, 3>(w, x0.w, acc[G][0]);
+        acc[G][1] = tap_fma<T, G, 3>(w, x1.w, acc[G][1]);
     }
+}
+template <int G, int KY, int PX, int STRIDE, int NX, int WT>
+__device__ __forceinline__ void row_fma(const Weights<WT>& w, const v4f (&x)[NX], v4f (&acc)[4][2])
+{
+    column_fma<G, KY, 0, PX, STRIDE>(w, x, acc);
+    column_fma<G, KY, 1, PX, STRIDE>(w, x, acc);
+    column_fma<G, KY, 2, PX, STRIDE>(w, x, acc);
 }
 
 template <int STRIDE, int PX, bool DEEP, int SPLIT>
@@ -201,17 +222,21 @@ __global__ __launch_bounds__(256 * SPLIT) void conv3x3_kernel(const float* __res
     const uint32_t* wo = woff + (size_t)bsafe * (n_sub + 1);
     const uint32_t* recs = records + (size_t)bsafe * n_sub * 8;
 
-    // Weights: one register per tap, lane l = [g][ci][co].  Fetched an entry ahead (WT = 9), or, with
-    // two pixels per lane, a row of taps ahead (WT = 3): that form needs the registers for the
-    // second pixel's window, and a row already carries 24 multiplies per present group.
+    // Weights are fetched an entry ahead (WT = 9), or, with two pixels per lane, a row of taps ahead (WT = 3):
+    // that form needs the registers for the second pixel's window, and a row already carries 24 multiplies per present group.
+    // (A row's load reads a tap too many; the table has slack behind it.)
     constexpr int WT = PX == 2 ? 3 : 9;
-    auto load_w = [&](uint32_t en, int ky, float (&w)[WT]) {
-        const float* wp = wts + (size_t)en * 576 + (WT == 3 ? ky * 192 : 0) + lane;
-#pragma unroll
-        for (int t = 0; t < WT; ++t) w[t] = wp[t * 64];
+    const int last_lane = 512 + (lane & 48) + (lane & 3) * 4 + ((lane >> 2) & 3);
+    auto load_w = [&](uint32_t en, int ky, Weights<WT>& w) {
+        const float* wp = wts + (size_t)en * 576 + (WT == 3 ? ky * 192 : 0);
+        w.four[0] = *(const v4f*)(wp + lane * 4);
+        if constexpr (WT == 9) {
+            w.four[1] = *(const v4f*)(wp + 256 + lane * 4);
+            w.last = wp[last_lane];
+        }
     };
-    float wa[WT], wb[WT];     // weights in use and weights on their way
-    float wn[SPLIT > 1 ? WT : 1];   // SPLIT > 1: first weights of the slice's next sub-chunk
+    Weights<WT> wa, wb;     // weights in use and weights on their way
+    Weights<WT> wn;         // SPLIT > 1: first weights of the slice's next sub-chunk
     // dv: descriptors of the sub-chunk being multiplied, one per lane (lanes 0..7); e: the entry
     // whose first weights are in wa.  A bundle's entries are numbered in channel order, so with
     // SPLIT = 1 the entry after a sub-chunk's last is the next sub-chunk's first and e just counts
@@ -250,7 +275,7 @@ __global__ __launch_bounds__(256 * SPLIT) void conv3x3_kernel(const float* __res
                     xr[c] = *(const v4f*)(xl + (xrow[ky] + (s16 ^ g16[j])) + (ky * IWP + c) * 128);
                 }
             };
-            auto row = [&](auto kytag, uint32_t m, const float (&w)[WT], const v4f (&xr)[NX]) {
+            auto row = [&](auto kytag, uint32_t m, const Weights<WT>& w, const v4f (&xr)[NX]) {
                 constexpr int KY = decltype(kytag)::value;
                 // Each row tests its own copy of the mask with scalar instructions: were the three
                 // rows' tests recognised as the same, the compiler would keep their results in
@@ -273,8 +298,8 @@ __global__ __launch_bounds__(256 * SPLIT) void conv3x3_kernel(const float* __res
             // of some entry, or the array's slack).
             // e_cur: this entry's index, e_fetch: the entry whose first weights are fetched meanwhile
             // (SPLIT > 1: not used after the sub-chunk's last entry).
-            auto entry = [&](uint32_t d, uint32_t d_nxt, uint32_t e_cur, uint32_t e_fetch, float (&w)[WT],
-                             float (&w_nxt)[WT], XW& p, XW& r) {
+            auto entry = [&](uint32_t d, uint32_t d_nxt, uint32_t e_cur, uint32_t e_fetch, Weights<WT>& w,
+                             Weights<WT>& w_nxt, XW& p, XW& r) {
                 if constexpr (WT == 3) {
                     // weights and activations both run one row ahead; on exit w_nxt and r hold the
                     // first row of the next entry
@@ -341,8 +366,7 @@ __global__ __launch_bounds__(256 * SPLIT) void conv3x3_kernel(const float* __res
             }
         }
         if constexpr (SPLIT > 1) {
-#pragma unroll
-            for (int t = 0; t < WT; ++t) wa[t] = wn[t];
+            wa = wn;
             e = e1;
             e1 = __builtin_amdgcn_readfirstlane(e2);
         }

@@ -47,7 +47,7 @@ struct Exact {
         if (act == SBN_ACT_RELU) acc = relu4(acc);
         *(v4f*)(y + pix * N + ch) = acc;
     }
-    // one entry: w = its group's [tap][ci][co], xp = its piece of the centre pixel
+    // one entry: w = its group's [tap][co][ci], xp = its piece of the centre pixel
     __device__ __forceinline__ void entry(v4f& acc, const v4f* w, const float* xp, int ox, int oy) const
     {
 #pragma unroll 1
@@ -60,15 +60,10 @@ struct Exact {
                 in[u] = ox + u - 1 >= 0 && ox + u - 1 < W;
                 xv[u] = *(const v4f*)(xp + ((long long)dy * W + (in[u] ? u - 1 : 0)) * K);
 #pragma unroll
-                for (int ci = 0; ci < 4; ++ci) wv[u][ci] = w[u * 16 + ci];
+                for (int co = 0; co < 4; ++co) wv[u][co] = w[u * 16 + co];
             }
 #pragma unroll
-            for (int u = 0; u < 3; ++u)
-                if (in[u])
-#pragma unroll
-                    for (int ci = 0; ci < 4; ++ci)
-#pragma unroll
-                        for (int co = 0; co < 4; ++co) acc[co] = __builtin_fmaf(wv[u][ci][co], xv[u][ci], acc[co]);
+            for (int u = 0; u < 3; ++u) add_piece(acc, wv[u], xv[u], in[u]);
         }
     }
     __device__ __forceinline__ void by_lane(int pix, int ch) const

@@ -51,7 +51,7 @@ int forced_kernel_form(int kind);                              // sbn_force_kern
 // (zeros where absent), transposed so that a 16-byte load per lane yields the
 // four input channels of one output channel:
 //     1x1:  wts[entry][g][co][ci]                 64 floats per entry
-//     3x3:  wts[entry][tap][g][ci][co]            9*64 floats per entry (4-byte loads per lane)
+//     3x3:  wts[entry][tap][g][co][ci]            9*64 floats per entry
 constexpr int kBundleGroups = 4;                       // groups of 4 filters per bundle
 constexpr int kBundleChannels = 4 * kBundleGroups;     // 16 output channels per bundle
 constexpr int kChunk = 64;                             // input channels per record

@@ -91,7 +91,7 @@ static void build_triples(sbn_packed* p)
                 for (int t = 0; t < taps; ++t, frag += 2 * 1536)
                     for (int f = 0; f < kBundleChannels; ++f)            // (removed groups' weights are zeros)
                         for (int ci = 0; ci < 4; ++ci) {
-                            const float v = taps == 1 ? w[f * 4 + ci] : w[t * 64 + f / 4 * 16 + ci * 4 + f % 4];
+                            const float v = w[t * 64 + f * 4 + ci];
                             float hi, mid, lo;
                             frag[f * 8 + ci] = to_bf16(v, &hi);
                             frag[f * 8 + ci + 512] = to_bf16(v - hi, &mid);
@@ -159,13 +159,8 @@ void build_device_layout(sbn_packed* p)
                     const int ch = p->kidx[e] + c;
                     float* const to = &L.wts[entry[(size_t)ch / 4] * wstride + (size_t)g * 16];
                     const float* const from = &p->vals[e * blk + (size_t)c * go + (size_t)s * 4];
-                    // 1x1: [g][co][ci] (16-byte loads per lane); 3x3: [tap][g][ci][co] (4-byte loads)
-                    if (taps == 1)
-                        for (int co = 0; co < 4; ++co) to[co * 4 + ch % 4] = from[co];
-                    else
-                        for (int t = 0; t < taps; ++t)
-                            for (int co = 0; co < 4; ++co)
-                                to[(size_t)t * kBundleGroups * 16 + (size_t)(ch % 4) * 4 + co] = from[(size_t)t * gi * go + co];
+                    for (int t = 0; t < taps; ++t)                   // [tap][g][co][ci]
+                        for (int co = 0; co < 4; ++co) to[(size_t)t * kBundleGroups * 16 + co * 4 + ch % 4] = from[(size_t)t * gi * go + co];
                 }
         }
         // records and chunk offsets
