@@ -326,13 +326,15 @@ int sbn_conv3x3_sparse(const sbn_packed_t* p, const float* x, float* y,
  * choice among the forms so far, without those tables; 2064, 2256: 64 x 128 and 128 x 256 tiles on
  * triples of bfloat16, for layers of c_in > 64 and a multiple of 4 that keep enough for the automatic choice to
  * come to use them or that were packed while one of the two was forced, the automatic
- * choice otherwise) or SBN_CONV3X3 (1, 2, 3: one pixel per lane, two pixels per
+ * choice otherwise; 3004, 3008: the few-pixel kernel, 16 pixels x 16 channels
+ * per workgroup of 4 or 8 waves that split the input channels) or SBN_CONV3X3 (1, 2, 3: one pixel per lane, two pixels per
  * lane, entry-ahead fetch; 32: entry-ahead with the input channels split over
  * two halves of an eight-wave workgroup; 2128, 2064, 2065: 128 x 64 tiles, 64 x 64
  * tiles and 64 x 64 tiles with two halves on triples of bfloat16, for layers of
  * stride 1 with the tables, as above, and images 4 to 127 wide
- * and at least 4 high, the automatic choice otherwise).  Layers whose shape leaves no choice (c_in <= 64,
- * c_in not a multiple of 4, stride 2) ignore it.  Unknown values: SBN_EINVAL.
+ * and at least 4 high, the automatic choice otherwise; 3004, 3008, 3016: the few-pixel
+ * kernel with 4, 8 or 16 waves, any stride).  Layers whose shape leaves no other choice (c_in <= 64,
+ * c_in not a multiple of 4, stride 2) ignore all but the few-pixel forms.  Unknown values: SBN_EINVAL.
  * Not synchronised with launches in flight on other threads.
  */
 int sbn_force_kernel_form(int kind, int form);

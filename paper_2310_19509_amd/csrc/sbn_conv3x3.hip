@@ -480,7 +480,9 @@ int launch_conv3x3(const sbn_packed* p, const float* x, float* y, int n, int h, 
         return fail(SBN_ESHAPE, "3x3 layers need c_in to be a multiple of 4 on the device (got %d)", p->c_in);
     hipStream_t st = (hipStream_t)stream;
     const int forced = forced_kernel_form(SBN_CONV3X3);
-    if (forced >= 2000 && conv3x3_wide_takes(p, n, h, w)) return launch_conv3x3_wide(p, x, y, n, h, w, forced, stream);
+    if (forced >= 3000 && few_takes(p, n, h, w)) return launch_few(p, x, y, n, h, w, forced, stream);
+    if (!forced && few_chosen(p, n, h, w)) return launch_few(p, x, y, n, h, w, 0, stream);
+    if (forced >= 2000 && forced < 3000 && conv3x3_wide_takes(p, n, h, w)) return launch_conv3x3_wide(p, x, y, n, h, w, forced, stream);
     if (!forced && conv3x3_wide_chosen(p, n, h, w)) return launch_conv3x3_wide(p, x, y, n, h, w, 0, stream);
     if (p->stride == 2) return launch<2, 1, false>(p, x, y, n, h, w, st);
     // Form, from timings of ResNet-50-shaped layers at batches 4..128 (thresholds in workgroups per

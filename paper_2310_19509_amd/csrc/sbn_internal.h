@@ -58,6 +58,8 @@ constexpr int kChunk = 64;                             // input channels per rec
 constexpr int kSlots = kChunk / 4;                     // descriptors per record
 constexpr double kStaticWalkMinFill = 0.60;            // share of (bundle, piece) pairs kept, from which the every-piece tables are built
 
+constexpr uint32_t kNoEntry = 0xFFFFF000u;             // outside any weight array; a few taps further the sum does not wrap
+
 struct DeviceLayout {
     int n_bundles = 0;
     int n_chunks = 0;                     // ceil(c_in / 64)
@@ -71,6 +73,7 @@ struct DeviceLayout {
     std::vector<uint32_t> records32;      // [n_bundles][n_chunks32][8]: the same entries per 32 channels,
     std::vector<uint32_t> woff32;         // [n_bundles][n_chunks32 + 1]   kb4_in_chunk < 8
     std::vector<float> wts;
+    std::vector<uint32_t> where;          // [n_bundles][n_chunks32 * 8]: byte offset in wts of the piece's entry, kNoEntry if no group keeps it
     std::vector<float> bias_padded;       // [n_bundles * 16], zeros when no bias
     // 1x1 layers that keep most of their pieces (see kStaticWalkMinFill) also get the tables with an
     // entry for EVERY piece, present or not: entry q of chunk c is piece q, so the kernel reads its
@@ -93,6 +96,7 @@ struct DeviceLayout {
     uint32_t* d_records32 = nullptr;
     uint32_t* d_woff32 = nullptr;
     float* d_wts = nullptr;
+    uint32_t* d_where = nullptr;
     float* d_bias = nullptr;
     uint32_t* d_desc_s = nullptr;         // NULL when the layer has no every-piece tables
     float* d_wts_s = nullptr;
@@ -139,6 +143,10 @@ int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long
 bool conv3x3_wide_takes(const sbn_packed* p, int n, int h, int w);       // whether the kernel takes these extents,
 bool conv3x3_wide_chosen(const sbn_packed* p, int n, int h, int w);      // and whether it is the faster one for them
 int launch_conv3x3_wide(const sbn_packed* p, const float* x, float* y, int n, int h, int w, int form, void* stream);
+// few output pixels, both kinds (sbn_few.hip); h = 1, w = 1 for 1x1 layers given as n pixels
+bool few_chosen(const sbn_packed* p, int n, int h, int w);
+bool few_takes(const sbn_packed* p, int n, int h, int w);
+int launch_few(const sbn_packed* p, const float* x, float* y, int n, int h, int w, int form, void* stream);
 int launch_conv3x3(const sbn_packed* p, const float* x, float* y, int n, int h, int w, void* stream);
 int launch_dw3x3(const float* x, float* y, const float* w_dev, const float* b_dev, int n, int h, int w,
                  int c, int stride, int act, void* stream);

@@ -115,6 +115,7 @@ void build_device_layout(sbn_packed* p)
     L.records.assign((size_t)L.n_bundles * L.n_chunks * kSlots, 0u);
     L.woff.assign((size_t)L.n_bundles * (L.n_chunks + 1), 0u);
     L.records32.assign((size_t)L.n_bundles * L.n_chunks32 * 8, 0u);
+    L.where.assign((size_t)L.n_bundles * L.n_chunks32 * 8, kNoEntry);
     L.woff32.assign((size_t)L.n_bundles * (L.n_chunks32 + 1), 0u);
     L.wts.clear();
     size_t n_entries = 0;
@@ -184,6 +185,10 @@ void build_device_layout(sbn_packed* p)
             wo32[c] = std::min(wo32[c], (uint32_t)entry[(size_t)kb4]);
         }
         for (int c = L.n_chunks32 - 1; c >= 0; --c) wo32[c] = std::min(wo32[c], wo32[c + 1]);
+        for (const int kb4 : kept) {
+            const size_t at = entry[(size_t)kb4] * wstride * sizeof(float);
+            L.where[(size_t)b * L.n_chunks32 * 8 + (size_t)kb4] = (uint32_t)std::min<size_t>(at, kNoEntry);
+        }
     }
     L.n_entries = n_entries;
     // every-piece tables for 1x1 layers of more than one chunk that keep most of their pieces
@@ -248,6 +253,9 @@ const char* check_device_layout(const sbn_packed* p)
     if (const char* e = check_tables(L.records, L.woff, L.n_bundles, L.n_chunks, kSlots, L.n_entries)) return e;
     if (const char* e = check_tables(L.records32, L.woff32, L.n_bundles, L.n_chunks32, 8, L.n_entries)) return e;
     if (L.wts.size() != L.n_entries * (size_t)p->kh * p->kw * kBundleGroups * 16) return "weight array size";
+    if (L.where.size() != (size_t)L.n_bundles * L.n_chunks32 * 8) return "entry offset table size";
+    for (const uint32_t at : L.where)
+        if (at != kNoEntry && (size_t)at + (size_t)p->kh * p->kw * 256 > L.wts.size() * sizeof(float)) return "entry offset out of range";
     if (L.bias_padded.size() != (size_t)L.n_bundles * kBundleChannels) return "bias array size";
     if (!L.desc_s.empty()) {
         const size_t per_bundle = (size_t)L.n_chunks * kSlots;
@@ -285,12 +293,13 @@ int upload_device_layout(sbn_packed* p)
     const size_t b_woff = align256(L.woff.size() * sizeof(uint32_t));
     const size_t b_rec32 = align256(L.records32.size() * sizeof(uint32_t));
     const size_t b_woff32 = align256(L.woff32.size() * sizeof(uint32_t));
+    const size_t b_where = align256(L.where.size() * sizeof(uint32_t));
     const size_t b_wts = align256((L.wts.size() + kSlots * wstride) * sizeof(float));
     const size_t b_bias = align256(L.bias_padded.size() * sizeof(float));
     const size_t b_desc_s = align256(L.desc_s.size() * sizeof(uint32_t));
     const size_t b_wts_s = align256(L.wts_s.size() * sizeof(float));
     const size_t b_wt = align256(L.wt.size() * sizeof(uint16_t));
-    const size_t total = b_rec + b_woff + b_rec32 + b_woff32 + b_wts + b_bias + b_desc_s + b_wts_s + b_wt;
+    const size_t total = b_rec + b_woff + b_rec32 + b_woff32 + b_where + b_wts + b_bias + b_desc_s + b_wts_s + b_wt;
     // (written once: not zeroed first, the gaps behind the arrays are; before the device is changed, as it may throw)
     std::unique_ptr<char[]> host(new char[total]);
     int prev = 0;
@@ -315,6 +324,7 @@ int upload_device_layout(sbn_packed* p)
     L.d_woff = (uint32_t*)put(L.woff.data(), L.woff.size() * sizeof(uint32_t), b_woff);
     L.d_records32 = (uint32_t*)put(L.records32.data(), L.records32.size() * sizeof(uint32_t), b_rec32);
     L.d_woff32 = (uint32_t*)put(L.woff32.data(), L.woff32.size() * sizeof(uint32_t), b_woff32);
+    L.d_where = (uint32_t*)put(L.where.data(), L.where.size() * sizeof(uint32_t), b_where);
     L.d_wts = (float*)put(L.wts.data(), L.wts.size() * sizeof(float), b_wts);
     L.d_bias = (float*)put(L.bias_padded.data(), L.bias_padded.size() * sizeof(float), b_bias);
     L.d_desc_s = (uint32_t*)put(L.desc_s.data(), L.desc_s.size() * sizeof(uint32_t), b_desc_s);       // NULL when there are none
