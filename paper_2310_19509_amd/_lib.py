@@ -12,6 +12,7 @@ import sys
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_PKG)
 LIB_PATH = os.path.join(_PKG, "libsbn.so")
+MARSHAL_PATH = os.path.join(_PKG, "_marshal.so")
 CSRC = os.path.join(_PKG, "csrc")
 
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -21,6 +22,25 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 
 def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".cpp")))
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """Compile _marshal.cpp (a CPython module on torch's headers, no device code) with g++."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + sysconfig.get_paths()["include"],
+           "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I" + os.path.join(rocm, "include"), os.path.join(_PKG, "_marshal.cpp"), "-L" + os.path.join(root, "lib"),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-o", MARSHAL_PATH]
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building _marshal.so failed:\n" + r.stdout)
+    return MARSHAL_PATH
 
 
 def build(verbose: bool = False) -> str:
@@ -98,6 +118,24 @@ SYMBOLS = {
 }
 
 _lib = None
+_marshal = None
+
+
+def marshal():
+    """The compiled marshalling module (_marshal.cpp), bound to the loaded library."""
+    global _marshal
+    if _marshal is None:
+        l = lib()
+        if not os.path.exists(MARSHAL_PATH):
+            build_marshal()
+        import importlib.util
+        spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        m.bind(*[C.cast(f, C.c_void_p).value for f in (l.sbn_conv1x1_sparse, l.sbn_conv3x3_sparse, l.sbn_chain_output_shape,
+                                                       l.sbn_pointwise_chain, l.sbn_pointwise_chain_static)])
+        _marshal = m
+    return _marshal
 
 
 def lib() -> C.CDLL:

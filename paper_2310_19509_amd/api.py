@@ -77,7 +77,7 @@ def _taps(kind: int) -> int:
 
 
 class Packed:
-    """Owner of an sbn_packed_t*; freed on garbage collection or by sbn_free."""
+    """Owner of an sbn_packed_t*; freed on garbage collection or by sbn_free.  _dims: (c_in, c_out, stride), for _marshal.cpp."""
 
     def __init__(self, handle: int):
         self.handle = handle
@@ -311,7 +311,9 @@ def sbn_pack(kind: int, w, go: int, gi: int, mask=None, bias=None, perm_out=None
     out = C.c_void_p()
     _check(_lib.lib().sbn_pack(C.byref(d), device, C.byref(out)))
     del keep
-    return Packed(out.value)
+    p = Packed(out.value)
+    p._dims = (d.c_in, d.c_out, max(1, d.stride))
+    return p
 
 
 def sbn_packed_info(p: Packed) -> dict:
@@ -381,7 +383,22 @@ def _check_extent(t, elements: int, what: str) -> None:
         raise ValueError(f"{what} holds {t.numel()} elements, the extents given need {elements}")
 
 
+# The two entry points of _marshal.cpp, which take the ordinary calls and answer None to the others: (layer, chain), once it is loaded.
+_native = None
+
+
+def _native_calls():
+    global _native
+    if _native is None:
+        m = _lib.marshal()
+        _native = (m.layer, m.chain)
+    return _native
+
+
 def sbn_conv1x1_sparse(p: Packed, x, y, n: int, h: int, w: int, stream=None) -> None:
+    rc = (_native or _native_calls())[0](0, p, x, y, n, h, w, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     if n > 0 and h > 0 and w > 0:
         info = _shape_of(p)
         _check_extent(x, n * h * w * info["c_in"], "x")
@@ -390,6 +407,9 @@ def sbn_conv1x1_sparse(p: Packed, x, y, n: int, h: int, w: int, stream=None) -> 
 
 
 def sbn_conv3x3_sparse(p: Packed, x, y, n: int, h: int, w: int, stream=None) -> None:
+    rc = (_native or _native_calls())[0](1, p, x, y, n, h, w, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     if n > 0 and h > 0 and w > 0:
         info = _shape_of(p)
         s = max(1, info["stride"])
@@ -475,6 +495,10 @@ def sbn_chain_set_fusion(c: Chain, enable: bool) -> None:
 
 
 def sbn_pointwise_chain(c: Chain, x, y, n: int, h: int, w: int, workspace, layer_outputs=None, stream=None) -> None:
+    if layer_outputs is None and workspace is not None:
+        rc = (_native or _native_calls())[1](c, x, y, n, h, w, workspace, stream)
+        if rc is not None:
+            return _check(rc) if rc else None
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     if n > 0 and h > 0 and w > 0:
         oh, ow, oc = sbn_chain_output_shape(c, n, h, w)
@@ -495,6 +519,10 @@ SBN_STATIC_WORKSPACE_BYTES = 32 << 20
 
 def sbn_pointwise_chain_static(c: Chain, x, y, n: int, h: int, w: int, layer_outputs=None, stream=None) -> None:
     """sbn_pointwise_chain with the library's built-in workspace: allocates nothing."""
+    if layer_outputs is None:
+        rc = (_native or _native_calls())[1](c, x, y, n, h, w, None, stream)
+        if rc is not None:
+            return _check(rc) if rc else None
     if n > 0 and h > 0 and w > 0:
         oh, ow, oc = sbn_chain_output_shape(c, n, h, w)
         _check_extent(x, n * h * w * c.c_in, "x")

@@ -1,0 +1,97 @@
+"""The compiled marshalling of the run calls: ordinary calls go through it, everything else keeps the behaviour of the Python
+code (checks, messages, streams)."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2310_19509_amd as S
+from paper_2310_19509_amd import _lib
+import workloads as W
+
+
+def layer(kind=S.SBN_CONV1X1, K=64, N=32, device=-1, **kw):
+    k = 3 if kind == S.SBN_CONV3X3 else 1
+    return S.sbn_pack(kind, W.he_weights(8100, N, k, k, K), 4, 4, device=device, **kw)
+
+
+def test_other_calls_are_answered_with_none_on_the_host():
+    m = _lib.marshal()
+    p = layer()
+    x, y = torch.zeros(1, 2, 2, 64), torch.zeros(1, 2, 2, 32)
+    for args in [(0, p, x, y, 1, 2, 2, None), (0, None, x, y, 1, 2, 2, None), (0, p, 16, 32, 1, 2, 2, None), (0, p, x, y, 1, 2, 2, 0),
+                 (0, p, x, y, 0, 2, 2, None), (0, p, x, y, np.int64(1), 2, 2, None), (0, p, x, y, 1 << 40, 2, 2, None), (2, p, x, y, 1, 2, 2, None)]:
+        assert m.layer(*args) is None
+    assert m.chain(None, x, y, 1, 2, 2, None, None) is None
+    with pytest.raises(AssertionError):                      # a host tensor: refused as before
+        S.sbn_conv1x1_sparse(p, x, y, 1, 2, 2)
+    with pytest.raises(ValueError):
+        S.sbn_conv1x1_sparse(p, x[:, :1], y, 1, 2, 2)
+    with pytest.raises(S.SbnError):                          # packed without a device copy
+        S.sbn_conv1x1_sparse(p, 256, 512, 1, 2, 2, 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,stride", [(S.SBN_CONV1X1, 1), (S.SBN_CONV3X3, 1), (S.SBN_CONV3X3, 2)])
+def test_layers(kind, stride):
+    m, fn = _lib.marshal(), S.sbn_conv1x1_sparse if kind == S.SBN_CONV1X1 else S.sbn_conv3x3_sparse
+    p = layer(kind, device=0, stride=stride)
+    x = torch.randn(2, 5, 7, 64, device="cuda")
+    o = (2, (5 - 1) // stride + 1, (7 - 1) // stride + 1, 32)
+    ref, y = torch.zeros(o, device="cuda"), torch.zeros(o, device="cuda")
+    fn(p, x, ref, 2, 5, 7, stream=torch.cuda.current_stream())          # the Python code's way
+    k = int(kind == S.SBN_CONV3X3)
+    assert m.layer(k, p, x, y, 2, 5, 7, None) == 0
+    assert torch.equal(ref, y)
+    # the current stream is the one the launch goes to: a fill before and a copy after it, on a stream of its own
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        big = torch.randn(4096, 4096, device="cuda")
+        for _ in range(8):
+            big = big @ big * 1e-4
+        y.fill_(7.0)
+        fn(p, x, y, 2, 5, 7)
+        got = y.clone()
+    side.synchronize()
+    assert torch.equal(ref, got)
+    # refused and accepted as by the Python code
+    class Sub(torch.Tensor):
+        pass
+    assert m.layer(k, p, x.as_subclass(Sub), y, 2, 5, 7, None) is None
+    assert m.layer(k, p, x.transpose(1, 2), y, 2, 5, 7, None) is None
+    assert m.layer(k, p, x.double(), y, 2, 5, 7, None) is None
+    with pytest.raises(ValueError):
+        fn(p, x[:1], y, 2, 5, 7)
+    with pytest.raises(ValueError):
+        fn(p, x, y[:1], 2, 5, 7)
+    with pytest.raises(AssertionError):
+        fn(p, x.transpose(1, 2), y, 2, 5, 7)
+    flat = torch.zeros(2 * 5 * 7 * 64 + 1, device="cuda")
+    with pytest.raises(S.SbnError):                          # not 16-byte aligned: the library's own check
+        fn(p, flat[1:], y, 2, 5, 7)
+    with pytest.raises(S.SbnError):
+        (S.sbn_conv3x3_sparse if k == 0 else S.sbn_conv1x1_sparse)(p, x, torch.zeros(2, 5, 7, 32, device="cuda"), 2, 5, 7)
+    S.sbn_free(p)
+    with pytest.raises(S.SbnError):
+        fn(p, x, y, 2, 5, 7)
+
+
+@pytest.mark.gpu
+def test_chains():
+    m = _lib.marshal()
+    items = [S.dw_item(W.he_weights(8101, 64, 3, 3, 1)[..., 0]), S.sparse_item(layer(device=0)), S.avgpool_item()]
+    c = S.sbn_chain_create(items)
+    x = torch.randn(2, 6, 6, 64, device="cuda")
+    ws = torch.empty(S.sbn_chain_workspace(c, 2, 6, 6) // 4, device="cuda")
+    ref, y = torch.zeros(2, 1, 1, 32, device="cuda"), torch.zeros(2, 1, 1, 32, device="cuda")
+    S.sbn_pointwise_chain(c, x, ref, 2, 6, 6, ws, stream=torch.cuda.current_stream())
+    assert m.chain(c, x, y, 2, 6, 6, ws, None) == 0 and torch.equal(ref, y)
+    y.zero_()
+    assert m.chain(c, x, y, 2, 6, 6, None, None) == 0 and torch.equal(ref, y)
+    with pytest.raises(ValueError):
+        S.sbn_pointwise_chain(c, x[:1], y, 2, 6, 6, ws)
+    with pytest.raises(ValueError):
+        S.sbn_pointwise_chain_static(c, x, y[:1], 2, 6, 6)
+    with pytest.raises(S.SbnError):
+        S.sbn_pointwise_chain(c, x, y, 2, 6, 6, ws[:8])
+    assert m.layer(0, c, x, y, 2, 6, 6, None) is None        # a chain is no layer
