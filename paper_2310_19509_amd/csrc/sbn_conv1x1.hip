@@ -123,8 +123,8 @@ struct Record {
 
 // P: pixel sets of 64 per wave.  NA: partial sums per (pixel set, group).
 // KC: channels staged per chunk, 64, or 32 for layers with c_in <= 32.
-// MULTI: c_in > KC, more than one chunk.  VEC: c_in % 4 == 0 (16-byte
-// activation loads); otherwise scalar loads with zero fill.
+// MULTI: c_in > KC, more than one chunk.  VEC: c_in % 4 == 0; otherwise the
+// last piece's channels past c_in are zeroed in LDS.
 //
 // Activations go global -> registers -> LDS.  (global_load_lds would save the
 // registers, but the compiler then drains the whole vector-memory counter
@@ -179,18 +179,18 @@ __device__ __forceinline__ void plain_tile(float* __restrict__ lds, float* __res
     // 32 register writes -- was measured 1.5 % slower over the 13-layer pass.)
 
     // ---- activation staging.  Thread t moves slots t, t+256, ... of the tile's
-    // T x (KC/4) 16-byte slots.  Rows past the last pixel repeat the last pixel
-    // (a lane only ever reads its own pixel's row); channels past c_in are never
-    // read by any entry (VEC) or are zero filled (!VEC).
+    // T x (KC/4) 16-byte slots (a lane only ever reads its own pixel's row).
     constexpr int C4 = KC / 4;
     constexpr int NL = T * C4 / 256;
     const float* xtile = x + pix0 * K;
     const int rows_valid = (int)(M - pix0 < T ? M - pix0 : T);
     v4f stage_reg[NL];
-    // VEC: the tile as a buffer of rows_valid rows; a slot's offset is row * K + column (bytes),
+    // The tile as a buffer of rows_valid rows; a slot's offset is row * K + column (bytes),
     // the chunk advances the scalar offset.  Rows past the last pixel and, in a ragged last chunk,
-    // channels past the end of the last row lie outside the buffer and read as zero; channels past
-    // c_in of other rows read the next row's first channels, which no entry ever uses.
+    // channels past the end of the last row lie outside the buffer and read as zero, word by word; channels past
+    // c_in of other rows read the next row's first channels, which no entry ever uses (VEC) or which are zeroed
+    // behind the stores to LDS (!VEC: where the piece that holds the last channel holds such ones too).  16-byte loads
+    // need an alignment of 4 bytes only: 3219 pixels, 90 x 200, 8.1 us with four 4-byte loads, now 6.3.
     const __amdgpu_buffer_rsrc_t xres = make_rsrc(xtile, (uint32_t)rows_valid * (uint32_t)K * 4u);
     uint32_t xoff[NL];
 #pragma unroll
@@ -200,29 +200,24 @@ __device__ __forceinline__ void plain_tile(float* __restrict__ lds, float* __res
     }
     auto issue_x = [&](int c) {
 #pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            if (VEC) {
-                stage_reg[i] = buf_load(xres, xoff[i], (uint32_t)c * (KC * 4));
-            } else {
-                const int slot = i * 256 + threadIdx.x;
-                const int row = slot / C4, col = (slot % C4) * 4;
-                const float* rp = xtile + (size_t)(row < rows_valid ? row : rows_valid - 1) * K;
-                v4f v;
-                for (int q = 0; q < 4; ++q) {
-                    const int ch = c * KC + col + q;
-                    const float t = rp[ch < K ? ch : 0];
-                    v[q] = ch < K ? t : 0.f;
-                }
-                stage_reg[i] = v;
-            }
-        }
+        for (int i = 0; i < NL; ++i) stage_reg[i] = buf_load(xres, xoff[i], (uint32_t)c * (KC * 4));
     };
-    auto write_x = [&](float* buf) {
+    auto write_x = [&](float* buf, int c) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
             const int slot = i * 256 + threadIdx.x;
             const int row = slot / C4, col = (slot % C4) * 4;
             *(v4f*)(buf + row * XS + col) = stage_reg[i];
+        }
+        if (!VEC && (c + 1) * KC > K) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                const int slot = i * 256 + threadIdx.x;
+                const int row = slot / C4, col = (slot % C4) * 4, left = K - c * KC - col;
+#pragma unroll
+                for (int q = 1; q < 4; ++q)
+                    if (left > 0 && left <= q) buf[row * XS + col + q] = 0.f;
+            }
         }
     };
 
@@ -252,7 +247,7 @@ __device__ __forceinline__ void plain_tile(float* __restrict__ lds, float* __res
             // This chunk's weights were fetched a chunk ago: everything but the loads just issued
             // has to be complete.  Saying so once here spares a wait in front of every group's
             // multiplies (the compiler cannot carry that knowledge across the group branches).
-            constexpr int NEW = (VEC ? NL : 4 * NL) + NW;
+            constexpr int NEW = NL + NW;
             static_assert(NEW < 64, "vmcnt is a 6-bit counter");
             __builtin_amdgcn_s_waitcnt((NEW & 15) | ((NEW >> 4) << 14) | (7 << 4) | (15 << 8));
         }
@@ -333,7 +328,7 @@ __device__ __forceinline__ void plain_tile(float* __restrict__ lds, float* __res
 #undef SBN_ENTRY
         chunk_done:;
         }
-        if (MULTI) write_x(xnext);
+        if (MULTI) write_x(xnext, c + 1);
         __syncthreads();                     // tile of the next chunk published / this one released
     };
 
@@ -342,7 +337,7 @@ __device__ __forceinline__ void plain_tile(float* __restrict__ lds, float* __res
     issue_x(0);
     load_weights(0, w_a);
     r_a = recs[0];
-    write_x(lds);
+    write_x(lds, 0);
     __syncthreads();
     if (MULTI) {
         for (int c = 0; c < n_chunks; c += 2) {
