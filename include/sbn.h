@@ -323,9 +323,10 @@ int sbn_conv3x3_sparse(const sbn_packed_t* p, const float* x, float* y,
  * 1112, 1121: forms 12, 21, 112, 121 on the every-piece tables of layers that
  * have them (sbn_packed_layout), the plain form otherwise -- forms below 1000
  * never use those tables, the automatic choice always does; 1: the automatic
- * choice among the forms so far, without those tables; 2064, 2256: 64 x 128 and 128 x 256 tiles on
+ * choice among the forms so far, without those tables; 2032, 2064, 2256: 32 x 32 tiles with the input
+ * channels split over four waves, 64 x 128 and 128 x 256 tiles on
  * triples of bfloat16, for layers of c_in > 64 and a multiple of 4 that keep enough for the automatic choice to
- * come to use them or that were packed while one of the two was forced, the automatic
+ * come to use them or that were packed while one of them was forced, the automatic
  * choice otherwise; 3004, 3008: the few-pixel kernel, 16 pixels x 16 channels
  * per workgroup of 4 or 8 waves that split the input channels) or SBN_CONV3X3 (1, 2, 3: one pixel per lane, two pixels per
  * lane, entry-ahead fetch; 32: entry-ahead with the input channels split over

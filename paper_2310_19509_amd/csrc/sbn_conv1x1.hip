@@ -826,6 +826,7 @@ int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long M, v
     // channels -> one bundle per workgroup, input channels split over its waves: as many waves as
     // keep the launch within about four waves per SIMD and leave every wave at least two
     // sub-chunks (timed on the deep MobileNet layers at batches 1..32)
+    if (!force && conv1x1_wide_few(p, M)) return launch_conv1x1_wide(p, x, y, M, 0, stream);
     const int n_sub = p->dev.n_chunks32;
     const long long wg_split = ((M + 63) / 64) * p->dev.n_bundles;
     if (!variant && n_sub >= 8 && wg_split <= 4ll * cus)

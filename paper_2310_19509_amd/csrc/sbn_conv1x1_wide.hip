@@ -319,6 +319,167 @@ __global__ __launch_bounds__(64 * NWV, PIPE ? 2 : 3) void conv1x1_wide_kernel(
     }
 }
 
+// For launches of a few 32 x 32 tiles per compute unit.  A workgroup owns one, and its four waves take the units of 32 input channels in
+// turn.  A wave shares nothing while it works: it stages its own activations through its own part of LDS (as they
+// are, in rows of 32 channels, the 16-byte slot s of pixel r at s ^ (r / 2 % 8), so that neither side meets a bank twice),
+// splits them in registers and multiplies; the loads of its next unit are in flight meanwhile, and there is no barrier
+// until the waves' results meet in LDS, where they are added in 64 bits.  Bound by the loads: 91 MB pass the L1 caches
+// for 1100 pixels, 512 x 512.  (Tiles of 32 x 64 and 64 x 32 halve that, but leave units idle: the same time there, up to a fifth more in
+// launches of fewer tiles; eight waves: a workgroup per unit instead of three, 11.9 us against 10.5.)
+constexpr int NS = 4;
+__global__ __launch_bounds__(64 * NS, 2) void conv1x1_wide_split_kernel(
+    const float* __restrict__ x, float* __restrict__ y, const uint16_t* __restrict__ wt, uint32_t wt_bytes,
+    const float* __restrict__ bias, const uint32_t* __restrict__ records, const uint32_t* __restrict__ woff,
+    const float* __restrict__ wts, long long M, int K, int N, int n_bundles, int n_chunks, int n_pairs, int n_pix_tiles,
+    int pix_fast, float tiny_sum, int act)
+{
+    __shared__ __attribute__((aligned(16))) char lds[NS][4096];          // 32 pixels x 32 channels, then 32 x 32 results
+    __shared__ uint8_t tiny_row[NS][32];           // 1: the wave met a non-zero activation below 2^-100 in the pixel
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int xcd = blockIdx.x & 7, jj = blockIdx.x >> 3;                // the tiles that share the larger operand on one XCD
+    const int n_fast = pix_fast ? n_pix_tiles : n_pairs;
+    const int slow = (jj / n_fast) * 8 + xcd, fast = jj % n_fast;
+    const int pix_tile = pix_fast ? fast : slow, pair = pix_fast ? slow : fast;      // 32 channels, two bundles
+    if (pix_tile >= n_pix_tiles || pair >= n_pairs) return;
+    const long long pix0 = (long long)pix_tile * 32;
+    const int rows = (int)(M - pix0 < 32 ? M - pix0 : 32);
+    const int n_units = (K + 31) / 32;
+
+    // ---- activations: slot i of a lane = row i * 8 + lane / 8, channels 4 * (lane % 8) of the unit.  Weights: three fragments (a, b, c)
+    // per step of 16 channels.  Past the last unit every lane's offset lies outside the buffers.
+    const __amdgpu_buffer_rsrc_t xres = make_rsrc(x + pix0 * K, (uint32_t)rows * (uint32_t)K * 4u);
+    const int slot = lane & 7;
+    const uint32_t xoff = ((uint32_t)(lane >> 3) * (uint32_t)K + (uint32_t)slot * 4u) * 4u;
+    const __amdgpu_buffer_rsrc_t wres = make_rsrc(wt, wt_bytes);
+    const uint32_t w0 = (uint32_t)pair * (uint32_t)(STEPS * n_chunks) * 3072u;
+    struct Set {
+        v4f x[4];
+        v8b w[2][3];
+    };
+    auto issue = [&](int u, Set& s) {
+        const bool real = u < n_units;
+        const int uu = real ? u : 0;
+        const uint32_t past = real && uu * 32 + slot * 4 < K ? 0u : 0x80000000u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s.x[i] = __builtin_bit_cast(v4f, buf_load(xres, (xoff + (uint32_t)i * (uint32_t)K * 32u) | past, (uint32_t)uu * 128u));
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                s.w[h][p] = __builtin_bit_cast(v8b, buf_load(wres, real ? (uint32_t)lane * 16u + p * 1024u : 0xFFFFFFF0u, real ? w0 + (uint32_t)(uu * 2 + h) * 3072u : 0u));
+    };
+
+    char* const wr = lds[wave] + (lane >> 3) * 128;
+    const char* const rd = lds[wave] + (lane & 31) * 128;
+    v16f main, cross;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) main[i] = cross[i] = 0.f;
+    uint32_t least = 0xFFFFFFFFu;
+    auto multiply = [&](const Set& s) {
+        wave_lds_order();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *(v4f*)(wr + i * 1024 + ((slot ^ (i * 4 + (lane >> 4))) & 7) * 16) = s.x[i];
+        wave_lds_order();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int at = h * 4 + (lane >> 5) * 2, f = (lane & 31) >> 1;
+            const v4f lo = *(const v4f*)(rd + ((at ^ f) & 7) * 16), hi = *(const v4f*)(rd + (((at + 1) ^ f) & 7) * 16);
+            least = least_magnitude(hi, least_magnitude(lo, least));
+            uint32_t p[3][4];
+            split2(lo.x, lo.y, p[0][0], p[1][0], p[2][0]);
+            split2(lo.z, lo.w, p[0][1], p[1][1], p[2][1]);
+            split2(hi.x, hi.y, p[0][2], p[1][2], p[2][2]);
+            split2(hi.z, hi.w, p[0][3], p[1][3], p[2][3]);
+            v8b q[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const v4u words = {p[k][0], p[k][1], p[k][2], p[k][3]};
+                q[k] = __builtin_bit_cast(v8b, words);
+            }
+            auto mul = [&](int wp, int xp, v16f& sum) { sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(s.w[h][wp], q[xp], sum, 0, 0, 0); };
+            mul(0, 2, cross);
+            mul(0, 0, main);
+            mul(2, 0, cross);
+            mul(1, 1, cross);
+            mul(1, 0, cross);
+            mul(0, 1, cross);
+        }
+    };
+
+    Set s0, s1;
+    issue(wave, s0);
+    for (int u = wave; u < n_units; u += 2 * NS) {
+        issue(u + NS, s1);
+        multiply(s0);
+        issue(u + 2 * NS, s0);
+        if (u + NS < n_units) multiply(s1);
+    }
+
+    // ---- the waves' results, [group of 4 + 4 channels][lane]; wave g then adds up group g
+    __syncthreads();
+    const unsigned long long met = __builtin_amdgcn_ballot_w64(least < kTiny);           // (two lanes per pixel)
+    if (lane < 32) tiny_row[wave][lane] = ((met | met >> 32) >> lane & 1u) != 0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        v4f o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = main[4 * g + i] + cross[4 * g + i];
+        *(v4f*)(lds[wave] + g * 1024 + lane * 16) = o;
+    }
+    __syncthreads();
+    const int ch = pair * 32 + wave * 8 + (lane >> 5) * 4, row = lane & 31;
+    double sum[4] = {0., 0., 0., 0.};
+    bool marked = false;
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+        const v4f v = *(const v4f*)(lds[n] + wave * 1024 + lane * 16);
+        marked |= tiny_row[n][row] != 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] += (double)v[i];
+    }
+    const v4f bv = *(const v4f*)(bias + (ch < n_bundles * 16 ? ch : 0));
+    v4f o;
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float s = (float)sum[i];
+        o[i] = (float)(sum[i] + (double)bv[i]);
+        bad |= o[i] - o[i] != 0.f || magnitude(s) < kTiny || (marked && __builtin_fabsf(s) < tiny_sum);
+    }
+    const uint32_t redo = bad && row < rows && ch < N ? 1u : 0u;
+    if (act == SBN_ACT_RELU) o = relu4(o);
+    const __amdgpu_buffer_rsrc_t yres = make_rsrc(y + pix0 * N, (uint32_t)rows * (uint32_t)N * 4u);
+    const uint32_t off = ch < N ? ((uint32_t)row * (uint32_t)N + (uint32_t)ch) * 4u : 0xFFFFFFF0u;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o), yres, (int)off, 0, 0);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(redo != 0) != 0, 0)) {
+        const Exact exact = {x, y, records, woff, wts, bias, K, N, n_chunks, act};
+        auto pixel = [&](int ln) { return pix0 + (ln & 31); };
+        auto channel = [&](int ln) { return pair * 32 + wave * 8 + (ln >> 5) * 4; };
+        do_again(redo, 1, [&](int, int ln) { exact.by_wave(pixel(ln), channel(ln), lane); }, [&](int) { exact.by_lane(pixel(lane), channel(lane)); });
+    }
+}
+
+// sums below this may have lost more than 2^-24 of themselves to activations below 2^-100 (c_in terms, each off by 2^-125 of a weight)
+float tiny_sum_of(const sbn_packed* p) { return std::max((float)p->c_in * p->dev.w_top * 0x1p-101f, 0x1p-100f); }
+
+int launch_split(const sbn_packed* p, const float* x, float* y, long long M, hipStream_t st)
+{
+    const sbn::DeviceLayout& L = p->dev;
+    const long long n_pix_tiles = (M + 31) / 32;
+    const int n_pairs = (L.n_bundles + 1) / 2, pix_fast = n_pairs >= 8 && n_pairs >= n_pix_tiles;      // (as in the few-pixel kernel)
+    const long long slow = pix_fast ? n_pairs : n_pix_tiles, fast = pix_fast ? n_pix_tiles : n_pairs;
+    const long long grid = (slow + 7) / 8 * 8 * fast;
+    if (grid > 0x7FFFFFFFll) return sbn::fail(SBN_EINVAL, "too many pixels for one launch (%lld)", M);
+    hipLaunchKernelGGL(conv1x1_wide_split_kernel, dim3((unsigned)grid), dim3(64 * NS), 0, st, x, y, L.d_wt,
+                       (uint32_t)(L.wt.size() * sizeof(uint16_t)), L.d_bias, L.d_records, L.d_woff, L.d_wts, M, p->c_in, p->c_out,
+                       L.n_bundles, L.n_chunks, n_pairs, (int)n_pix_tiles, pix_fast, tiny_sum_of(p), p->act);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return sbn::fail(SBN_EHIP, "conv1x1 launch: %s", hipGetErrorString(e));
+    return SBN_OK;
+}
+
 template <int PX, int NWV, bool PIPE>
 int launch(const sbn_packed* p, const float* x, float* y, long long M, hipStream_t st)
 {
@@ -333,11 +494,9 @@ int launch(const sbn_packed* p, const float* x, float* y, long long M, hipStream
     const long long grid = pix_slots * n_col_tiles;
     if (grid > 0x7FFFFFFFll || n_pix_tiles + pix_slots > 0x7FFFFFFFll)
         return sbn::fail(SBN_EINVAL, "too many pixels for one launch (%lld)", M);
-    // sums below this may have lost more than 2^-24 of themselves to activations below 2^-100 (c_in terms, each off by 2^-125 of a weight)
-    const float tiny_sum = std::max((float)p->c_in * L.w_top * 0x1p-101f, 0x1p-100f);
     hipLaunchKernelGGL((conv1x1_wide_kernel<PX, NWV, PIPE>), dim3((unsigned)grid), dim3(64 * NWV), 0, st, x, y, L.d_wt,
                        (uint32_t)(L.wt.size() * sizeof(uint16_t)), L.d_bias, L.d_records, L.d_woff, L.d_wts, M, p->c_in, p->c_out,
-                       L.n_bundles, L.n_chunks, n_col_tiles, (int)n_pix_tiles, (int)pix_slots, tiny_sum, p->act);
+                       L.n_bundles, L.n_chunks, n_col_tiles, (int)n_pix_tiles, (int)pix_slots, tiny_sum_of(p), p->act);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return sbn::fail(SBN_EHIP, "conv1x1 launch: %s", hipGetErrorString(e));
     return SBN_OK;
@@ -347,13 +506,20 @@ int launch(const sbn_packed* p, const float* x, float* y, long long M, hipStream
 
 namespace sbn {
 
+// Up to 3.5 tiles of 32 x 32 per compute unit the launch waits for its loads, which the kernel of such tiles has more of in
+// flight; no lower line: the few-pixel kernel is asked first.  Of 66 random layers of 200 to 9000 pixels and 96 to 1024 channels,
+// sparsity 0 to 40 %, every one gained, 1.29 times on average (30 %, us: 1100 pixels, 512 x 512 12.0 / 10.5; 784, 1024 x 1024 23.6 / 20.3;
+// 3136, 256 x 256 10.5 / 8.4; 275, 1024 x 1024 13.4 / 11.2).  In 1000 to 1500 tiles it loses as much.
+static bool split_pays(const sbn_packed* p, long long M) { return 2 * ((M + 31) / 32) * ((p->dev.n_bundles + 1) / 2) <= 7ll * p->dev.cus; }
+
 // Launches of a few more 64 x 128 tiles than compute units, where some units have two and most one, need more of a margin
 // (2254 pixels, 55 % kept: 512 x 1024 21.1 us against 19.5 of the 32-bit form, 1024 x 1024 35.5 against 34.3; 1 568 pixels 14 against 18).
 bool conv1x1_wide_chosen(const sbn_packed* p, long long M)
 {
     const long long tiles = (M + 63) / 64 * ((p->c_out + 127) / 128), cus = p->dev.cus;
-    return p->dev.d_wt && conv1x1_wide_margin(p) >= (tiles > cus && 3 * tiles < 4 * cus ? 1.45 : 1.0);
+    return p->dev.d_wt && conv1x1_wide_margin(p) >= (tiles > cus && 3 * tiles < 4 * cus && !split_pays(p, M) ? 1.45 : 1.0);
 }
+bool conv1x1_wide_few(const sbn_packed* p, long long M) { return conv1x1_wide_chosen(p, M) && split_pays(p, M); }
 
 // form 0: 128 x 256 tiles where they fill three quarters of the rounds that one tile per compute unit makes, else 64 x 128
 // tiles (512 x 512: 100352 pixels, 6.1 rounds, 261 us against 310; 50176 pixels, 3.06 of 4 rounds, 149 against 165; 9000 pixels,
@@ -363,6 +529,7 @@ int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long
 {
     hipStream_t st = (hipStream_t)stream;
     if (!p->dev.d_wt) return fail(SBN_EINVAL, "internal error: the layer has no bfloat16 triples");
+    if (!form && split_pays(p, M)) form = 2032;
     if (!form) {
         const long long col_tiles = (p->c_out + 255) / 256, tiles = (M + 127) / 128 * col_tiles, cus = p->dev.cus;
         const long long rounds = (tiles + cus - 1) / cus;
@@ -370,6 +537,7 @@ int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long
         const bool filled = 4 * tiles >= 3 * rounds * cus;
         form = fits && filled && p->c_in >= 384 ? 2256 : 2064;
     }
+    if (form == 2032) return launch_split(p, x, y, M, st);
     return form == 2256 ? launch<4, 8, true>(p, x, y, M, st) : launch<2, 4, false>(p, x, y, M, st);
 }
 

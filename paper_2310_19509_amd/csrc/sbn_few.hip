@@ -100,13 +100,6 @@ struct Exact {
     }
 };
 
-// As in sbn_conv1x1.hip: lanes of a wave exchange data through LDS without a barrier; no instruction.
-__device__ __forceinline__ void wave_lds_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 __device__ __forceinline__ float relu(float v)                           // (as relu4)
 {
     const int b = __builtin_bit_cast(int, v);

@@ -139,6 +139,7 @@ void release_device_layout(sbn_packed* p);
 // Kernel launchers (defined in the .hip files).
 int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long m, void* stream);
 bool conv1x1_wide_chosen(const sbn_packed* p, long long m);
+bool conv1x1_wide_few(const sbn_packed* p, long long m);                 // chosen, in its form for launches of few tiles
 int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long m, int form, void* stream);
 bool conv3x3_wide_takes(const sbn_packed* p, int n, int h, int w);       // whether the kernel takes these extents,
 bool conv3x3_wide_chosen(const sbn_packed* p, int n, int h, int w);      // and whether it is the faster one for them

@@ -57,6 +57,14 @@ __device__ __forceinline__ void split4_to(char* p, int part, const v4f& v)
     *(v2u*)(p + 2 * part) = (v2u){c0, c1};
 }
 
+// Lanes of one wave exchange data through LDS without a barrier (a wave's LDS instructions are executed in order): keeps the
+// compiler from moving LDS accesses across this point, no instruction.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ v4f relu4(v4f v)                              // as in the 32-bit form
 {
     typedef int v4i __attribute__((ext_vector_type(4)));

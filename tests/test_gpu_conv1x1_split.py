@@ -1,0 +1,53 @@
+"""The 32 x 32 form on triples of bfloat16 (gpu), by the checks and tolerances of the other forms on triples: edges, every bit of
+single products, values of very different size, data outside the triples' range."""
+import numpy as np
+import pytest
+
+import test_gpu_conv1x1_pairs as T
+
+pytestmark = pytest.mark.gpu
+FORM = 2032
+
+
+@pytest.mark.parametrize("args", [
+    (1, 128, 128, 0, 4, 4),            # one pixel, four units
+    (31, 68, 96, 0, 4, 4),             # three units, the last one of one piece, a wave without any
+    (32, 132, 4, 10, 4, 4),            # a pair of bundles with one group
+    (33, 192, 136, 10, 8, 4),          # one pixel in the second tile
+    (65, 256, 260, 30, 4, 1),          # a single bundle in the last pair
+    (97, 324, 48, 50, 4, 2),
+    (300, 1024, 256, 80, 8, 8),        # eight units per wave
+], ids=str)
+def test_tile_edges(args):
+    T.test_tile_edges(FORM, *args)
+
+
+@pytest.mark.parametrize("kind", ["tiny pixel", "huge value", "first chunks tiny", "later chunks tiny", "all tiny", "all huge", "zero pixels"])
+def test_unusual_magnitudes(kind):
+    T.test_unusual_magnitudes(FORM, kind)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3e38])
+def test_infinities_and_nan(value):
+    T.test_infinities_and_nan_reach_what_keeps_their_block_and_nothing_else(FORM, value)
+
+
+@pytest.mark.parametrize("args", [(128, 128, 0, 4, 4), (324, 260, 30, 4, 1), (1024, 96, 70, 4, 2)], ids=str)
+def test_single_products(args):
+    T.test_single_products_keep_every_bit(FORM, *args)
+
+
+@pytest.mark.parametrize("kind", [("large activations, small weights", 40), ("removed", 1e20), ("one piece", 1e20),
+                                  ("small beside one", 1e-40), ("all", 1e-36), ("all", 1e30)], ids=str)
+def test_large_and_small(kind):
+    T.test_large_values_cost_small_ones_nothing(FORM, kind)
+
+
+def test_outside_the_range_and_long_sums(monkeypatch):
+    monkeypatch.setattr(T, "FORMS", (FORM,))
+    T.test_activations_below_the_range_against_huge_weights()
+    for args in [(128, 128, 0), (512, 512, 30), (1024, 256, 70)]:
+        T.test_long_sums_are_no_further_off_than_32_bit_ones(*args)
+    T.test_marks_stay_with_their_tile(FORM)
+    for spoilt in (1, 13, 200):
+        T.test_outputs_done_again_one_by_one_and_side_by_side(FORM, spoilt)
