@@ -521,9 +521,11 @@ bool conv1x1_wide_chosen(const sbn_packed* p, long long M)
 }
 bool conv1x1_wide_few(const sbn_packed* p, long long M) { return conv1x1_wide_chosen(p, M) && split_pays(p, M); }
 
-// form 0: 128 x 256 tiles where they fill three quarters of the rounds that one tile per compute unit makes, else 64 x 128
-// tiles (512 x 512: 100352 pixels, 6.1 rounds, 261 us against 310; 50176 pixels, 3.06 of 4 rounds, 149 against 165; 9000 pixels,
-// 0.55 of a round, 40 against 34; 1024 x 1024, 6272 pixels, 0.77 of a round, 73 against 86).  Layers of few chunks
+// form 0: 128 x 256 tiles where they fill three quarters of one round of a tile per compute unit, or four fifths of several,
+// else 64 x 128 tiles (512 x 512: 62720 pixels, 3.8 rounds, 163 us against 186; 37632, 2.3 of 3, 116 against 105; 25088, 1.5 of 2, 80
+// against 74; 9000, 0.55 of one, 40 against 34; 1024 x 1024, 6272 pixels, 0.77 of one, 73 against 86).  A last round that would be
+// a third full or less, after three or more, leaves as a launch of its own, which takes the form that suits its pixels (100352 pixels,
+// 6.1 rounds, 270 -> 263 us; 50176, 3.06 rounds, 152 -> 138; 75264, 0.6 of the fifth, 200 -> 202: not taken).  Layers of few chunks
 // spend too much of a tile on its ends (128 x 128, 200704 pixels: 83 against 69; 256 x 256, 50176: 52 against 45).
 int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long M, int form, void* stream)
 {
@@ -534,7 +536,14 @@ int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long
         const long long col_tiles = (p->c_out + 255) / 256, tiles = (M + 127) / 128 * col_tiles, cus = p->dev.cus;
         const long long rounds = (tiles + cus - 1) / cus;
         const bool fits = col_tiles * 256 * 7 <= p->c_out * 8;                        // at most an eighth of the channels past c_out
-        const bool filled = 4 * tiles >= 3 * rounds * cus;
+        const bool filled = rounds == 1 ? 4 * tiles >= 3 * cus : 5 * tiles >= 4 * rounds * cus;
+        // whole rounds, and the pixels of a last round that would fill a third of the chip or less by themselves
+        const long long slots = 8 * std::max<long long>(1, cus / 8 / col_tiles);      // pixel tiles of a round (as in launch)
+        const long long whole = M / 128 / slots * slots * 128, rest = M - whole;
+        if (fits && p->c_in >= 384 && whole >= 3 * 128 * slots && rest > 0 && 3 * rest <= 128 * slots) {
+            if (int rc = launch<4, 8, true>(p, x, y, whole, st)) return rc;
+            return launch_conv1x1(p, x + whole * p->c_in, y + whole * p->c_out, rest, stream);
+        }
         form = fits && filled && p->c_in >= 384 ? 2256 : 2064;
     }
     if (form == 2032) return launch_split(p, x, y, M, st);

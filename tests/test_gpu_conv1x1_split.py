@@ -1,9 +1,12 @@
 """The 32 x 32 form on triples of bfloat16 (gpu), by the checks and tolerances of the other forms on triples: edges, every bit of
-single products, values of very different size, data outside the triples' range."""
+single products, values of very different size, data outside the triples' range; and launches in two parts."""
 import numpy as np
 import pytest
+import torch
 
+import paper_2310_19509_amd as S
 import test_gpu_conv1x1_pairs as T
+import workloads as W
 
 pytestmark = pytest.mark.gpu
 FORM = 2032
@@ -51,3 +54,22 @@ def test_outside_the_range_and_long_sums(monkeypatch):
     T.test_marks_stay_with_their_tile(FORM)
     for spoilt in (1, 13, 200):
         T.test_outputs_done_again_one_by_one_and_side_by_side(FORM, spoilt)
+
+
+@pytest.mark.parametrize("m,K,N", [(50176, 512, 512), (49152 + 1, 388, 512)])
+def test_whole_rounds_and_the_rest(m, K, N):
+    """A launch whose last round would be short leaves as two: every pixel as in one launch of the form of the whole rounds."""
+    p, w, mask, b = T.pack(K, N, 30)
+    x = torch.from_numpy(W.uniform_activation(9020, (1, 1, m, K))).cuda()
+    y, one = torch.full((1, 1, m, N), float("nan"), device="cuda"), torch.empty((1, 1, m, N), device="cuda")
+    S.sbn_conv1x1_sparse(p, x, y, 1, 1, m)
+    S.sbn_force_kernel_form(S.SBN_CONV1X1, 2256)
+    try:
+        S.sbn_conv1x1_sparse(p, x, one, 1, 1, m)
+        torch.cuda.synchronize()
+    finally:
+        S.sbn_force_kernel_form(S.SBN_CONV1X1, 0)
+    whole = m // 128 // 128 * 128 * 128            # (256 compute units, two column tiles)
+    assert torch.equal(y[0, 0, :whole], one[0, 0, :whole])
+    scale = x[0, 0].abs() @ torch.from_numpy(np.abs(T.kept_weights(w, mask, 4, 4))).float().cuda().T
+    assert ((y - one).abs()[0, 0] <= (K / 16 + 16) * 2.0 ** -23 * scale + 2.0 ** -22).all()
