@@ -321,7 +321,7 @@ bool few_takes(const sbn_packed* p, int n, int h, int w)
 //               49, 1024 x 1024       8.1 / 4.6    1, 1024 x 1000  8.0 / 4.3    1100, 512 x 512   12.2 / 12.2  (2208 tiles: not taken)
 //   3x3, 50 %   3 x 9 x 9, 256 x 200 23.5 / 9.0    1 x 28 x 28, 128 x 128  14.3 / 8.9   1 x 7 x 7, 512 x 512  41.5 / 13.7
 //               3 x 45 x 45, 64 x 128, stride 2  14.4 / 9.3                     8 x 14 x 14, 256 x 256  24.7 / 34.3 (1568 tiles: not taken)
-// (mean gain over the layers taken: 1.45 and 1.9 times; 3 of 800 lose more than 3 %, at most 10 %).  Both limits shrink with what the
+// (mean gain over the layers taken: 1x1 1.45, 3x3 1.8, 3x3 of stride 2, which the other kernel takes singly buffered, 2.5 times; 2 of 820 lose more than 3 %, at most 7 %).  Both limits shrink with what the
 // layer keeps, which the other forms' time follows and this one's does not.  As many waves as leave the chip about one round of
 // workgroups (tiles per compute unit up to 1: eight, up to 6: four).  Relative error (2-norm, units of 1e-8): 3 to 5.5, the forms replaced 4 to 22.
 static int few_waves(const sbn_packed* p, long long m)
@@ -330,7 +330,7 @@ static int few_waves(const sbn_packed* p, long long m)
     const long long tiles = (m + 15) / 16 * p->dev.n_bundles, units = (long long)taps * p->dev.n_chunks32;
     const double kept = 16.0 * (double)p->dev.n_present / ((double)p->c_in * p->c_out);
     const double left = taps == 1 ? 0.4 + 0.6 * kept : 0.2 + 0.8 * kept;
-    if ((double)tiles > (taps == 1 ? 6.0 : 4.7) * cus * left || (double)(tiles * units) > (taps == 1 ? 120.0 : 240.0) * cus * left) return 0;
+    if ((double)tiles > (taps == 1 ? 6.0 : p->stride == 1 ? 4.7 : 7.8) * cus * left || (double)(tiles * units) > (taps == 1 ? 120.0 : 470.0) * cus * left) return 0;
     if (taps == 9 && units >= 64 && 4 * tiles <= cus) return 16;
     return tiles <= cus ? 8 : 4;
 }
