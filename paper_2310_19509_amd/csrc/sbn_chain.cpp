@@ -69,6 +69,15 @@ Shape next_shape(const sbn_chain::Item& it, Shape s)
     return s;
 }
 
+// Few 8 x 8 tiles leave most of the chip idle for the length of a tile's phases; two launches then spread better.  (us, fused against two
+// launches, 128 x 128, stride 1: 25 tiles 11.5 / 7.3, 49 tiles 11.7 / 10.5, 98 tiles 11.8 / 11.3, 196 tiles 12.9 / 15.2; 64 x 128,
+// stride 2: 49 tiles 8.7 / 8.0, 98 tiles 9.1 / 9.1; 32 x 64: 196 tiles 6.4 / 8.1; 64 x 64: 49 tiles 7.5 / 6.8.)
+bool dwpw_pays(const sbn_packed* p, const Shape& out)
+{
+    const long long tiles = out.n * ((out.h + 7) / 8) * ((out.w + 7) / 8);
+    return tiles * 16 > (p->dev.n_bundles > 4 && p->c_in > 64 ? 6 : 4) * (long long)p->dev.cus;
+}
+
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 size_t max_intermediate(const sbn_chain* c, int n, int h, int w)
@@ -198,7 +207,7 @@ int run_chain(const sbn_chain* c, const float* x, float* y, int n, int h, int w,
         // output never exists in memory), unless the caller asked for a copy of it.
         if (c->fuse_dw && it.item == SBN_ITEM_DW3X3 && i + 1 < c->items.size() &&
             c->items[i + 1].item == SBN_ITEM_SPARSE && dwpw_fusable(c->items[i + 1].packed, it.channels, it.stride) &&
-            !(layer_outputs && layer_outputs[i])) {
+            !(layer_outputs && layer_outputs[i]) && dwpw_pays(c->items[i + 1].packed, next_shape(it, s))) {
             const sbn_chain::Item& pw = c->items[i + 1];
             const bool last2 = i + 2 == c->items.size();
             float* dst2 = last2 ? y : buf[which];
