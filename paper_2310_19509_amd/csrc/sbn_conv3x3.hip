@@ -485,19 +485,32 @@ int launch_conv3x3(const sbn_packed* p, const float* x, float* y, int n, int h, 
     if (forced >= 2000 && forced < 3000 && conv3x3_wide_takes(p, n, h, w)) return launch_conv3x3_wide(p, x, y, n, h, w, forced, stream);
     if (!forced && conv3x3_wide_chosen(p, n, h, w)) return launch_conv3x3_wide(p, x, y, n, h, w, 0, stream);
     if (p->stride == 2) return launch<2, 1, false>(p, x, y, n, h, w, st);
-    // Form, from timings of ResNet-50-shaped layers at batches 4..128 (thresholds in workgroups per
-    // compute unit of the device the layer lives on): up to one
-    // plain workgroup per CU the waves would sit alone on their SIMDs, so the input channels are
-    // split over two slices (entry-ahead fetch); up to two per CU the entry-ahead form; above that
-    // two pixels per lane when 16-wide tiles waste no more lanes than 8-wide ones (they need 7 %
-    // less time per pixel), else one pixel per lane, row-ahead (four workgroups per CU).
+    // Form, from 6247 random layers (stride 1, 32 to 512 channels in, 16 to 512 out, 7 to 112 wide, 50 to 95 %, three sets of buffers in turn,
+    // back to back; mean time over the best form's: 1.008, the rule before this one 1.072).  A compute unit holds four workgroups of the
+    // row-ahead form and three of the entry-ahead form, so that workgroups per compute unit (wg1 / cus) decide:
+    //   up to 1 the waves would sit alone on their SIMDs: the input channels are split over two slices (entry-ahead / split 1.1 at
+    //   0.8, 0.8 at 1.2); up to 3 entry-ahead, which has its round to itself (row-ahead / entry-ahead 1.08 to 1.18 up to 2, 1.05 to 1.13 up to 3);
+    //   up to 4 row-ahead (0.86 to 0.92: the fourth is a second round of the other); up to 6 entry-ahead (1.0 to 1.1), up to 8 row-ahead
+    //   (single layers 0.85, mean 0.94 to 1.03), above that by the channels (32: 0.95, 96: 1.0, 256: 1.03).
+    // Two pixels per lane, one sum for each: only where 16-wide tiles waste nothing, and there for a full round of three such workgroups (15 x 78 x 78,
+    // 192 x 20, 50 %: 54.8 us, entry-ahead 66.7) or layers of few channels (24 x 76 x 76, 32 x 332, 95 %: 78.6, row-ahead 89.2).  32 x 28 x 28,
+    // 128 x 128, 70 %: 41.9 us with two pixels, 37.4 row-ahead.
     int form = forced >= 2000 ? 0 : forced;             // testing / benchmarking override
     if (!form) {
         const long long col_tiles = (p->dev.n_bundles + 3) / 4;
         const long long tiles1 = (long long)((w + 7) / 8) * ((h + 7) / 8), tiles2 = (long long)((w + 15) / 16) * ((h + 7) / 8);
-        const long long wg1 = n * tiles1 * col_tiles;
-        const long long cus = p->dev.cus;
-        form = wg1 <= cus ? 32 : wg1 <= 2 * cus ? 3 : w > 8 && tiles2 * 2 * 93 < tiles1 * 100 ? 2 : 1;
+        const long long wg1 = n * tiles1 * col_tiles, cus = p->dev.cus;
+        if (wg1 <= cus)
+            form = 32;
+        else if (wg1 <= 3 * cus)
+            form = 3;
+        else if (2 * tiles2 == tiles1 &&
+                 ((wg1 > 5 * cus && wg1 <= 6 * cus) || (p->c_in <= 32 && wg1 > 4 * cus) || (p->c_in <= 64 && wg1 > 14 * cus)))
+            form = 2;
+        else if (wg1 <= 8 * cus)
+            form = wg1 > 4 * cus && wg1 <= 6 * cus ? 3 : 1;
+        else
+            form = p->c_in >= 192 ? 3 : 1;
     }
     switch (form) {
     case 2: return launch<1, 2, false>(p, x, y, n, h, w, st);

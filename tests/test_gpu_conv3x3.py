@@ -172,3 +172,29 @@ def test_activations_beyond_4_gib():
     ref, bound = R.sparse_conv_reference(xd[idx].cpu().numpy(), wt, mask, 4, 4, bias=b, stride=1, pad=1, act=R.ACT_RELU)
     assert_within_bound(yd[idx].cpu().numpy(), ref, bound, "images around 4 GiB")
     assert not torch.isnan(yd[::97, ::11, ::13]).any()
+
+
+@pytest.mark.parametrize("n,h,w,K,N,form", [
+    (32, 28, 28, 128, 128, 1),         # four workgroups per compute unit
+    (5, 30, 70, 128, 192, 3),          # a little over two
+    (11, 64, 64, 192, 132, 3),         # eight and a quarter
+    (24, 46, 46, 32, 64, 1),           # three and a third
+    (22, 64, 64, 192, 64, 2),          # five and a half, even columns of tiles
+])
+def test_the_automatic_choice_by_workgroups(n, h, w, K, N, form):
+    """The same bits as the form that the rule names on a device of 256 compute units (the two one-pixel forms add in the same order)."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are for 256 compute units")
+    wt = W.he_weights(8900, N, 3, 3, K)
+    p = S.sbn_pack(S.SBN_CONV3X3, wt, 4, 4, mask=S.sbn_prune_magnitude(wt, S.SBN_CONV3X3, 4, 4, 90), device=0)
+    x = torch.randn((n, h, w, K), device="cuda", generator=torch.Generator(device="cuda").manual_seed(8901))
+    ys = []
+    for f in (0, form):
+        ys.append(torch.full((n, h, w, N), float("nan"), device="cuda"))
+        S.sbn_force_kernel_form(S.SBN_CONV3X3, f)
+        try:
+            S.sbn_conv3x3_sparse(p, x, ys[-1], n, h, w)
+            torch.cuda.synchronize()
+        finally:
+            S.sbn_force_kernel_form(S.SBN_CONV3X3, 0)
+    assert torch.isfinite(ys[1]).all() and torch.equal(ys[0], ys[1])
