@@ -801,6 +801,7 @@ int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long M, v
         p->dev.wts_s.size() * sizeof(float) >= 0xFFFFFFFFull)
         return fail(SBN_EINVAL, "the layer's device weights exceed 4 GiB");
     int force = forced_kernel_form(SBN_CONV1X1);  // testing / benchmarking override
+    if (!force && conv1x1_split_chosen(p, M)) return launch_conv1x1_wide(p, x, y, M, 2032, stream);
     if (M <= 0x7FFFFFFFll) {
         if (force >= 3000 && few_takes(p, (int)M, 1, 1)) return launch_few(p, x, y, (int)M, 1, 1, force, stream);
         if (!force && few_chosen(p, (int)M, 1, 1)) return launch_few(p, x, y, (int)M, 1, 1, 0, stream);

@@ -506,11 +506,28 @@ int launch(const sbn_packed* p, const float* x, float* y, long long M, hipStream
 
 namespace sbn {
 
-// Up to 3.5 tiles of 32 x 32 per compute unit the launch waits for its loads, which the kernel of such tiles has more of in
+// Up to four tiles of 32 x 32 per compute unit the launch waits for its loads, which the kernel of such tiles has more of in
 // flight; no lower line: the few-pixel kernel is asked first.  Of 66 random layers of 200 to 9000 pixels and 96 to 1024 channels,
 // sparsity 0 to 40 %, every one gained, 1.29 times on average (30 %, us: 1100 pixels, 512 x 512 12.0 / 10.5; 784, 1024 x 1024 23.6 / 20.3;
-// 3136, 256 x 256 10.5 / 8.4; 275, 1024 x 1024 13.4 / 11.2).  In 1000 to 1500 tiles it loses as much.
-static bool split_pays(const sbn_packed* p, long long M) { return 2 * ((M + 31) / 32) * ((p->dev.n_bundles + 1) / 2) <= 7ll * p->dev.cus; }
+// 3136, 256 x 256 10.5 / 8.4; 275, 1024 x 1024 13.4 / 11.2).  In 1100 to 1500 tiles it loses as much.
+static long long split_tiles(const sbn_packed* p, long long M) { return (M + 31) / 32 * ((p->dev.n_bundles + 1) / 2); }
+static bool split_pays(const sbn_packed* p, long long M) { return split_tiles(p, M) <= 4ll * p->dev.cus; }
+
+// The same tiles for layers that keep too little for the other forms on triples, from 1.25 per compute unit on (below, the few-pixel kernel and the
+// 32-bit forms have their round to themselves).  With more than 64 output channels that keep less than 0.45, and with little kept at all, the 32-bit
+// forms gain on launches of few pixels.  7006 random layers, 400 to 300000 pixels, 16 to 1024 channels each way, 30 to 95 % (us, before / so):
+//   up to 64 output channels, 122 of them taken: 1.49 times faster on average, none slower by 3 %
+//     12544, 1024 x 64, 70 %  53.1 / 20.7    8200, 1024 x 56, 90 %  38.1 / 15.7    11720, 256 x 64, 30 %  11.8 / 7.3    15680, 528 x 64, 60 %  23.6 / 14.5
+//   more, 112 taken: 1.29 times, two slower, at most by 4 %
+//     7186, 1024 x 128, 50 %  36.4 / 20.8    7892, 928 x 128, 70 %  35.8 / 19.8    10192, 512 x 96, 60 %  21.1 / 13.1
+//   not taken: 743, 1024 x 1024, 80 %  15.5 / 17.4    528, 512 x 1024, 80 %  8.5 / 10.1    6272, 192 x 128, 70 %  6.8 / 7.9    784, 272 x 544, 95 %  5.4 / 7.4
+bool conv1x1_split_chosen(const sbn_packed* p, long long M)
+{
+    const long long tiles = split_tiles(p, M), cus = p->dev.cus;
+    if (!p->dev.d_wt || !conv1x1_split_pays(p) || 4 * tiles <= 5 * cus || tiles > 4 * cus) return false;
+    const double share = 16.0 * (double)p->dev.n_present / ((double)p->c_in * p->c_out);
+    return p->c_out <= 64 ? share >= 0.15 || tiles > 2 * cus : share >= 0.45 || M >= 4ll * p->c_out;
+}
 
 // Launches of a few more 64 x 128 tiles than compute units, where some units have two and most one, need more of a margin
 // (2254 pixels, 55 % kept: 512 x 1024 21.1 us against 19.5 of the 32-bit form, 1024 x 1024 35.5 against 34.3; 1 568 pixels 14 against 18).

@@ -85,7 +85,7 @@ struct DeviceLayout {
     // The weights as triples of bfloat16 for the wide matrix instructions (see sbn_conv1x1_wide.hip), w = a + b + c exactly, zeros for removed weights.  One FRAGMENT = the A operand of a 32 x 32 x 16
     // multiply, [lane 64][8]: lane l holds filter l % 32 of the 32 (two bundles), channels 8 * (l / 32) .. + 7 of the 16.
     // wt[pair of bundles][step][a, b, c][64][8]; 1x1: a step = 16 input channels, four per chunk; 3x3: 32 input channels
-    // are 18 steps, two per tap (past c_in and c_out: zeros).  Empty unless conv1x1_wide_pays or conv3x3_wide_pays (or a
+    // are 18 steps, two per tap (past c_in and c_out: zeros).  Empty unless conv1x1_wide_pays, conv1x1_split_pays or conv3x3_wide_pays (or a
     // wide form was forced while the layer was packed).
     std::vector<uint16_t> wt;
     float w_top = 0.0f;                   // largest magnitude of a weight
@@ -130,6 +130,7 @@ const char* check_device_layout(const sbn_packed* p);
 // builds the triples only where a launch can come to use them.
 double conv1x1_wide_margin(const sbn_packed* p);
 bool conv1x1_wide_pays(const sbn_packed* p);
+bool conv1x1_split_pays(const sbn_packed* p);
 bool conv3x3_wide_pays(const sbn_packed* p);
 double conv3x3_share_kept(const sbn_packed* p);
 // Uploads p->dev to p->device.  Returns SBN_OK or an error code.
@@ -140,6 +141,7 @@ void release_device_layout(sbn_packed* p);
 int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long m, void* stream);
 bool conv1x1_wide_chosen(const sbn_packed* p, long long m);
 bool conv1x1_wide_few(const sbn_packed* p, long long m);                 // chosen, in its form for launches of few tiles
+bool conv1x1_split_chosen(const sbn_packed* p, long long m);             // that form for layers that keep less
 int launch_conv1x1_wide(const sbn_packed* p, const float* x, float* y, long long m, int form, void* stream);
 bool conv3x3_wide_takes(const sbn_packed* p, int n, int h, int w);       // whether the kernel takes these extents,
 bool conv3x3_wide_chosen(const sbn_packed* p, int n, int h, int w);      // and whether it is the faster one for them

@@ -29,6 +29,17 @@ double conv1x1_wide_margin(const sbn_packed* p)
 }
 bool conv1x1_wide_pays(const sbn_packed* p) { return conv1x1_wide_margin(p) >= 1.0; }
 
+// Layers that gain from the 32 x 32 tiles alone, at the right number of pixels (conv1x1_split_chosen): those tiles read the activations
+// once per 32 output channels and split the input channels, where the 32-bit form that splits them reads them once per 16 and the others
+// do not split them.  Up to 64 output channels at almost any share kept, more from 0.3 on.
+bool conv1x1_split_pays(const sbn_packed* p)
+{
+    if ((p->c_out + 31) / 32 * 32 * 3 > p->c_out * 4) return false;     // (a quarter of the channels of the tiles idle)
+    const double share = 16.0 * (double)p->dev.n_present / ((double)p->c_in * p->c_out);
+    if (p->c_out <= 64) return p->c_in >= 192 && share >= (p->c_in >= 512 ? 0.05 : 0.15);
+    return p->c_out > 80 && p->c_in >= 256 && share >= 0.3;
+}
+
 // Kernels in 4 x 4 blocks that a layer keeps, over all that the wide multiplies go through (input channels in 32s,
 // output channels in 64s).  The multiplies' time does not depend on it, the 32-bit form's does; us, 32-bit form against this one (layers in
 // turn, so that weights are not in the L2):
@@ -63,20 +74,21 @@ static void build_triples(sbn_packed* p)
     L.wt.clear();
     L.w_top = 0.0f;
     const int taps = p->kh * p->kw;
-    const bool pays = taps == 1 ? conv1x1_wide_pays(p) : conv3x3_wide_pays(p);
+    const bool pays = taps == 1 ? conv1x1_wide_pays(p) || conv1x1_split_pays(p) : conv3x3_wide_pays(p);
     if (p->c_in % 4 || (taps == 1 && p->c_in <= kChunk) || p->stride != 1 || (!pays && forced_kernel_form(p->kind) < 2000)) return;
     const size_t n_pairs = ((size_t)L.n_bundles + 1) / 2, n_steps = taps == 1 ? (size_t)L.n_chunks * 4 : (size_t)L.n_chunks32 * 18;
     if (n_pairs * n_steps * 3072 >= 0xFFFFFFFFull) return;               // 32-bit byte offsets on the device
     // Infinite, NaN and nearly infinite weights (the first bfloat16 would overflow), and weights whose last bits
     // lie below the smallest normal bfloat16, stay with the 32-bit kernels.
-    uint32_t top = 0;
-    for (const float v : L.wts) {
+    uint32_t top = 0, outside = 0;
+    for (const float v : L.wts) {                                        // (no branch: a vector loop)
         uint32_t u;
         std::memcpy(&u, &v, 4);
         u &= 0x7FFFFFFFu;
-        if (u >= 0x7F7F8000u || (u != 0 && u < 0x0D800000u)) return;     // (2^-100)
+        outside |= (uint32_t)(u - 1u < 0x0D800000u - 1u);                // (2^-100)
         top = std::max(top, u);
     }
+    if (outside || top >= 0x7F7F8000u) return;
     std::memcpy(&L.w_top, &top, 4);
     L.wt.assign(n_pairs * n_steps * 1536, 0);
     const size_t wstride = (size_t)taps * 64;
@@ -89,7 +101,8 @@ static void build_triples(sbn_packed* p)
                 uint16_t* frag = &L.wt[((size_t)(b / 2) * n_steps + (size_t)c * 2 * taps + piece / 4) * 1536 +
                                        (size_t)(piece % 4 / 2 * 32 + b % 2 * kBundleChannels) * 8 + piece % 2 * 4];
                 for (int t = 0; t < taps; ++t, frag += 2 * 1536)
-                    for (int f = 0; f < kBundleChannels; ++f)            // (removed groups' weights are zeros)
+                    for (int f = 0; f < kBundleChannels; ++f) {
+                        if (!(r[q] >> (f / 4) & 1u)) continue;           // (a removed group's weights are zeros)
                         for (int ci = 0; ci < 4; ++ci) {
                             const float v = w[t * 64 + f * 4 + ci];
                             float hi, mid, lo;
@@ -97,6 +110,7 @@ static void build_triples(sbn_packed* p)
                             frag[f * 8 + ci + 512] = to_bf16(v - hi, &mid);
                             frag[f * 8 + ci + 1024] = to_bf16(v - hi - mid, &lo);
                         }
+                    }
             }
         }
 }

@@ -73,3 +73,28 @@ def test_whole_rounds_and_the_rest(m, K, N):
     assert torch.equal(y[0, 0, :whole], one[0, 0, :whole])
     scale = x[0, 0].abs() @ torch.from_numpy(np.abs(T.kept_weights(w, mask, 4, 4))).float().cuda().T
     assert ((y - one).abs()[0, 0] <= (K / 16 + 16) * 2.0 ** -23 * scale + 2.0 ** -22).all()
+
+
+@pytest.mark.parametrize("m,K,N,pct,taken", [
+    (12544, 1024, 64, 70, True),       # up to 64 output channels
+    (5121, 512, 64, 90, False),        # 1.26 tiles per compute unit, little kept
+    (8225, 512, 64, 95, True),         # a little over two
+    (5121, 192, 64, 80, True),         # the fewest input channels, a tile more than 1.25
+    (16385, 192, 64, 80, False),       # a tile more than four
+    (7186, 1024, 96, 70, True),        # more output channels, three tenths kept
+    (7186, 1024, 96, 75, False),
+    (3000, 260, 256, 60, True),
+    (750, 512, 512, 60, False),        # few pixels for the channels
+])
+def test_layers_that_keep_less(m, K, N, pct, taken):
+    """The automatic choice and the forced form agree bit for bit where the rule takes the form, for 256 compute units; and are close elsewhere."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are for 256 compute units")
+    w = W.he_weights(9030, N, 1, 1, K)
+    mask = S.sbn_prune_magnitude(w, S.SBN_CONV1X1, 4, 4, pct)
+    auto, forced = S.sbn_pack(S.SBN_CONV1X1, w, 4, 4, mask=mask), T.pack_wide(w, 4, 4, mask=mask)
+    x = W.uniform_activation(9031, (1, 1, m, K))
+    y, one = T.run(auto, x, N, 0), T.run(forced, x, N, FORM)
+    assert np.array_equal(y, one) == taken
+    scale = np.abs(x[0, 0]) @ np.abs(T.kept_weights(w, mask, 4, 4)).astype(np.float32).T
+    assert (np.abs(y - one)[0, 0] <= K * 2.0 ** -23 * scale).all()
