@@ -515,7 +515,8 @@ static bool split_pays(const sbn_packed* p, long long M) { return split_tiles(p,
 
 // The same tiles for layers that keep too little for the other forms on triples, from 1.25 per compute unit on (below, the few-pixel kernel and the
 // 32-bit forms have their round to themselves).  With more than 64 output channels that keep less than 0.45, and with little kept at all, the 32-bit
-// forms gain on launches of few pixels.  7006 random layers, 400 to 300000 pixels, 16 to 1024 channels each way, 30 to 95 % (us, before / so):
+// forms gain on launches of few pixels; up to 64 output channels of at least 768 gain from 0.6 tiles on (18 layers, 1.46 times, none slower:
+// 4735 pixels, 1024 x 64, 60 % 23.1 / 12.0; from 512 channels on 11 of 48 lose).  7006 random layers, 400 to 300000 pixels, 16 to 1024 channels each way, 30 to 95 % (us, before / so):
 //   up to 64 output channels, 122 of them taken: 1.49 times faster on average, none slower by 3 %
 //     12544, 1024 x 64, 70 %  53.1 / 20.7    8200, 1024 x 56, 90 %  38.1 / 15.7    11720, 256 x 64, 30 %  11.8 / 7.3    15680, 528 x 64, 60 %  23.6 / 14.5
 //   more, 112 taken: 1.29 times, two slower, at most by 4 %
@@ -524,7 +525,9 @@ static bool split_pays(const sbn_packed* p, long long M) { return split_tiles(p,
 bool conv1x1_split_chosen(const sbn_packed* p, long long M)
 {
     const long long tiles = split_tiles(p, M), cus = p->dev.cus;
-    if (!p->dev.d_wt || !conv1x1_split_pays(p) || 4 * tiles <= 5 * cus || tiles > 4 * cus) return false;
+    if (!p->dev.d_wt || !conv1x1_split_pays(p) || tiles > 4 * cus) return false;
+    if (p->c_out <= 64 && p->c_in >= 768 && 5 * tiles > 3 * cus) return true;
+    if (4 * tiles <= 5 * cus) return false;
     const double share = 16.0 * (double)p->dev.n_present / ((double)p->c_in * p->c_out);
     return p->c_out <= 64 ? share >= 0.15 || tiles > 2 * cus : share >= 0.45 || M >= 4ll * p->c_out;
 }

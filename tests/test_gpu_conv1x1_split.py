@@ -81,6 +81,9 @@ def test_whole_rounds_and_the_rest(m, K, N):
     (8225, 512, 64, 95, True),         # a little over two
     (5121, 192, 64, 80, True),         # the fewest input channels, a tile more than 1.25
     (16385, 192, 64, 80, False),       # a tile more than four
+    (2500, 768, 64, 60, True),         # many input channels: from 0.6 tiles on
+    (2400, 768, 64, 60, False),
+    (2500, 764, 64, 60, False),
     (7186, 1024, 96, 70, True),        # more output channels, three tenths kept
     (7186, 1024, 96, 75, False),
     (3000, 260, 256, 60, True),
