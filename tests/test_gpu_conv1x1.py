@@ -289,3 +289,31 @@ def test_activations_beyond_4_gib():
     ref, bound = R.sparse_conv_reference(xs, wt, mask, 4, 4, bias=b, act=R.ACT_RELU)
     assert_within_bound(yd[idx].cpu().numpy().reshape(ref.shape), ref, bound, "rows around 4 GiB")
     assert not torch.isnan(yd[::100003]).any()
+
+
+@pytest.mark.parametrize("m,K,N,pct,taken", [
+    (1318, 128, 256, 70, True),        # 1.3 workgroups of 64 pixels and 16 output channels per compute unit
+    (2048, 68, 256, 60, True),         # exactly two, the fewest input channels
+    (2049, 128, 256, 70, False),       # a pixel more
+    (1318, 224, 256, 90, False),       # too little kept, the most input channels (seven times 32)
+])
+def test_few_input_channels_are_split_between_one_and_two_workgroups(m, K, N, pct, taken):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are for 256 compute units")
+    w = W.he_weights(9040, N, 1, 1, K)
+    mask = S.sbn_prune_magnitude(w, S.SBN_CONV1X1, 4, 4, pct)
+    p = S.sbn_pack(S.SBN_CONV1X1, w, 4, 4, mask=mask, device=0)
+    x = W.uniform_activation(9041, (1, 1, m, K))
+    xd, ys = torch.from_numpy(x).cuda(), []
+    for form in (0, 504):
+        ys.append(torch.full((1, 1, m, N), float("nan"), device="cuda"))
+        S.sbn_force_kernel_form(S.SBN_CONV1X1, form)
+        try:
+            S.sbn_conv1x1_sparse(p, xd, ys[-1], 1, 1, m)
+            torch.cuda.synchronize()
+        finally:
+            S.sbn_force_kernel_form(S.SBN_CONV1X1, 0)
+    assert torch.equal(*ys) == taken
+    ref, bound = R.sparse_conv_reference(x, w, mask, 4, 4)
+    # (32-bit sums of at most K products)
+    assert (np.abs(ys[0].cpu().numpy().astype(np.float64) - ref) <= K * 2.0 ** -23 * bound + np.abs(ref) * 2.0 ** -23).all()
