@@ -514,8 +514,8 @@ static long long split_tiles(const sbn_packed* p, long long M) { return (M + 31)
 static bool split_pays(const sbn_packed* p, long long M) { return split_tiles(p, M) <= 4ll * p->dev.cus; }
 
 // The same tiles for layers that keep too little for the other forms on triples, from 1.25 per compute unit on (below, the few-pixel kernel and the
-// 32-bit forms have their round to themselves).  With more than 64 output channels that keep less than 0.45, and with little kept at all, the 32-bit
-// forms gain on launches of few pixels; up to 64 output channels of at least 768 gain from 0.6 tiles on (18 layers, 1.46 times, none slower:
+// 32-bit forms have their round to themselves).  With more than 64 output channels, and with little kept at all, the 32-bit
+// forms gain on launches of few pixels, whose time is that of the weights; up to 64 output channels of at least 768 gain from 0.6 tiles on (18 layers, 1.46 times, none slower:
 // 4735 pixels, 1024 x 64, 60 % 23.1 / 12.0; from 512 channels on 11 of 48 lose).  7006 random layers, 400 to 300000 pixels, 16 to 1024 channels each way, 30 to 95 % (us, before / so):
 //   up to 64 output channels, 122 of them taken: 1.49 times faster on average, none slower by 3 %
 //     12544, 1024 x 64, 70 %  53.1 / 20.7    8200, 1024 x 56, 90 %  38.1 / 15.7    11720, 256 x 64, 30 %  11.8 / 7.3    15680, 528 x 64, 60 %  23.6 / 14.5
@@ -529,7 +529,7 @@ bool conv1x1_split_chosen(const sbn_packed* p, long long M)
     if (p->c_out <= 64 && p->c_in >= 768 && 5 * tiles > 3 * cus) return true;
     if (4 * tiles <= 5 * cus) return false;
     const double share = 16.0 * (double)p->dev.n_present / ((double)p->c_in * p->c_out);
-    return p->c_out <= 64 ? share >= 0.15 || tiles > 2 * cus : share >= 0.45 || M >= 4ll * p->c_out;
+    return p->c_out <= 64 ? share >= 0.15 || tiles > 2 * cus : M >= 4ll * p->c_out;
 }
 
 // Launches of a few more 64 x 128 tiles than compute units, where some units have two and most one, need more of a margin
@@ -539,7 +539,12 @@ bool conv1x1_wide_chosen(const sbn_packed* p, long long M)
     const long long tiles = (M + 63) / 64 * ((p->c_out + 127) / 128), cus = p->dev.cus;
     return p->dev.d_wt && conv1x1_wide_margin(p) >= (tiles > cus && 3 * tiles < 4 * cus && !split_pays(p, M) ? 1.45 : 1.0);
 }
-bool conv1x1_wide_few(const sbn_packed* p, long long M) { return conv1x1_wide_chosen(p, M) && split_pays(p, M); }
+// Fewer pixels than four times the output channels read mostly weights, 6 bytes for each of the layer's against 4 for each kept: a tie at a margin near 1
+// when they lie in the L2 (1372 pixels, 512 x 512, 50 %, 11.3 against 11.5 us), a loss when they do not (13 layers in turn on seven images 129 against 125).
+bool conv1x1_wide_few(const sbn_packed* p, long long M)
+{
+    return conv1x1_wide_chosen(p, M) && split_pays(p, M) && (M >= 4ll * p->c_out || conv1x1_wide_margin(p) >= 1.25);
+}
 
 // form 0: 128 x 256 tiles where they fill three quarters of one round of a tile per compute unit, or four fifths of several,
 // else 64 x 128 tiles (512 x 512: 62720 pixels, 3.8 rounds, 163 us against 186; 37632, 2.3 of 3, 116 against 105; 25088, 1.5 of 2, 80

@@ -88,6 +88,8 @@ def test_whole_rounds_and_the_rest(m, K, N):
     (7186, 1024, 96, 75, False),
     (3000, 260, 256, 60, True),
     (750, 512, 512, 60, False),        # few pixels for the channels
+    (1372, 512, 512, 50, False),       # (a margin of 1.07)
+    (1372, 512, 512, 40, True),        # (1.28)
 ])
 def test_layers_that_keep_less(m, K, N, pct, taken):
     """The automatic choice and the forced form agree bit for bit where the rule takes the form, for 256 compute units; and are close elsewhere."""
