@@ -75,7 +75,9 @@ static void build_triples(sbn_packed* p)
     L.w_top = 0.0f;
     const int taps = p->kh * p->kw;
     const bool pays = taps == 1 ? conv1x1_wide_pays(p) || conv1x1_split_pays(p) : conv3x3_wide_pays(p);
-    if (p->c_in % 4 || (taps == 1 && p->c_in <= kChunk) || p->stride != 1 || (!pays && forced_kernel_form(p->kind) < 2000)) return;
+    const int forced = forced_kernel_form(p->kind);
+    const bool wanted = forced >= 2000 && forced < 3000;                 // (the few-pixel forms, from 3000 on, do not read them)
+    if (p->c_in % 4 || (taps == 1 && p->c_in <= kChunk) || p->stride != 1 || (!pays && !wanted)) return;
     const size_t n_pairs = ((size_t)L.n_bundles + 1) / 2, n_steps = taps == 1 ? (size_t)L.n_chunks * 4 : (size_t)L.n_chunks32 * 18;
     if (n_pairs * n_steps * 3072 >= 0xFFFFFFFFull) return;               // 32-bit byte offsets on the device
     // Infinite, NaN and nearly infinite weights (the first bfloat16 would overflow), and weights whose last bits

@@ -178,6 +178,23 @@ def test_dense_tables_are_built_only_where_a_launch_can_use_them(kind, K, N, pct
     assert not wide or lay["table_bytes"] > 6 * k * k * K * N
 
 
+@pytest.mark.parametrize("kind,form,wide", [(S.SBN_CONV1X1, 2032, True), (S.SBN_CONV1X1, 2064, True), (S.SBN_CONV1X1, 3004, False),
+                                            (S.SBN_CONV1X1, 3008, False), (S.SBN_CONV3X3, 2128, True), (S.SBN_CONV3X3, 3004, False),
+                                            (S.SBN_CONV3X3, 3016, False), (S.SBN_CONV1X1, 1012, False), (S.SBN_CONV3X3, 32, False)])
+def test_dense_tables_come_with_the_forms_that_read_them(kind, form, wide):
+    """A layer too sparse for them gets them when it is packed while a form that reads them is forced, and with no other form."""
+    k = 3 if kind == S.SBN_CONV3X3 else 1
+    w = W.he_weights(335, 64, k, k, 128)
+    mask = S.sbn_prune_magnitude(w, kind, 4, 4, 90)
+    plain = S.sbn_packed_layout(S.sbn_pack(kind, w, 4, 4, mask=mask, device=-1))["table_bytes"]
+    S.sbn_force_kernel_form(kind, form)
+    try:
+        forced = S.sbn_packed_layout(S.sbn_pack(kind, w, 4, 4, mask=mask, device=-1))["table_bytes"]
+    finally:
+        S.sbn_force_kernel_form(kind, 0)
+    assert forced == plain + wide * 6 * k * k * 128 * 64
+
+
 # ---------------------------------------------------------------- rearrangement
 
 def _layers(seed, chans, go=4, gi=4):
