@@ -12,7 +12,7 @@ import sys
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_PKG)
 LIB_PATH = os.path.join(_PKG, "libsbn.so")
-MARSHAL_PATH = os.path.join(_PKG, "_marshal.so")
+MARSHAL_SOURCE = os.path.join(_PKG, "_marshal.cpp")
 CSRC = os.path.join(_PKG, "csrc")
 
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -24,23 +24,43 @@ def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".cpp")))
 
 
-def build_marshal(verbose: bool = False) -> str:
-    """Compile _marshal.cpp (a CPython module on torch's headers, no device code) with g++."""
-    import sysconfig
+def marshal_path() -> str:
+    """Where the compiled _marshal.cpp lies: it is bound to the layout of torch's and Python's objects, so
+    the name carries a hash of their versions and of the source, and a file built for others is not loaded."""
+    import hashlib
     import torch
+    key = hashlib.sha256(f"{torch.__version__} {sys.version} ".encode() + open(MARSHAL_SOURCE, "rb").read()).hexdigest()[:12]
+    return os.path.join(_PKG, f"_marshal_{key}.so")
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """Compile _marshal.cpp (a CPython module on torch's headers, no device code) with g++.  The file appears
+    under its name when it is complete: two processes may build at the same time."""
+    import sysconfig
+    import tempfile
+    import torch
+    path = marshal_path()
+    fd, part = tempfile.mkstemp(prefix="_marshal_", suffix=".part.so", dir=_PKG)
+    os.close(fd)
     root = os.path.dirname(torch.__file__)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + sysconfig.get_paths()["include"],
            "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
-           "-I" + os.path.join(rocm, "include"), os.path.join(_PKG, "_marshal.cpp"), "-L" + os.path.join(root, "lib"),
-           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-o", MARSHAL_PATH]
+           "-I" + os.path.join(rocm, "include"), MARSHAL_SOURCE, "-L" + os.path.join(root, "lib"),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-o", part]
     if verbose:
         print(" ".join(cmd), file=sys.stderr)
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("building _marshal.so failed:\n" + r.stdout)
-    return MARSHAL_PATH
+    try:
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if r.returncode != 0:
+            raise RuntimeError("building _marshal.cpp failed:\n" + r.stdout)
+        os.chmod(part, 0o755)
+        os.replace(part, path)
+    finally:
+        if os.path.exists(part):
+            os.remove(part)
+    return path
 
 
 def build(verbose: bool = False) -> str:
@@ -126,10 +146,11 @@ def marshal():
     global _marshal
     if _marshal is None:
         l = lib()
-        if not os.path.exists(MARSHAL_PATH):
+        path = marshal_path()
+        if not os.path.exists(path):
             build_marshal()
         import importlib.util
-        spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
+        spec = importlib.util.spec_from_file_location("_marshal", path)
         m = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(m)
         m.bind(*[C.cast(f, C.c_void_p).value for f in (l.sbn_conv1x1_sparse, l.sbn_conv3x3_sparse, l.sbn_chain_output_shape,

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import paper_2310_19509_amd as S
-from paper_2310_19509_amd import _lib
+from paper_2310_19509_amd import _lib, api
 import workloads as W
 
 
@@ -29,6 +29,36 @@ def test_other_calls_are_answered_with_none_on_the_host():
         S.sbn_conv1x1_sparse(p, x[:, :1], y, 1, 2, 2)
     with pytest.raises(S.SbnError):                          # packed without a device copy
         S.sbn_conv1x1_sparse(p, 256, 512, 1, 2, 2, 0)
+
+
+@pytest.fixture
+def elsewhere(tmp_path, monkeypatch):
+    """The module not loaded yet, its folder an empty one."""
+    _lib.lib()
+    monkeypatch.setattr(_lib, "_PKG", str(tmp_path))
+    monkeypatch.setattr(_lib, "_marshal", None)
+    monkeypatch.setattr(api, "_native", None)
+    return tmp_path
+
+
+def compiler(path, body):
+    path.write_text("#!/bin/sh\n" + body)
+    path.chmod(0o755)
+    return str(path)
+
+
+def test_another_torch_has_a_file_of_its_own(elsewhere, monkeypatch):
+    path = _lib.marshal_path()
+    monkeypatch.setattr(torch, "__version__", "0.0")
+    assert _lib.marshal_path() != path
+
+
+def test_the_file_appears_when_it_is_complete(elsewhere, monkeypatch):
+    """While the compiler still writes, nothing lies under the name that a second process would load."""
+    path = _lib.marshal_path()
+    monkeypatch.setenv("CXX", compiler(elsewhere / "cxx", f'for out; do :; done; printf half > "$out"; [ -e "{path}" ] && exit 1; printf whole > "$out"'))
+    assert _lib.build_marshal() == path
+    assert open(path).read() == "whole"
 
 
 @pytest.mark.gpu
