@@ -390,8 +390,14 @@ _native = None
 def _native_calls():
     global _native
     if _native is None:
-        m = _lib.marshal()
-        _native = (m.layer, m.chain)
+        _lib.lib()                                # (without the library itself no call can be served: its error is the caller's)
+        try:
+            m = _lib.marshal()
+            _native = (m.layer, m.chain)
+        except Exception as e:                    # no compiler, no headers, a file that does not load
+            import warnings
+            warnings.warn(f"_marshal.cpp is not usable, run calls are marshalled in Python (slower by some microseconds): {e}")
+            _native = ((lambda *args: None),) * 2
     return _native
 
 

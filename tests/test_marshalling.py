@@ -1,6 +1,8 @@
 """The compiled marshalling of the run calls: ordinary calls go through it, everything else keeps the behaviour of the Python
 code (checks, messages, streams)."""
 
+import warnings
+
 import numpy as np
 import pytest
 import torch
@@ -47,6 +49,29 @@ def compiler(path, body):
     return str(path)
 
 
+def test_calls_without_the_module(elsewhere, monkeypatch):
+    """No compiler: one warning, and the Python code answers every call; no half-written file is left to be loaded."""
+    monkeypatch.setenv("CXX", compiler(elsewhere / "cxx", 'for out; do :; done; printf half > "$out"; exit 1'))
+    p = layer()
+    with pytest.warns(UserWarning, match="marshalled in Python"):
+        with pytest.raises(S.SbnError):                      # packed without a device copy: the library's own answer
+            S.sbn_conv1x1_sparse(p, 256, 512, 1, 2, 2, 0)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        with pytest.raises(S.SbnError):
+            S.sbn_conv1x1_sparse(p, 256, 512, 1, 2, 2, 0)
+        with pytest.raises(AssertionError):
+            S.sbn_conv1x1_sparse(p, torch.zeros(1, 2, 2, 64), torch.zeros(1, 2, 2, 32), 1, 2, 2)
+    assert [f.name for f in elsewhere.iterdir()] == ["cxx"]
+
+
+def test_a_file_that_does_not_load(elsewhere, monkeypatch):
+    open(_lib.marshal_path(), "w").write("not a shared object")
+    with pytest.warns(UserWarning, match="marshalled in Python"):
+        with pytest.raises(S.SbnError):
+            S.sbn_conv1x1_sparse(layer(), 256, 512, 1, 2, 2, 0)
+
+
 def test_another_torch_has_a_file_of_its_own(elsewhere, monkeypatch):
     path = _lib.marshal_path()
     monkeypatch.setattr(torch, "__version__", "0.0")
@@ -59,6 +84,18 @@ def test_the_file_appears_when_it_is_complete(elsewhere, monkeypatch):
     monkeypatch.setenv("CXX", compiler(elsewhere / "cxx", f'for out; do :; done; printf half > "$out"; [ -e "{path}" ] && exit 1; printf whole > "$out"'))
     assert _lib.build_marshal() == path
     assert open(path).read() == "whole"
+
+
+@pytest.mark.gpu
+def test_the_python_code_gives_the_same_results(elsewhere, monkeypatch):
+    monkeypatch.setenv("CXX", "false")
+    x, y, ref = torch.randn(2, 5, 7, 64, device="cuda"), torch.zeros(2, 5, 7, 32, device="cuda"), torch.zeros(2, 5, 7, 32, device="cuda")
+    p = layer(device=0)
+    with pytest.warns(UserWarning, match="marshalled in Python"):
+        S.sbn_conv1x1_sparse(p, x, ref, 2, 5, 7)
+    monkeypatch.undo()
+    S.sbn_conv1x1_sparse(p, x, y, 2, 5, 7)
+    assert torch.equal(y, ref) and not torch.equal(y, torch.zeros_like(y))
 
 
 @pytest.mark.gpu
