@@ -421,13 +421,17 @@ int sbn_pointwise_chain_static(const sbn_chain_t* c, const float* x, float* y, i
                                float* const* layer_outputs, void* stream);
 
 /*
- * By default a depthwise item directly in front of a 1x1 layer with at most
- * 128 input and 128 output channels (input channels a multiple of 32) runs
+ * A depthwise item directly in front of a 1x1 layer with at most
+ * 128 input and 128 output channels (input channels a multiple of 32) can run
  * inside that layer's launch: the depthwise result is computed tile by tile in
  * on-chip memory and never written out (those layers are bound by memory
- * traffic).  Results agree with the separate launches up to fp32 summation
+ * traffic).  By default it does where the output has enough tiles of 8 x 8 pixels to
+ * fill the chip: more than one for every four compute units, or than six
+ * for every sixteen where the 1x1 layer has more than 64 channels on both sides;
+ * with fewer, two launches spread better.  Results agree with the separate launches up to fp32 summation
  * order inside the depthwise layer.  enable = 0 switches this off for the
- * chain (every item its own launch); a copy of the depthwise output requested
+ * chain (every item its own launch), 1 is the default, 2 runs every pair that
+ * can run so as one launch, whatever its size; a copy of the depthwise output requested
  * through layer_outputs switches it off for that pair.
  */
 int sbn_chain_set_fusion(sbn_chain_t* c, int enable);

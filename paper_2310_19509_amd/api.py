@@ -496,8 +496,8 @@ def sbn_chain_output_shape(c: Chain, n: int, h: int, w: int):
 
 
 def sbn_chain_set_fusion(c: Chain, enable: bool) -> None:
-    """Switch the fused depthwise + small 1x1 launches of a chain on (default) or off."""
-    _check(_lib.lib().sbn_chain_set_fusion(c.handle, 1 if enable else 0))
+    """Switch the fused depthwise + small 1x1 launches of a chain on (default: where they pay) or off; 2: on whatever the size."""
+    _check(_lib.lib().sbn_chain_set_fusion(c.handle, 2 if type(enable) is int and enable == 2 else 1 if enable else 0))
 
 
 def sbn_pointwise_chain(c: Chain, x, y, n: int, h: int, w: int, workspace, layer_outputs=None, stream=None) -> None:

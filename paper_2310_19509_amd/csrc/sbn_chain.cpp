@@ -25,7 +25,7 @@ struct sbn_chain {
     int device = 0;
     int c_in = 0;
     void* d_blob = nullptr;
-    bool fuse_dw = true;           // run a depthwise item and the small 1x1 layer after it as one launch
+    int fuse_dw = 1;               // run a depthwise item and the small 1x1 layer after it as one launch: 0 never, 1 where it pays, 2 always
     bool multi_layer = false;      // few pixels: consecutive depthwise / 1x1 items as phases of one launch (opt-in)
     unsigned* d_sync = nullptr;    // its grid barrier's words (in d_blob)
     int cus = 256;                 // compute units of the device
@@ -207,7 +207,7 @@ int run_chain(const sbn_chain* c, const float* x, float* y, int n, int h, int w,
         // output never exists in memory), unless the caller asked for a copy of it.
         if (c->fuse_dw && it.item == SBN_ITEM_DW3X3 && i + 1 < c->items.size() &&
             c->items[i + 1].item == SBN_ITEM_SPARSE && dwpw_fusable(c->items[i + 1].packed, it.channels, it.stride) &&
-            !(layer_outputs && layer_outputs[i]) && dwpw_pays(c->items[i + 1].packed, next_shape(it, s))) {
+            !(layer_outputs && layer_outputs[i]) && (c->fuse_dw == 2 || dwpw_pays(c->items[i + 1].packed, next_shape(it, s)))) {
             const sbn_chain::Item& pw = c->items[i + 1];
             const bool last2 = i + 2 == c->items.size();
             float* dst2 = last2 ? y : buf[which];
@@ -471,7 +471,7 @@ int sbn_chain_set_fusion(sbn_chain_t* c, int enable)
 {
     clear_error();
     if (!c) return fail(SBN_EINVAL, "sbn_chain_set_fusion: chain is NULL");
-    c->fuse_dw = enable != 0;
+    c->fuse_dw = enable == 2 ? 2 : enable != 0;
     return SBN_OK;
 }
 

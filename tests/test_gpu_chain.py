@@ -337,11 +337,16 @@ def test_depthwise_fused_into_small_pointwise_layer(n, h, w, K, N, stride, pct, 
     x = W.uniform_activation(seed + 5, (n, h, w, K))
     xd = torch.from_numpy(x).cuda()
     y_fused = torch.full((n, oh, ow, oc), float("nan"), device="cuda")
+    ws.fill_(float("nan"))
+    S.sbn_chain_set_fusion(chain, 2)                       # whatever the size
     S.sbn_pointwise_chain(chain, xd, y_fused, n, h, w, ws)
+    torch.cuda.synchronize()
+    assert ws.isnan().all()                                # the depthwise output was never in memory
     S.sbn_chain_set_fusion(chain, False)
     y_plain = torch.full((n, oh, ow, oc), float("nan"), device="cuda")
     S.sbn_pointwise_chain(chain, xd, y_plain, n, h, w, ws)
     torch.cuda.synchronize()
+    assert not ws.isnan().all()
 
     mid, bound_dw = R.dwconv3x3_nhwc(x, dw_w, dw_b, stride=stride, act=R.ACT_RELU if relu_dw else R.ACT_NONE)
     ref, bound_pw = R.sparse_conv_reference(mid, wt, mask, 4, 4, bias=b, perm_out=po, act=act_pw)
@@ -349,6 +354,40 @@ def test_depthwise_fused_into_small_pointwise_layer(n, h, w, K, N, stride, pct, 
     bound = bound_pw + (bound_dw.reshape(-1, K) @ wm.T).reshape(bound_pw.shape)
     assert_within_bound(y_fused.cpu().numpy(), ref, bound, f"fused {n,h,w,K,N,stride,pct}")
     assert_within_bound(y_plain.cpu().numpy(), ref, bound, f"separate {n,h,w,K,N,stride,pct}")
+
+
+@pytest.mark.parametrize("tiles,K,N,stride,fused", [
+    (64, 32, 64, 1, False), (65, 32, 64, 1, True),         # one tile of 8 x 8 pixels for every four compute units
+    (65, 64, 128, 2, True),                                # more than 64 channels on one side only
+    (96, 96, 72, 1, False), (97, 96, 72, 1, True),         # on both: six for every sixteen
+])
+def test_pairs_are_fused_from_enough_tiles_on(tiles, K, N, stride, fused):
+    """Which pairs run as one launch on a device of 256 compute units, by the switch's three values: one that does never
+    writes the depthwise output to the workspace.  The results against the oracle's two layers, as above."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are for 256 compute units")
+    h, w = 8 * stride, 8 * stride * tiles
+    dw_w, wt = W.normal_weights(9801, (K, 3, 3), 0.4), W.he_weights(9802, N, 1, 1, K)
+    mask = S.sbn_prune_magnitude(wt, S.SBN_CONV1X1, 4, 4, 50)
+    p = S.sbn_pack(S.SBN_CONV1X1, wt, 4, 4, mask=mask, act=S.SBN_ACT_RELU)
+    chain = S.sbn_chain_create([S.dw_item(dw_w, None, stride=stride, act=S.SBN_ACT_RELU), S.sparse_item(p)])
+    oh, ow, oc = S.sbn_chain_output_shape(chain, 1, h, w)
+    x = W.uniform_activation(9803, (1, h, w, K))
+    xd = torch.from_numpy(x).cuda()
+    mid, bound_dw = R.dwconv3x3_nhwc(x, dw_w, None, stride=stride, act=R.ACT_RELU)
+    ref, bound_pw = R.sparse_conv_reference(mid, wt, mask, 4, 4, act=R.ACT_RELU)
+    wm = np.abs(R.apply_mask(wt, mask, 4, 4).reshape(N, K).astype(np.float64))
+    bound = bound_pw + (bound_dw.reshape(-1, K) @ wm.T).reshape(bound_pw.shape)
+    ws = torch.empty(S.sbn_chain_workspace(chain, 1, h, w) // 4, device="cuda")
+    for enable, expect in ((None, fused), (0, False), (2, True), (True, fused), (1, fused)):
+        if enable is not None:
+            S.sbn_chain_set_fusion(chain, enable)
+        ws.fill_(float("nan"))
+        y = torch.full((1, oh, ow, oc), float("nan"), device="cuda")
+        S.sbn_pointwise_chain(chain, xd, y, 1, h, w, ws)
+        torch.cuda.synchronize()
+        assert bool(ws.isnan().all()) == expect, enable
+        assert_within_bound(y.cpu().numpy(), ref, bound, f"enable={enable} {tiles,K,N,stride}")
 
 
 def test_fusion_is_skipped_when_the_depthwise_output_is_requested():

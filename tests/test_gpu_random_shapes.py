@@ -91,10 +91,12 @@ def test_random_depthwise_plus_pointwise_pairs(seed):
         ref, bound_pw = R.sparse_conv_reference(mid, wt, mask, 4, 4, bias=b, perm_out=po, act=act_pw)
         wm = np.abs(R.apply_mask(R.permute_weights(wt, po, None), mask, 4, 4).reshape(N, K).astype(np.float64))
         bound = bound_pw + (bound_dw.reshape(-1, K) @ wm.T).reshape(bound_pw.shape)
-        for fused in (True, False):
+        for fused in (2, 0):                               # (2: whatever the size)
             S.sbn_chain_set_fusion(chain, fused)
+            ws.fill_(float("nan"))
             yd = torch.full((n, oh, ow, oc), float("nan"), device="cuda")
             S.sbn_pointwise_chain(chain, xd, yd, n, h, w, ws)
             torch.cuda.synchronize()
+            assert bool(ws.isnan().all()) == bool(fused)   # the depthwise output exists in memory or does not
             assert_within_bound(yd.cpu().numpy(), ref, bound,
                                 f"fused={fused} n,h,w={n,h,w} K={K} N={N} stride={stride} pct={pct}")
