@@ -66,7 +66,7 @@ struct DeviceLayout {
     size_t n_entries = 0;
     size_t n_present = 0;                 // (entry, group) pairs kept: 4 x 4 blocks (times taps) that the 32-bit forms multiply
     int n_chunks32 = 0;                   // ceil(c_in / 32)
-    int cus = 256;                        // compute units of the device the layer lives on (set at upload)
+    int cus = 256;                        // compute units of the device the layer lives on (set when the layout is built)
     // host staging
     std::vector<uint32_t> records;        // [n_bundles][n_chunks][16]
     std::vector<uint32_t> woff;           // [n_bundles][n_chunks + 1]

@@ -31,13 +31,17 @@ bool conv1x1_wide_pays(const sbn_packed* p) { return conv1x1_wide_margin(p) >= 1
 
 // Layers that gain from the 32 x 32 tiles alone, at the right number of pixels (conv1x1_split_chosen): those tiles read the activations
 // once per 32 output channels and split the input channels, where the 32-bit form that splits them reads them once per 16 and the others
-// do not split them.  Up to 64 output channels at almost any share kept, more from 0.3 on.
+// do not split them.  Up to 64 output channels at almost any share kept, more from 0.3 on, where the most pixels that the form takes (four
+// tiles per compute unit) are more than the fewest (four times the output channels): below 512 on 256 compute units.  (At 512 the one launch
+// between the two lines, 2048 pixels, is a tie at 70 %: 12.4 us against 12.3 of the 32-bit form with 512 input channels, 60 % 12.4 and 12.8; the tables are
+// 1.6 MB, nearly as much as the layer's others, and 0.8 of its 1.4 ms of packing on the host.)
 bool conv1x1_split_pays(const sbn_packed* p)
 {
     if ((p->c_out + 31) / 32 * 32 * 3 > p->c_out * 4) return false;     // (a quarter of the channels of the tiles idle)
     const double share = 16.0 * (double)p->dev.n_present / ((double)p->c_in * p->c_out);
     if (p->c_out <= 64) return p->c_in >= 192 && share >= (p->c_in >= 512 ? 0.05 : 0.15);
-    return p->c_out > 80 && p->c_in >= 256 && share >= 0.3;
+    const long long most = 4ll * p->dev.cus / ((p->dev.n_bundles + 1) / 2) * 32;
+    return p->c_out > 80 && p->c_in >= 256 && share >= 0.3 && most > 4ll * p->c_out;
 }
 
 // Kernels in 4 x 4 blocks that a layer keeps, over all that the wide multiplies go through (input channels in 32s,
@@ -121,6 +125,9 @@ void build_device_layout(sbn_packed* p)
 {
     DeviceLayout& L = p->dev;
     const int taps = p->kh * p->kw, go = p->go, gi = p->gi;
+    int ndev = 0, cus = 0;                                           // the rules and the launchers count by it
+    if (p->device >= 0 && hipGetDeviceCount(&ndev) == hipSuccess && p->device < ndev &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess && cus > 0) L.cus = cus;
     const int n_groups4 = p->c_out / 4;                              // go is 4 or 8
     L.n_bundles = (n_groups4 + kBundleGroups - 1) / kBundleGroups;
     L.n_chunks = (p->c_in + kChunk - 1) / kChunk;
@@ -321,8 +328,6 @@ int upload_device_layout(sbn_packed* p)
     int prev = 0;
     (void)hipGetDevice(&prev);
     if ((e = hipSetDevice(p->device)) != hipSuccess) return fail(SBN_EHIP, "hipSetDevice: %s", hipGetErrorString(e));
-    int cus = 0;                           // the launchers size their grids by it
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess && cus > 0) L.cus = cus;
     char* blob = nullptr;
     if ((e = hipMalloc((void**)&blob, total)) != hipSuccess) {
         (void)hipSetDevice(prev);

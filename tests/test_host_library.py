@@ -163,6 +163,11 @@ def test_packed_layout_reports_entries_and_every_piece_tables():
     (S.SBN_CONV1X1, 512, 512, 50, 1, True),
     (S.SBN_CONV1X1, 512, 512, 72, 1, False),
     (S.SBN_CONV1X1, 512, 80, 0, 1, False),
+    (S.SBN_CONV1X1, 1024, 64, 90, 1, True),            # the 32 x 32 tiles alone,
+    (S.SBN_CONV1X1, 512, 256, 60, 1, True),
+    (S.SBN_CONV1X1, 512, 512, 60, 1, False),           # which need pixels enough for the channels in few tiles
+    (S.SBN_CONV1X1, 256, 512, 60, 1, False),
+    (S.SBN_CONV1X1, 1024, 1024, 65, 1, False),
 ])
 def test_dense_tables_are_built_only_where_a_launch_can_use_them(kind, K, N, pct, stride, wide):
     """The tables of the wide multiplies take 6 bytes per weight, kept or not (c_in and c_out here are whole tiles)."""
