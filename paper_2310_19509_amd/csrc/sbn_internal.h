@@ -58,6 +58,8 @@ constexpr int kChunk = 64;                             // input channels per rec
 constexpr int kSlots = kChunk / 4;                     // descriptors per record
 constexpr double kStaticWalkMinFill = 0.60;            // share of (bundle, piece) pairs kept, from which the every-piece tables are built
 
+// HIP takes fewer than 2^32 work items in a dimension of a launch: workgroups of 256 threads that one launch can have.
+constexpr long long kMaxGroups256 = 0xFFFFFFFFll / 256;
 constexpr uint32_t kNoEntry = 0xFFFFF000u;             // outside any weight array; a few taps further the sum does not wrap
 
 struct DeviceLayout {

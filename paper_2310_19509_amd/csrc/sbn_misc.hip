@@ -3,6 +3,8 @@
 // between the sparse pointwise layers when a whole network is chained.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "sbn_internal.h"
 
 namespace {
@@ -410,10 +412,16 @@ int launch_avgpool(const float* x, float* y, int n, int hw, int c, void* stream)
     if ((long long)n * c * hw == 0) return SBN_OK;
     if (c % 4) return fail(SBN_ESHAPE, "the average pool needs a multiple of 4 channels (got %d)", c);
     const int c_tiles = (c + kPoolChannels - 1) / kPoolChannels;
-    if ((long long)n * c_tiles > 0x7FFFFFFFll) return fail(SBN_EINVAL, "too many images for one average pool (%d)", n);
-    hipLaunchKernelGGL(avgpool_kernel, dim3((unsigned)((long long)n * c_tiles)), dim3(256), 0, (hipStream_t)stream, x, y,
-                       hw, c, c_tiles);
-    return check_launch("avgpool");
+    // As many images at a time as one launch takes (1024 channels: 1 048 575).
+    const int most = (int)std::max<long long>(1, kMaxGroups256 / c_tiles);
+    for (int at = 0; at < n; at += most) {
+        const int some = std::min(most, n - at);
+        hipLaunchKernelGGL(avgpool_kernel, dim3((unsigned)((long long)some * c_tiles)), dim3(256), 0, (hipStream_t)stream,
+                           x + (long long)at * hw * c, y + (long long)at * c, hw, c, c_tiles);
+        if (int rc = check_launch("avgpool")) return rc;
+        if (n - at <= most) break;                                       // (at + most may not fit an int)
+    }
+    return SBN_OK;
 }
 
 }  // namespace sbn

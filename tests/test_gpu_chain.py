@@ -546,3 +546,20 @@ def test_mobilenet_batch1_multi_layer_tail_matches_item_by_item():
     assert torch.isfinite(y_multi).all()
     scale = float(y_items.abs().max())
     assert float((y_multi - y_items).abs().max()) <= 1e-4 * max(scale, 1.0)
+
+
+def test_average_pool_of_more_images_than_one_launch_takes():
+    """2^22 + 1 images of one pixel x 256 channels: four workgroups of 256 threads each, a little over the 2^32 work items
+    that HIP takes per launch.  The pool of one pixel is that pixel, so every value is known."""
+    n, c = (1 << 22) + 1, 256
+    if torch.cuda.mem_get_info()[0] < 20 * (1 << 30):
+        pytest.skip("needs 20 GiB of device memory")
+    w = np.zeros((c, 3, 3), np.float32)
+    w[:, 1, 1] = 1.0                                       # (a depthwise layer that copies: a chain cannot start with the pool)
+    chain = S.sbn_chain_create([S.dw_item(w, None, act=S.SBN_ACT_NONE), S.avgpool_item()])
+    x = torch.rand((n, 1, 1, c), device="cuda", generator=torch.Generator(device="cuda").manual_seed(9810))
+    y = torch.full((n, 1, 1, c), float("nan"), device="cuda")
+    ws = torch.empty(S.sbn_chain_workspace(chain, n, 1, 1) // 4, device="cuda")
+    S.sbn_pointwise_chain(chain, x, y, n, 1, 1, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(x, y)
