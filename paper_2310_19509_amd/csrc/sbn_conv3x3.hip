@@ -500,7 +500,9 @@ int launch_conv3x3(const sbn_packed* p, const float* x, float* y, int n, int h, 
         const long long col_tiles = (p->dev.n_bundles + 3) / 4;
         const long long tiles1 = (long long)((w + 7) / 8) * ((h + 7) / 8), tiles2 = (long long)((w + 15) / 16) * ((h + 7) / 8);
         const long long wg1 = n * tiles1 * col_tiles, cus = p->dev.cus;
-        if (wg1 <= cus)
+        if ((n * tiles1 + 7) / 8 * 8 * col_tiles > kMaxGroups256)       // (half as many workgroups: up to twice the pixels in a launch)
+            form = 2;
+        else if (wg1 <= cus)
             form = 32;
         else if (wg1 <= 3 * cus)
             form = 3;

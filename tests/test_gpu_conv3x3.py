@@ -174,6 +174,25 @@ def test_activations_beyond_4_gib():
     assert not torch.isnan(yd[::97, ::11, ::13]).any()
 
 
+def test_more_one_pixel_tiles_than_one_launch_takes():
+    """69906 images of 128 x 120: a little more than the 2^24 workgroups of 256 threads that HIP takes per launch with one pixel per
+    lane (15 tiles of 8 columns), half of it with two (8 of 16), and columns that the latter's last tile wastes."""
+    n, h, w, c = 69906, 128, 120, 4
+    if torch.cuda.mem_get_info()[0] < 45 * (1 << 30):
+        pytest.skip("needs 45 GiB of device memory")
+    wt, b = W.he_weights(8910, c, 3, 3, c), W.small_bias(8911, c)
+    p = S.sbn_pack(S.SBN_CONV3X3, wt, 4, 4, bias=b)
+    x = torch.rand((n, h, w, c), device="cuda", generator=torch.Generator(device="cuda").manual_seed(8912))
+    y = torch.full((n, h, w, c), float("nan"), device="cuda")
+    S.sbn_conv3x3_sparse(p, x, y, n, h, w)
+    torch.cuda.synchronize()
+    at = torch.tensor([0, 1, n // 2, n - 1], device="cuda")
+    ref, bound = R.sparse_conv_reference(x[at].cpu().numpy(), wt, np.ones((1, 1), np.uint8), 4, 4, bias=b, stride=1, pad=1)
+    assert_within_bound(y[at].cpu().numpy(), ref, bound, "first, middle and last images")
+    for i in range(0, n, 8192):                            # every pixel is written
+        assert not y[i:i + 8192].isnan().any()
+
+
 @pytest.mark.parametrize("n,h,w,K,N,form", [
     (32, 28, 28, 128, 128, 1),         # four workgroups per compute unit
     (5, 30, 70, 128, 192, 3),          # a little over two
