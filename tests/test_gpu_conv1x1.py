@@ -43,8 +43,8 @@ CASES = [
     (2, 5, 5, 64, 32, 8, 8, 30, False, True, True),         # gi=8
     (1, 3, 3, 24, 24, 4, 4, 30, True, False, True),         # K, N not multiples of 32 / 16
     (1, 3, 3, 40, 72, 8, 4, 50, True, True, False),         # K=40, N=72
-    (1, 3, 3, 6, 12, 4, 2, 30, True, False, False),         # K not a multiple of 4 (scalar staging)
-    (1, 3, 3, 70, 12, 4, 1, 50, True, False, True),         # K=70, two chunks, scalar staging
+    (1, 3, 3, 6, 12, 4, 2, 30, True, False, False),         # K not a multiple of 4
+    (1, 3, 3, 70, 12, 4, 1, 50, True, False, True),         # K=70, two chunks and no multiple of 4
     (1, 7, 7, 1024, 1024, 4, 4, 30, True, True, False),     # widest layer
     (1, 7, 7, 512, 1024, 8, 4, 70, True, False, False),
     (3, 9, 11, 128, 256, 4, 4, 30, True, True, True),       # M=297: several tiles + ragged tail
@@ -91,6 +91,45 @@ def test_every_multi_chunk_kernel_form(variant, n, h, w, K, N, pct):
     finally:
         S.sbn_force_kernel_form(S.SBN_CONV1X1, 0)
     assert_within_bound(y, ref, bound, f"variant {variant} case {n,h,w,K,N,pct}")
+
+
+@pytest.mark.parametrize("m", [65, 200])
+@pytest.mark.parametrize("K,N,go,gi", [(65, 12, 4, 1), (66, 20, 4, 2), (67, 64, 8, 1), (70, 72, 8, 2), (90, 200, 8, 2), (130, 36, 4, 1),
+                                       (63, 16, 4, 1), (30, 24, 8, 2), (5, 8, 4, 1)])
+def test_channel_counts_that_are_no_multiple_of_four(m, K, N, go, gi):
+    """The plain form (12: not the few-pixel kernel) over a ragged last tile of pixels.  A row's last 16-byte load brings the next pixel's
+    first channels, which must not come through, not even as zero times infinity."""
+    wt, b = W.he_weights(7610 + K, N, 1, 1, K), W.small_bias(7611, N) * 20
+    x = W.uniform_activation(7612, (1, 1, m, K))
+    spoilt = x.copy()
+    hit = np.arange(1, m, 3)
+    for i, v in zip(hit, np.resize([np.inf, np.nan, -np.inf, 3e38], len(hit))):
+        spoilt[0, 0, i, :3] = v
+    rest = np.setdiff1d(np.arange(m), hit)
+    S.sbn_force_kernel_form(S.SBN_CONV1X1, 12)
+    try:
+        for pct in (0, 50):
+            y, ref, bound = run_layer(x, wt, go, gi, bias=b, pct=pct)
+            assert_within_bound(y, ref, bound, f"{m,K,N,go,gi,pct}")
+            y2 = run_layer(spoilt, wt, go, gi, bias=b, pct=pct)[0]
+            assert np.array_equal(y[0, 0, rest], y2[0, 0, rest])
+            assert pct or not np.isfinite(y2[0, 0, hit]).all()
+    finally:
+        S.sbn_force_kernel_form(S.SBN_CONV1X1, 0)
+
+
+def test_the_automatic_choice_for_an_odd_layer_of_several_chunks():
+    """Too many pixels for the few-pixel kernel: the same bits as the plain form."""
+    n, h, w, K, N, go, gi = 3, 37, 29, 90, 200, 8, 2
+    wt, b = W.he_weights(7620, N, 1, 1, K), W.small_bias(7621, N)
+    x = W.uniform_activation(7622, (n, h, w, K))
+    y, ref, bound = run_layer(x, wt, go, gi, bias=b, act=S.SBN_ACT_RELU, pct=40)
+    assert_within_bound(y, ref, bound, "odd layer")
+    S.sbn_force_kernel_form(S.SBN_CONV1X1, 12)
+    try:
+        assert np.array_equal(y, run_layer(x, wt, go, gi, bias=b, act=S.SBN_ACT_RELU, pct=40)[0])
+    finally:
+        S.sbn_force_kernel_form(S.SBN_CONV1X1, 0)
 
 
 def test_uneven_rows_from_hand_mask():

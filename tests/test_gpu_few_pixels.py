@@ -110,3 +110,38 @@ def test_the_automatic_choice_takes_it_for_one_image(m, K, N, pct):
     x = W.uniform_activation(7105, (1, 1, m, K))
     y = run(S.SBN_CONV1X1, p, x, N, 1, 0)
     assert any(np.array_equal(y, run(S.SBN_CONV1X1, p, x, N, 1, f)) for f in (3004, 3008))
+
+
+@pytest.mark.parametrize("kind,h,w,K,N,pct,stride,form", [
+    # 16 pixels x 16 channels = a tile, 32 channels of a tap = a unit
+    (S.SBN_CONV3X3, 16, 16, 256, 64, 0, 1, 3016),      # 64 tiles of 72 units: sixteen waves
+    (S.SBN_CONV3X3, 17, 16, 256, 64, 0, 1, 3008),      # 68 tiles
+    (S.SBN_CONV3X3, 16, 16, 224, 64, 0, 1, 3008),      # 63 units
+    (S.SBN_CONV3X3, 31, 32, 256, 64, 0, 2, 3016),      # (stride 2: 16 x 16 pixels)
+    (S.SBN_CONV3X3, 32, 32, 32, 64, 0, 1, 3008),       # a tile per compute unit
+    (S.SBN_CONV3X3, 33, 32, 32, 64, 0, 1, 3004),
+    (S.SBN_CONV3X3, 60, 80, 32, 64, 0, 1, 3004),       # 4.7 tiles per compute unit
+    (S.SBN_CONV3X3, 60, 81, 32, 64, 0, 1, None),
+    (S.SBN_CONV3X3, 48, 60, 32, 64, 50, 1, 3004),      # half kept: 0.6 of it
+    (S.SBN_CONV3X3, 49, 60, 32, 64, 50, 1, None),
+    (S.SBN_CONV3X3, 52, 64, 512, 64, 0, 1, 3004),      # 470 units per compute unit
+    (S.SBN_CONV3X3, 53, 64, 512, 64, 0, 1, None),
+    (S.SBN_CONV3X3, 167, 189, 32, 64, 0, 2, 3004),     # stride 2: 7.8 tiles
+    (S.SBN_CONV3X3, 168, 191, 32, 64, 0, 2, None),
+    (S.SBN_CONV1X1, 32, 32, 256, 64, 0, 1, 3008),      # a tile per compute unit
+    (S.SBN_CONV1X1, 25, 41, 256, 64, 0, 1, 3004),
+    (S.SBN_CONV1X1, 64, 96, 64, 64, 0, 1, 3004),       # six tiles
+    (S.SBN_CONV1X1, 5, 1229, 64, 64, 0, 1, None),
+    (S.SBN_CONV1X1, 32, 60, 1024, 128, 0, 1, 3004),    # 120 units
+    (S.SBN_CONV1X1, 17, 113, 1024, 128, 0, 1, None),
+])
+def test_the_automatic_choice_on_both_sides_of_its_lines(kind, h, w, K, N, pct, stride, form):
+    """The same bits as the form that the rule names on a device of 256 compute units; as none of them where it takes another kernel."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are for 256 compute units")
+    p = layer(kind, K, N, pct, 4, 4, stride)[0]
+    x = W.uniform_activation(7106, (1, h, w, K))
+    y = run(kind, p, x, N, stride, 0)
+    for f in (3004, 3008) if kind == S.SBN_CONV1X1 else (3004, 3008, 3016):
+        same = np.array_equal(y, run(kind, p, x, N, stride, f))
+        assert same if f == form else form or not same, f
