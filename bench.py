@@ -98,8 +98,8 @@ def profiled_traffic(name, files):
     return val if sha == kernel_source_hash(files) else None
 
 
-SOURCES_1X1 = ("sbn_conv1x1.hip", "sbn_conv1x1_wide.hip", "sbn_wide.h", "sbn_layout.cpp", "sbn_internal.h")
-SOURCES_3X3 = ("sbn_conv3x3.hip", "sbn_conv3x3_wide.hip", "sbn_wide.h", "sbn_layout.cpp", "sbn_internal.h")
+SOURCES_1X1 = ("sbn_conv1x1.hip", "sbn_conv1x1_wide.hip", "sbn_few.hip", "sbn_wide.h", "sbn_layout.cpp", "sbn_internal.h")
+SOURCES_3X3 = ("sbn_conv3x3.hip", "sbn_conv3x3_wide.hip", "sbn_few.hip", "sbn_wide.h", "sbn_layout.cpp", "sbn_internal.h")
 
 
 def run_copy(a, torch, S):

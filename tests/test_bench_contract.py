@@ -18,6 +18,21 @@ def test_entry_points_exist():
     assert callable(g.build) and callable(g.smoke)
 
 
+def test_traffic_figures_end_with_the_sources_of_the_kernels_they_were_read_from():
+    """Every kernel that a launch of the two kinds of layers can be sent to counts."""
+    import re
+    sys.path.insert(0, ROOT)
+    import bench
+    csrc = os.path.join(ROOT, "paper_2310_19509_amd", "csrc")
+    for own, sources in (("sbn_conv1x1.hip", bench.SOURCES_1X1), ("sbn_conv3x3.hip", bench.SOURCES_3X3)):
+        called = set(re.findall(r"\b(launch_\w+)\(p, ", open(os.path.join(csrc, own)).read()))
+        assert "launch_few" in called
+        for f in os.listdir(csrc):
+            text = open(os.path.join(csrc, f)).read()
+            if f.endswith(".hip") and any(re.search(rf"^int {name}\([^;]*\n{{", text, re.M) for name in called):
+                assert f in sources, (own, f)
+
+
 def test_product_never_imports_the_oracle():
     """The library and its binding must not route through the CPU oracle."""
     pkg = os.path.join(ROOT, "paper_2310_19509_amd")
