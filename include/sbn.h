@@ -325,8 +325,9 @@ int sbn_conv3x3_sparse(const sbn_packed_t* p, const float* x, float* y,
  * never use those tables, the automatic choice always does; 1: the automatic
  * choice among the forms so far, without those tables; 2032, 2064, 2256: 32 x 32 tiles with the input
  * channels split over four waves, 64 x 128 and 128 x 256 tiles on
- * triples of bfloat16, for layers of c_in > 64 and a multiple of 4 that keep enough for the automatic choice to
- * come to use them or that were packed while one of them was forced, the automatic
+ * triples of bfloat16 (6 bytes per weight of the dense layer, beside the other tables on the device), for layers of c_in > 64 and a
+ * multiple of 4 that keep enough for the automatic choice to
+ * come to use them at some number of pixels or that were packed while one of them was forced, the automatic
  * choice otherwise; 3004, 3008: the few-pixel kernel, 16 pixels x 16 channels
  * per workgroup of 4 or 8 waves that split the input channels) or SBN_CONV3X3 (1, 2, 3: one pixel per lane, two pixels per
  * lane, entry-ahead fetch; 32: entry-ahead with the input channels split over

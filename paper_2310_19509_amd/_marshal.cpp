@@ -1,6 +1,6 @@
 // The run calls' argument marshalling for the ordinary case: plain contiguous float32 tensors on a GPU, sizes as Python
 // integers, the current stream.  One layer of a network on one image takes the GPU 3 to 5 us; the same checks and
-// conversions through Python attributes and ctypes took the host 7.4 us a call, this takes 3.7 (3 of them the launch).
+// conversions through Python attributes and ctypes take the host 7.7 us a call, this takes 3.4 (3 of them the launch).
 // Anything else (addresses, other streams, subclasses, wrapped tensors, errors) is answered with None, and the Python code of
 // api.py, which has the checks and their messages, does it.
 #include <Python.h>

@@ -115,7 +115,9 @@ __global__ __launch_bounds__(64 * NWV, PIPE ? 2 : 3) void conv1x1_wide_kernel(
     constexpr int NL = T * 16 / (64 * NWV);        // 16-byte slots per lane and chunk
     constexpr int ROWS = 16;                       // rows that a wave stages, four lanes to a row
     // LDS image, a, b and c alike: per 8 channels a plane of T rows of 16 bytes.  The 32 rows that a read
-    // takes from each of two planes and the 16 that a write stores then cover all banks evenly.
+    // takes from each of two planes cover all banks evenly; the two planes that a write goes to lie a multiple of 256
+    // bytes apart, so that rows of both meet in a bank.  (Counters: 0.59 conflict cycles per active LDS cycle in the
+    // 128 x 256 form, 0.79 in the other.)
     constexpr int PLANE = T * 16, PART = 8 * PLANE, IMAGE = 3 * PART;
     static_assert(ROWS * NWV == T && NL == 4, "tile shape");
     __shared__ __attribute__((aligned(16))) char lds[2][IMAGE];
