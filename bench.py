@@ -385,6 +385,14 @@ def time_steps(torch, fn, steps, warmup):
     return e0.elapsed_time(e1) / steps
 
 
+def fused_pairs(W, images, cus):
+    """The library's rule (include/sbn.h, sbn_chain_set_fusion) for the depthwise layers of MobileNet-v1 that run inside the 1x1
+    layer behind them."""
+    return [i for i, (d, p) in enumerate(zip(W.MOBILENET_V1_DW, W.MOBILENET_V1_PW))
+            if p.c_in % 32 == 0 and p.c_in <= 128 and p.c_out <= 128
+            and images * ((d.hw_out + 7) // 8) ** 2 * 16 > (6 if p.c_in > 64 and p.c_out > 64 else 4) * cus]
+
+
 def run_mobilenet(a, torch, S, W):
     """Config 4: whole MobileNet-v1 forward as one chain (layers depend on each other); the batch
     runs as a few sub-batches on separate streams unless --pipeline 1."""
@@ -456,9 +464,9 @@ def run_mobilenet(a, torch, S, W):
     act_bytes = 4.0 * B * (hw * hw * 3 + 2 * sum(d.hw_out ** 2 * d.c for d in W.MOBILENET_V1_DW)
                            + W.STEM["hw_out"] ** 2 * W.STEM["c_out"]
                            + sum(p.hw ** 2 * (p.c_in + p.c_out) for p in W.MOBILENET_V1_PW))
-    # pairs that run as one launch (the library's rule): their depthwise output is never written or read
-    fused = [] if a.no_fuse else [i for i, (d, p) in enumerate(zip(W.MOBILENET_V1_DW, W.MOBILENET_V1_PW))
-                                  if p.c_in % 32 == 0 and p.c_in <= 128 and p.c_out <= 128]
+    # pairs that run as one launch: their depthwise output is never written or read
+    images = B // a.pipeline if a.pipeline > 1 and B >= a.pipeline and not a.graph else B
+    fused = [] if a.no_fuse else fused_pairs(W, images, torch.cuda.get_device_properties(0).multi_processor_count)
     act_bytes -= 4.0 * B * 2 * sum(W.MOBILENET_V1_DW[i].hw_out ** 2 * W.MOBILENET_V1_DW[i].c for i in fused)
     t_roof = sum(matrix_floor_s(2.0 * int(m["mask"].sum()) * a.go * 4 * B * L.hw * L.hw, 2.0 * B * L.hw * L.hw * L.c_in * L.c_out)
                  for m, L in zip([m for m in meta if m["kind"] == "pw"][:13], W.MOBILENET_V1_PW))

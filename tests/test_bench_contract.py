@@ -33,6 +33,15 @@ def test_traffic_figures_end_with_the_sources_of_the_kernels_they_were_read_from
                 assert f in sources, (own, f)
 
 
+def test_launches_counted_by_the_rule_of_the_library():
+    """One image has 196 tiles of 8 x 8 pixels in the first block and 49 in the second and third, on 256 compute units."""
+    sys.path.insert(0, ROOT)
+    import bench
+    import workloads as W
+    assert bench.fused_pairs(W, 64, 256) == [0, 1, 2] and bench.fused_pairs(W, 2, 256) == [0, 1, 2]
+    assert bench.fused_pairs(W, 1, 256) == [0]
+
+
 def test_product_never_imports_the_oracle():
     """The library and its binding must not route through the CPU oracle."""
     pkg = os.path.join(ROOT, "paper_2310_19509_amd")
