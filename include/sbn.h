@@ -445,7 +445,7 @@ int sbn_chain_set_fusion(sbn_chain_t* c, int enable);
  * of 4 and at least 128) are queued as ONE launch: a grid of resident
  * workgroups walks the items as phases with a grid-wide barrier in between.
  * On MI355X this is SLOWER than one launch per item (whole MobileNet-v1 on one
- * image: 0.36 ms against 0.15 ms): a grid-wide barrier has to write one XCD's
+ * image: 0.36 ms against 0.12 ms): a grid-wide barrier has to write one XCD's
  * L2 back and invalidate the others', about 14 us, where the boundary between
  * two launches costs about 6 us.  The path is kept for callers that must bound
  * the number of launches.  Results agree with the separate launches up to fp32
