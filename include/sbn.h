@@ -60,7 +60,7 @@ extern "C" {
 
 /* activations applied after bias */
 #define SBN_ACT_NONE 0
-#define SBN_ACT_RELU 1
+#define SBN_ACT_RELU 1        /* of NaN: 0 */
 
 typedef struct sbn_packed sbn_packed_t;
 typedef struct sbn_chain  sbn_chain_t;

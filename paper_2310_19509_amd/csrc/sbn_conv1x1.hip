@@ -44,16 +44,16 @@ namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// max(v, 0) per component as ONE instruction each: a signed integer maximum on the bit patterns
-// (a float with its sign bit set is a negative integer; -0.0 and negative NaNs become +0.0).
-// fmaxf() costs two (the compiler first re-quiets its operand), and every VALU instruction takes
-// matrix-pipe issue time.
-__device__ __forceinline__ v4f relu4(v4f v)
+// max(v, 0) per component as ONE instruction each; NaN becomes 0, as in every kernel here (what a layer answers must not
+// depend on the form it runs in).  fmaxf() costs two (the compiler first re-quiets its operand, the result of an addition or a
+// multiply, which is quiet), and every VALU instruction takes matrix-pipe issue time: up to 1 % of a pass.
+__device__ __forceinline__ float relu(float v)
 {
-    typedef int v4i __attribute__((ext_vector_type(4)));
-    const v4i b = __builtin_bit_cast(v4i, v);
-    return __builtin_bit_cast(v4f, (v4i){b.x > 0 ? b.x : 0, b.y > 0 ? b.y : 0, b.z > 0 ? b.z : 0, b.w > 0 ? b.w : 0});
+    float r;
+    asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(v));
+    return r;
 }
+__device__ __forceinline__ v4f relu4(v4f v) { return (v4f){relu(v.x), relu(v.y), relu(v.z), relu(v.w)}; }
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 // Vector instructions share their issue port with the matrix instructions: a plain VALU

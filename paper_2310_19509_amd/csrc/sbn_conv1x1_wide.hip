@@ -31,7 +31,7 @@
 //     other's waits.
 //   PX = 4, NWV = 8, PIPE: 128 x 256 tiles halve the weights' and the conversions' share of the work; one
 //     workgroup per compute unit walks its tiles as one stream of chunks.
-// In both the next chunk's conversion goes between the multiplies of this one.  The matrix unit is busy 65 % of the
+// In both the next chunk's conversion goes between the multiplies of this one.  The matrix unit is busy 63 % of the
 // time in the second form (512 x 512, 100352 pixels, 260 us: 1.2 PFLOP/s; a loop of these multiplies alone on random
 // data reaches 1.85): activations, weights and LDS reads that arrive late cost 22 %, uneven rounds 13 %.
 #include <hip/hip_runtime.h>
@@ -63,7 +63,7 @@ struct Exact {
     __device__ __forceinline__ void store(v4f acc, long long pix, int ch) const
     {
         acc += *(const v4f*)(bias + ch);
-        if (act == SBN_ACT_RELU) acc = relu4(acc);
+        if (act == SBN_ACT_RELU) acc = relu4_of_any(acc);
         *(v4f*)(y + pix * N + ch) = acc;
     }
     __device__ __forceinline__ void by_lane(long long pix, int ch) const

@@ -44,7 +44,7 @@ struct Exact {
     __device__ __forceinline__ void store(v4f acc, long long pix, int ch) const
     {
         acc += *(const v4f*)(bias + ch);
-        if (act == SBN_ACT_RELU) acc = relu4(acc);
+        if (act == SBN_ACT_RELU) acc = relu4_of_any(acc);
         *(v4f*)(y + pix * N + ch) = acc;
     }
     // one entry: w = its group's [tap][co][ci], xp = its piece of the centre pixel

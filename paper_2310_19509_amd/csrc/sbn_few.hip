@@ -48,7 +48,7 @@ struct Exact {
     __device__ __forceinline__ void store(v4f acc, long long pix, int ch) const
     {
         acc += *(const v4f*)(a.bias + ch);
-        if (a.act == SBN_ACT_RELU) acc = relu4(acc);
+        if (a.act == SBN_ACT_RELU) acc = relu4_of_any(acc);
         *(v4f*)(a.y + pix * a.N + ch) = acc;
     }
     // w: its group's [co][ci] of the entry's first tap; ch: first channel of the piece

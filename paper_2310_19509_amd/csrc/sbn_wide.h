@@ -65,12 +65,16 @@ __device__ __forceinline__ void wave_lds_order()
     __builtin_amdgcn_wave_barrier();
 }
 
-__device__ __forceinline__ v4f relu4(v4f v)                              // as in the 32-bit form
+// One instruction each, by the sign bit: for results that are finite.  The others are done again.
+__device__ __forceinline__ v4f relu4(v4f v)
 {
     typedef int v4i __attribute__((ext_vector_type(4)));
     const v4i b = __builtin_bit_cast(v4i, v);
     return __builtin_bit_cast(v4f, (v4i){b.x > 0 ? b.x : 0, b.y > 0 ? b.y : 0, b.z > 0 ? b.z : 0, b.w > 0 ? b.w : 0});
 }
+
+// For results that are done again: NaN becomes 0, as in the 32-bit forms.
+__device__ __forceinline__ v4f relu4_of_any(v4f v) { return (v4f){fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f)}; }
 
 // acc[co] += sum over ci of w[co][ci] * x[ci] (the 1x1 tables' order), for a piece that is kept
 __device__ __forceinline__ void add_piece(v4f& acc, const v4f (&w)[4], const v4f& x, bool kept)

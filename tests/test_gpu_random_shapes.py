@@ -64,6 +64,49 @@ def test_random_layers_every_form(seed):
         S.sbn_force_kernel_form(S.SBN_CONV3X3, 0)
 
 
+@pytest.mark.parametrize("kind", [S.SBN_CONV1X1, S.SBN_CONV3X3])
+def test_relu_of_nan_is_zero_in_every_form(kind):
+    """act = ReLU gives 0 for a NaN, of either sign, as the oracle's does: what a launch answers must not depend on its form."""
+    k, K, N, n, h, w = 1 if kind == S.SBN_CONV1X1 else 3, 96, 96, 2, 9, 11
+    rng = np.random.default_rng(31)
+    wt = (rng.standard_normal((N, k, k, K)) * 0.1).astype(np.float32)
+    mask = S.sbn_prune_magnitude(wt, kind, 4, 4, 50)
+    x = rng.uniform(-1, 1, (n, h, w, K)).astype(np.float32)
+    x[0, 4, 5, 37], x[1, 4, 5, 37] = np.array([0x7FC00000, 0xFFC00000], np.uint32).view(np.float32)
+    x[1, 0, 0, 8:16] = np.inf                              # (and of sums of both infinities)
+    run = S.sbn_conv1x1_sparse if kind == S.SBN_CONV1X1 else S.sbn_conv3x3_sparse
+    keeps = np.repeat(mask[:, 37 // 4] != 0, 4)
+    try:
+        S.sbn_force_kernel_form(kind, 2064)
+        p = S.sbn_pack(kind, wt, 4, 4, mask=mask, act=S.SBN_ACT_RELU)
+        xd = torch.from_numpy(x).cuda()
+        for form in FORMS[kind]:
+            S.sbn_force_kernel_form(kind, form)
+            yd = torch.full((n, h, w, N), float("nan"), device="cuda")
+            run(p, xd, yd, n, h, w)
+            y = yd.cpu().numpy()
+            assert not np.isnan(y).any(), form
+            assert (y[:, 4, 5][:, keeps] == 0).all() and (y[:, 4, 5][:, ~keeps] > 0).any(), form
+    finally:
+        S.sbn_force_kernel_form(kind, 0)
+
+
+def test_relu_of_nan_is_zero_in_fused_and_separate_launches():
+    K, N, n, h, w = 64, 64, 1, 9, 11
+    rng = np.random.default_rng(32)
+    wt = (rng.standard_normal((N, 1, 1, K)) * 0.1).astype(np.float32)
+    p = S.sbn_pack(S.SBN_CONV1X1, wt, 4, 4, act=S.SBN_ACT_RELU)
+    chain = S.sbn_chain_create([S.dw_item((rng.standard_normal((K, 3, 3)) * 0.4).astype(np.float32), act=S.SBN_ACT_NONE), S.sparse_item(p)])
+    x = rng.uniform(-1, 1, (n, h, w, K)).astype(np.float32)
+    x[0, 4, 5, 7] = np.nan
+    ws = torch.empty(S.sbn_chain_workspace(chain, n, h, w) // 4, device="cuda")
+    for fused in (1, 0, 2):
+        S.sbn_chain_set_fusion(chain, fused)
+        y = torch.full((n, h, w, N), float("nan"), device="cuda")
+        S.sbn_pointwise_chain(chain, torch.from_numpy(x).cuda(), y, n, h, w, ws)
+        assert not y.isnan().any() and (y[0, 3:6, 4:7] == 0).all(), fused
+
+
 @pytest.mark.parametrize("seed", [21, 22])
 def test_random_depthwise_plus_pointwise_pairs(seed):
     """Random (depthwise 3x3, small 1x1) pairs through the chain: the fused launch and the two separate
