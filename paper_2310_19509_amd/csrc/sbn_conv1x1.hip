@@ -53,7 +53,12 @@ __device__ __forceinline__ float relu(float v)
     asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(v));
     return r;
 }
-__device__ __forceinline__ v4f relu4(v4f v) { return (v4f){relu(v.x), relu(v.y), relu(v.z), relu(v.w)}; }
+// the activation, without a branch: a row's reads and stores stay free to move past one another
+__device__ __forceinline__ v4f activate(v4f v, bool on)
+{
+    const v4f r = {relu(v.x), relu(v.y), relu(v.z), relu(v.w)};
+    return (v4f){on ? r.x : v.x, on ? r.y : v.y, on ? r.z : v.z, on ? r.w : v.w};
+}
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 // Vector instructions share their issue port with the matrix instructions: a plain VALU
@@ -391,7 +396,7 @@ __device__ __forceinline__ void plain_tile(float* __restrict__ lds, float* __res
             const uint32_t off = ch_base + col < N ? ((uint32_t)row * (uint32_t)N + (uint32_t)(ch_base + col)) * 4u : 0xFFFFFFF0u;
             v4f o = *(const v4f*)(lds + row * XS + col);
             if (TWO) o += *(const v4f*)(lds_b + row * XS + col);
-            if (act == SBN_ACT_RELU) o = relu4(o);
+            o = activate(o, act == SBN_ACT_RELU);
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o), yres, (int)off, 0, 2 /* slc: streaming */);
         }
     }
@@ -543,7 +548,7 @@ __device__ __forceinline__ void splitk_tile(float* __restrict__ lds_pool, const 
 #pragma unroll
         for (int s = 1; s < NW; ++s) o += *(const v4f*)(lds_all[s] + row * XS + col);
         o += *(const v4f*)(bias + bundle * 16 + col);
-        if (act == SBN_ACT_RELU) o = relu4(o);
+        o = activate(o, act == SBN_ACT_RELU);
         const long long pix = pix0 + row;
         if (pix < M && bundle * 16 + col < N) *(v4f*)(y + pix * N + bundle * 16 + col) = o;
     }
