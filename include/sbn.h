@@ -317,7 +317,8 @@ int sbn_conv3x3_sparse(const sbn_packed_t* p, const float* x, float* y,
  * later launches of that kind in the process (0 = back to automatic), so that
  * every form can be checked on every shape; results never depend on the form
  * beyond rounding.  kind: SBN_CONV1X1 (forms 11, 12, 14, 21, 22: pixels
- * per lane and accumulator sets; 504, 508, 516: 4, 8, 16 waves splitting the
+ * per lane and accumulator sets; 402, 404: form 12 with two, four slices of
+ * waves that share the input channels; 504, 508, 516: 4, 8, 16 waves splitting the
  * input channels; 112, 121: forms 12 / 21 with the last pixel tiles run as
  * four-wave channel-splitting workgroups inside the same launch; 1012, 1021,
  * 1112, 1121: forms 12, 21, 112, 121 on the every-piece tables of layers that

@@ -26,7 +26,8 @@
 // full rows of 16-byte stores.
 //
 // Forms (launch_conv1x1 picks one per launch): the workgroup form above with 64 or
-// 128 pixels per tile (plain_tile); the few-pixel form, one bundle per workgroup with
+// 128 pixels per tile (plain_tile); the sliced form, a 64-pixel tile whose input channels are shared
+// by slices of four waves; the few-pixel form, one bundle per workgroup with
 // the input channels split over its waves (splitk_tile); the mixed launch, whole
 // rounds of workgroup tiles plus the remaining pixels as few-pixel workgroups in one
 // grid; and, for layers that keep most of their pieces, the walk over the
@@ -568,6 +569,156 @@ __global__ __launch_bounds__(64 * NW) void conv1x1_splitk_kernel(const float* __
     splitk_tile<NW>(lds_pool, x, y, records, woff, wts, bias, M, K, N, n_chunks, pix0, bundle, act);
 }
 
+// Sliced form, between the few-pixel form and launches that fill the chip.  A tile as in the workgroup form (64 pixels x 64
+// output channels, so that staged activations serve four bundles; the split form above reads them once per bundle), but S slices of four waves
+// share its chunks: slice s takes the chunks s, s + S, ..., stages them in its own part of LDS, and the slices' sums meet in LDS at the
+// end, where they are added in 64 bits.  Up to one such workgroup per compute unit the launch is a chain of round trips and of entries, which
+// this shortens: 784 pixels, 90 %, blocks of 8 x 4, 1024 x 1024 16.1 -> 11.7 us (3.1 of them for an empty launch; without the loads 9.4, without
+// the multiplies 10.8), 512 x 1024 10.3 -> 7.9.  Two slices or four: launch_conv1x1.
+// The first two chunks of a slice are asked for at once, and each chunk two of its slice's chunks before it is needed.
+// Entries past a chunk's last one lie outside the weights' buffer and are not fetched.  Needs c_in % 4 == 0.
+template <int S>
+__global__ __launch_bounds__(256 * S, 4) void conv1x1_sliced_kernel(const float* __restrict__ x, float* __restrict__ y,
+                                                                const uint32_t* __restrict__ records,
+                                                                const uint32_t* __restrict__ woff,
+                                                                const float* __restrict__ wts,
+                                                                const float* __restrict__ bias, long long M, int K, int N,
+                                                                int n_bundles, int n_chunks, int n_col_tiles,
+                                                                int n_pix_tiles, int act)
+{
+    constexpr int NB = S == 2 ? 2 : 1;                   // LDS buffers of a slice
+    constexpr int KC = 64, NS = KC / 4, NW = NS / 4, XS = KC + 4, NA = 2, T = 64, NL = 4;
+    __shared__ __attribute__((aligned(16))) float lds_all[S][NB][T * XS];
+
+    int pix_tile, col_tile;
+    xcd_tile(blockIdx.x, n_col_tiles, pix_tile, col_tile);
+    if (pix_tile >= n_pix_tiles) return;
+    const int lane = threadIdx.x & 63;
+    const int slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), tid = threadIdx.x & 255;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const long long pix0 = (long long)pix_tile * T;
+    const int bundle = col_tile * 4 + wave;
+    const bool active = bundle < n_bundles;
+    const int bsafe = active ? bundle : 0;
+
+    v4f acc[1][4][NA];
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int a = 0; a < NA; ++a) acc[0][g][a] = (v4f){0.f, 0.f, 0.f, 0.f};
+
+    // ---- activations (addresses as in the workgroup form); past the last chunk the buffer is empty
+    const int rows_valid = (int)(M - pix0 < T ? M - pix0 : T);
+    const uint32_t tile_bytes = (uint32_t)rows_valid * (uint32_t)K * 4u;
+    const float* xtile = x + pix0 * K;
+    const uint32_t xoff0 = ((uint32_t)(tid >> 4) * (uint32_t)K + (uint32_t)(tid & 15) * 4u) * 4u;
+    auto issue_x = [&](int c, v4f (&r)[NL]) {
+        const bool real = c < n_chunks;
+        const __amdgpu_buffer_rsrc_t xres = make_rsrc(xtile, real ? tile_bytes : 0u);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) r[i] = buf_load(xres, xoff0 + (uint32_t)i * 64u * (uint32_t)K, real ? (uint32_t)c * (KC * 4) : 0u);
+    };
+    auto write_x = [&](float* buf, const v4f (&r)[NL]) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) *(v4f*)(buf + (i * 16 + (tid >> 4)) * XS + (tid & 15) * 4) = r[i];
+    };
+
+    const uint32_t* wo = woff + (size_t)bsafe * (n_chunks + 1);
+    const Record<NS>* recs = (const Record<NS>*)__builtin_assume_aligned(records, 4 * NS) + (size_t)bsafe * n_chunks;
+    auto load_weights = [&](int c, v4f (&w)[NW], Record<NS>& r) {
+        const int cc = c < n_chunks ? c : n_chunks - 1;
+        const uint32_t e0 = __builtin_amdgcn_readfirstlane(wo[cc]), e1 = __builtin_amdgcn_readfirstlane(wo[cc + 1]);
+        const __amdgpu_buffer_rsrc_t wres = make_rsrc(wts, e1 * 256u);
+#pragma unroll
+        for (int q4 = 0; q4 < NW; ++q4) w[q4] = buf_load(wres, (uint32_t)lane * 16u + q4 * 1024u, e0 * 256u);
+        r = recs[cc];
+    };
+
+    auto multiply = [&](const float* buf, const v4f (&w)[NW], const Record<NS>& r) {
+        const char* lds_lane = (const char*)buf + lane * (XS * 4);
+        v4f xa[1], xb[1];
+        auto read_x = [&](uint32_t d, v4f (&xv)[1]) { xv[0] = *(const v4f*)(lds_lane + (d >> 8)); };
+        read_x(r.d[0], xa);
+#define SBN_ENTRY(Q, XC, XN)                                                   \
+    if (__builtin_expect(r.d[Q] == 0, 0)) goto chunk_done;                     \
+    if (Q + 1 < NS) read_x(r.d[(Q + 1) % NS], XN);                             \
+    __builtin_amdgcn_s_waitcnt(0xC07F | ((Q == 0 || Q + 1 >= NS ? 0 : 1) << 8)); \
+    entry_fma<1, NA, Q>(r.d[Q], w[Q / 4], XC, acc);
+        SBN_ENTRY(0, xa, xb)
+        SBN_ENTRY(1, xb, xa)
+        SBN_ENTRY(2, xa, xb)
+        SBN_ENTRY(3, xb, xa)
+        SBN_ENTRY(4, xa, xb)
+        SBN_ENTRY(5, xb, xa)
+        SBN_ENTRY(6, xa, xb)
+        SBN_ENTRY(7, xb, xa)
+        SBN_ENTRY(8, xa, xb)
+        SBN_ENTRY(9, xb, xa)
+        SBN_ENTRY(10, xa, xb)
+        SBN_ENTRY(11, xb, xa)
+        SBN_ENTRY(12, xa, xb)
+        SBN_ENTRY(13, xb, xa)
+        SBN_ENTRY(14, xa, xb)
+        SBN_ENTRY(15, xb, xa)
+#undef SBN_ENTRY
+    chunk_done:;
+    };
+
+    // One of the slice's chunks: its activations, asked for two chunks ago, go to LDS, those of the chunk two ahead are
+    // asked for, and after the multiplies the weights of that chunk too.  (Every slice goes through the same barriers.)
+    auto step = [&](int c, float* buf, v4f (&xr)[NL], v4f (&w)[NW], Record<NS>& r) {
+        if (NB == 1) __syncthreads();                    // the buffer's last chunk has been multiplied
+        write_x(buf, xr);
+        __syncthreads();
+        issue_x(c + 2 * S, xr);
+        // All but the loads of the next chunk and those just issued have arrived (one wait here spares one per group).
+        constexpr int NEW = 2 * NL + NW;
+        __builtin_amdgcn_s_waitcnt((NEW & 15) | ((NEW >> 4) << 14) | (7 << 4) | (15 << 8));
+        if (active && c < n_chunks) multiply(buf, w, r);
+        load_weights(c + 2 * S, w, r);
+    };
+
+    v4f xa[NL], xb[NL], wa[NW], wb[NW];
+    Record<NS> ra, rb;
+    issue_x(slice, xa);
+    load_weights(slice, wa, ra);
+    issue_x(slice + S, xb);
+    load_weights(slice + S, wb, rb);
+    const int n_steps = (n_chunks + S - 1) / S;
+    for (int j = 0; j < n_steps; j += 2) {
+        step(slice + j * S, lds_all[slice][0], xa, wa, ra);
+        if (j + 1 < n_steps) step(slice + (j + 1) * S, lds_all[slice][NB - 1], xb, wb, rb);
+    }
+
+    // ---- the slices' sums meet in LDS
+    __syncthreads();
+    if (active) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) *(v4f*)(lds_all[slice][0] + lane * XS + wave * 16 + g * 4) = acc[0][g][0] + acc[0][g][1];
+    }
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t yres = make_rsrc(y + pix0 * N, (uint32_t)rows_valid * (uint32_t)N * 4u);
+#pragma unroll
+    for (int i = 0; i < 4 / S; ++i) {
+        const int slot = i * (256 * S) + threadIdx.x;
+        const int row = slot / 16, col = (slot % 16) * 4, ch = col_tile * 64 + col;
+        double sum[4] = {0., 0., 0., 0.};
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const v4f v = *(const v4f*)(lds_all[s][0] + row * XS + col);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sum[k] += (double)v[k];
+        }
+        const v4f b = *(const v4f*)(bias + (ch < N ? ch : 0));
+        v4f o;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = (float)(sum[k] + (double)b[k]);
+        o = activate(o, act == SBN_ACT_RELU);
+        const uint32_t off = ch < N ? ((uint32_t)row * (uint32_t)N + (uint32_t)ch) * 4u : 0xFFFFFFF0u;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o), yres, (int)off, 0, 0);
+    }
+}
+
 // Mixed form for launches of a few rounds of workgroups.  A launch of W workgroup tiles on C
 // compute units finishes when the busiest unit does: ceil(W / C) tiles, although the work is
 // only W / C.  Here the first n_plain workgroups (a whole number of tiles per compute unit) run
@@ -725,6 +876,21 @@ int launch_splitk(const sbn_packed* p, const float* x, float* y, long long M, hi
     return SBN_OK;
 }
 
+template <int S>
+int launch_sliced(const sbn_packed* p, const float* x, float* y, long long M, hipStream_t st)
+{
+    const sbn::DeviceLayout& L = p->dev;
+    const long long n_pix_tiles = (M + 63) / 64;
+    const int n_col_tiles = (L.n_bundles + 3) / 4;
+    const long long grid = ((n_pix_tiles + 7) / 8) * 8 * n_col_tiles;
+    if (S * grid > sbn::kMaxGroups256) return sbn::fail(SBN_EINVAL, "too many pixels for one launch (%lld)", M);
+    hipLaunchKernelGGL(conv1x1_sliced_kernel<S>, dim3((unsigned)grid), dim3(256 * S), 0, st, x, y, L.d_records, L.d_woff, L.d_wts,
+                       L.d_bias, M, p->c_in, p->c_out, L.n_bundles, L.n_chunks, n_col_tiles, (int)n_pix_tiles, p->act);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return sbn::fail(SBN_EHIP, "conv1x1 launch: %s", hipGetErrorString(e));
+    return SBN_OK;
+}
+
 template <int P, int NA, int KC, bool MULTI, bool VEC, bool STATIC = false>
 int launch(const sbn_packed* p, const float* x, float* y, long long M, hipStream_t st)
 {
@@ -797,6 +963,25 @@ int launch_chain_tail(const TailArgs& a, unsigned* sync, int cus, void* stream)
     return SBN_OK;
 }
 
+// Sparse layers of at least four chunks whose 64 x 64 tiles leave compute units without one, or with one and little more: 402 or 404 (two
+// slices or four), else 0.  12455 random layers of 100 to 100000 pixels and 128 to 1024 input channels, against the rules without these forms:
+//   up to one tile per compute unit, more than 0.4 + the share kept of one (times faster, with 1024 / 512 / 256 input channels)
+//     share kept 0.05  1.6 1.5 1.3    0.1  1.5 1.4 1.3    0.2  1.2 1.3 1.2    0.3  1.1 1.1 1.2    0.4  1.1 1.1 1.0
+//     below: 0.35 tiles, share 0.2 and 0.4  0.9 and 0.7
+//   1 to 1.75 tiles, shares up to 0.3: 1.1 to 1.2 from 576 input channels on, 1.0 to 1.1 at 512; slower with 256, and from 1.75 tiles on.
+// Four slices take as long as two from seven chunks on, and no sum is then longer than in the split form (784 pixels, error in 1e-8 of split form / two / four:
+// 1024 input channels, 80 %  8.5 / 10.1 / 7.8; 448, 70 %  7.6 / 8.7 / 7.0; 320, 90 %  6.1 / 6.0 / 5.4); more than one tile per compute unit need
+// two slices (four: one workgroup per compute unit at a time), which replace form 12 (1024, 90 %: 7.9 instead of 9.8).
+static int sliced_form(const sbn_packed* p, long long M)
+{
+    if (p->c_in <= 192 || (p->c_out + 63) / 64 * 64 * 3 > p->c_out * 4) return 0;
+    const long long cus = p->dev.cus, pix_tiles = (M + 63) / 64;
+    const double share = 16.0 * (double)p->dev.n_present / ((double)p->c_in * p->c_out);
+    const double tiles = (double)(pix_tiles * ((p->dev.n_bundles + 3) / 4)) / (double)cus;
+    if (tiles <= 1.0) return share <= 0.42 && tiles > 0.4 + share ? (p->c_in > 320 ? 404 : 402) : 0;
+    return p->c_in >= 512 && share <= 0.31 && tiles <= 1.75 && pix_tiles * p->dev.n_bundles > 4 * cus ? 402 : 0;
+}
+
 int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long M, void* stream)
 {
     hipStream_t st = (hipStream_t)stream;
@@ -833,6 +1018,7 @@ int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long M, v
     // keep the launch within about four waves per SIMD and leave every wave at least two
     // sub-chunks (timed on the deep MobileNet layers at batches 1..32)
     if (!force && conv1x1_wide_few(p, M)) return launch_conv1x1_wide(p, x, y, M, 0, stream);
+    if (!force) variant = sliced_form(p, M);
     const int n_sub = p->dev.n_chunks32;
     const long long wg_split = ((M + 63) / 64) * p->dev.n_bundles;
     if (!variant && n_sub >= 8 && wg_split <= 4ll * cus)
@@ -883,6 +1069,8 @@ int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long M, v
     case 14: return launch<1, 4, 64, true, true>(p, x, y, M, st);
     case 21: return launch<2, 1, 32, true, true>(p, x, y, M, st);
     case 22: return launch<2, 2, 32, true, true>(p, x, y, M, st);
+    case 402: return launch_sliced<2>(p, x, y, M, st);
+    case 404: return launch_sliced<4>(p, x, y, M, st);
     case 504: return launch_splitk<4>(p, x, y, M, st);
     case 508: return launch_splitk<8>(p, x, y, M, st);
     case 516: return launch_splitk<16>(p, x, y, M, st);

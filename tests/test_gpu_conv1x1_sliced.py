@@ -1,0 +1,84 @@
+"""The 1x1 form whose workgroups share a tile's input channels between slices of four waves (gpu): edges of tiles, chunks and slices against
+the oracle, which of them the launch rule takes, and non-finite values."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2310_19509_amd as S
+from helpers import assert_within_bound
+from test_gpu_conv1x1 import run_layer
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def forced():
+    yield lambda form: S.sbn_force_kernel_form(S.SBN_CONV1X1, form)
+    S.sbn_force_kernel_form(S.SBN_CONV1X1, 0)
+
+
+@pytest.mark.parametrize("form", [402, 404])
+@pytest.mark.parametrize("m,K,N,go,gi,pct", [
+    (1, 68, 4, 4, 4, 0),               # two chunks: slices without any; one pixel, one group
+    (63, 128, 16, 4, 4, 50),
+    (64, 132, 64, 4, 1, 70),           # the third chunk of one piece
+    (65, 196, 68, 4, 4, 90),           # one pixel and one group in second tiles
+    (130, 256, 72, 8, 4, 95),
+    (200, 324, 120, 8, 2, 50),         # six chunks: slices of two and of one
+    (129, 576, 192, 4, 8, 100),        # nothing kept
+    (70, 1024, 64, 8, 8, 60),
+])
+def test_edges(forced, form, m, K, N, go, gi, pct):
+    wt, b = W.he_weights(8100 + K, N, 1, 1, K), W.small_bias(8101, N) * 20
+    x = W.uniform_activation(8102, (1, 1, m, K))
+    forced(form)
+    y, ref, bound = run_layer(x, wt, go, gi, bias=b, act=S.SBN_ACT_RELU, pct=pct)
+    assert_within_bound(y, ref, bound, f"{form, m, K, N, go, gi, pct}")
+
+
+@pytest.mark.parametrize("form", [402, 404])
+def test_infinities_and_nan_reach_what_keeps_their_block_and_nothing_else(forced, form):
+    m, K, N = 70, 324, 72
+    wt = W.he_weights(8110, N, 1, 1, K)
+    x = W.uniform_activation(8111, (1, 1, m, K))
+    spoilt = x.copy()
+    where = [(0, 0), (5, 63), (30, 64), (63, 200), (64, 323)]
+    for i, (pix, ch) in enumerate(where):
+        spoilt[0, 0, pix, ch] = (np.inf, np.nan, -np.inf)[i % 3]
+    forced(form)
+    y, y2 = run_layer(x, wt, 4, 4, pct=50)[0][0, 0], run_layer(spoilt, wt, 4, 4, pct=50)[0][0, 0]
+    kept = S.sbn_prune_magnitude(wt, S.SBN_CONV1X1, 4, 4, 50).reshape(N // 4, K // 4) != 0
+    reached = np.zeros((m, N), bool)
+    for pix, ch in where:
+        reached[pix] = np.repeat(kept[:, ch // 4], 4)
+    assert reached.any() and not np.isfinite(y2[reached]).any()
+    assert np.array_equal(y[~reached], y2[~reached])
+
+
+@pytest.mark.parametrize("m,K,N,pct,form", [
+    (784, 1024, 1024, 90, 404),        # 0.81 tiles per compute unit
+    (784, 256, 1024, 80, 402),
+    (3136, 512, 512, 90, 402),         # 1.53 tiles
+    (3136, 512, 512, 50, 0),
+    (784, 192, 1024, 90, 0),
+    (4096, 1024, 512, 90, 0),          # 2 tiles
+])
+def test_rule(forced, m, K, N, pct, form):
+    """Counted for 256 compute units: the bits of the forced form, and on the other side of the lines other bits than either."""
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    wt = W.he_weights(8120 + K, N, 1, 1, K)
+    mask = S.sbn_prune_magnitude(wt, S.SBN_CONV1X1, 4, 4, pct)
+    p = S.sbn_pack(S.SBN_CONV1X1, wt, 4, 4, mask=mask)
+    x = torch.from_numpy(W.uniform_activation(8121, (1, 1, m, K))).cuda()
+
+    def run(f):
+        y = torch.full((1, 1, m, N), float("nan"), device="cuda")
+        forced(f)
+        S.sbn_conv1x1_sparse(p, x, y, 1, 1, m)
+        torch.cuda.synchronize()
+        return y
+
+    auto, two, four = run(0), run(402), run(404)
+    assert not torch.equal(two, four)
+    assert [torch.equal(auto, two), torch.equal(auto, four)] == [form == 402, form == 404]
