@@ -4,12 +4,12 @@
 // the early blocks of MobileNet-v1 are bound by HBM traffic, and the intermediate tensor is
 // half of it.)
 //
-// One workgroup = an 8x8 tile of output pixels (one per lane) x ALL output channels: four waves
+// A workgroup walks 8x8 tiles of output pixels (one per lane) x ALL output channels: four waves
 // (64 channels) or eight (128), a wave per bundle, so that the depthwise result of a tile is
-// computed once.  Per sub-chunk of 32 channels:
+// computed once.  As many workgroups as the chip holds; their tiles and sub-chunks of 32 channels are one stream:
 //   1. the depthwise layer's input tile with its halo, (7s+3)^2 pixels x 32 channels, goes
-//      global -> registers -> LDS (zeros outside the image = the padding); the loads are issued
-//      before the previous sub-chunk is multiplied;
+//      global -> registers -> LDS (the buffer's bounds give the zeros of the padding); the loads are issued
+//      one step ahead, across tiles too;
 //   2. every thread computes the depthwise outputs of one or two vertically adjacent pixels x 4
 //      channels (weights and bias of the whole layer sit in LDS) and writes them to the activation tile
 //      X[64 pixels][32 channels] that the 1x1 arithmetic reads.  For a layer with 3:9 pattern
@@ -19,10 +19,15 @@
 //      the body that loads and multiplies only those six taps;
 //   3. the wave walks the bundle's entries of the sub-chunk exactly as the 1x1 kernel does: a
 //      16-byte LDS read per entry, 4 v_mfma_f32_4x4x1 per present group.
+// Results are turned round between four lanes and leave as 64 bytes per pixel, without LDS or a barrier.
+// MobileNet-v1's first three blocks at batch 64, 50 % (us, a workgroup per tile / so): 82 / 73, 81 / 63, 85 / 68.  The workgroup per tile spent half of
+// its vector instructions on tile coordinates (integer divisions) and on padding, and three round trips on the parameters before its first
+// load; vector and matrix instructions now take 41 to 45 us of the issue port, the traffic (309, 309 and 206 MB) 60, 60 and 40 us.
 // Used when the 1x1 layer has at most 128 input and 128 output channels; wider layers are bound by
 // the matrix pipe, not by memory traffic, and keep the two launches.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "sbn_internal.h"
@@ -30,6 +35,7 @@
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 constexpr int TH = 8, TW = 8;          // output tile: 64 pixels, lane = oy * 8 + ox
 constexpr int KC = 32;                 // channels per sub-chunk
@@ -62,19 +68,60 @@ __device__ __forceinline__ void entry_fma(uint32_t m, const v4f& w, const v4f& x
     if (__builtin_expect((m & 8u) != 0, 1)) group_fma<Q, 3>(w, xv, acc);
 }
 
+// One instruction; NaN becomes 0.
+__device__ __forceinline__ float relu(float v)
+{
+    float r;
+    asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+__device__ __forceinline__ v4f relu4(v4f v) { return (v4f){relu(v.x), relu(v.y), relu(v.z), relu(v.w)}; }
+
+constexpr uint32_t kOutside = 0x80000000u;             // offset past the end of every buffer here
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+
 struct Record8 {
     uint32_t d[8];
 };
 
+// Four lanes' v[0 .. 3] turned round among them: lane q of a quad then holds in v[k] what lane k held in v[q].
+__device__ __forceinline__ void turn_quad(v4f (&v)[4], int lane)
+{
+    auto step = [&](auto ctrl_c, int bit, v4f& lo, v4f& hi) {          // lo stays where the bit is clear, hi where it is set
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float a = lo[i], b = hi[i];
+            const float a_of = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, a), decltype(ctrl_c)::value, 0xF, 0xF, true));
+            const float b_of = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, b), decltype(ctrl_c)::value, 0xF, 0xF, true));
+            lo[i] = lane & bit ? b_of : a;
+            hi[i] = lane & bit ? b : a_of;
+        }
+    };
+    constexpr std::integral_constant<int, 0xB1> by1{};                 // quad_perm [1, 0, 3, 2]
+    constexpr std::integral_constant<int, 0x4E> by2{};                 // quad_perm [2, 3, 0, 1]
+    step(by1, 1, v[0], v[1]);
+    step(by1, 1, v[2], v[3]);
+    step(by2, 2, v[0], v[2]);
+    step(by2, 2, v[1], v[3]);
+}
+
+// Waves per SIMD that the registers leave room for, and with that the workgroups of a compute unit.  (One more wave per SIMD, 96 registers: the forms of
+// four waves and of stride 2 spill, 73 -> 173 and 63 -> 79 us; the other 68 either way.)
+constexpr int waves_per_simd(int stride, int nwv) { return stride == 2 && nwv == 4 ? 2 : 4; }
+
 template <int STRIDE, int NWV, bool PAT>
-__global__ __launch_bounds__(64 * NWV) void dwpw_kernel(const float* __restrict__ x, float* __restrict__ y,
+__global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV)) void dwpw_kernel(const float* __restrict__ x, float* __restrict__ y,
                                                    const float* __restrict__ dw_w, const float* __restrict__ dw_b,
                                                    const uint32_t* __restrict__ dw_taps, int dw_act,
                                                    const uint32_t* __restrict__ records,
                                                    const uint32_t* __restrict__ woff, const float* __restrict__ wts,
                                                    const float* __restrict__ bias, int H, int W, int OH, int OW, int K,
-                                                   int N, int n_bundles, int n_sub, int n_col_tiles, int tiles_x,
-                                                   int tiles_y, int n_pix_tiles, int act)
+                                                   int N, int n_bundles, int n_sub, int tiles_x,
+                                                   int tiles_y, int n_pix_tiles, int step, int step_x, int step_y, int step_n, int act)
 {
     constexpr int IW = (TW - 1) * STRIDE + 3, IH = (TH - 1) * STRIDE + 3;     // input tile
     constexpr int NPIX = IW * IH;
@@ -82,66 +129,79 @@ __global__ __launch_bounds__(64 * NWV) void dwpw_kernel(const float* __restrict_
     constexpr int NSLOT = NPIX * (KC / 4);
     constexpr int NT = 64 * NWV;                               // threads
     constexpr int NL = (NSLOT + NT - 1) / NT;
-    constexpr int OS = 16 * NWV + 4;                           // row stride of the output tile in floats
     constexpr int NO = 8 / NWV;                                // depthwise output pixels per thread
-    constexpr int ABUF = PAT ? 2 * NPIXP * 16 : NPIX * KC, OBUF = 64 * OS;
-    __shared__ __attribute__((aligned(16))) float lds_a[ABUF > OBUF ? ABUF : OBUF];   // input tile [pixel][32], PAT: [16-channel half][pixel][16]; output tile at the end
+    __shared__ __attribute__((aligned(16))) float lds_a[PAT ? 2 * NPIXP * 16 : (NPIX + 1) * KC];   // input tile [pixel][32], PAT: [16-channel half][pixel][16]
     __shared__ __attribute__((aligned(16))) float lds_x[64 * XS];                     // depthwise result
     __shared__ __attribute__((aligned(16))) float lds_p[10 * KMAX];                   // depthwise weights [9][K], bias [K]
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int id = blockIdx.x;
-    const int xcd = id & 7, j = id >> 3;
-    const int pix_tile = (j / n_col_tiles) * 8 + xcd;
-    const int col_tile = j % n_col_tiles;
-    if (pix_tile >= n_pix_tiles) return;
-    const int tx = pix_tile % tiles_x, ty = (pix_tile / tiles_x) % tiles_y;
-    const long long img = pix_tile / (tiles_x * tiles_y);
-    const int oy0 = ty * TH, ox0 = tx * TW;
-    const int iy0 = oy0 * STRIDE - 1, ix0 = ox0 * STRIDE - 1;
-    const int bundle = col_tile * NWV + wave;
+    const int bundle = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = bundle;
     const bool active = bundle < n_bundles;
     const int bsafe = active ? bundle : 0;
 
-    v4f acc[4][2];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) acc[g][0] = acc[g][1] = (v4f){0.f, 0.f, 0.f, 0.f};
+    // ---- the workgroup's tiles: every step-th, in steps of the coordinates
+    struct At {
+        int x, y, n;
+    };
+    auto next = [&](At t) -> At {
+        t.x += step_x;
+        t.y += step_y;
+        t.n += step_n;
+        if (t.x >= tiles_x) {
+            t.x -= tiles_x;
+            ++t.y;
+        }
+        if (t.y >= tiles_y) {
+            t.y -= tiles_y;
+            ++t.n;
+        }
+        return t;
+    };
+    int tile = blockIdx.x;
+    At at = {tile % tiles_x, tile / tiles_x % tiles_y, tile / (tiles_x * tiles_y)};
 
-    // ---- depthwise parameters of the whole layer
-    for (int i = threadIdx.x; i < 9 * K; i += NT) lds_p[i] = dw_w[i];
-    for (int i = threadIdx.x; i < K; i += NT) lds_p[9 * KMAX + i] = dw_b[i];
-
-    // ---- input tile staging: thread t moves 16-byte slots t, t+NT, ...; slot = pixel * 8 + column
-    const float* xi = x + img * H * W * K;
+    // ---- input tile staging: thread t moves 16-byte slots t, t+NT, ...; slot = pixel * 8 + column.  Slots outside the image
+    //      lie outside the buffer and read as zeros.
     const int col4 = (threadIdx.x & 7) * 4;
-    int goff[NL];
-    uint32_t inside = 0;
+    auto slot_pixel = [](int i, int tid) {
+        const int pix = i * (NT / 8) + (tid >> 3);
+        return pix < NPIX ? pix : NPIX - 1;
+    };
+    uint32_t place[NL], off[NL];                             // of the slots: from the tile's corner, from the buffer's start
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-        int pix = i * (NT / 8) + (threadIdx.x >> 3);
-        pix = pix < NPIX ? pix : NPIX - 1;
-        const int iy = iy0 + pix / IW, ix = ix0 + pix % IW;
-        if (iy >= 0 && iy < H && ix >= 0 && ix < W) inside |= 1u << i;
-        goff[i] = (min(max(iy, 0), H - 1) * W + min(max(ix, 0), W - 1)) * K;
+        const int pix = slot_pixel(i, threadIdx.x);
+        place[i] = (uint32_t)(((pix / IW) * W + pix % IW) * K + col4) * 4u;
     }
-    v4f stage_reg[NL];
-    auto issue_a = [&](int sc) {
-        const int ch = sc * KC + col4;                       // K is a multiple of 32: always inside
+    __amdgpu_buffer_rsrc_t xres;
+    auto aim = [&](const At& t) {
+        const int iy0 = t.y * (TH * STRIDE) - 1, ix0 = t.x * (TW * STRIDE) - 1, r0 = max(iy0, 0);
+        xres = make_rsrc(x + ((long long)t.n * H + r0) * W * K, (uint32_t)(min(H - r0, IH) * W * K) * 4u);
+        const uint32_t corner = (uint32_t)(((iy0 - r0) * W + ix0) * K) * 4u;
 #pragma unroll
-        for (int i = 0; i < NL; ++i) stage_reg[i] = *(const v4f*)(xi + goff[i] + ch);
+        for (int i = 0; i < NL; ++i) off[i] = place[i] + corner;
+        if (iy0 < 0 || ix0 < 0 || iy0 + IH > H || ix0 + IW > W) {
+            int tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));                    // (worked out here: kept across the tiles the slots' pixels cost registers)
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                const int pix = slot_pixel(i, tid);
+                const int iy = iy0 + pix / IW, ix = ix0 + pix % IW;
+                if ((uint32_t)iy >= (uint32_t)H || (uint32_t)ix >= (uint32_t)W) off[i] = kOutside;
+            }
+        }
     };
-    auto write_a = [&]() {
+    v4f stage_reg[NL];
+    auto issue_a = [&](int sc) {                             // K is a multiple of 32: always inside
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            stage_reg[i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xres, (int)off[i], sc * (KC * 4), 0));
+    };
+    auto write_a = [&]() {                                   // (slots past the tile go to a pixel behind it: no branch)
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            const int pix = i * (NT / 8) + (threadIdx.x >> 3);
-            const v4f v = (inside >> i) & 1u ? stage_reg[i] : (v4f){0.f, 0.f, 0.f, 0.f};
-            if (pix < NPIX) {
-                if (PAT)
-                    *(v4f*)(lds_a + ((col4 >> 4) * NPIXP + pix) * 16 + (col4 & 15)) = v;
-                else
-                    *(v4f*)(lds_a + pix * KC + col4) = v;
-            }
+            const int pix = min(i * (NT / 8) + (int)(threadIdx.x >> 3), NPIX);
+            *(v4f*)(PAT ? lds_a + ((col4 >> 4) * NPIXP + pix) * 16 + (col4 & 15) : lds_a + pix * KC + col4) = stage_reg[i];
         }
     };
 
@@ -150,9 +210,7 @@ __global__ __launch_bounds__(64 * NWV) void dwpw_kernel(const float* __restrict_
     const int oxp = (threadIdx.x >> 3) & 7, oyp = (threadIdx.x >> 6) * NO;
     auto dw_dense = [&](int sc) {
         const int ch = sc * KC + col4;
-        v4f wt[9];
-#pragma unroll
-        for (int t = 0; t < 9; ++t) wt[t] = *(const v4f*)(lds_p + t * K + ch);
+        const float* wp = lds_p + ch;
         const v4f b = *(const v4f*)(lds_p + 9 * KMAX + ch);
         v4f o[NO];
 #pragma unroll
@@ -168,19 +226,14 @@ __global__ __launch_bounds__(64 * NWV) void dwpw_kernel(const float* __restrict_
                 const int ky = r - jo * STRIDE;
                 if (ky >= 0 && ky < 3) {
 #pragma unroll
-                    for (int kx = 0; kx < 3; ++kx) o[jo] += wt[ky * 3 + kx] * a[kx];
+                    for (int kx = 0; kx < 3; ++kx) o[jo] += *(const v4f*)(wp + (ky * 3 + kx) * KMAX) * a[kx];
                 }
             }
         }
 #pragma unroll
         for (int jo = 0; jo < NO; ++jo) {
             v4f v = o[jo];
-            if (dw_act == SBN_ACT_RELU) {
-                v.x = fmaxf(v.x, 0.f);
-                v.y = fmaxf(v.y, 0.f);
-                v.z = fmaxf(v.z, 0.f);
-                v.w = fmaxf(v.w, 0.f);
-            }
+            if (dw_act == SBN_ACT_RELU) v = relu4(v);
             *(v4f*)(lds_x + ((oyp + jo) * TW + oxp) * XS + col4) = v;
         }
     };
@@ -221,19 +274,14 @@ __global__ __launch_bounds__(64 * NWV) void dwpw_kernel(const float* __restrict_
                 if (ky >= 0 && ky < 3) {
 #pragma unroll
                     for (int kx = 0; kx < 3; ++kx)
-                        if ((TAPS >> (ky * 3 + kx)) & 1u) o[jo] += *(const v4f*)(wp + (ky * 3 + kx) * K) * a[kx];
+                        if ((TAPS >> (ky * 3 + kx)) & 1u) o[jo] += *(const v4f*)(wp + (ky * 3 + kx) * KMAX) * a[kx];
                 }
             }
         }
 #pragma unroll
         for (int jo = 0; jo < NO; ++jo) {
             v4f v = o[jo];
-            if (dw_act == SBN_ACT_RELU) {
-                v.x = fmaxf(v.x, 0.f);
-                v.y = fmaxf(v.y, 0.f);
-                v.z = fmaxf(v.z, 0.f);
-                v.w = fmaxf(v.w, 0.f);
-            }
+            if (dw_act == SBN_ACT_RELU) v = relu4(v);
             *(v4f*)(xo + jo * TW * XS) = v;
         }
     };
@@ -272,7 +320,7 @@ __global__ __launch_bounds__(64 * NWV) void dwpw_kernel(const float* __restrict_
         w[0] = src[0];
         w[1] = src[64];
     };
-    auto multiply = [&](const Record8& r, const v4f (&w)[2]) {
+    auto multiply = [&](const Record8& r, const v4f (&w)[2], v4f (&acc)[4][2]) {
         const char* xl = (const char*)lds_x + lane * (XS * 4);
         v4f xa, xb;
 #define SBN_ENTRY(Q, XC, XN)                                             \
@@ -292,57 +340,94 @@ __global__ __launch_bounds__(64 * NWV) void dwpw_kernel(const float* __restrict_
     sub_chunk_done:;
     };
 
-    v4f w_cur[2], w_nxt[2];
-    Record8 r_cur, r_nxt;
-    issue_a(0);
-    load_weights(0, w_cur);
-    r_cur = recs[0];
-    write_a();
-    __syncthreads();                                   // input tile and depthwise parameters visible
-    dw_compute(0);
-    __syncthreads();
-    for (int sc = 0; sc < n_sub; ++sc) {
-        const bool more = sc + 1 < n_sub;              // uniform over the workgroup
-        const int scn = more ? sc + 1 : sc;
-        issue_a(scn);                                  // in flight while this sub-chunk is multiplied
-        load_weights(scn, w_nxt);
-        r_nxt = recs[scn];
-        if (active) multiply(r_cur, w_cur);
-        if (more) write_a();                           // the input tile was consumed before the multiply
-        __syncthreads();                               // X released, next input tile visible
-        if (more) {
-            dw_compute(sc + 1);
-            __syncthreads();
+    // ---- activation, rows of 64 bytes.  Pixels past the image and channels past c_out lie outside the buffer and are dropped.
+    const uint32_t yplace = bundle * 16 + (lane & 3) * 4 < N
+                                ? (uint32_t)(((lane >> 3) * OW + (lane & 4)) * N + bundle * 16 + (lane & 3) * 4) * 4u
+                                : kOutside;
+    auto finish = [&](const At& t, v4f (&acc)[4][2]) {
+        v4f o[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) o[g] = acc[g][0] + acc[g][1];
+        turn_quad(o, lane);
+        if (act == SBN_ACT_RELU) {                     // (behind the turn: the compiler does not see an asm's write in front of a lane move's read)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] = relu4(o[k]);
         }
-        w_cur[0] = w_nxt[0];
-        w_cur[1] = w_nxt[1];
-        r_cur = r_nxt;
-    }
+        const int oy0 = t.y * TH, ox0 = t.x * TW;
+        const __amdgpu_buffer_rsrc_t yres = make_rsrc(y + ((long long)t.n * OH + oy0) * OW * N, (uint32_t)(min(OH - oy0, TH) * OW * N) * 4u);
+        // (The place within the row goes into the lane's offset: behind a store with a scalar offset the compiler writes
+        // the data's registers again in the next instruction, and the store has then been seen to take the new value.)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t to = ox0 + (lane & 4) + k < OW ? yplace + (uint32_t)((ox0 + k) * N * 4) : kOutside;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o[k]), yres, (int)to, 0, 0);
+        }
+    };
 
-    // ---- epilogue: bias, activation, transpose through LDS (the input tile's memory), 256-byte rows
-    if (active) {
+    aim(at);
+    issue_a(0);
+    // the depthwise layer's parameters, asked for together behind the first input tile
+    {
+        constexpr int NP = (10 * KMAX / 4 + NT - 1) / NT;
+        v4f v[NP];
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int s = i * NT + threadIdx.x, row = s / (KMAX / 4), ch = s % (KMAX / 4) * 4;
+            v[i] = *(const v4f*)(row < 9 ? dw_w + row * K + min(ch, K - 4) : dw_b + min(ch, K - 4));
+        }
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int s = i * NT + threadIdx.x;
+            if (s < 10 * KMAX / 4) *(v4f*)(lds_p + s * 4) = v[i];
+        }
+    }
+    v4f acc[4][2];
+    // (in one place and out of the compiler's sight: it otherwise keeps several sets of them, over 200 registers)
+    auto pin = [&] {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) asm volatile("" : "+a"(acc[g][h]));
+    };
+    auto start = [&] {                                 // the first partial sum of a group starts from the bias
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            v4f o = acc[g][0] + acc[g][1] + *(const v4f*)(bias + bundle * 16 + g * 4);
-            if (act == SBN_ACT_RELU) {
-                o.x = fmaxf(o.x, 0.f);
-                o.y = fmaxf(o.y, 0.f);
-                o.z = fmaxf(o.z, 0.f);
-                o.w = fmaxf(o.w, 0.f);
-            }
-            *(v4f*)(lds_a + lane * OS + wave * 16 + g * 4) = o;
+            acc[g][0] = *(const v4f*)(bias + bsafe * 16 + g * 4);
+            acc[g][1] = (v4f){0.f, 0.f, 0.f, 0.f};
         }
-    }
-    __syncthreads();
-    const int ch_base = col_tile * (16 * NWV);
-    float* yi = y + img * OH * OW * N;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {                      // 64 pixels x 4 * NWV 16-byte columns = 4 * NT slots
-        const int slot = i * NT + threadIdx.x;
-        const int pl = slot / (4 * NWV), col = (slot % (4 * NWV)) * 4;
-        const int oy = oy0 + pl / 8, ox = ox0 + pl % 8;
-        if (oy < OH && ox < OW && ch_base + col < N)
-            *(v4f*)(yi + ((long long)oy * OW + ox) * N + ch_base + col) = *(const v4f*)(lds_a + pl * OS + col);
+        pin();
+    };
+    // A workgroup barrier for LDS alone: memory accesses stay in flight across it.
+    auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    start();
+    int sc = 0;
+    v4f w[2];
+    load_weights(0, w);
+    write_a();
+    for (;;) {
+        barrier();                               // input tile visible (and the parameters); X free
+        const Record8 r = recs[sc];
+        const bool last = sc + 1 == n_sub;
+        const int scn = last ? 0 : sc + 1;
+        const int tile_next = last ? tile + step : tile;
+        const bool again = tile_next < n_pix_tiles;
+        const At at_next = last && again ? next(at) : at;
+        if (last && again) aim(at_next);
+        issue_a(scn);                                  // in flight while this sub-chunk is worked on (behind the last tile unused)
+        dw_compute(sc);
+        barrier();                               // X visible, input tile free
+        if (active) multiply(r, w, acc);
+        pin();
+        load_weights(scn, w);
+        write_a();                                     // (in front of the stores: loads and stores come back in order)
+        if (last) {
+            if (active) finish(at, acc);
+            start();
+        }
+        if (!again) break;
+        tile = tile_next;
+        at = at_next;
+        sc = scn;
     }
 }
 
@@ -354,15 +439,15 @@ int launch(const sbn_packed* p, const float* x, float* y, const float* dw_w, con
     const int oh = (h - 1) / STRIDE + 1, ow = (w - 1) / STRIDE + 1;
     const int tiles_x = (ow + TW - 1) / TW, tiles_y = (oh + TH - 1) / TH;
     const long long n_pix_tiles = (long long)n * tiles_x * tiles_y;
-    const int n_col_tiles = (L.n_bundles + NWV - 1) / NWV;
-    const long long grid = ((n_pix_tiles + 7) / 8) * 8 * n_col_tiles;
+    const long long grid = std::min<long long>(n_pix_tiles, 4ll * waves_per_simd(STRIDE, NWV) / NWV * L.cus);
     if ((long long)h * w * p->c_in > 0x7FFFFFFFll)
         return sbn::fail(SBN_EINVAL, "one image of %d x %d x %d elements is too large for 32-bit offsets", h, w, p->c_in);
-    if (grid > 0x7FFFFFFFll || n_pix_tiles > 0x7FFFFFFFll)
+    if (grid > 0x7FFFFFFFll || n_pix_tiles + grid > 0x7FFFFFFFll)
         return sbn::fail(SBN_EINVAL, "too many output tiles for one launch (%lld)", n_pix_tiles);
     hipLaunchKernelGGL((dwpw_kernel<STRIDE, NWV, PAT>), dim3((unsigned)grid), dim3(64 * NWV), 0, st, x, y, dw_w, dw_b, dw_taps, dw_act, L.d_records32,
-                       L.d_woff32, L.d_wts, L.d_bias, h, w, oh, ow, p->c_in, p->c_out, L.n_bundles, L.n_chunks32, n_col_tiles,
-                       tiles_x, tiles_y, (int)n_pix_tiles, p->act);
+                       L.d_woff32, L.d_wts, L.d_bias, h, w, oh, ow, p->c_in, p->c_out, L.n_bundles, L.n_chunks32,
+                       tiles_x, tiles_y, (int)n_pix_tiles, (int)grid, (int)(grid % tiles_x), (int)(grid / tiles_x % tiles_y),
+                       (int)(grid / tiles_x / tiles_y), p->act);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return sbn::fail(SBN_EHIP, "fused depthwise + 1x1 launch: %s", hipGetErrorString(e));
     return SBN_OK;
@@ -372,22 +457,23 @@ int launch(const sbn_packed* p, const float* x, float* y, const float* dw_w, con
 
 namespace sbn {
 
-bool dwpw_fusable(const sbn_packed* p, int channels, int stride)
+// (a tile's rows have to lie within 32-bit offsets)
+bool dwpw_fusable(const sbn_packed* p, int channels, int stride, int w)
 {
     return p->kind == SBN_CONV1X1 && p->c_in == channels && channels % KC == 0 && channels <= KMAX && p->c_out <= 128 &&
-           (stride == 1 || stride == 2);
+           (stride == 1 || stride == 2) && (2ll * TH + 1) * w * std::max(p->c_in, p->c_out) <= 1ll << 28;
 }
 
 int launch_dwpw(const sbn_packed* p, const float* x, float* y, const float* dw_w, const float* dw_b,
                 const uint32_t* dw_taps, int dw_stride, int dw_act, int n, int h, int w, void* stream)
 {
-    if (!dwpw_fusable(p, p->c_in, dw_stride))
+    if (!dwpw_fusable(p, p->c_in, dw_stride, w))
         return fail(SBN_EINVAL, "internal error: fused depthwise + 1x1 launch for a layer it does not cover");
     hipStream_t st = (hipStream_t)stream;
     const bool wide = p->dev.n_bundles > 4;      // more than 64 output channels: eight waves cover up to 128
 #define SBN_DWPW(S, NWV, PAT) launch<S, NWV, PAT>(p, x, y, dw_w, dw_b, dw_taps, dw_act, n, h, w, st)
     // Pattern bodies everywhere but in the eight-wave stride-2 form: there they need 134 registers,
-    // one workgroup per CU instead of two (109 us against 79 us for MobileNet-v1's second block at
+    // one workgroup per CU instead of two (with a workgroup per tile 109 us against 79 us for MobileNet-v1's second block at
     // batch 64), so that form multiplies the stored zeros of the removed taps instead.
     if (dw_taps && !(wide && dw_stride == 2)) {
         if (wide) return SBN_DWPW(1, 8, true);

@@ -1,0 +1,50 @@
+"""Depthwise + 1x1 pairs in one launch (csrc/sbn_dwpw.hip) where a workgroup walks several tiles: more tiles than workgroups are
+resident, in every form of the kernel (four and eight waves, stride 1 and 2, dense and pattern-pruned), against the oracle's two
+layers.  Tolerance as for the fused pairs in test_gpu_chain.py: the 1x1 layer's, plus the depthwise layer's carried through the weights."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2310_19509_amd as S
+import workloads as W
+from helpers import assert_within_bound
+from oracle import reference as R
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,h,w,K,N,stride,patterned,one_launch", [
+    (66, 33, 31, 32, 64, 1, False, True),        # 1320 tiles, ragged both ways
+    (60, 40, 24, 64, 60, 1, True, True),         # 900 whole tiles, fewer channels than the waves cover
+    (108, 25, 17, 32, 12, 1, True, True),        # 1296 tiles, most of them at a border
+    (35, 33, 31, 96, 128, 1, False, True),
+    (35, 33, 31, 128, 100, 1, True, True),
+    (35, 65, 61, 64, 128, 2, False, True),
+    (35, 66, 62, 32, 64, 2, False, True),
+    (35, 66, 62, 64, 40, 2, True, True),
+    (600, 5, 3, 64, 96, 1, False, True),         # an image smaller than a tile: every step moves to another image
+    (1, 1, 123400, 128, 8, 1, False, False),     # rows past the offsets' range: two launches, whatever the switch says
+])
+def test_tiles_in_a_stream(n, h, w, K, N, stride, patterned, one_launch):
+    seed = 9900 + K + N + stride
+    dw_w, dw_b = W.normal_weights(seed, (K, 3, 3), 0.4), W.small_bias(seed + 1, K) * 10
+    pattern = S.sbn_dw_pattern_select(dw_w, 16) if patterned else None
+    wt, b = W.he_weights(seed + 2, N, 1, 1, K), W.small_bias(seed + 3, N) * 10
+    mask = S.sbn_prune_magnitude(wt, S.SBN_CONV1X1, 4, 4, 50)
+    p = S.sbn_pack(S.SBN_CONV1X1, wt, 4, 4, mask=mask, bias=b, act=S.SBN_ACT_RELU)
+    chain = S.sbn_chain_create([S.dw_item(dw_w, dw_b, stride=stride, act=S.SBN_ACT_RELU, pattern=pattern, go=16), S.sparse_item(p)])
+    if patterned:
+        dw_w = R.dw_pattern_apply(dw_w, pattern, 16)
+    oh, ow, oc = S.sbn_chain_output_shape(chain, n, h, w)
+    x = W.uniform_activation(seed + 5, (n, h, w, K))
+    ws = torch.full((S.sbn_chain_workspace(chain, n, h, w) // 4,), float("nan"), device="cuda")
+    y = torch.full((n, oh, ow, oc), float("nan"), device="cuda")
+    S.sbn_chain_set_fusion(chain, 2)
+    S.sbn_pointwise_chain(chain, torch.from_numpy(x).cuda(), y, n, h, w, ws)
+    torch.cuda.synchronize()
+    assert bool(ws.isnan().all()) == one_launch
+    mid, bound_dw = R.dwconv3x3_nhwc(x, dw_w, dw_b, stride=stride, act=R.ACT_RELU)
+    ref, bound_pw = R.sparse_conv_reference(mid, wt, mask, 4, 4, bias=b, act=R.ACT_RELU)
+    wm = np.abs(R.apply_mask(wt, mask, 4, 4).reshape(N, K).astype(np.float64))
+    bound = bound_pw + (bound_dw.reshape(-1, K) @ wm.T).reshape(bound_pw.shape)
+    assert_within_bound(y.cpu().numpy(), ref, bound, f"{n, h, w, K, N, stride, patterned}")
