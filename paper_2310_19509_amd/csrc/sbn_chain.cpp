@@ -206,7 +206,8 @@ int run_chain(const sbn_chain* c, const float* x, float* y, int n, int h, int w,
         // A depthwise layer in front of a small 1x1 layer runs inside that layer's launch (its
         // output never exists in memory), unless the caller asked for a copy of it.
         if (c->fuse_dw && it.item == SBN_ITEM_DW3X3 && i + 1 < c->items.size() &&
-            c->items[i + 1].item == SBN_ITEM_SPARSE && dwpw_fusable(c->items[i + 1].packed, it.channels, it.stride, s.w) &&
+            c->items[i + 1].item == SBN_ITEM_SPARSE && dwpw_fusable(c->items[i + 1].packed, it.channels, it.stride) &&
+            dwpw_rows_fit(c->items[i + 1].packed, s.w) &&
             !(layer_outputs && layer_outputs[i]) && (c->fuse_dw == 2 || dwpw_pays(c->items[i + 1].packed, next_shape(it, s)))) {
             const sbn_chain::Item& pw = c->items[i + 1];
             const bool last2 = i + 2 == c->items.size();

@@ -457,17 +457,16 @@ int launch(const sbn_packed* p, const float* x, float* y, const float* dw_w, con
 
 namespace sbn {
 
-// (a tile's rows have to lie within 32-bit offsets)
-bool dwpw_fusable(const sbn_packed* p, int channels, int stride, int w)
+bool dwpw_fusable(const sbn_packed* p, int channels, int stride)
 {
     return p->kind == SBN_CONV1X1 && p->c_in == channels && channels % KC == 0 && channels <= KMAX && p->c_out <= 128 &&
-           (stride == 1 || stride == 2) && (2ll * TH + 1) * w * std::max(p->c_in, p->c_out) <= 1ll << 28;
+           (stride == 1 || stride == 2);
 }
 
 int launch_dwpw(const sbn_packed* p, const float* x, float* y, const float* dw_w, const float* dw_b,
                 const uint32_t* dw_taps, int dw_stride, int dw_act, int n, int h, int w, void* stream)
 {
-    if (!dwpw_fusable(p, p->c_in, dw_stride, w))
+    if (!dwpw_fusable(p, p->c_in, dw_stride) || !dwpw_rows_fit(p, w))
         return fail(SBN_EINVAL, "internal error: fused depthwise + 1x1 launch for a layer it does not cover");
     hipStream_t st = (hipStream_t)stream;
     const bool wide = p->dev.n_bundles > 4;      // more than 64 output channels: eight waves cover up to 128

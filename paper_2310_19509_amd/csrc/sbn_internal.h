@@ -158,7 +158,9 @@ int launch_dw3x3(const float* x, float* y, const float* w_dev, const float* b_de
 int launch_stem3x3(const float* x, float* y, const float* w_dev, const float* b_dev, int n, int h, int w, int c_in,
                    int c_out, int stride, int act, void* stream);
 // depthwise 3x3 fused into the 1x1 layer that consumes it (small layers only: see dwpw_fusable)
-bool dwpw_fusable(const sbn_packed* p, int channels, int stride, int w);
+bool dwpw_fusable(const sbn_packed* p, int channels, int stride);
+// a tile's 17 rows of the wider side have to lie within 2^30 bytes (its 32-bit offsets)
+inline bool dwpw_rows_fit(const sbn_packed* p, int w) { return 17ll * w * (p->c_in > p->c_out ? p->c_in : p->c_out) <= 1ll << 28; }
 // dw_taps: NULL, or per 16 channels (in running order) the 9-bit mask of the taps the group keeps
 int launch_dwpw(const sbn_packed* p, const float* x, float* y, const float* dw_w, const float* dw_b,
                 const uint32_t* dw_taps, int dw_stride, int dw_act, int n, int h, int w, void* stream);
