@@ -19,10 +19,14 @@
 //      the body that loads and multiplies only those six taps;
 //   3. the wave walks the bundle's entries of the sub-chunk exactly as the 1x1 kernel does: a
 //      16-byte LDS read per entry, 4 v_mfma_f32_4x4x1 per present group.
+// With a stem in front (STEM) step 1 works out the 10x10 pixels of the stem's output under a tile instead: each wave 16 of the 32
+// channels of 64 pixels, 108 multiplies, from inputs that its lanes loaded a tile ahead.
 // Results are turned round between four lanes and leave as 64 bytes per pixel, without LDS or a barrier.
 // MobileNet-v1's first three blocks at batch 64, 50 % (us, a workgroup per tile / so): 82 / 73, 81 / 63, 85 / 68.  The workgroup per tile spent half of
 // its vector instructions on tile coordinates (integer divisions) and on padding, and three round trips on the parameters before its first
 // load; vector and matrix instructions now take 41 to 45 us of the issue port, the traffic (309, 309 and 206 MB) 60, 60 and 40 us.
+// The stem in front of the first: 36 + 74 us and 515 MB in two launches, 96 and 244 MB in one (3456 of 5500 matrix cycles per tile are the stem's: 28 % of
+// the lanes of its 100 pixels idle, and 1.56 of them per pixel of the tile; instructions take 61 us of the issue port).
 // Used when the 1x1 layer has at most 128 input and 128 output channels; wider layers are bound by
 // the matrix pipe, not by memory traffic, and keep the two launches.
 #include <hip/hip_runtime.h>
@@ -35,6 +39,7 @@
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v3f __attribute__((ext_vector_type(3)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 constexpr int TH = 8, TW = 8;          // output tile: 64 pixels, lane = oy * 8 + ox
@@ -88,6 +93,24 @@ struct Record8 {
     uint32_t d[8];
 };
 
+// A stem in front (3 -> 32 channels, 3x3, stride 2): x is then its input, and every tile's 10 x 10 pixels of its output are worked out where
+// the others are loaded.  w [9][3][32], b [32]; h, w_in: extents of its input.
+struct StemArgs {
+    const float* w;
+    const float* b;
+    int h, w_in, act;
+};
+
+// Pair P = (input k, group g of 4 channels) of 16 channels: its weights lie in block P % 16 of register P / 16
+template <int P>
+__device__ __forceinline__ void stem_pairs(const float (&wreg)[7], const float (&xin)[27], v4f (&acc)[4])
+{
+    if constexpr (P < 27 * 4) {
+        acc[P % 4] = mfma_bcast<P % 16>(wreg[P / 16], xin[P / 4], acc[P % 4]);
+        stem_pairs<P + 1>(wreg, xin, acc);
+    }
+}
+
 // Four lanes' v[0 .. 3] turned round among them: lane q of a quad then holds in v[k] what lane k held in v[q].
 __device__ __forceinline__ void turn_quad(v4f (&v)[4], int lane)
 {
@@ -110,27 +133,30 @@ __device__ __forceinline__ void turn_quad(v4f (&v)[4], int lane)
 }
 
 // Waves per SIMD that the registers leave room for, and with that the workgroups of a compute unit.  (One more wave per SIMD, 96 registers: the forms of
-// four waves and of stride 2 spill, 73 -> 173 and 63 -> 79 us; the other 68 either way.)
-constexpr int waves_per_simd(int stride, int nwv) { return stride == 2 && nwv == 4 ? 2 : 4; }
+// four waves and of stride 2 spill, 73 -> 173 and 63 -> 79 us; the other 68 either way; with the stem 96 -> 120.)
+constexpr int waves_per_simd(int stride, int nwv, bool stem) { return stem ? 3 : stride == 2 && nwv == 4 ? 2 : 4; }
 
-template <int STRIDE, int NWV, bool PAT>
-__global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV)) void dwpw_kernel(const float* __restrict__ x, float* __restrict__ y,
+template <int STRIDE, int NWV, bool PAT, bool STEM>
+__global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM)) void dwpw_kernel(const float* __restrict__ x, float* __restrict__ y,
                                                    const float* __restrict__ dw_w, const float* __restrict__ dw_b,
                                                    const uint32_t* __restrict__ dw_taps, int dw_act,
                                                    const uint32_t* __restrict__ records,
                                                    const uint32_t* __restrict__ woff, const float* __restrict__ wts,
                                                    const float* __restrict__ bias, int H, int W, int OH, int OW, int K,
                                                    int N, int n_bundles, int n_sub, int tiles_x,
-                                                   int tiles_y, int n_pix_tiles, int step, int step_x, int step_y, int step_n, int act)
+                                                   int tiles_y, int n_pix_tiles, int step, int step_x, int step_y, int step_n, int act,
+                                                   StemArgs stem)
 {
+    static_assert(!STEM || (STRIDE == 1 && NWV == 4), "the stem joins the form of four waves and stride 1");
     constexpr int IW = (TW - 1) * STRIDE + 3, IH = (TH - 1) * STRIDE + 3;     // input tile
     constexpr int NPIX = IW * IH;
     constexpr int NPIXP = NPIX + (6 - NPIX % 4) % 4;           // = 2 mod 4: the two halves of a pixel pair fill all banks
     constexpr int NSLOT = NPIX * (KC / 4);
     constexpr int NT = 64 * NWV;                               // threads
     constexpr int NL = (NSLOT + NT - 1) / NT;
+    constexpr int AS = STEM ? KC + 4 : KC;                     // row stride of the input tile (STEM: a lane writes a pixel)
     constexpr int NO = 8 / NWV;                                // depthwise output pixels per thread
-    __shared__ __attribute__((aligned(16))) float lds_a[PAT ? 2 * NPIXP * 16 : (NPIX + 1) * KC];   // input tile [pixel][32], PAT: [16-channel half][pixel][16]
+    __shared__ __attribute__((aligned(16))) float lds_a[PAT ? 2 * NPIXP * 16 : (NPIX + 1) * AS];   // input tile [pixel][32], PAT: [16-channel half][pixel][16]
     __shared__ __attribute__((aligned(16))) float lds_x[64 * XS];                     // depthwise result
     __shared__ __attribute__((aligned(16))) float lds_p[10 * KMAX];                   // depthwise weights [9][K], bias [K]
 
@@ -167,19 +193,43 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV)) void dwpw_ke
         const int pix = i * (NT / 8) + (tid >> 3);
         return pix < NPIX ? pix : NPIX - 1;
     };
-    uint32_t place[NL], off[NL];                             // of the slots: from the tile's corner, from the buffer's start
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        const int pix = slot_pixel(i, threadIdx.x);
-        place[i] = (uint32_t)(((pix / IW) * W + pix % IW) * K + col4) * 4u;
-    }
+    // STEM: a wave works out 16 channels of 64 of the tile's 100 pixels, a lane per pixel: its 3 x 3 x 3 inputs are loaded where
+    // the others load the tile, pixel by pixel (those outside the input lie outside the buffer).
+    const int spix = (bundle & 1) * 64 + lane, shalf = bundle >> 1;
+    const int spy = min(spix, NPIX - 1) / IW, spx = min(spix, NPIX - 1) % IW;
     __amdgpu_buffer_rsrc_t xres;
+    constexpr int NPLACE = STEM ? 1 : NL, NOFF = STEM ? 9 : NL;
+    uint32_t place[NPLACE], off[NOFF];                       // of the slots: from the tile's corner, from the buffer's start
+    if constexpr (STEM) {
+        place[0] = (uint32_t)(spy * 2 * stem.w_in + spx * 2) * 12u;
+    } else {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int pix = slot_pixel(i, threadIdx.x);
+            place[i] = (uint32_t)(((pix / IW) * W + pix % IW) * K + col4) * 4u;
+        }
+    }
     auto aim = [&](const At& t) {
+        if constexpr (STEM) {
+            const int iy0 = t.y * (2 * TH) - 3, ix0 = t.x * (2 * TW) - 3, r0 = max(iy0, 0);
+            xres = make_rsrc(x + ((long long)t.n * stem.h + r0) * stem.w_in * 3, (uint32_t)(min(stem.h - r0, 2 * IH + 1) * stem.w_in) * 12u);
+            const uint32_t first = place[0] + (uint32_t)((iy0 - r0) * stem.w_in + ix0) * 12u;
+            const bool border = iy0 < 0 || ix0 < 0 || iy0 + 2 * IH + 1 > stem.h || ix0 + 2 * IW + 1 > stem.w_in;
+#pragma unroll
+            for (int k = 0; k < 9; ++k) off[k] = first + (uint32_t)(k / 3 * stem.w_in + k % 3) * 12u;
+            if (border) {
+                const int iy = iy0 + 2 * spy, ix = ix0 + 2 * spx;
+#pragma unroll
+                for (int k = 0; k < 9; ++k)
+                    if ((uint32_t)(iy + k / 3) >= (uint32_t)stem.h || (uint32_t)(ix + k % 3) >= (uint32_t)stem.w_in) off[k] = kOutside;
+            }
+            return;
+        }
         const int iy0 = t.y * (TH * STRIDE) - 1, ix0 = t.x * (TW * STRIDE) - 1, r0 = max(iy0, 0);
         xres = make_rsrc(x + ((long long)t.n * H + r0) * W * K, (uint32_t)(min(H - r0, IH) * W * K) * 4u);
         const uint32_t corner = (uint32_t)(((iy0 - r0) * W + ix0) * K) * 4u;
 #pragma unroll
-        for (int i = 0; i < NL; ++i) off[i] = place[i] + corner;
+        for (int i = 0; i < NL; ++i) off[i] = place[STEM ? 0 : i] + corner;
         if (iy0 < 0 || ix0 < 0 || iy0 + IH > H || ix0 + IW > W) {
             int tid = threadIdx.x;
             asm volatile("" : "+v"(tid));                    // (worked out here: kept across the tiles the slots' pixels cost registers)
@@ -191,17 +241,51 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV)) void dwpw_ke
             }
         }
     };
+    float xin[STEM ? 27 : 1], swreg[STEM ? 7 : 1];
+    if constexpr (STEM) {
+#pragma unroll
+        for (int i = 0; i < 7; ++i) {
+            const int e = min(i * 64 + lane, 27 * 16 - 1);    // [input][16 channels]
+            swreg[i] = stem.w[(e >> 4) * 32 + shalf * 16 + (e & 15)];
+        }
+    }
     v4f stage_reg[NL];
     auto issue_a = [&](int sc) {                             // K is a multiple of 32: always inside
+        if constexpr (STEM) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) {
+                const v3f v = __builtin_bit_cast(v3f, __builtin_amdgcn_raw_buffer_load_b96(xres, (int)off[k], 0, 0));
+                xin[k * 3] = v.x;
+                xin[k * 3 + 1] = v.y;
+                xin[k * 3 + 2] = v.z;
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < NL; ++i)
             stage_reg[i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xres, (int)off[i], sc * (KC * 4), 0));
     };
-    auto write_a = [&]() {                                   // (slots past the tile go to a pixel behind it: no branch)
+    auto write_a = [&](const At& t) {                        // (slots past the tile go to a pixel behind it: no branch)
+        if constexpr (STEM) {
+            v4f o[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) o[g] = *(const v4f*)(stem.b + shalf * 16 + g * 4);
+            stem_pairs<0>(swreg, xin, o);
+            const int sy = t.y * TH - 1 + spy, sx = t.x * TW - 1 + spx, pix = min(spix, NPIX);
+            const bool real = (uint32_t)sy < (uint32_t)H && (uint32_t)sx < (uint32_t)W;      // (outside: the depthwise layer's padding)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[g][i] = real ? o[g][i] : 0.f;
+                if (stem.act == SBN_ACT_RELU) o[g] = relu4(o[g]);
+                *(v4f*)(PAT ? lds_a + (shalf * NPIXP + pix) * 16 + g * 4 : lds_a + pix * AS + shalf * 16 + g * 4) = o[g];
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
             const int pix = min(i * (NT / 8) + (int)(threadIdx.x >> 3), NPIX);
-            *(v4f*)(PAT ? lds_a + ((col4 >> 4) * NPIXP + pix) * 16 + (col4 & 15) : lds_a + pix * KC + col4) = stage_reg[i];
+            *(v4f*)(PAT ? lds_a + ((col4 >> 4) * NPIXP + pix) * 16 + (col4 & 15) : lds_a + pix * AS + col4) = stage_reg[i];
         }
     };
 
@@ -215,12 +299,12 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV)) void dwpw_ke
         v4f o[NO];
 #pragma unroll
         for (int jo = 0; jo < NO; ++jo) o[jo] = b;
-        const float* a0 = lds_a + ((oyp * STRIDE) * IW + oxp * STRIDE) * KC + col4;
+        const float* a0 = lds_a + ((oyp * STRIDE) * IW + oxp * STRIDE) * AS + col4;
 #pragma unroll
         for (int r = 0; r < (NO - 1) * STRIDE + 3; ++r) {
             v4f a[3];
 #pragma unroll
-            for (int kx = 0; kx < 3; ++kx) a[kx] = *(const v4f*)(a0 + (r * IW + kx) * KC);
+            for (int kx = 0; kx < 3; ++kx) a[kx] = *(const v4f*)(a0 + (r * IW + kx) * AS);
 #pragma unroll
             for (int jo = 0; jo < NO; ++jo) {
                 const int ky = r - jo * STRIDE;
@@ -387,7 +471,10 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV)) void dwpw_ke
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) asm volatile("" : "+a"(acc[g][h]));
+            for (int h = 0; h < 2; ++h) {
+                if constexpr (STEM) asm volatile("" : "+v"(acc[g][h]));
+                else asm volatile("" : "+a"(acc[g][h]));
+            }
     };
     auto start = [&] {                                 // the first partial sum of a group starts from the bias
 #pragma unroll
@@ -403,7 +490,7 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV)) void dwpw_ke
     int sc = 0;
     v4f w[2];
     load_weights(0, w);
-    write_a();
+    write_a(at);
     for (;;) {
         barrier();                               // input tile visible (and the parameters); X free
         const Record8 r = recs[sc];
@@ -419,7 +506,7 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV)) void dwpw_ke
         if (active) multiply(r, w, acc);
         pin();
         load_weights(scn, w);
-        write_a();                                     // (in front of the stores: loads and stores come back in order)
+        write_a(at_next);                              // (in front of the stores: loads and stores come back in order)
         if (last) {
             if (active) finish(at, acc);
             start();
@@ -431,23 +518,23 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV)) void dwpw_ke
     }
 }
 
-template <int STRIDE, int NWV, bool PAT>
+template <int STRIDE, int NWV, bool PAT, bool STEM = false>
 int launch(const sbn_packed* p, const float* x, float* y, const float* dw_w, const float* dw_b, const uint32_t* dw_taps,
-           int dw_act, int n, int h, int w, hipStream_t st)
+           int dw_act, int n, int h, int w, hipStream_t st, const StemArgs& stem = {})
 {
     const sbn::DeviceLayout& L = p->dev;
     const int oh = (h - 1) / STRIDE + 1, ow = (w - 1) / STRIDE + 1;
     const int tiles_x = (ow + TW - 1) / TW, tiles_y = (oh + TH - 1) / TH;
     const long long n_pix_tiles = (long long)n * tiles_x * tiles_y;
-    const long long grid = std::min<long long>(n_pix_tiles, 4ll * waves_per_simd(STRIDE, NWV) / NWV * L.cus);
+    const long long grid = std::min<long long>(n_pix_tiles, 4ll * waves_per_simd(STRIDE, NWV, STEM) / NWV * L.cus);
     if ((long long)h * w * p->c_in > 0x7FFFFFFFll)
         return sbn::fail(SBN_EINVAL, "one image of %d x %d x %d elements is too large for 32-bit offsets", h, w, p->c_in);
     if (grid > 0x7FFFFFFFll || n_pix_tiles + grid > 0x7FFFFFFFll)
         return sbn::fail(SBN_EINVAL, "too many output tiles for one launch (%lld)", n_pix_tiles);
-    hipLaunchKernelGGL((dwpw_kernel<STRIDE, NWV, PAT>), dim3((unsigned)grid), dim3(64 * NWV), 0, st, x, y, dw_w, dw_b, dw_taps, dw_act, L.d_records32,
+    hipLaunchKernelGGL((dwpw_kernel<STRIDE, NWV, PAT, STEM>), dim3((unsigned)grid), dim3(64 * NWV), 0, st, x, y, dw_w, dw_b, dw_taps, dw_act, L.d_records32,
                        L.d_woff32, L.d_wts, L.d_bias, h, w, oh, ow, p->c_in, p->c_out, L.n_bundles, L.n_chunks32,
                        tiles_x, tiles_y, (int)n_pix_tiles, (int)grid, (int)(grid % tiles_x), (int)(grid / tiles_x % tiles_y),
-                       (int)(grid / tiles_x / tiles_y), p->act);
+                       (int)(grid / tiles_x / tiles_y), p->act, stem);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return sbn::fail(SBN_EHIP, "fused depthwise + 1x1 launch: %s", hipGetErrorString(e));
     return SBN_OK;
@@ -481,6 +568,23 @@ int launch_dwpw(const sbn_packed* p, const float* x, float* y, const float* dw_w
     if (wide) return dw_stride == 2 ? SBN_DWPW(2, 8, false) : SBN_DWPW(1, 8, false);
     return dw_stride == 2 ? SBN_DWPW(2, 4, false) : SBN_DWPW(1, 4, false);
 #undef SBN_DWPW
+}
+
+bool stem_dwpw_fusable(const sbn_packed* p, int c_in, int c_out, int stride, int dw_stride, int w)
+{
+    return c_in == 3 && c_out == 32 && stride == 2 && dw_stride == 1 && dwpw_fusable(p, 32, 1) && p->dev.n_bundles <= 4 &&
+           dwpw_rows_fit(p, w);                   // (w: the stem's input; 21 rows of it, 12 bytes a pixel, are less than 17 of 32 channels)
+}
+
+int launch_stem_dwpw(const sbn_packed* p, const float* x, float* y, const float* stem_w, const float* stem_b, int stem_act, const float* dw_w,
+                     const float* dw_b, const uint32_t* dw_taps, int dw_act, int n, int h, int w, void* stream)
+{
+    if (!stem_dwpw_fusable(p, 3, 32, 2, 1, w)) return fail(SBN_EINVAL, "internal error: fused stem + depthwise + 1x1 launch for a layer it does not cover");
+    const StemArgs stem = {stem_w, stem_b, h, w, stem_act};
+    const int sh = (h - 1) / 2 + 1, sw = (w - 1) / 2 + 1;
+    hipStream_t st = (hipStream_t)stream;
+    return dw_taps ? launch<1, 4, true, true>(p, x, y, dw_w, dw_b, dw_taps, dw_act, n, sh, sw, st, stem)
+                   : launch<1, 4, false, true>(p, x, y, dw_w, dw_b, dw_taps, dw_act, n, sh, sw, st, stem);
 }
 
 }  // namespace sbn

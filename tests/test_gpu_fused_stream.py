@@ -48,3 +48,50 @@ def test_tiles_in_a_stream(n, h, w, K, N, stride, patterned, one_launch):
     wm = np.abs(R.apply_mask(wt, mask, 4, 4).reshape(N, K).astype(np.float64))
     bound = bound_pw + (bound_dw.reshape(-1, K) @ wm.T).reshape(bound_pw.shape)
     assert_within_bound(y.cpu().numpy(), ref, bound, f"{n, h, w, K, N, stride, patterned}")
+
+
+@pytest.mark.parametrize("n,h,w,N,patterned,acts,copies", [
+    (1, 16, 16, 64, False, (1, 1, 1), None),     # one tile, a border on every side
+    (2, 37, 45, 36, False, (1, 0, 0), None),     # odd extents: the last row and column of windows reach past the input
+    (2, 36, 47, 12, True, (0, 1, 1), None),
+    (40, 66, 81, 64, False, (1, 1, 1), None),    # 1200 tiles: several per workgroup
+    (3, 1, 1, 64, True, (1, 1, 1), None),        # one pixel
+    (1, 2, 301, 64, False, (1, 1, 1), None),
+    (2, 37, 45, 36, False, (1, 1, 1), 2),        # a copy of the result is the same launch
+    (2, 37, 45, 36, False, (1, 1, 1), 1),        # of what is never in memory: the stem by itself
+    (2, 37, 45, 36, False, (1, 1, 1), 0),        # ... and the pair as one
+])
+def test_stem_in_the_first_pairs_launch(n, h, w, N, patterned, acts, copies):
+    """A 3 -> 32 channel stem of stride 2, a depthwise layer and a 1x1 layer as one launch against the oracle's three layers; every layer's
+    bound is carried through the weights of those behind it (ReLU between them is 1-Lipschitz)."""
+    K, seed = 32, 9950 + N
+    act = [S.SBN_ACT_RELU if a else S.SBN_ACT_NONE for a in acts]
+    st_w, st_b = W.he_weights(seed, 32, 3, 3, 3), W.small_bias(seed + 1, 32) * 10
+    dw_w, dw_b = W.normal_weights(seed + 2, (K, 3, 3), 0.4), W.small_bias(seed + 3, K) * 10
+    pattern = S.sbn_dw_pattern_select(dw_w, 16) if patterned else None
+    wt, b = W.he_weights(seed + 4, N, 1, 1, K), W.small_bias(seed + 5, N) * 10
+    mask = S.sbn_prune_magnitude(wt, S.SBN_CONV1X1, 4, 4, 50)
+    p = S.sbn_pack(S.SBN_CONV1X1, wt, 4, 4, mask=mask, bias=b, act=act[2])
+    chain = S.sbn_chain_create([S.stem_item(st_w, st_b, stride=2, act=act[0]),
+                                S.dw_item(dw_w, dw_b, act=act[1], pattern=pattern, go=16), S.sparse_item(p)])
+    if patterned:
+        dw_w = R.dw_pattern_apply(dw_w, pattern, 16)
+    oh, ow, oc = S.sbn_chain_output_shape(chain, n, h, w)
+    x = W.uniform_activation(seed + 6, (n, h, w, 3))
+    ws = torch.full((S.sbn_chain_workspace(chain, n, h, w) // 4,), float("nan"), device="cuda")
+    y = torch.full((n, oh, ow, oc), float("nan"), device="cuda")
+    outs = None if copies is None else [torch.full((n, oh, ow, 32 if i < 2 else oc), float("nan"), device="cuda") if i == copies else None
+                                        for i in range(3)]
+    S.sbn_chain_set_fusion(chain, 2)
+    S.sbn_pointwise_chain(chain, torch.from_numpy(x).cuda(), y, n, h, w, ws, **({} if outs is None else {"layer_outputs": outs}))
+    torch.cuda.synchronize()
+    assert bool(ws.isnan().all()) == (copies in (None, 2))
+    stem, b0 = R.conv_nhwc(x, st_w, st_b, stride=2, pad=1, act=acts[0] and R.ACT_RELU or R.ACT_NONE)
+    mid, b1 = R.dwconv3x3_nhwc(stem, dw_w, dw_b, act=acts[1] and R.ACT_RELU or R.ACT_NONE)
+    b1 = b1 + R.dwconv3x3_nhwc(b0.astype(np.float32), np.abs(dw_w), None)[0]
+    ref, bound = R.sparse_conv_reference(mid, wt, mask, 4, 4, bias=b, act=acts[2] and R.ACT_RELU or R.ACT_NONE)
+    wm = np.abs(R.apply_mask(wt, mask, 4, 4).reshape(N, K).astype(np.float64))
+    bound = bound + (b1.reshape(-1, K).astype(np.float64) @ wm.T).reshape(bound.shape)
+    assert_within_bound(y.cpu().numpy(), ref, bound, f"{n, h, w, N, patterned, acts}")
+    if copies == 2:
+        assert torch.equal(outs[2], y)
