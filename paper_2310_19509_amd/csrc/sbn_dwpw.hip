@@ -424,14 +424,14 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM)) void d
     sub_chunk_done:;
     };
 
-    // ---- activation, rows of 64 bytes.  Pixels past the image and channels past c_out lie outside the buffer and are dropped.
+    // ---- bias, activation, rows of 64 bytes.  Pixels past the image and channels past c_out lie outside the buffer and are dropped.
     const uint32_t yplace = bundle * 16 + (lane & 3) * 4 < N
                                 ? (uint32_t)(((lane >> 3) * OW + (lane & 4)) * N + bundle * 16 + (lane & 3) * 4) * 4u
                                 : kOutside;
     auto finish = [&](const At& t, v4f (&acc)[4][2]) {
         v4f o[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) o[g] = acc[g][0] + acc[g][1];
+        for (int g = 0; g < 4; ++g) o[g] = acc[g][0] + acc[g][1] + *(const v4f*)(bias + bundle * 16 + g * 4);
         turn_quad(o, lane);
         if (act == SBN_ACT_RELU) {                     // (behind the turn: the compiler does not see an asm's write in front of a lane move's read)
 #pragma unroll
@@ -476,12 +476,9 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM)) void d
                 else asm volatile("" : "+a"(acc[g][h]));
             }
     };
-    auto start = [&] {                                 // the first partial sum of a group starts from the bias
+    auto start = [&] {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            acc[g][0] = *(const v4f*)(bias + bsafe * 16 + g * 4);
-            acc[g][1] = (v4f){0.f, 0.f, 0.f, 0.f};
-        }
+        for (int g = 0; g < 4; ++g) acc[g][0] = acc[g][1] = (v4f){0.f, 0.f, 0.f, 0.f};
         pin();
     };
     // A workgroup barrier for LDS alone: memory accesses stay in flight across it.
