@@ -22,7 +22,7 @@
 // With a stem in front (STEM) step 1 works out the 10x10 pixels of the stem's output under a tile instead: each wave 16 of the 32
 // channels of 64 pixels, 108 multiplies, from inputs that its lanes loaded a tile ahead.
 // Results are turned round between four lanes and leave as 64 bytes per pixel, without LDS or a barrier.
-// MobileNet-v1's first three blocks at batch 64, 50 % (us, a workgroup per tile / so): 82 / 73, 81 / 63, 85 / 68.  The workgroup per tile spent half of
+// MobileNet-v1's first three blocks at batch 64, 50 % (us, a workgroup per tile / so): 82 / 75, 81 / 60, 85 / 69.  The workgroup per tile spent half of
 // its vector instructions on tile coordinates (integer divisions) and on padding, and three round trips on the parameters before its first
 // load; vector and matrix instructions now take 41 to 45 us of the issue port, the traffic (309, 309 and 206 MB) 60, 60 and 40 us.
 // The stem in front of the first: 36 + 74 us and 515 MB in two launches, 96 and 244 MB in one (3456 of 5500 matrix cycles per tile are the stem's: 28 % of
