@@ -387,10 +387,10 @@ def time_steps(torch, fn, steps, warmup):
 
 def fused_pairs(W, images, cus):
     """The library's rule (include/sbn.h, sbn_chain_set_fusion) for the depthwise layers of MobileNet-v1 that run inside the 1x1
-    layer behind them."""
+    layer behind them; the first, behind the stem, does whatever the size."""
     return [i for i, (d, p) in enumerate(zip(W.MOBILENET_V1_DW, W.MOBILENET_V1_PW))
             if p.c_in % 32 == 0 and p.c_in <= 128 and p.c_out <= 128
-            and images * ((d.hw_out + 7) // 8) ** 2 * 16 > (6 if p.c_in > 64 and p.c_out > 64 else 4) * cus]
+            and (i == 0 or images * ((d.hw_out + 7) // 8) ** 2 * 16 > (6 if p.c_in > 64 and p.c_out > 64 else 4) * cus)]
 
 
 def run_mobilenet(a, torch, S, W):

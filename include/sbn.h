@@ -432,8 +432,8 @@ int sbn_pointwise_chain_static(const sbn_chain_t* c, const float* x, float* y, i
  * for every sixteen where the 1x1 layer has more than 64 channels on both sides;
  * with fewer, two launches spread better.  Results agree with the separate launches up to fp32 summation
  * order inside the depthwise layer.  A dense stem (3 input, 32 output channels, stride 2) as the chain's first item, in
- * front of such a pair of stride 1 with at most 64 output channels, runs inside the same launch by the same rule, unless a
- * copy of its output is requested.  enable = 0 switches this off for the
+ * front of such a pair of stride 1 with at most 64 output channels, runs inside the same launch whatever the size, unless a
+ * copy of its or of the depthwise output is requested.  enable = 0 switches this off for the
  * chain (every item its own launch), 1 is the default, 2 runs every pair that
  * can run so as one launch, whatever its size; a copy of the depthwise output requested
  * through layer_outputs switches it off for that pair.

@@ -203,13 +203,13 @@ int run_chain(const sbn_chain* c, const float* x, float* y, int n, int h, int w,
                 continue;
             }
         }
-        // The usual stem in front of such a pair (below) joins its launch, by the pair's rule: 224 x 224, 1 / 11 (160 x 160) / 64 images 12 / 21 / 110 us
-        // in two launches, 8 / 16 / 96 in one.
+        // The usual stem in front of a pair that can run as one launch (below) makes all three one, whatever the size: alone in a graph, three
+        // launches / one, 64 output channels, 1 tile of 8 x 8 pixels 8.5 / 5.4 us, 16 tiles 9.3 / 5.6, 64 tiles 10.3 / 5.5, 196 tiles 12.9 / 6.0, 588 tiles
+        // 17.5 / 10.2; 64 images of 224 x 224, stem and pair 110 / 96.
         if (c->fuse_dw && i == 0 && it.item == SBN_ITEM_STEM3X3 && c->items.size() > 2 && c->items[1].item == SBN_ITEM_DW3X3 &&
             c->items[2].item == SBN_ITEM_SPARSE && stem_dwpw_fusable &&
             stem_dwpw_fusable(c->items[2].packed, it.channels, it.c_out, it.stride, c->items[1].stride, s.w) &&
-            !(layer_outputs && (layer_outputs[0] || layer_outputs[1])) &&
-            (c->fuse_dw == 2 || dwpw_pays(c->items[2].packed, next_shape(it, s)))) {
+            !(layer_outputs && (layer_outputs[0] || layer_outputs[1]))) {
             const sbn_chain::Item &dw = c->items[1], &pw = c->items[2];
             float* dst = c->items.size() == 3 ? y : buf[which];
             if (int rc = launch_stem_dwpw(pw.packed, src, dst, it.d_w, it.d_b, it.act, dw.d_w, dw.d_b, dw.d_taps, dw.act, (int)s.n, s.h, s.w, stream))

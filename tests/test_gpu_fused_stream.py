@@ -78,11 +78,10 @@ def test_stem_in_the_first_pairs_launch(n, h, w, N, patterned, acts, copies):
         dw_w = R.dw_pattern_apply(dw_w, pattern, 16)
     oh, ow, oc = S.sbn_chain_output_shape(chain, n, h, w)
     x = W.uniform_activation(seed + 6, (n, h, w, 3))
-    ws = torch.full((S.sbn_chain_workspace(chain, n, h, w) // 4,), float("nan"), device="cuda")
+    ws = torch.full((S.sbn_chain_workspace(chain, n, h, w) // 4,), float("nan"), device="cuda")     # (fusion as it is by default: whatever the size)
     y = torch.full((n, oh, ow, oc), float("nan"), device="cuda")
     outs = None if copies is None else [torch.full((n, oh, ow, 32 if i < 2 else oc), float("nan"), device="cuda") if i == copies else None
                                         for i in range(3)]
-    S.sbn_chain_set_fusion(chain, 2)
     S.sbn_pointwise_chain(chain, torch.from_numpy(x).cuda(), y, n, h, w, ws, **({} if outs is None else {"layer_outputs": outs}))
     torch.cuda.synchronize()
     assert bool(ws.isnan().all()) == (copies in (None, 2))
