@@ -134,10 +134,11 @@ __device__ __forceinline__ void turn_quad(v4f (&v)[4], int lane)
 
 // Waves per SIMD that the registers leave room for, and with that the workgroups of a compute unit.  (One more wave per SIMD, 96 registers: the forms of
 // four waves and of stride 2 spill, 73 -> 173 and 63 -> 79 us; the other 68 either way; with the stem 96 -> 120.)
-constexpr int waves_per_simd(int stride, int nwv, bool stem) { return stem ? 3 : stride == 2 && nwv == 4 ? 2 : 4; }
+// Stride 2 with four waves comes with two and, LEAN, with three: launch_dwpw.
+constexpr int waves_per_simd(int stride, int nwv, bool stem, bool lean) { return stem || lean ? 3 : stride == 2 && nwv == 4 ? 2 : 4; }
 
-template <int STRIDE, int NWV, bool PAT, bool STEM>
-__global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM)) void dwpw_kernel(const float* __restrict__ x, float* __restrict__ y,
+template <int STRIDE, int NWV, bool PAT, bool STEM, bool LEAN>
+__global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM, LEAN)) void dwpw_kernel(const float* __restrict__ x, float* __restrict__ y,
                                                    const float* __restrict__ dw_w, const float* __restrict__ dw_b,
                                                    const uint32_t* __restrict__ dw_taps, int dw_act,
                                                    const uint32_t* __restrict__ records,
@@ -148,6 +149,7 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM)) void d
                                                    StemArgs stem)
 {
     static_assert(!STEM || (STRIDE == 1 && NWV == 4), "the stem joins the form of four waves and stride 1");
+    static_assert(!LEAN || (STRIDE == 2 && NWV == 4), "the other forms have one number of waves");
     constexpr int IW = (TW - 1) * STRIDE + 3, IH = (TH - 1) * STRIDE + 3;     // input tile
     constexpr int NPIX = IW * IH;
     constexpr int NPIXP = NPIX + (6 - NPIX % 4) % 4;           // = 2 mod 4: the two halves of a pixel pair fill all banks
@@ -198,11 +200,11 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM)) void d
     const int spix = (bundle & 1) * 64 + lane, shalf = bundle >> 1;
     const int spy = min(spix, NPIX - 1) / IW, spx = min(spix, NPIX - 1) % IW;
     __amdgpu_buffer_rsrc_t xres;
-    constexpr int NPLACE = STEM ? 1 : NL, NOFF = STEM ? 9 : NL;
+    constexpr int NPLACE = STEM || LEAN ? 1 : NL, NOFF = STEM ? 9 : NL;
     uint32_t place[NPLACE], off[NOFF];                       // of the slots: from the tile's corner, from the buffer's start
     if constexpr (STEM) {
         place[0] = (uint32_t)(spy * 2 * stem.w_in + spx * 2) * 12u;
-    } else {
+    } else if constexpr (!LEAN) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
             const int pix = slot_pixel(i, threadIdx.x);
@@ -228,15 +230,19 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM)) void d
         const int iy0 = t.y * (TH * STRIDE) - 1, ix0 = t.x * (TW * STRIDE) - 1, r0 = max(iy0, 0);
         xres = make_rsrc(x + ((long long)t.n * H + r0) * W * K, (uint32_t)(min(H - r0, IH) * W * K) * 4u);
         const uint32_t corner = (uint32_t)(((iy0 - r0) * W + ix0) * K) * 4u;
+        const bool border = iy0 < 0 || ix0 < 0 || iy0 + IH > H || ix0 + IW > W;
+        if constexpr (!LEAN) {
 #pragma unroll
-        for (int i = 0; i < NL; ++i) off[i] = place[STEM ? 0 : i] + corner;
-        if (iy0 < 0 || ix0 < 0 || iy0 + IH > H || ix0 + IW > W) {
+            for (int i = 0; i < NL; ++i) off[i] = place[STEM ? 0 : i] + corner;
+        }
+        if (LEAN || border) {
             int tid = threadIdx.x;
             asm volatile("" : "+v"(tid));                    // (worked out here: kept across the tiles the slots' pixels cost registers)
 #pragma unroll
             for (int i = 0; i < NL; ++i) {
                 const int pix = slot_pixel(i, tid);
                 const int iy = iy0 + pix / IW, ix = ix0 + pix % IW;
+                if constexpr (LEAN) off[i] = (uint32_t)((pix / IW * W + pix % IW) * K + col4) * 4u + corner;
                 if ((uint32_t)iy >= (uint32_t)H || (uint32_t)ix >= (uint32_t)W) off[i] = kOutside;
             }
         }
@@ -472,7 +478,7 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM)) void d
         for (int g = 0; g < 4; ++g)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                if constexpr (STEM) asm volatile("" : "+v"(acc[g][h]));
+                if constexpr (STEM || LEAN) asm volatile("" : "+v"(acc[g][h]));
                 else asm volatile("" : "+a"(acc[g][h]));
             }
     };
@@ -515,7 +521,7 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM)) void d
     }
 }
 
-template <int STRIDE, int NWV, bool PAT, bool STEM = false>
+template <int STRIDE, int NWV, bool PAT, bool STEM = false, bool LEAN = false>
 int launch(const sbn_packed* p, const float* x, float* y, const float* dw_w, const float* dw_b, const uint32_t* dw_taps,
            int dw_act, int n, int h, int w, hipStream_t st, const StemArgs& stem = {})
 {
@@ -523,12 +529,12 @@ int launch(const sbn_packed* p, const float* x, float* y, const float* dw_w, con
     const int oh = (h - 1) / STRIDE + 1, ow = (w - 1) / STRIDE + 1;
     const int tiles_x = (ow + TW - 1) / TW, tiles_y = (oh + TH - 1) / TH;
     const long long n_pix_tiles = (long long)n * tiles_x * tiles_y;
-    const long long grid = std::min<long long>(n_pix_tiles, 4ll * waves_per_simd(STRIDE, NWV, STEM) / NWV * L.cus);
+    const long long grid = std::min<long long>(n_pix_tiles, 4ll * waves_per_simd(STRIDE, NWV, STEM, LEAN) / NWV * L.cus);
     if ((long long)h * w * p->c_in > 0x7FFFFFFFll)
         return sbn::fail(SBN_EINVAL, "one image of %d x %d x %d elements is too large for 32-bit offsets", h, w, p->c_in);
     if (grid > 0x7FFFFFFFll || n_pix_tiles + grid > 0x7FFFFFFFll)
         return sbn::fail(SBN_EINVAL, "too many output tiles for one launch (%lld)", n_pix_tiles);
-    hipLaunchKernelGGL((dwpw_kernel<STRIDE, NWV, PAT, STEM>), dim3((unsigned)grid), dim3(64 * NWV), 0, st, x, y, dw_w, dw_b, dw_taps, dw_act, L.d_records32,
+    hipLaunchKernelGGL((dwpw_kernel<STRIDE, NWV, PAT, STEM, LEAN>), dim3((unsigned)grid), dim3(64 * NWV), 0, st, x, y, dw_w, dw_b, dw_taps, dw_act, L.d_records32,
                        L.d_woff32, L.d_wts, L.d_bias, h, w, oh, ow, p->c_in, p->c_out, L.n_bundles, L.n_chunks32,
                        tiles_x, tiles_y, (int)n_pix_tiles, (int)grid, (int)(grid % tiles_x), (int)(grid / tiles_x % tiles_y),
                        (int)(grid / tiles_x / tiles_y), p->act, stem);
@@ -555,15 +561,25 @@ int launch_dwpw(const sbn_packed* p, const float* x, float* y, const float* dw_w
     hipStream_t st = (hipStream_t)stream;
     const bool wide = p->dev.n_bundles > 4;      // more than 64 output channels: eight waves cover up to 128
 #define SBN_DWPW(S, NWV, PAT) launch<S, NWV, PAT>(p, x, y, dw_w, dw_b, dw_taps, dw_act, n, h, w, st)
+#define SBN_DWPW_LEAN(PAT) launch<2, 4, PAT, false, true>(p, x, y, dw_w, dw_b, dw_taps, dw_act, n, h, w, st)
+    // Four waves, stride 2: three workgroups per compute unit (LEAN: a tile's places in memory are worked out anew at every tile, which spares the
+    // registers) or two.  us, two / three: 576 tiles, 32 x 64 10.6 / 9.2, 560, 64 x 60 14.4 / 12.4, 540, 128 x 24 20.8 / 17.1, 11820, 32 x 32 94 / 76;
+    // two where a unit gets more than four tiles of several sub-chunks: 12168, 64 x 60 162 / 174, 11880, 128 x 52 274 / 280 (4500 random sizes,
+    // two / three, least and median: up to 4 tiles per unit 0.94, 1.06; up to 8 0.89, 1.03; more than 16 0.88, 0.98, with 32 channels 0.89, 1.03).
+    const long long tiles = (long long)n * (((h - 1) / dw_stride + TH) / TH) * (((w - 1) / dw_stride + TW) / TW);
+    const bool lean = p->c_in == KC || tiles <= 4ll * p->dev.cus;
     // Pattern bodies everywhere but in the eight-wave stride-2 form: there they need 134 registers,
     // one workgroup per CU instead of two (with a workgroup per tile 109 us against 79 us for MobileNet-v1's second block at
     // batch 64), so that form multiplies the stored zeros of the removed taps instead.
     if (dw_taps && !(wide && dw_stride == 2)) {
         if (wide) return SBN_DWPW(1, 8, true);
-        return dw_stride == 2 ? SBN_DWPW(2, 4, true) : SBN_DWPW(1, 4, true);
+        if (dw_stride == 2) return lean ? SBN_DWPW_LEAN(true) : SBN_DWPW(2, 4, true);
+        return SBN_DWPW(1, 4, true);
     }
     if (wide) return dw_stride == 2 ? SBN_DWPW(2, 8, false) : SBN_DWPW(1, 8, false);
-    return dw_stride == 2 ? SBN_DWPW(2, 4, false) : SBN_DWPW(1, 4, false);
+    if (dw_stride == 2) return lean ? SBN_DWPW_LEAN(false) : SBN_DWPW(2, 4, false);
+    return SBN_DWPW(1, 4, false);
+#undef SBN_DWPW_LEAN
 #undef SBN_DWPW
 }
 

@@ -13,15 +13,27 @@ from oracle import reference as R
 pytestmark = pytest.mark.gpu
 
 
+def resident(K, N, stride, tiles):
+    """Workgroups that the kernel's form for these sizes keeps on the chip: as many as the waves that a compute unit holds of it allow."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if N > 64:
+        return 2 * cus
+    return (4 if stride == 1 else 3 if K == 32 or tiles <= 4 * cus else 2) * cus
+
+
 @pytest.mark.parametrize("n,h,w,K,N,stride,patterned,one_launch", [
     (66, 33, 31, 32, 64, 1, False, True),        # 1320 tiles, ragged both ways
-    (60, 40, 24, 64, 60, 1, True, True),         # 900 whole tiles, fewer channels than the waves cover
+    (72, 40, 24, 64, 60, 1, True, True),         # 1080 whole tiles of two sub-chunks, fewer channels than the waves cover
+    (72, 33, 23, 96, 36, 1, False, True),        # 1080 of three
     (108, 25, 17, 32, 12, 1, True, True),        # 1296 tiles, most of them at a border
     (35, 33, 31, 96, 128, 1, False, True),
     (35, 33, 31, 128, 100, 1, True, True),
     (35, 65, 61, 64, 128, 2, False, True),
-    (35, 66, 62, 32, 64, 2, False, True),
-    (35, 66, 62, 64, 40, 2, True, True),
+    (60, 66, 62, 32, 64, 2, False, True),        # stride 2, four waves: 1200 tiles, three workgroups per compute unit
+    (45, 65, 61, 64, 40, 2, True, True),         # 900 tiles
+    (45, 66, 62, 96, 8, 2, False, True),
+    (60, 65, 62, 64, 40, 2, True, True),         # 1200 tiles of several sub-chunks: two
+    (60, 66, 61, 96, 64, 2, False, True),
     (600, 5, 3, 64, 96, 1, False, True),         # an image smaller than a tile: every step moves to another image
     (1, 1, 123400, 128, 8, 1, False, False),     # rows past the offsets' range: two launches, whatever the switch says
 ])
@@ -36,6 +48,8 @@ def test_tiles_in_a_stream(n, h, w, K, N, stride, patterned, one_launch):
     if patterned:
         dw_w = R.dw_pattern_apply(dw_w, pattern, 16)
     oh, ow, oc = S.sbn_chain_output_shape(chain, n, h, w)
+    tiles = n * ((oh + 7) // 8) * ((ow + 7) // 8)
+    assert not one_launch or tiles > resident(K, N, stride, tiles), tiles
     x = W.uniform_activation(seed + 5, (n, h, w, K))
     ws = torch.full((S.sbn_chain_workspace(chain, n, h, w) // 4,), float("nan"), device="cuda")
     y = torch.full((n, oh, ow, oc), float("nan"), device="cuda")
