@@ -571,8 +571,8 @@ __global__ __launch_bounds__(64 * NW) void conv1x1_splitk_kernel(const float* __
 
 // Sliced form, between the few-pixel form and launches that fill the chip.  A tile as in the workgroup form (64 pixels x 64
 // output channels, so that staged activations serve four bundles; the split form above reads them once per bundle), but S slices of four waves
-// share its chunks: slice s takes the chunks s, s + S, ..., stages them in its own part of LDS, and the slices' sums meet in LDS at the
-// end, where they are added in 64 bits.  Up to one such workgroup per compute unit the launch is a chain of round trips and of entries, which
+// share its chunks: slice s takes the chunks s, s + S, ..., stages them in its own part of LDS, and the slices' partial sums meet in LDS at
+// the end, all of them as they are, and are added in 64 bits.  Up to one such workgroup per compute unit the launch is a chain of round trips and of entries, which
 // this shortens: 784 pixels, 90 %, blocks of 8 x 4, 1024 x 1024 16.1 -> 11.7 us (3.1 of them for an empty launch; without the loads 9.4, without
 // the multiplies 10.8), 512 x 1024 10.3 -> 7.9.  Two slices or four: launch_conv1x1.
 // The first two chunks of a slice are asked for at once, and each chunk two of its slice's chunks before it is needed.
@@ -586,9 +586,8 @@ __global__ __launch_bounds__(256 * S, 4) void conv1x1_sliced_kernel(const float*
                                                                 int n_bundles, int n_chunks, int n_col_tiles,
                                                                 int n_tiles, int per_xcd, int act)
 {
-    constexpr int NB = S == 2 ? 2 : 1;                   // LDS buffers of a slice
     constexpr int KC = 64, NS = KC / 4, NW = NS / 4, XS = KC + 4, NA = 2, T = 64, NL = 4;
-    __shared__ __attribute__((aligned(16))) float lds_all[S][NB][T * XS];
+    __shared__ __attribute__((aligned(16))) float lds_all[S][2][T * XS];
 
     // Each XCD takes an equal run of the tiles, all column tiles of a pixel tile next to one another.  (Whole pixel tiles per XCD, as xcd_tile deals
     // them, give one XCD 40 of the 180 tiles of 9 x 20, two rounds on its 32 compute units: 526 pixels, 352 x 1288, 70 % 16.6 us.)
@@ -669,7 +668,6 @@ __global__ __launch_bounds__(256 * S, 4) void conv1x1_sliced_kernel(const float*
     // One of the slice's chunks: its activations, asked for two chunks ago, go to LDS, those of the chunk two ahead are
     // asked for, and after the multiplies the weights of that chunk too.  (Every slice goes through the same barriers.)
     auto step = [&](int c, float* buf, v4f (&xr)[NL], v4f (&w)[NW], Record<NS>& r) {
-        if (NB == 1) __syncthreads();                    // the buffer's last chunk has been multiplied
         write_x(buf, xr);
         __syncthreads();
         issue_x(c + 2 * S, xr);
@@ -689,14 +687,16 @@ __global__ __launch_bounds__(256 * S, 4) void conv1x1_sliced_kernel(const float*
     const int n_steps = (n_chunks + S - 1) / S;
     for (int j = 0; j < n_steps; j += 2) {
         step(slice + j * S, lds_all[slice][0], xa, wa, ra);
-        if (j + 1 < n_steps) step(slice + (j + 1) * S, lds_all[slice][NB - 1], xb, wb, rb);
+        if (j + 1 < n_steps) step(slice + (j + 1) * S, lds_all[slice][1], xb, wb, rb);
     }
 
-    // ---- the slices' sums meet in LDS
+    // ---- the slices' partial sums meet in LDS
     __syncthreads();
     if (active) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) *(v4f*)(lds_all[slice][0] + lane * XS + wave * 16 + g * 4) = acc[0][g][0] + acc[0][g][1];
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int a = 0; a < NA; ++a) *(v4f*)(lds_all[slice][a] + lane * XS + wave * 16 + g * 4) = acc[0][g][a];
     }
     __syncthreads();
     const __amdgpu_buffer_rsrc_t yres = make_rsrc(y + pix0 * N, (uint32_t)rows_valid * (uint32_t)N * 4u);
@@ -706,8 +706,8 @@ __global__ __launch_bounds__(256 * S, 4) void conv1x1_sliced_kernel(const float*
         const int row = slot / 16, col = (slot % 16) * 4, ch = col_tile * 64 + col;
         double sum[4] = {0., 0., 0., 0.};
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-            const v4f v = *(const v4f*)(lds_all[s][0] + row * XS + col);
+        for (int s = 0; s < S * NA; ++s) {
+            const v4f v = *(const v4f*)(lds_all[s / NA][s % NA] + row * XS + col);
 #pragma unroll
             for (int k = 0; k < 4; ++k) sum[k] += (double)v[k];
         }
@@ -971,16 +971,24 @@ int launch_chain_tail(const TailArgs& a, unsigned* sync, int cus, void* stream)
 //     share kept 0.05  1.6 1.5 1.3    0.1  1.5 1.4 1.3    0.2  1.2 1.3 1.2    0.3  1.1 1.1 1.2    0.4  1.1 1.1 1.0
 //     below: 0.35 tiles, share 0.2 and 0.4  0.9 and 0.7
 //   1 to 1.75 tiles, shares up to 0.3: 1.1 to 1.2 from 576 input channels on, 1.0 to 1.1 at 512; slower with 256, and from 1.75 tiles on.
-// Four slices take as long as two from seven chunks on, and no sum is then longer than in the split form (784 pixels, error in 1e-8 of split form / two / four:
-// 1024 input channels, 80 %  8.5 / 10.1 / 7.8; 448, 70 %  7.6 / 8.7 / 7.0; 320, 90 %  6.1 / 6.0 / 5.4); more than one tile per compute unit need
-// two slices (four: one workgroup per compute unit at a time), which replace form 12 (1024, 90 %: 7.9 instead of 9.8).
+// Up to one tile per compute unit no layer's error may exceed that of the split form (4, 8 or 16 waves, partial sums added in 32 bits) or of
+// form 12: four slices where the sums are long, two (a channel's way twice as long) up to 256 channels and for sparse layers up to 320, and neither where
+// the split form has eight waves and a wave of four slices would add up twice as much of a long sum.  Greatest of error / error of what it replaces,
+// 6900 random layers that keep up to 42 %: two slices, up to 256 channels 0.98, up to 320 0.97 at 30 % and 1.02 at 40 %; four slices 0.98, against
+// eight waves 0.99 where 360 channels are kept and 1.13 at 720.  More than one tile per compute unit need
+// two slices (four: one workgroup per compute unit at a time), which replace form 12 (0.95; 1024, 90 %: 7.9e-8 instead of 9.8e-8).
 static int sliced_form(const sbn_packed* p, long long M)
 {
     if (p->c_in <= 192 || (p->c_out + 63) / 64 * 64 * 3 > p->c_out * 4) return 0;
     const long long cus = p->dev.cus, pix_tiles = (M + 63) / 64;
     const double share = 16.0 * (double)p->dev.n_present / ((double)p->c_in * p->c_out);
     const double tiles = (double)(pix_tiles * ((p->dev.n_bundles + 3) / 4)) / (double)cus;
-    if (tiles <= 1.0) return share <= 0.42 && tiles > 0.4 + share ? (p->c_in > 320 ? 404 : 402) : 0;
+    if (tiles <= 1.0) {
+        if (share > 0.42 || tiles <= 0.4 + share) return 0;
+        if (p->c_in >= 512 && pix_tiles * p->dev.n_bundles <= 2 * cus && p->c_in * share > 360.) return 0;
+        if (p->c_in > 320) return 404;
+        return p->c_in <= 256 || share <= 0.3 ? 402 : 0;
+    }
     return p->c_in >= 512 && share <= 0.31 && tiles <= 1.75 && pix_tiles * p->dev.n_bundles > 4 * cus ? 402 : 0;
 }
 

@@ -84,6 +84,37 @@ def test_rule(forced, m, K, N, pct, form):
     assert [torch.equal(auto, two), torch.equal(auto, four)] == [form == 402, form == 404]
 
 
+@pytest.mark.parametrize("m,K,N,pct,replaced", [
+    (3508, 200, 208, 99, 12),          # two slices, short sums: what counts is how few additions round
+    (1143, 320, 776, 60, 504),         # long ones for two slices
+    (784, 1024, 1024, 80, 504),        # four slices
+    (3234, 3656, 152, 81, 508),        # where the split form has eight waves
+    (6395, 592, 256, 99, 12),          # more than one tile per compute unit
+    (3136, 1024, 512, 70, 12),
+])
+def test_no_further_from_the_exact_sum_than_the_form_it_replaces(forced, m, K, N, pct, replaced):
+    """The rule's choice against the 32-bit form that would run without it: the same products, and in the sliced form every partial sum is
+    shorter or joins in 64 bits, so the error's norm over all outputs must not be larger."""
+    wt = W.he_weights(8140 + K, N, 1, 1, K)
+    mask = S.sbn_prune_magnitude(wt, S.SBN_CONV1X1, 4, 4, pct)
+    b = W.small_bias(8141, N)
+    p = S.sbn_pack(S.SBN_CONV1X1, wt, 4, 4, mask=mask, bias=b)
+    x = np.maximum(W.uniform_activation(8142, (1, 1, m, K)), 0)
+    xd = torch.from_numpy(x).cuda()
+    kept = wt.reshape(N, K).astype(np.float64) * np.repeat(np.repeat(mask.reshape(N // 4, K // 4) != 0, 4, 0), 4, 1)
+    ref = x[0, 0].astype(np.float64) @ kept.T + b
+
+    def error(form):
+        y = torch.full((1, 1, m, N), float("nan"), device="cuda")
+        forced(form)
+        S.sbn_conv1x1_sparse(p, xd, y, 1, 1, m)
+        torch.cuda.synchronize()
+        return np.linalg.norm(y.cpu().numpy()[0, 0] - ref) / np.linalg.norm(ref)
+
+    chosen, before = error(0), error(replaced)
+    assert chosen <= before, (chosen, before)
+
+
 def test_tiles_are_spread_evenly(forced):
     """180 tiles of 64 x 64 are one round of workgroups of a device of 256 compute units, as 160 are, although 9 pixel tiles do not divide
     among its eight dies (with two rounds on one of them the launch takes 1.8 times as long)."""
