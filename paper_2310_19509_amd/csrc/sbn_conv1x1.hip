@@ -572,7 +572,7 @@ __global__ __launch_bounds__(64 * NW) void conv1x1_splitk_kernel(const float* __
 // Sliced form, between the few-pixel form and launches that fill the chip.  A tile as in the workgroup form (64 pixels x 64
 // output channels, so that staged activations serve four bundles; the split form above reads them once per bundle), but S slices of four waves
 // share its chunks: slice s takes the chunks s, s + S, ..., stages them in its own part of LDS, and the slices' partial sums meet in LDS at
-// the end, all of them as they are, and are added in 64 bits.  Up to one such workgroup per compute unit the launch is a chain of round trips and of entries, which
+// the end and are added in 64 bits (add_pairs: of two slices, each one's two first in 32 bits).  Up to one such workgroup per compute unit the launch is a chain of round trips and of entries, which
 // this shortens: 784 pixels, 90 %, blocks of 8 x 4, 1024 x 1024 16.1 -> 11.7 us (3.1 of them for an empty launch; without the loads 9.4, without
 // the multiplies 10.8), 512 x 1024 10.3 -> 7.9.  Two slices or four: launch_conv1x1.
 // The first two chunks of a slice are asked for at once, and each chunk two of its slice's chunks before it is needed.
@@ -584,7 +584,7 @@ __global__ __launch_bounds__(256 * S, 4) void conv1x1_sliced_kernel(const float*
                                                                 const float* __restrict__ wts,
                                                                 const float* __restrict__ bias, long long M, int K, int N,
                                                                 int n_bundles, int n_chunks, int n_col_tiles,
-                                                                int n_tiles, int per_xcd, int act)
+                                                                int n_tiles, int per_xcd, int add_pairs, int act)
 {
     constexpr int KC = 64, NS = KC / 4, NW = NS / 4, XS = KC + 4, NA = 2, T = 64, NL = 4;
     __shared__ __attribute__((aligned(16))) float lds_all[S][2][T * XS];
@@ -691,12 +691,15 @@ __global__ __launch_bounds__(256 * S, 4) void conv1x1_sliced_kernel(const float*
     }
 
     // ---- the slices' partial sums meet in LDS
+    const bool pairs = S == 2 && add_pairs != 0;
     __syncthreads();
     if (active) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int a = 0; a < NA; ++a) *(v4f*)(lds_all[slice][a] + lane * XS + wave * 16 + g * 4) = acc[0][g][a];
+        for (int g = 0; g < 4; ++g) {
+            const int at = lane * XS + wave * 16 + g * 4;
+            *(v4f*)(lds_all[slice][0] + at) = pairs ? acc[0][g][0] + acc[0][g][1] : acc[0][g][0];
+            if (!pairs) *(v4f*)(lds_all[slice][1] + at) = acc[0][g][1];
+        }
     }
     __syncthreads();
     const __amdgpu_buffer_rsrc_t yres = make_rsrc(y + pix0 * N, (uint32_t)rows_valid * (uint32_t)N * 4u);
@@ -706,10 +709,18 @@ __global__ __launch_bounds__(256 * S, 4) void conv1x1_sliced_kernel(const float*
         const int row = slot / 16, col = (slot % 16) * 4, ch = col_tile * 64 + col;
         double sum[4] = {0., 0., 0., 0.};
 #pragma unroll
-        for (int s = 0; s < S * NA; ++s) {
-            const v4f v = *(const v4f*)(lds_all[s / NA][s % NA] + row * XS + col);
+        for (int s = 0; s < S; ++s) {
+            const v4f v = *(const v4f*)(lds_all[s][0] + row * XS + col);
 #pragma unroll
             for (int k = 0; k < 4; ++k) sum[k] += (double)v[k];
+        }
+        if (!pairs) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const v4f v = *(const v4f*)(lds_all[s][1] + row * XS + col);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) sum[k] += (double)v[k];
+            }
         }
         const v4f b = *(const v4f*)(bias + (ch < N ? ch : 0));
         v4f o;
@@ -878,6 +889,9 @@ int launch_splitk(const sbn_packed* p, const float* x, float* y, long long M, hi
     return SBN_OK;
 }
 
+// share of a layer's 4 x 4 pieces that it keeps
+double share_kept(const sbn_packed* p) { return 16.0 * (double)p->dev.n_present / ((double)p->c_in * p->c_out); }
+
 template <int S>
 int launch_sliced(const sbn_packed* p, const float* x, float* y, long long M, hipStream_t st)
 {
@@ -886,8 +900,12 @@ int launch_sliced(const sbn_packed* p, const float* x, float* y, long long M, hi
     const int n_col_tiles = (L.n_bundles + 3) / 4;
     const long long n_tiles = n_pix_tiles * n_col_tiles, per_xcd = (n_tiles + 7) / 8, grid = 8 * per_xcd;
     if (S * grid > sbn::kMaxGroups256) return sbn::fail(SBN_EINVAL, "too many pixels for one launch (%lld)", M);
+    // Pairs added in 32 bits where the error stays at or below that of the form replaced (greatest of error / error; elsewhere 1.03 to 1.18): more than one
+    // tile per compute unit 0.97, 225 to 256 channels 0.98.  (3136 pixels, 512 x 512, 90 % 10.5 us, 10.9 without; 784, 256 x 1024, 80 % 6.9, 7.2.)
+    const double share = share_kept(p);
+    const bool add_pairs = share > 0.055 && (n_tiles > L.cus || (p->c_in > 224 && p->c_in <= 256 && share <= 0.21));
     hipLaunchKernelGGL(conv1x1_sliced_kernel<S>, dim3((unsigned)grid), dim3(256 * S), 0, st, x, y, L.d_records, L.d_woff, L.d_wts,
-                       L.d_bias, M, p->c_in, p->c_out, L.n_bundles, L.n_chunks, n_col_tiles, (int)n_tiles, (int)per_xcd, p->act);
+                       L.d_bias, M, p->c_in, p->c_out, L.n_bundles, L.n_chunks, n_col_tiles, (int)n_tiles, (int)per_xcd, (int)add_pairs, p->act);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return sbn::fail(SBN_EHIP, "conv1x1 launch: %s", hipGetErrorString(e));
     return SBN_OK;
@@ -966,30 +984,59 @@ int launch_chain_tail(const TailArgs& a, unsigned* sync, int cus, void* stream)
 }
 
 // Sparse layers of at least four chunks whose 64 x 64 tiles leave compute units without one, or with one and little more: 402 or 404 (two
-// slices or four), else 0.  12455 random layers of 100 to 100000 pixels and 128 to 1024 input channels, against the rules without these forms:
-//   up to one tile per compute unit, more than 0.4 + the share kept of one (times faster, with 1024 / 512 / 256 input channels)
-//     share kept 0.05  1.6 1.5 1.3    0.1  1.5 1.4 1.3    0.2  1.2 1.3 1.2    0.3  1.1 1.1 1.2    0.4  1.1 1.1 1.0
-//     below: 0.35 tiles, share 0.2 and 0.4  0.9 and 0.7
-//   1 to 1.75 tiles, shares up to 0.3: 1.1 to 1.2 from 576 input channels on, 1.0 to 1.1 at 512; slower with 256, and from 1.75 tiles on.
-// Up to one tile per compute unit no layer's error may exceed that of the split form (4, 8 or 16 waves, partial sums added in 32 bits) or of
-// form 12: four slices where the sums are long, two (a channel's way twice as long) up to 256 channels and for sparse layers up to 320, and neither where
-// the split form has eight waves and a wave of four slices would add up twice as much of a long sum.  Greatest of error / error of what it replaces,
-// 6900 random layers that keep up to 42 %: two slices, up to 256 channels 0.98, up to 320 0.97 at 30 % and 1.02 at 40 %; four slices 0.98, against
-// eight waves 0.99 where 360 channels are kept and 1.13 at 720.  More than one tile per compute unit need
-// two slices (four: one workgroup per compute unit at a time), which replace form 12 (0.95; 1024, 90 %: 7.9e-8 instead of 9.8e-8).
+// slices or four), else 0.  Both sides measured on 12500 random layers of 192 to 8192 input channels, blocks of 4 and 8 by 1 to 8, 55 to 99 %.
+//
+// Up to one tile per compute unit, against the split form: more than 0.4 + the share kept (0.35 tiles, share 0.2 and 0.4  0.9 and 0.7 times as
+// fast); up to 224 channels 4.5 % and more (below 0.88 to 1.1).  `split`, a unit's workgroups of the split form in fours, is the work without what a
+// tile has past c_out.  Layers of few outputs gain most, since the split form reads the pixels once per 16 of them (up to 256 outputs 1.2 to 3.4, from 513
+// channels on, with up to 128 from 385, at any such size; others from half a tile of such work on); with more than 512 outputs and up to 768 channels
+// the line is 0.6 + half the share (below it 0.78 to 1.1, above 0.95 to 1.5); where the split form has eight waves and up to 1536 channels, only up to
+// 256 outputs gain (others 0.82 to 1.1).  Median over what is taken 1.3, 16 of 3200 below 0.95.  From 321 to 384 channels two slices are 1.1 times
+// as fast as four, from 385 on four.
+//
+// No layer's error may exceed that of the split form (4, 8 or 16 waves, partial sums added in 32 bits): two slices (a channel's
+// way is twice as long) up to 256 channels and, where at most 30 % is kept, up to 384; neither where the split form has eight waves and a wave of
+// four slices would add up twice as much of a long sum.  Greatest of error / error of what it replaces: two slices, up to 256 channels 0.98, up to
+// 384 1.00 at 30 % and 1.05 at 40 %; four slices 0.98, against eight waves 0.99 where 360 channels are kept and 1.13 at 720.
+//
+// More than one tile per compute unit, against form 12: two slices (four: one workgroup per compute unit at a time; error at most 0.96 of form 12's).
+// They gain with the input channels, with the outputs (form 12 reads the pixels of a column tile again from L2) and where form 12 spreads badly: a
+// mixed launch by the tiles per unit that it leaves to split workgroups (`rest`), else by the busiest XCD's tiles per unit.  Where 6 % and more is kept, up to
+// 768 channels and 4 / 8 / 12 / 19 column tiles, rest 0.1 0.88 / 0.92 / 1.02 / 1.03 (median), 0.3 0.95 / 1.02 / 1.04 / 1.03, 0.5 1.05 / 1.06 / 1.08 / 1.10;
+// unmixed 1.08; less kept 0.91 / 0.95 / 0.94 / 1.05, 0.98 / 0.95 / 0.99 / 0.99, 0.95 / 1.10 / 1.15 / 1.08; 20 column tiles and more 1.05 to 1.7; from
+// 1025 channels on 1.05 to 1.5 but for two column tiles.  Up to two of them 0.75 to 1.1.
 static int sliced_form(const sbn_packed* p, long long M)
 {
     if (p->c_in <= 192 || (p->c_out + 63) / 64 * 64 * 3 > p->c_out * 4) return 0;
-    const long long cus = p->dev.cus, pix_tiles = (M + 63) / 64;
-    const double share = 16.0 * (double)p->dev.n_present / ((double)p->c_in * p->c_out);
-    const double tiles = (double)(pix_tiles * ((p->dev.n_bundles + 3) / 4)) / (double)cus;
+    const long long cus = p->dev.cus, pix_tiles = (M + 63) / 64, col_tiles = (p->dev.n_bundles + 3) / 4, n = pix_tiles * col_tiles;
+    const double share = share_kept(p);
+    const double tiles = (double)n / (double)cus, split = (double)(pix_tiles * p->dev.n_bundles) / (4.0 * (double)cus);
     if (tiles <= 1.0) {
-        if (share > 0.42 || tiles <= 0.4 + share) return 0;
-        if (p->c_in >= 512 && pix_tiles * p->dev.n_bundles <= 2 * cus && p->c_in * share > 360.) return 0;
-        if (p->c_in > 320) return 404;
-        return p->c_in <= 256 || share <= 0.3 ? 402 : 0;
+        if (share > 0.42 || tiles <= 0.4 + share || (p->c_in <= 224 && share < 0.045)) return 0;
+        if (col_tiles > 8) {
+            if (p->c_in <= 768 && split < 0.6 + 0.5 * share) return 0;
+        } else if (col_tiles > 4) {
+            if (p->c_in <= 768 && split < (p->c_in <= 384 ? 0.55 + 0.5 * share : 0.5)) return 0;
+        } else if (split < (p->c_in > 512 || (p->c_in > 384 && col_tiles <= 2) ? 0.0 : 0.5)) {
+            return 0;
+        }
+        const bool eight_waves = p->c_in > 480 && split <= 0.5;
+        if (eight_waves && (p->c_in * share > 360. || (col_tiles > 4 && p->c_in <= 1536))) return 0;
+        if (p->c_in <= 256 || (p->c_in <= 384 && share <= 0.305)) return 402;
+        return p->c_in > 384 || split >= 0.75 ? 404 : 0;
     }
-    return p->c_in >= 512 && share <= 0.31 && tiles <= 1.75 && pix_tiles * p->dev.n_bundles > 4 * cus ? 402 : 0;
+    if (p->c_in < 512 || share > 0.31 || tiles > 1.75 || split <= 1.0) return 0;
+    if (p->c_in > 1024) return col_tiles > 2 || share > 0.15 ? 402 : 0;
+    if (col_tiles <= 2) return 0;
+    const bool long_sums = p->c_in > 768, some_kept = share > 0.055;
+    const long long rem = n % cus;                      // (the mixed launch as launch_conv1x1 lays it out)
+    if (rem && 2 * rem <= cus) {
+        const double rest = (double)((pix_tiles - (n - rem) / col_tiles / 8 * 8) * col_tiles) / (double)cus;
+        if (long_sums) return rest >= (col_tiles > 12 || (some_kept && col_tiles > 4) ? 0.0 : some_kept ? 0.2 : col_tiles > 4 ? 0.4 : 0.6) ? 402 : 0;
+        return rest >= (col_tiles > 19 || (some_kept && col_tiles > 12) ? 0.0 : some_kept && col_tiles > 8 ? 0.3 : 0.5) ? 402 : 0;
+    }
+    const double busiest = (double)((pix_tiles + 7) / 8 * 8 * col_tiles) / (double)cus;
+    return some_kept || (col_tiles > 4 && busiest >= (long_sums ? 1.6 : 1.9)) ? 402 : 0;
 }
 
 int launch_conv1x1(const sbn_packed* p, const float* x, float* y, long long M, void* stream)

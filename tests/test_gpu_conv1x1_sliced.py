@@ -63,6 +63,21 @@ def test_infinities_and_nan_reach_what_keeps_their_block_and_nothing_else(forced
     (3136, 512, 512, 50, 0),
     (784, 192, 1024, 90, 0),
     (4096, 1024, 512, 90, 0),          # 2 tiles
+    (569, 384, 1264, 70, 0),           # 0.70 tiles, more than 512 outputs: 1.1 times slower than the split form
+    (690, 384, 1264, 70, 402),         # 0.86
+    (4485, 680, 112, 95, 404),         # 0.55, of few outputs
+    (821, 384, 912, 60, 0),            # 0.72: two slices would add up too long
+    (768, 576, 880, 80, 0),            # 0.66
+    (768, 576, 1200, 80, 404),         # 0.89
+    (407, 960, 1056, 95, 0),           # the split form has eight waves,
+    (5464, 720, 104, 95, 404),         # 16 outputs to each of which read the pixels again where they are many
+    (2600, 520, 512, 97, 0),           # 1.28 tiles, of little work
+    (2600, 640, 512, 80, 0),           # 1.28 tiles, 0.28 of them for split workgroups,
+    (2304, 704, 640, 80, 402),         # 1.41, 0.47
+    (12800, 1024, 128, 80, 0),         # 1.56, few outputs
+    (1157, 1008, 1264, 99, 402),       # 1.48, 20 column tiles
+    (2368, 768, 448, 95, 0),           # 1.01 tiles, 0.14 of them for split workgroups
+    (2112, 768, 832, 95, 402),         # 1.68, 33 pixel tiles: 2.03 tiles per unit
 ])
 def test_rule(forced, m, K, N, pct, form):
     """Counted for 256 compute units: the bits of the forced form, and on the other side of the lines other bits than either."""
@@ -85,11 +100,14 @@ def test_rule(forced, m, K, N, pct, form):
 
 
 @pytest.mark.parametrize("m,K,N,pct,replaced", [
-    (3508, 200, 208, 99, 12),          # two slices, short sums: what counts is how few additions round
-    (1143, 320, 776, 60, 504),         # long ones for two slices
+    (3508, 200, 208, 99, 12),          # short sums: what counts is how few additions round
+    (3508, 200, 208, 95, 12),          # two slices
+    (784, 256, 1024, 80, 504),         # that add pairs in 32 bits
+    (1143, 320, 776, 60, 504),         # long sums for two slices
     (784, 1024, 1024, 80, 504),        # four slices
     (3234, 3656, 152, 81, 508),        # where the split form has eight waves
     (6395, 592, 256, 99, 12),          # more than one tile per compute unit
+    (1157, 1008, 1264, 99, 12),
     (3136, 1024, 512, 70, 12),
 ])
 def test_no_further_from_the_exact_sum_than_the_form_it_replaces(forced, m, K, N, pct, replaced):
