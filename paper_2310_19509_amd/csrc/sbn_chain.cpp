@@ -212,7 +212,9 @@ int run_chain(const sbn_chain* c, const float* x, float* y, int n, int h, int w,
             !(layer_outputs && (layer_outputs[0] || layer_outputs[1]))) {
             const sbn_chain::Item &dw = c->items[1], &pw = c->items[2];
             float* dst = c->items.size() == 3 ? y : buf[which];
-            if (int rc = launch_stem_dwpw(pw.packed, src, dst, it.d_w, it.d_b, it.act, dw.d_w, dw.d_b, dw.d_taps, dw.act, (int)s.n, s.h, s.w, stream))
+            // (exact: where the pair alone would be two launches, the 1x1 layer's in a form of more exact sums)
+            const bool exact = c->fuse_dw != 2 && !dwpw_pays(pw.packed, next_shape(dw, next_shape(it, s)));
+            if (int rc = launch_stem_dwpw(pw.packed, src, dst, it.d_w, it.d_b, it.act, dw.d_w, dw.d_b, dw.d_taps, dw.act, (int)s.n, s.h, s.w, exact, stream))
                 return rc;
             s = next_shape(pw, next_shape(dw, next_shape(it, s)));
             if (layer_outputs && layer_outputs[2]) {

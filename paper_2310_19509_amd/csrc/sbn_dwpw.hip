@@ -135,10 +135,16 @@ __device__ __forceinline__ void turn_quad(v4f (&v)[4], int lane)
 // Waves per SIMD that the registers leave room for, and with that the workgroups of a compute unit.  (One more wave per SIMD, 96 registers: the forms of
 // four waves and of stride 2 spill, 73 -> 173 and 63 -> 79 us; the other 68 either way; with the stem 96 -> 120.)
 // Stride 2 with four waves comes with two and, LEAN, with three: launch_dwpw.
-constexpr int waves_per_simd(int stride, int nwv, bool stem, bool lean) { return stem || lean ? 3 : stride == 2 && nwv == 4 ? 2 : 4; }
+constexpr int waves_per_simd(int stride, int nwv, bool stem, bool lean, bool exact)
+{
+    return exact ? 2 : stem || lean ? 3 : stride == 2 && nwv == 4 ? 2 : 4;
+}
 
-template <int STRIDE, int NWV, bool PAT, bool STEM, bool LEAN>
-__global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM, LEAN)) void dwpw_kernel(const float* __restrict__ x, float* __restrict__ y,
+// EXACT: with a stem, where the launch has so few tiles that the 1x1 layer by itself would run in the few-pixel form: no 32-bit sum runs over more than 4
+// products (four sets of accumulators), and they and the bias are added in 64 bits, so that the error is that form's (0.98 to 1.01 of it; with one set and the
+// bias added in 32 bits 1.02 to 1.10).  60 sizes of up to 64 tiles 9.4 to 10.6 us in three launches, 6.0 to 6.5 with one set, 6.5 to 7.0 so.
+template <int STRIDE, int NWV, bool PAT, bool STEM, bool LEAN, bool EXACT>
+__global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM, LEAN, EXACT)) void dwpw_kernel(const float* __restrict__ x, float* __restrict__ y,
                                                    const float* __restrict__ dw_w, const float* __restrict__ dw_b,
                                                    const uint32_t* __restrict__ dw_taps, int dw_act,
                                                    const uint32_t* __restrict__ records,
@@ -150,6 +156,8 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM, LEAN)) 
 {
     static_assert(!STEM || (STRIDE == 1 && NWV == 4), "the stem joins the form of four waves and stride 1");
     static_assert(!LEAN || (STRIDE == 2 && NWV == 4), "the other forms have one number of waves");
+    static_assert(!EXACT || STEM, "one sub-chunk only");
+    constexpr int NSET = EXACT ? 4 : 1;
     constexpr int IW = (TW - 1) * STRIDE + 3, IH = (TH - 1) * STRIDE + 3;     // input tile
     constexpr int NPIX = IW * IH;
     constexpr int NPIXP = NPIX + (6 - NPIX % 4) % 4;           // = 2 mod 4: the two halves of a pixel pair fill all banks
@@ -410,13 +418,13 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM, LEAN)) 
         w[0] = src[0];
         w[1] = src[64];
     };
-    auto multiply = [&](const Record8& r, const v4f (&w)[2], v4f (&acc)[4][2]) {
+    auto multiply = [&](const Record8& r, const v4f (&w)[2], v4f (&acc)[NSET][4][2]) {
         const char* xl = (const char*)lds_x + lane * (XS * 4);
         v4f xa, xb;
 #define SBN_ENTRY(Q, XC, XN)                                             \
     if (__builtin_expect(r.d[Q] == 0, 0)) goto sub_chunk_done;           \
     if (Q + 1 < 8) XN = *(const v4f*)(xl + (r.d[(Q + 1) & 7] >> 8));      \
-    entry_fma<Q>(r.d[Q], w[Q / 4], XC, acc);
+    entry_fma<Q>(r.d[Q], w[Q / 4], XC, acc[Q / 2 % NSET]);
         xa = *(const v4f*)(xl + (r.d[0] >> 8));
         SBN_ENTRY(0, xa, xb)
         SBN_ENTRY(1, xb, xa)
@@ -434,10 +442,23 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM, LEAN)) 
     const uint32_t yplace = bundle * 16 + (lane & 3) * 4 < N
                                 ? (uint32_t)(((lane >> 3) * OW + (lane & 4)) * N + bundle * 16 + (lane & 3) * 4) * 4u
                                 : kOutside;
-    auto finish = [&](const At& t, v4f (&acc)[4][2]) {
+    auto finish = [&](const At& t, v4f (&acc)[NSET][4][2]) {
         v4f o[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) o[g] = acc[g][0] + acc[g][1] + *(const v4f*)(bias + bundle * 16 + g * 4);
+        for (int g = 0; g < 4; ++g) {
+            const v4f b = *(const v4f*)(bias + bundle * 16 + g * 4);
+            if constexpr (EXACT) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    double sum = (double)b[i];
+#pragma unroll
+                    for (int h = 0; h < 2 * NSET; ++h) sum += (double)acc[h / 2][g][h % 2][i];
+                    o[g][i] = (float)sum;
+                }
+            } else {
+                o[g] = acc[0][g][0] + acc[0][g][1] + b;
+            }
+        }
         turn_quad(o, lane);
         if (act == SBN_ACT_RELU) {                     // (behind the turn: the compiler does not see an asm's write in front of a lane move's read)
 #pragma unroll
@@ -471,20 +492,22 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM, LEAN)) 
             if (s < 10 * KMAX / 4) *(v4f*)(lds_p + s * 4) = v[i];
         }
     }
-    v4f acc[4][2];
+    v4f acc[NSET][4][2];
     // (in one place and out of the compiler's sight: it otherwise keeps several sets of them, over 200 registers)
     auto pin = [&] {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if constexpr (STEM || LEAN) asm volatile("" : "+v"(acc[g][h]));
-                else asm volatile("" : "+a"(acc[g][h]));
+            for (int h = 0; h < 2 * NSET; ++h) {
+                if constexpr (STEM || LEAN) asm volatile("" : "+v"(acc[h / 2][g][h % 2]));
+                else asm volatile("" : "+a"(acc[h / 2][g][h % 2]));
             }
     };
     auto start = [&] {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) acc[g][0] = acc[g][1] = (v4f){0.f, 0.f, 0.f, 0.f};
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int h = 0; h < 2 * NSET; ++h) acc[h / 2][g][h % 2] = (v4f){0.f, 0.f, 0.f, 0.f};
         pin();
     };
     // A workgroup barrier for LDS alone: memory accesses stay in flight across it.
@@ -521,7 +544,7 @@ __global__ __launch_bounds__(64 * NWV, waves_per_simd(STRIDE, NWV, STEM, LEAN)) 
     }
 }
 
-template <int STRIDE, int NWV, bool PAT, bool STEM = false, bool LEAN = false>
+template <int STRIDE, int NWV, bool PAT, bool STEM = false, bool LEAN = false, bool EXACT = false>
 int launch(const sbn_packed* p, const float* x, float* y, const float* dw_w, const float* dw_b, const uint32_t* dw_taps,
            int dw_act, int n, int h, int w, hipStream_t st, const StemArgs& stem = {})
 {
@@ -529,12 +552,12 @@ int launch(const sbn_packed* p, const float* x, float* y, const float* dw_w, con
     const int oh = (h - 1) / STRIDE + 1, ow = (w - 1) / STRIDE + 1;
     const int tiles_x = (ow + TW - 1) / TW, tiles_y = (oh + TH - 1) / TH;
     const long long n_pix_tiles = (long long)n * tiles_x * tiles_y;
-    const long long grid = std::min<long long>(n_pix_tiles, 4ll * waves_per_simd(STRIDE, NWV, STEM, LEAN) / NWV * L.cus);
+    const long long grid = std::min<long long>(n_pix_tiles, 4ll * waves_per_simd(STRIDE, NWV, STEM, LEAN, EXACT) / NWV * L.cus);
     if ((long long)h * w * p->c_in > 0x7FFFFFFFll)
         return sbn::fail(SBN_EINVAL, "one image of %d x %d x %d elements is too large for 32-bit offsets", h, w, p->c_in);
     if (grid > 0x7FFFFFFFll || n_pix_tiles + grid > 0x7FFFFFFFll)
         return sbn::fail(SBN_EINVAL, "too many output tiles for one launch (%lld)", n_pix_tiles);
-    hipLaunchKernelGGL((dwpw_kernel<STRIDE, NWV, PAT, STEM, LEAN>), dim3((unsigned)grid), dim3(64 * NWV), 0, st, x, y, dw_w, dw_b, dw_taps, dw_act, L.d_records32,
+    hipLaunchKernelGGL((dwpw_kernel<STRIDE, NWV, PAT, STEM, LEAN, EXACT>), dim3((unsigned)grid), dim3(64 * NWV), 0, st, x, y, dw_w, dw_b, dw_taps, dw_act, L.d_records32,
                        L.d_woff32, L.d_wts, L.d_bias, h, w, oh, ow, p->c_in, p->c_out, L.n_bundles, L.n_chunks32,
                        tiles_x, tiles_y, (int)n_pix_tiles, (int)grid, (int)(grid % tiles_x), (int)(grid / tiles_x % tiles_y),
                        (int)(grid / tiles_x / tiles_y), p->act, stem);
@@ -590,14 +613,16 @@ bool stem_dwpw_fusable(const sbn_packed* p, int c_in, int c_out, int stride, int
 }
 
 int launch_stem_dwpw(const sbn_packed* p, const float* x, float* y, const float* stem_w, const float* stem_b, int stem_act, const float* dw_w,
-                     const float* dw_b, const uint32_t* dw_taps, int dw_act, int n, int h, int w, void* stream)
+                     const float* dw_b, const uint32_t* dw_taps, int dw_act, int n, int h, int w, bool exact, void* stream)
 {
     if (!stem_dwpw_fusable(p, 3, 32, 2, 1, w)) return fail(SBN_EINVAL, "internal error: fused stem + depthwise + 1x1 launch for a layer it does not cover");
     const StemArgs stem = {stem_w, stem_b, h, w, stem_act};
     const int sh = (h - 1) / 2 + 1, sw = (w - 1) / 2 + 1;
     hipStream_t st = (hipStream_t)stream;
-    return dw_taps ? launch<1, 4, true, true>(p, x, y, dw_w, dw_b, dw_taps, dw_act, n, sh, sw, st, stem)
-                   : launch<1, 4, false, true>(p, x, y, dw_w, dw_b, dw_taps, dw_act, n, sh, sw, st, stem);
+#define SBN_STEM(PAT, EXACT) launch<1, 4, PAT, true, false, EXACT>(p, x, y, dw_w, dw_b, dw_taps, dw_act, n, sh, sw, st, stem)
+    if (exact) return dw_taps ? SBN_STEM(true, true) : SBN_STEM(false, true);
+    return dw_taps ? SBN_STEM(true, false) : SBN_STEM(false, false);
+#undef SBN_STEM
 }
 
 }  // namespace sbn

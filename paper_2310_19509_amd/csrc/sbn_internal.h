@@ -167,7 +167,7 @@ int launch_dwpw(const sbn_packed* p, const float* x, float* y, const float* dw_w
 // the usual stem (3 -> 32 channels, stride 2) in front of such a pair in the same launch.  (Weak: the chain's host code also links without the kernels.)
 __attribute__((weak)) bool stem_dwpw_fusable(const sbn_packed* p, int c_in, int c_out, int stride, int dw_stride, int w);
 __attribute__((weak)) int launch_stem_dwpw(const sbn_packed* p, const float* x, float* y, const float* stem_w, const float* stem_b, int stem_act,
-                                           const float* dw_w, const float* dw_b, const uint32_t* dw_taps, int dw_act, int n, int h, int w, void* stream);
+                                           const float* dw_w, const float* dw_b, const uint32_t* dw_taps, int dw_act, int n, int h, int w, bool exact, void* stream);
 int launch_avgpool(const float* x, float* y, int n, int hw, int c, void* stream);
 int launch_copy(const void* src, void* dst, size_t bytes, void* stream);
 
