@@ -207,8 +207,7 @@ int run_chain(const sbn_chain* c, const float* x, float* y, int n, int h, int w,
         // launches / one, 64 output channels, 1 tile of 8 x 8 pixels 8.5 / 5.4 us, 16 tiles 9.3 / 5.6, 64 tiles 10.3 / 5.5, 196 tiles 12.9 / 6.0, 588 tiles
         // 17.5 / 10.2; 64 images of 224 x 224, stem and pair 110 / 96.
         if (c->fuse_dw && i == 0 && it.item == SBN_ITEM_STEM3X3 && c->items.size() > 2 && c->items[1].item == SBN_ITEM_DW3X3 &&
-            c->items[2].item == SBN_ITEM_SPARSE && stem_dwpw_fusable &&
-            stem_dwpw_fusable(c->items[2].packed, it.channels, it.c_out, it.stride, c->items[1].stride, s.w) &&
+            c->items[2].item == SBN_ITEM_SPARSE && stem_dwpw_fusable(c->items[2].packed, it.channels, it.c_out, it.stride, c->items[1].stride, s.w) &&
             !(layer_outputs && (layer_outputs[0] || layer_outputs[1]))) {
             const sbn_chain::Item &dw = c->items[1], &pw = c->items[2];
             float* dst = c->items.size() == 3 ? y : buf[which];

@@ -164,10 +164,10 @@ inline bool dwpw_rows_fit(const sbn_packed* p, int w) { return 17ll * w * (p->c_
 // dw_taps: NULL, or per 16 channels (in running order) the 9-bit mask of the taps the group keeps
 int launch_dwpw(const sbn_packed* p, const float* x, float* y, const float* dw_w, const float* dw_b,
                 const uint32_t* dw_taps, int dw_stride, int dw_act, int n, int h, int w, void* stream);
-// the usual stem (3 -> 32 channels, stride 2) in front of such a pair in the same launch.  (Weak: the chain's host code also links without the kernels.)
-__attribute__((weak)) bool stem_dwpw_fusable(const sbn_packed* p, int c_in, int c_out, int stride, int dw_stride, int w);
-__attribute__((weak)) int launch_stem_dwpw(const sbn_packed* p, const float* x, float* y, const float* stem_w, const float* stem_b, int stem_act,
-                                           const float* dw_w, const float* dw_b, const uint32_t* dw_taps, int dw_act, int n, int h, int w, bool exact, void* stream);
+// the usual stem (3 -> 32 channels, stride 2) in front of such a pair in the same launch
+bool stem_dwpw_fusable(const sbn_packed* p, int c_in, int c_out, int stride, int dw_stride, int w);
+int launch_stem_dwpw(const sbn_packed* p, const float* x, float* y, const float* stem_w, const float* stem_b, int stem_act,
+                     const float* dw_w, const float* dw_b, const uint32_t* dw_taps, int dw_act, int n, int h, int w, bool exact, void* stream);
 int launch_avgpool(const float* x, float* y, int n, int hw, int c, void* stream);
 int launch_copy(const void* src, void* dst, size_t bytes, void* stream);
 

@@ -5,6 +5,8 @@ import ctypes as C
 import math
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -26,6 +28,15 @@ def test_library_exports_every_declared_symbol():
     for name in declared:
         getattr(lib, name)
     _lib.lib()
+
+
+@pytest.mark.skipif(shutil.which("nm") is None, reason="needs nm")
+def test_no_launcher_is_a_weak_symbol():
+    """A launcher or launch rule that a link leaves out is an error of the link, not a null address to be tested for at run time."""
+    out = subprocess.run(["nm", "-C", _lib.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    kinds = {m[2]: m[1] for m in re.finditer(r"^\S* (\w) sbn::(\w+)\(", out, re.M)}
+    assert {"launch_conv1x1", "launch_dwpw", "launch_stem_dwpw", "stem_dwpw_fusable"} <= set(kinds)
+    assert [k for k, v in kinds.items() if v in "wWvV" and k.startswith(("launch_", "stem_", "dwpw_fus", "few_", "conv"))] == []
 
 
 @pytest.mark.parametrize("kind,go,gi,pct", [(S.SBN_CONV1X1, 4, 4, 30), (S.SBN_CONV1X1, 8, 4, 50),
