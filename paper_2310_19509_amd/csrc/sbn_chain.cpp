@@ -207,7 +207,8 @@ int run_chain(const sbn_chain* c, const float* x, float* y, int n, int h, int w,
         // launches / one, 64 output channels, 1 tile of 8 x 8 pixels 8.5 / 5.4 us, 16 tiles 9.3 / 5.6, 64 tiles 10.3 / 5.5, 196 tiles 12.9 / 6.0, 588 tiles
         // 17.5 / 10.2; 64 images of 224 x 224, stem and pair 110 / 96.
         if (c->fuse_dw && i == 0 && it.item == SBN_ITEM_STEM3X3 && c->items.size() > 2 && c->items[1].item == SBN_ITEM_DW3X3 &&
-            c->items[2].item == SBN_ITEM_SPARSE && stem_dwpw_fusable(c->items[2].packed, it.channels, it.c_out, it.stride, c->items[1].stride, s.w) &&
+            c->items[2].item == SBN_ITEM_SPARSE && stem_dwpw_fusable(c->items[2].packed, it.channels, it.c_out, it.stride, c->items[1].stride) &&
+            dwpw_extents_fit(c->items[2].packed, 1, s.n, next_shape(it, s).h, next_shape(it, s).w) &&
             !(layer_outputs && (layer_outputs[0] || layer_outputs[1]))) {
             const sbn_chain::Item &dw = c->items[1], &pw = c->items[2];
             float* dst = c->items.size() == 3 ? y : buf[which];
@@ -229,7 +230,7 @@ int run_chain(const sbn_chain* c, const float* x, float* y, int n, int h, int w,
         // output never exists in memory), unless the caller asked for a copy of it.
         if (c->fuse_dw && it.item == SBN_ITEM_DW3X3 && i + 1 < c->items.size() &&
             c->items[i + 1].item == SBN_ITEM_SPARSE && dwpw_fusable(c->items[i + 1].packed, it.channels, it.stride) &&
-            dwpw_rows_fit(c->items[i + 1].packed, s.w) &&
+            dwpw_extents_fit(c->items[i + 1].packed, it.stride, s.n, s.h, s.w) &&
             !(layer_outputs && layer_outputs[i]) && (c->fuse_dw == 2 || dwpw_pays(c->items[i + 1].packed, next_shape(it, s)))) {
             const sbn_chain::Item& pw = c->items[i + 1];
             const bool last2 = i + 2 == c->items.size();

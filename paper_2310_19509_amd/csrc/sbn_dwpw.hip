@@ -553,10 +553,6 @@ int launch(const sbn_packed* p, const float* x, float* y, const float* dw_w, con
     const int tiles_x = (ow + TW - 1) / TW, tiles_y = (oh + TH - 1) / TH;
     const long long n_pix_tiles = (long long)n * tiles_x * tiles_y;
     const long long grid = std::min<long long>(n_pix_tiles, 4ll * waves_per_simd(STRIDE, NWV, STEM, LEAN, EXACT) / NWV * L.cus);
-    if ((long long)h * w * p->c_in > 0x7FFFFFFFll)
-        return sbn::fail(SBN_EINVAL, "one image of %d x %d x %d elements is too large for 32-bit offsets", h, w, p->c_in);
-    if (grid > 0x7FFFFFFFll || n_pix_tiles + grid > 0x7FFFFFFFll)
-        return sbn::fail(SBN_EINVAL, "too many output tiles for one launch (%lld)", n_pix_tiles);
     hipLaunchKernelGGL((dwpw_kernel<STRIDE, NWV, PAT, STEM, LEAN, EXACT>), dim3((unsigned)grid), dim3(64 * NWV), 0, st, x, y, dw_w, dw_b, dw_taps, dw_act, L.d_records32,
                        L.d_woff32, L.d_wts, L.d_bias, h, w, oh, ow, p->c_in, p->c_out, L.n_bundles, L.n_chunks32,
                        tiles_x, tiles_y, (int)n_pix_tiles, (int)grid, (int)(grid % tiles_x), (int)(grid / tiles_x % tiles_y),
@@ -579,7 +575,7 @@ bool dwpw_fusable(const sbn_packed* p, int channels, int stride)
 int launch_dwpw(const sbn_packed* p, const float* x, float* y, const float* dw_w, const float* dw_b,
                 const uint32_t* dw_taps, int dw_stride, int dw_act, int n, int h, int w, void* stream)
 {
-    if (!dwpw_fusable(p, p->c_in, dw_stride) || !dwpw_rows_fit(p, w))
+    if (!dwpw_fusable(p, p->c_in, dw_stride) || !dwpw_extents_fit(p, dw_stride, n, h, w))
         return fail(SBN_EINVAL, "internal error: fused depthwise + 1x1 launch for a layer it does not cover");
     hipStream_t st = (hipStream_t)stream;
     const bool wide = p->dev.n_bundles > 4;      // more than 64 output channels: eight waves cover up to 128
@@ -606,18 +602,18 @@ int launch_dwpw(const sbn_packed* p, const float* x, float* y, const float* dw_w
 #undef SBN_DWPW
 }
 
-bool stem_dwpw_fusable(const sbn_packed* p, int c_in, int c_out, int stride, int dw_stride, int w)
+bool stem_dwpw_fusable(const sbn_packed* p, int c_in, int c_out, int stride, int dw_stride)
 {
-    return c_in == 3 && c_out == 32 && stride == 2 && dw_stride == 1 && dwpw_fusable(p, 32, 1) && p->dev.n_bundles <= 4 &&
-           dwpw_rows_fit(p, w);                   // (w: the stem's input; 21 rows of it, 12 bytes a pixel, are less than 17 of 32 channels)
+    return c_in == 3 && c_out == 32 && stride == 2 && dw_stride == 1 && dwpw_fusable(p, 32, 1) && p->dev.n_bundles <= 4;
 }
 
 int launch_stem_dwpw(const sbn_packed* p, const float* x, float* y, const float* stem_w, const float* stem_b, int stem_act, const float* dw_w,
                      const float* dw_b, const uint32_t* dw_taps, int dw_act, int n, int h, int w, bool exact, void* stream)
 {
-    if (!stem_dwpw_fusable(p, 3, 32, 2, 1, w)) return fail(SBN_EINVAL, "internal error: fused stem + depthwise + 1x1 launch for a layer it does not cover");
+    const int sh = (h - 1) / 2 + 1, sw = (w - 1) / 2 + 1;      // (21 rows of 2 sw pixels, 12 bytes each, are less than 17 of sw with 32 channels)
+    if (!stem_dwpw_fusable(p, 3, 32, 2, 1) || !dwpw_extents_fit(p, 1, n, sh, sw))
+        return fail(SBN_EINVAL, "internal error: fused stem + depthwise + 1x1 launch for a layer it does not cover");
     const StemArgs stem = {stem_w, stem_b, h, w, stem_act};
-    const int sh = (h - 1) / 2 + 1, sw = (w - 1) / 2 + 1;
     hipStream_t st = (hipStream_t)stream;
 #define SBN_STEM(PAT, EXACT) launch<1, 4, PAT, true, false, EXACT>(p, x, y, dw_w, dw_b, dw_taps, dw_act, n, sh, sw, st, stem)
     if (exact) return dw_taps ? SBN_STEM(true, true) : SBN_STEM(false, true);

@@ -159,13 +159,17 @@ int launch_stem3x3(const float* x, float* y, const float* w_dev, const float* b_
                    int c_out, int stride, int act, void* stream);
 // depthwise 3x3 fused into the 1x1 layer that consumes it (small layers only: see dwpw_fusable)
 bool dwpw_fusable(const sbn_packed* p, int channels, int stride);
-// a tile's 17 rows of the wider side have to lie within 2^30 bytes (its 32-bit offsets)
-inline bool dwpw_rows_fit(const sbn_packed* p, int w) { return 17ll * w * (p->c_in > p->c_out ? p->c_in : p->c_out) <= 1ll << 28; }
+// n, h, w: the depthwise layer's input.  A tile's 17 rows of the wider side have to lie within 2^30 bytes (its 32-bit offsets), and the tiles and
+// what a workgroup steps past the last of them within an int; images may be as large as they are.
+inline bool dwpw_extents_fit(const sbn_packed* p, int stride, long long n, int h, int w)
+{
+    return 17ll * w * (p->c_in > p->c_out ? p->c_in : p->c_out) <= 1ll << 28 && n * (((h - 1) / stride + 8) / 8) * (((w - 1) / stride + 8) / 8) <= 1ll << 30;
+}
 // dw_taps: NULL, or per 16 channels (in running order) the 9-bit mask of the taps the group keeps
 int launch_dwpw(const sbn_packed* p, const float* x, float* y, const float* dw_w, const float* dw_b,
                 const uint32_t* dw_taps, int dw_stride, int dw_act, int n, int h, int w, void* stream);
 // the usual stem (3 -> 32 channels, stride 2) in front of such a pair in the same launch
-bool stem_dwpw_fusable(const sbn_packed* p, int c_in, int c_out, int stride, int dw_stride, int w);
+bool stem_dwpw_fusable(const sbn_packed* p, int c_in, int c_out, int stride, int dw_stride);
 int launch_stem_dwpw(const sbn_packed* p, const float* x, float* y, const float* stem_w, const float* stem_b, int stem_act,
                      const float* dw_w, const float* dw_b, const uint32_t* dw_taps, int dw_act, int n, int h, int w, bool exact, void* stream);
 int launch_avgpool(const float* x, float* y, int n, int hw, int c, void* stream);

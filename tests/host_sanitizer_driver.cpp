@@ -28,7 +28,7 @@ int static_workspace_init(int) { return SBN_OK; }
 int launch_chain_tail(const TailArgs&, unsigned*, int, void*) { return unreachable("chain tail"); }
 bool dwpw_fusable(const sbn_packed*, int, int) { return false; }
 int launch_dwpw(const sbn_packed*, const float*, float*, const float*, const float*, const uint32_t*, int, int, int, int, int, void*) { return unreachable("dwpw"); }
-bool stem_dwpw_fusable(const sbn_packed*, int, int, int, int, int) { return false; }
+bool stem_dwpw_fusable(const sbn_packed*, int, int, int, int) { return false; }
 int launch_stem_dwpw(const sbn_packed*, const float*, float*, const float*, const float*, int, const float*, const float*, const uint32_t*, int, int, int, int, bool, void*) { return unreachable("stem + dwpw"); }
 }  // namespace sbn
 

@@ -140,3 +140,32 @@ def test_small_stems_are_no_further_from_the_exact_result_than_three_launches():
             errors.append(float((y.cpu().double() - ref).norm()))
         ratios.append(errors[0] / errors[1])
     assert np.mean(ratios) <= 1.015, ratios
+
+
+@pytest.mark.parametrize("stem", [False, True])
+def test_images_of_more_than_two_to_the_31_elements(stem):
+    """A depthwise input of 2.2 * 10^9 elements in one launch: the last rows against the oracle (they lie furthest from the tensors' starts), each
+    of whose layers leaves out what the cut above them spoils."""
+    K, N, h, w, seed = 32, 4, 60000, 1150, 9995
+    st_w, dw_w, wt = W.he_weights(seed, 32, 3, 3, 3), W.normal_weights(seed + 1, (K, 3, 3), 0.4), W.he_weights(seed + 2, N, 1, 1, K)
+    items = [S.dw_item(dw_w, None), S.sparse_item(S.sbn_pack(S.SBN_CONV1X1, wt, 4, 4))]
+    chain = S.sbn_chain_create([S.stem_item(st_w, None)] + items if stem else items)
+    shape = (1, 2 * h, 2 * w, 3) if stem else (1, h, w, K)
+    x = torch.rand(shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(seed)).mul_(2).sub_(1)
+    ws = torch.zeros(S.sbn_chain_workspace(chain, *shape[:3]) // 4, device="cuda")
+    ws[:4096].fill_(float("nan"))
+    y = torch.full((1, h, w, N), float("nan"), device="cuda")
+    S.sbn_pointwise_chain(chain, x, y, *shape[:3], ws)
+    torch.cuda.synchronize()
+    assert bool(ws[:4096].isnan().all())
+    assert not bool(y.isnan().any())
+    tail = x[:, -24 if stem else -12:].cpu().numpy()
+    b0 = None
+    if stem:
+        tail, b0 = R.conv_nhwc(tail, st_w, None, stride=2, pad=1, act=R.ACT_RELU)
+    mid, bound = R.dwconv3x3_nhwc(tail, dw_w, None, act=R.ACT_RELU)
+    if stem:
+        bound = bound + R.dwconv3x3_nhwc(b0.astype(np.float32), np.abs(dw_w), None)[0]
+    ref, bound_pw = R.sparse_conv_reference(mid, wt, None, 4, 4)
+    bound = bound_pw + (bound.reshape(-1, K).astype(np.float64) @ np.abs(wt.reshape(N, K).astype(np.float64)).T).reshape(bound_pw.shape)
+    assert_within_bound(y[:, -8:].cpu().numpy(), ref[:, -8:], bound[:, -8:], f"stem {stem}")
