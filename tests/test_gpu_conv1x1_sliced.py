@@ -81,7 +81,8 @@ def test_infinities_and_nan_reach_what_keeps_their_block_and_nothing_else(forced
 ])
 def test_rule(forced, m, K, N, pct, form):
     """Counted for 256 compute units: the bits of the forced form, and on the other side of the lines other bits than either."""
-    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are for 256 compute units")
     wt = W.he_weights(8120 + K, N, 1, 1, K)
     mask = S.sbn_prune_magnitude(wt, S.SBN_CONV1X1, 4, 4, pct)
     p = S.sbn_pack(S.SBN_CONV1X1, wt, 4, 4, mask=mask)

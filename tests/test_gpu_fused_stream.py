@@ -69,6 +69,7 @@ def test_tiles_in_a_stream(n, h, w, K, N, stride, patterned, one_launch):
     (2, 37, 45, 36, False, (1, 0, 0), None),     # odd extents: the last row and column of windows reach past the input
     (2, 36, 47, 12, True, (0, 1, 1), None),
     (40, 66, 81, 64, False, (1, 1, 1), None),    # 1200 tiles: several per workgroup
+    (40, 66, 81, 60, True, (1, 1, 1), None),
     (3, 1, 1, 64, True, (1, 1, 1), None),        # one pixel
     (1, 2, 301, 64, False, (1, 1, 1), None),
     (2, 37, 45, 36, False, (1, 1, 1), 2),        # a copy of the result is the same launch
@@ -169,3 +170,58 @@ def test_images_of_more_than_two_to_the_31_elements(stem):
     ref, bound_pw = R.sparse_conv_reference(mid, wt, None, 4, 4)
     bound = bound_pw + (bound.reshape(-1, K).astype(np.float64) @ np.abs(wt.reshape(N, K).astype(np.float64)).T).reshape(bound_pw.shape)
     assert_within_bound(y[:, -8:].cpu().numpy(), ref[:, -8:], bound[:, -8:], f"stem {stem}")
+
+
+@pytest.mark.parametrize("stem,n,h,w,K,N,stride,patterned", [
+    (False, 2, 21, 19, 64, 60, 1, False),
+    (False, 2, 21, 19, 32, 64, 1, True),
+    (False, 2, 21, 19, 64, 128, 1, True),        # eight waves
+    (False, 2, 37, 35, 64, 40, 2, False),        # three workgroups per unit
+    (False, 65, 37, 35, 96, 40, 2, True),        # two: more than four tiles per unit
+    (False, 2, 37, 35, 96, 100, 2, False),
+    (True, 2, 37, 45, 32, 36, 1, False),         # sums in 64 bits
+    (True, 6, 70, 66, 32, 64, 1, True),          # and in 32
+])
+def test_infinities_and_nan_reach_what_reads_them_and_nothing_else(stem, n, h, w, K, N, stride, patterned):
+    """Without activations every output that a spoilt input reaches over kept taps and blocks is not finite and every other keeps its bits; with
+    ReLU (of NaN: 0) infinities lie where they do in separate launches (whose depthwise kernel multiplies the zeros of removed taps: not compared where
+    there are any)."""
+    seed = 9960 + K + N
+    st_w, dw_w, wt = W.he_weights(seed, 32, 3, 3, 3), W.normal_weights(seed + 1, (K, 3, 3), 0.4), W.he_weights(seed + 2, N, 1, 1, K)
+    pattern = S.sbn_dw_pattern_select(dw_w, 16) if patterned else None
+    mask = S.sbn_prune_magnitude(wt, S.SBN_CONV1X1, 4, 4, 50)
+    c_in = 3 if stem else K
+    x = W.uniform_activation(seed + 3, (n, h, w, c_in))
+    spoilt = x.copy()
+    where = [(0, 0, 0, 0), (0, h - 1, w - 1, c_in - 1), (n - 1, 7, 8, 1), (n - 1, 16, w - 1, 2), (n - 1, h - 1, 15, 0)]
+    for i, at in enumerate(where):
+        spoilt[at] = (np.inf, np.nan, -np.inf)[i % 3]
+
+    def run(x, act, fusion):
+        p = S.sbn_pack(S.SBN_CONV1X1, wt, 4, 4, mask=mask, act=act)
+        items = [S.dw_item(dw_w, None, stride=stride, act=act, pattern=pattern), S.sparse_item(p)]
+        chain = S.sbn_chain_create([S.stem_item(st_w, None, act=act)] + items if stem else items)
+        S.sbn_chain_set_fusion(chain, fusion)
+        oh, ow, oc = S.sbn_chain_output_shape(chain, n, h, w)
+        ws = torch.full((S.sbn_chain_workspace(chain, n, h, w) // 4,), 7.0, device="cuda")
+        y = torch.full((n, oh, ow, oc), 7.0, device="cuda")
+        S.sbn_pointwise_chain(chain, torch.from_numpy(x).cuda(), y, n, h, w, ws)
+        torch.cuda.synchronize()
+        assert bool((ws == 7.0).all()) == (fusion != 0)
+        return y.cpu().numpy()
+
+    fused = 1 if stem else 2
+    taps = R.dw_pattern_apply(np.ones((K, 3, 3), np.float32), pattern, 16) if patterned else np.ones((K, 3, 3), np.float32)
+    reach = (~np.isfinite(spoilt)).astype(np.float32)
+    if stem:
+        reach = (R.conv_nhwc(reach, np.ones((32, 3, 3, 3), np.float32), None, stride=2, pad=1)[0] > 0).astype(np.float32)
+    reach = R.dwconv3x3_nhwc(reach, taps, None, stride=stride)[0] > 0
+    kept = np.repeat(np.repeat(mask.reshape(N // 4, K // 4) != 0, 4, 0), 4, 1)
+    reach = reach.reshape(-1, K).astype(np.float32) @ kept.T.astype(np.float32) > 0
+    clean, y = run(x, S.SBN_ACT_NONE, fused).reshape(-1, N), run(spoilt, S.SBN_ACT_NONE, fused).reshape(-1, N)
+    assert reach.any() and not np.isfinite(y[reach]).any()
+    assert np.array_equal(y[~reach], clean[~reach])
+
+    one, separate = run(spoilt, S.SBN_ACT_RELU, fused), run(spoilt, S.SBN_ACT_RELU, 0)
+    assert not np.isnan(one).any() and np.isinf(one).any()
+    assert patterned or np.array_equal(np.isinf(one), np.isinf(separate))
