@@ -436,7 +436,9 @@ int sbn_pointwise_chain_static(const sbn_chain_t* c, const float* x, float* y, i
  * copy of its or of the depthwise output is requested.  enable = 0 switches this off for the
  * chain (every item its own launch), 1 is the default, 2 runs every pair that
  * can run so as one launch, whatever its size; a copy of the depthwise output requested
- * through layer_outputs switches it off for that pair.
+ * through layer_outputs switches it off for that pair.  Past the range of one launch's offsets,
+ * rows of more than 2^28 / 17 floats on the wider side (of the depthwise input's width and the
+ * larger of the channel counts), or 2^30 tiles, the items run separately whatever the switch says.
  */
 int sbn_chain_set_fusion(sbn_chain_t* c, int enable);
 

@@ -69,9 +69,10 @@ Shape next_shape(const sbn_chain::Item& it, Shape s)
     return s;
 }
 
-// Few 8 x 8 tiles leave most of the chip idle for the length of a tile's phases; two launches then spread better.  (us, fused against two
-// launches, 128 x 128, stride 1: 25 tiles 11.5 / 7.3, 49 tiles 11.7 / 10.5, 98 tiles 11.8 / 11.3, 196 tiles 12.9 / 15.2; 64 x 128,
-// stride 2: 49 tiles 8.7 / 8.0, 98 tiles 9.1 / 9.1; 32 x 64: 196 tiles 6.4 / 8.1; 64 x 64: 49 tiles 7.5 / 6.8.)
+// Few 8 x 8 tiles leave most of the chip idle for the length of a tile's phases; two launches then spread better.  (us alone in a graph, fused against two
+// launches, 128 x 128, stride 1: 25 tiles 9.9 / 7.4, 49 tiles 10.0 / 10.6, 98 tiles 10.3 / 11.1, 196 tiles 10.9 / 14.3; 64 x 128,
+// stride 2: 49 tiles 7.8 / 8.0, 98 tiles 8.2 / 9.1; 32 x 64: 49 tiles 5.3 / 6.2, 196 tiles 5.7 / 8.1; 64 x 64: 49 tiles 6.6 / 6.7, stride 2, 64 tiles 7.7 / 6.5,
+// 98 tiles 7.7 / 8.7.  Where they part lies lower with 32 channels and at stride 1; the line is one for all.)
 bool dwpw_pays(const sbn_packed* p, const Shape& out)
 {
     const long long tiles = out.n * ((out.h + 7) / 8) * ((out.w + 7) / 8);
@@ -204,8 +205,8 @@ int run_chain(const sbn_chain* c, const float* x, float* y, int n, int h, int w,
             }
         }
         // The usual stem in front of a pair that can run as one launch (below) makes all three one, whatever the size: alone in a graph, three
-        // launches / one, 64 output channels, 1 tile of 8 x 8 pixels 8.5 / 5.4 us, 16 tiles 9.3 / 5.6, 64 tiles 10.3 / 5.5, 196 tiles 12.9 / 6.0, 588 tiles
-        // 17.5 / 10.2; 64 images of 224 x 224, stem and pair 110 / 96.
+        // launches / one, 64 output channels, 1 tile of 8 x 8 pixels 9.2 / 6.7 us, 16 tiles 10.4 / 6.9, 64 tiles 11.0 / 7.0, 196 tiles 13.7 / 6.8, 588 tiles
+        // 18.8 / 11.2; 64 images of 224 x 224 108 / 86, stem and fused pair 113.
         if (c->fuse_dw && i == 0 && it.item == SBN_ITEM_STEM3X3 && c->items.size() > 2 && c->items[1].item == SBN_ITEM_DW3X3 &&
             c->items[2].item == SBN_ITEM_SPARSE && stem_dwpw_fusable(c->items[2].packed, it.channels, it.c_out, it.stride, c->items[1].stride) &&
             dwpw_extents_fit(c->items[2].packed, 1, s.n, next_shape(it, s).h, next_shape(it, s).w) &&

@@ -573,8 +573,8 @@ __global__ __launch_bounds__(64 * NW) void conv1x1_splitk_kernel(const float* __
 // output channels, so that staged activations serve four bundles; the split form above reads them once per bundle), but S slices of four waves
 // share its chunks: slice s takes the chunks s, s + S, ..., stages them in its own part of LDS, and the slices' partial sums meet in LDS at
 // the end and are added in 64 bits (add_pairs: of two slices, each one's two first in 32 bits).  Up to one such workgroup per compute unit the launch is a chain of round trips and of entries, which
-// this shortens: 784 pixels, 90 %, blocks of 8 x 4, 1024 x 1024 16.1 -> 11.7 us (3.1 of them for an empty launch; without the loads 9.4, without
-// the multiplies 10.8), 512 x 1024 10.3 -> 7.9.  Two slices or four: launch_conv1x1.
+// this shortens: 784 pixels, 90 %, blocks of 8 x 4, 1024 x 1024 15.6 -> 11.6 us (3.1 of them for an empty launch; without the loads 9.4, without
+// the multiplies 10.8), 512 x 1024 9.6 -> 8.4.  Two slices or four: launch_conv1x1.
 // The first two chunks of a slice are asked for at once, and each chunk two of its slice's chunks before it is needed.
 // Entries past a chunk's last one lie outside the weights' buffer and are not fetched.  Needs c_in % 4 == 0.
 template <int S>

@@ -25,8 +25,8 @@
 // MobileNet-v1's first three blocks at batch 64, 50 % (us, a workgroup per tile / so): 82 / 75, 81 / 60, 85 / 69.  The workgroup per tile spent half of
 // its vector instructions on tile coordinates (integer divisions) and on padding, and three round trips on the parameters before its first
 // load; vector and matrix instructions now take 41 to 45 us of the issue port, the traffic (309, 309 and 206 MB) 60, 60 and 40 us.
-// The stem in front of the first: 36 + 74 us and 515 MB in two launches, 96 and 244 MB in one (3456 of 5500 matrix cycles per tile are the stem's: 28 % of
-// the lanes of its 100 pixels idle, and 1.56 of them per pixel of the tile; instructions take 61 us of the issue port).
+// The stem in front of the first: 36 + 74 us and 450 MB of tensors in two launches, 96 and 244 MB (301 counted) in one (3456 of 5500 matrix cycles per tile are the stem's: 28 of
+// the 128 lanes that work out its 100 pixels idle, and 1.56 of them per pixel of the tile; instructions take 61 us of the issue port).
 // Used when the 1x1 layer has at most 128 input and 128 output channels; wider layers are bound by
 // the matrix pipe, not by memory traffic, and keep the two launches.
 #include <hip/hip_runtime.h>
